@@ -55,35 +55,32 @@ __global__ void k_quantize_pack(const QParams p) {
 // the same launch.  (Walking several tiles per workgroup with the next tile's loads
 // in flight was measured and is slower: the packed stores of a long-lived workgroup spread
 // out in time and the mixed read/write stream to HBM loses more than the prefetch gains.)
+// Bound by the read stream, with vector issue at about two thirds of it.  Before / after non-temporal
+// whole-line loads, the short rounding and the XCD-wise tile order (same machine, median of 25):
+//   d = 138 M, K = 8, s = 2, bucket 4096     851 -> 762 us = 6.18 TB/s
+//   d = 25.6 M, K = 16, s = 256, bucket 8192 380 -> 329 us = 6.38 TB/s
+//   d = 11 M, K = 8, s = 4, bucket 2048       77 ->  63 us = 6.24 TB/s
+//   d = 1 M, K = 8, s = 16, bucket 512      10.1 -> 9.3 us (launch and one round of loads)
 template <int M, int LOG2N, bool CENTER>
-__global__ void __launch_bounds__(Geo<LOG2N>::NW * 64) k_quantize_pack_fast(const QParams p) {
-    constexpr int CH = Geo<LOG2N>::CH;
-    constexpr uint32_t TILE = Geo<LOG2N>::TILE;
+__global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_fast(const QParams p) {
+    constexpr int CH = Geo<M, LOG2N>::CH;
+    constexpr uint32_t TILE = Geo<M, LOG2N>::TILE;
     __shared__ float sm[32];
 
-    const uint32_t per_worker = p.full_tiles + p.tail_tiles;
+    // Grid: (tiles, workers), so that nothing has to be divided; with a center (8 * workers, y, z).
+    const uint32_t tiles = p.full_tiles + p.tail_tiles;
     uint32_t k, t;
     if (CENTER) {
-        // All workers read the same `center`.  Workgroups are handed to the 8 XCDs round-robin by
-        // id, so the K workgroups of one tile get ids 8 apart: they run on one XCD one after the
-        // other, and all but the first find the tile of `center` in that XCD's L2.
-        const uint32_t K = p.group_workers;
-        const uint32_t tiles8 = p.full_tiles & ~7u;
-        const uint32_t span = 8u * K;
-        if (blockIdx.x < (tiles8 >> 3) * span) {
-            const uint32_t g = blockIdx.x / span, r = blockIdx.x - g * span;
-            k = r >> 3;
-            t = g * 8u + (r & 7u);
-        } else {                                          // fewer than 8 tiles left, and the ragged one
-            const uint32_t rest = per_worker - tiles8;
-            const uint32_t r = blockIdx.x - (tiles8 >> 3) * span;
-            k = r / rest;
-            t = tiles8 + (r - k * rest);
-        }
+        // All workers read the same `center`: the K workgroups of one tile get ids 8 apart, so they run
+        // on one XCD one after the other, and all but the first find the tile of `center` in its L2.
+        k = blockIdx.x >> 3;
+        t = (blockIdx.z * gridDim.y + blockIdx.y) * 8u + (blockIdx.x & 7u);
+        if (t >= tiles) return;
     } else {
-        k = blockIdx.x / per_worker;
-        t = blockIdx.x - k * per_worker;
+        k = blockIdx.y;
+        t = blockIdx.x;
     }
+    t = xcd_tile(t, tiles, p.xcd_group);
     if (t >= p.full_tiles) {                              // the ragged last tile of the worker (at most one)
         guarded_tile<M, CH, QESGD_NORM_L2, false>(p, k, t, sm);
         return;
@@ -93,11 +90,10 @@ __global__ void __launch_bounds__(Geo<LOG2N>::NW * 64) k_quantize_pack_fast(cons
     unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
     FastCtx cx;
     cx.norms = reinterpret_cast<float*>(out + p.norms_off);
-    cx.signs = reinterpret_cast<uint32_t*>(out + p.signs_off);
-    cx.levels = reinterpret_cast<uint32_t*>(out + p.levels_off);
+    cx.signs = out + p.signs_off;
+    cx.levels = out + p.levels_off;
     cx.lane = threadIdx.x & 63u;
     cx.wave = threadIdx.x >> 6;
-    cx.lane_off = cx.wave * (uint32_t)(CH * kChunk) + cx.lane * kLaneElems;   // coordinate offset inside a tile
     cx.worker = p.worker0 + k;
     cx.round = p.round;
     cx.key0 = p.key0;
@@ -105,7 +101,8 @@ __global__ void __launch_bounds__(Geo<LOG2N>::NW * 64) k_quantize_pack_fast(cons
     cx.smax = p.smax;
 
     float buf[CH][8];
-    load_tile<CH, CENTER>(xk + (uint64_t)t * TILE, ck + (uint64_t)t * TILE, cx.lane_off, buf);
+    const uint64_t w0 = (uint64_t)t * TILE + cx.wave * (uint32_t)(CH * kChunk);
+    load_tile<CH, CENTER>(xk + w0, ck + w0, cx.lane, buf);
     process_tile<M, LOG2N>(cx, buf, t, sm);
 }
 
@@ -113,9 +110,9 @@ __global__ void __launch_bounds__(Geo<LOG2N>::NW * 64) k_quantize_pack_fast(cons
 // of `center` in registers and takes the workers one after the other with the next worker's loads
 // in flight, so `center` is read once per tile instead of once per tile and worker.
 template <int M, int LOG2N>
-__global__ void __launch_bounds__(Geo<LOG2N>::NW * 64) k_quantize_pack_center(const QParams p) {
-    constexpr int CH = Geo<LOG2N>::CH;
-    constexpr uint32_t TILE = Geo<LOG2N>::TILE;
+__global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_center(const QParams p) {
+    constexpr int CH = Geo<M, LOG2N>::CH;
+    constexpr uint32_t TILE = Geo<M, LOG2N>::TILE;
     __shared__ float sm[2][32];             // alternate per worker: one barrier per tile suffices
     const uint32_t t = blockIdx.x;
     const uint32_t K = p.group_workers;
@@ -126,41 +123,37 @@ __global__ void __launch_bounds__(Geo<LOG2N>::NW * 64) k_quantize_pack_center(co
     FastCtx cx;
     cx.lane = threadIdx.x & 63u;
     cx.wave = threadIdx.x >> 6;
-    cx.lane_off = cx.wave * (uint32_t)(CH * kChunk) + cx.lane * kLaneElems;
     cx.round = p.round;
     cx.key0 = p.key0;
     cx.key1 = p.key1;
     cx.smax = p.smax;
     const uint64_t e0 = (uint64_t)t * TILE;
-    float4 ca[CH], cb[CH], a[CH], b[CH], na[CH], nb2[CH];
+    const uint64_t w0 = e0 + cx.wave * (uint32_t)(CH * kChunk) + half_offset(cx.lane);
+    vec4 ca[CH], cb[CH], a[CH], b[CH], na[CH], nb2[CH];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const uint32_t o = cx.lane_off + (uint32_t)c * kChunk;
-        ca[c] = *reinterpret_cast<const float4*>(p.center + e0 + o);
-        cb[c] = *reinterpret_cast<const float4*>(p.center + e0 + o + 4);
-        a[c] = *reinterpret_cast<const float4*>(p.x + e0 + o);
-        b[c] = *reinterpret_cast<const float4*>(p.x + e0 + o + 4);
+        const uint64_t o = w0 + (uint32_t)c * kChunk;
+        ca[c] = load_stream(p.center + o);
+        cb[c] = load_stream(p.center + o + kChunk / 2);
+        a[c] = load_stream(p.x + o);
+        b[c] = load_stream(p.x + o + kChunk / 2);
     }
     for (uint32_t k = 0; k < K; ++k) {
         if (k + 1 < K) {
-            const float* __restrict__ xn = p.x + (uint64_t)(k + 1) * p.x_stride + e0;
+            const float* __restrict__ xn = p.x + (uint64_t)(k + 1) * p.x_stride + w0;
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-                const uint32_t o = cx.lane_off + (uint32_t)c * kChunk;
-                na[c] = *reinterpret_cast<const float4*>(xn + o);
-                nb2[c] = *reinterpret_cast<const float4*>(xn + o + 4);
+                na[c] = load_stream(xn + (uint32_t)c * kChunk);
+                nb2[c] = load_stream(xn + (uint32_t)c * kChunk + kChunk / 2);
             }
         }
         float v[CH][8];
 #pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            v[c][0] = a[c].x - ca[c].x; v[c][1] = a[c].y - ca[c].y; v[c][2] = a[c].z - ca[c].z; v[c][3] = a[c].w - ca[c].w;
-            v[c][4] = b[c].x - cb[c].x; v[c][5] = b[c].y - cb[c].y; v[c][6] = b[c].z - cb[c].z; v[c][7] = b[c].w - cb[c].w;
-        }
+        for (int c = 0; c < CH; ++c) halves_to_lane(a[c] - ca[c], b[c] - cb[c], v[c]);
         unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
         cx.norms = reinterpret_cast<float*>(out + p.norms_off);
-        cx.signs = reinterpret_cast<uint32_t*>(out + p.signs_off);
-        cx.levels = reinterpret_cast<uint32_t*>(out + p.levels_off);
+        cx.signs = out + p.signs_off;
+        cx.levels = out + p.levels_off;
         cx.worker = p.worker0 + k;
         process_tile<M, LOG2N>(cx, v, t, sm[k & 1u]);
         if (k + 1 < K) {
@@ -213,10 +206,9 @@ __global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
         guarded_partial_tile<KIND>(p, k, t, sm);
         return;
     }
-    const uint32_t lane_off = wave * (2u * kChunk) + lane * kLaneElems;
+    const uint64_t w0 = (uint64_t)t * kPartialTile + wave * (2u * kChunk);
     float v[2][8];
-    load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + (uint64_t)t * kPartialTile,
-                         p.center + (uint64_t)t * kPartialTile, lane_off, v);
+    load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, v);
     const float t0 = lane_butterfly<KIND>(lane_tree<KIND>(v[0]), 64);
     const float t1 = lane_butterfly<KIND>(lane_tree<KIND>(v[1]), 64);
     if (lane == 0) sm[wave] = t0 + t1;
@@ -237,22 +229,24 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
     }
     unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
     const float* __restrict__ norms = reinterpret_cast<const float*>(out + p.norms_off);
-    uint32_t* __restrict__ signs = reinterpret_cast<uint32_t*>(out + p.signs_off);
-    uint32_t* __restrict__ levels = reinterpret_cast<uint32_t*>(out + p.levels_off);
-    const uint32_t lane_off = wave * (2u * kChunk) + lane * kLaneElems;
-    const uint64_t e0 = (uint64_t)t * kPartialTile;
+    const uint64_t e0 = (uint64_t)t * kPartialTile, g0 = e0 / kLaneElems;
+    const uint64_t w0 = e0 + wave * (2u * kChunk);
     float v[2][8];
-    load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + e0, p.center + e0, lane_off, v);
-    const float inv = inverse_step(norms[e0 >> p.log2N], p.smax);
+    load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, v);
+    const Scale sc = scale_of_norm<M>(norms[e0 >> p.log2N]);
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-        const uint64_t i = e0 + lane_off + (uint32_t)c * kChunk;
-        const uint64_t g = i >> 3;
+        const uint32_t idx = (wave * 2u + (uint32_t)c) * kWaveSize + lane;
         uint32_t rnd[4];
-        philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        philox4x32_10((uint32_t)g0 + idx, (uint32_t)(g0 >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
         uint32_t sign_byte, bits[4];
-        round_and_pack<M>(v[c], rnd, inv, p.smax, sign_byte, bits);
-        store_codes<M>(signs, levels, i, 8u, lane, sign_byte, bits);
+        round_and_pack<M>(v[c], rnd, sc, sign_byte, bits);
+        if (32 % M == 0) {
+            store_codes_full<M>(out + p.signs_off + g0, out + p.levels_off + g0 * M, idx, sign_byte, bits);
+        } else {
+            store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off),
+                           (g0 + idx) * kLaneElems, 8u, lane, sign_byte, bits);
+        }
     }
 }
 
@@ -364,44 +358,48 @@ void launch_m(const QParams& p, uint32_t m, uint32_t norm_kind, dim3 grid, dim3 
 }
 
 template <int M, int LOG2N>
-void launch_fast_one(const QParams& p, uint32_t blocks, hipStream_t st) {
+void launch_fast_one(const QParams& p, hipStream_t st) {
+    const uint32_t tiles = p.full_tiles + p.tail_tiles;
     // With a center and enough tiles to fill the chip many times over (measured: it pays from about
     // 64 waves per SIMD on), a workgroup takes one tile of every worker and reads `center` once.
-    if (p.center && p.group_workers > 1 && (uint64_t)p.full_tiles * Geo<LOG2N>::NW >= 65536u) {
-        hipLaunchKernelGGL((k_quantize_pack_center<M, LOG2N>), dim3(p.full_tiles + p.tail_tiles),
-                           dim3(Geo<LOG2N>::NW * 64), 0, st, p);
+    if (p.center && p.group_workers > 1 && (uint64_t)p.full_tiles * Geo<M, LOG2N>::NW >= 65536u) {
+        hipLaunchKernelGGL((k_quantize_pack_center<M, LOG2N>), dim3(tiles), dim3((Geo<M, LOG2N>::NW * 64)), 0, st, p);
         return;
     }
-    if (p.center)
-        hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, true>), dim3(blocks), dim3(Geo<LOG2N>::NW * 64), 0, st, p);
-    else
-        hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, false>), dim3(blocks), dim3(Geo<LOG2N>::NW * 64), 0, st, p);
+    if (p.center) {
+        const uint32_t octets = (tiles + 7u) / 8u, gz = (octets + 65534u) / 65535u, gy = (octets + gz - 1u) / gz;
+        hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, true>), dim3(8u * p.group_workers, gy, gz),
+                           dim3((Geo<M, LOG2N>::NW * 64)), 0, st, p);
+        return;
+    }
+    hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, false>), dim3(tiles, p.group_workers),
+                       dim3((Geo<M, LOG2N>::NW * 64)), 0, st, p);
 }
 
 template <int M>
-void launch_fast_n(const QParams& p, uint32_t blocks, hipStream_t st) {
+void launch_fast_n(const QParams& p, hipStream_t st) {
     switch (p.log2N) {
-        case 5: launch_fast_one<M, 5>(p, blocks, st); break;
-        case 6: launch_fast_one<M, 6>(p, blocks, st); break;
-        case 7: launch_fast_one<M, 7>(p, blocks, st); break;
-        case 8: launch_fast_one<M, 8>(p, blocks, st); break;
-        case 9: launch_fast_one<M, 9>(p, blocks, st); break;
-        case 10: launch_fast_one<M, 10>(p, blocks, st); break;
-        case 11: launch_fast_one<M, 11>(p, blocks, st); break;
-        case 12: launch_fast_one<M, 12>(p, blocks, st); break;
-        case 13: launch_fast_one<M, 13>(p, blocks, st); break;
-        case 14: launch_fast_one<M, 14>(p, blocks, st); break;
-        default: launch_fast_one<M, 15>(p, blocks, st); break;
+        case 5: launch_fast_one<M, 5>(p, st); break;
+        case 6: launch_fast_one<M, 6>(p, st); break;
+        case 7: launch_fast_one<M, 7>(p, st); break;
+        case 8: launch_fast_one<M, 8>(p, st); break;
+        case 9: launch_fast_one<M, 9>(p, st); break;
+        case 10: launch_fast_one<M, 10>(p, st); break;
+        case 11: launch_fast_one<M, 11>(p, st); break;
+        case 12: launch_fast_one<M, 12>(p, st); break;
+        case 13: launch_fast_one<M, 13>(p, st); break;
+        case 14: launch_fast_one<M, 14>(p, st); break;
+        default: launch_fast_one<M, 15>(p, st); break;
     }
 }
 
-void launch_fast(const QParams& p, uint32_t m, uint32_t blocks, hipStream_t st) {
+void launch_fast(const QParams& p, uint32_t m, hipStream_t st) {
     switch (m) {
-        case 1: launch_fast_n<1>(p, blocks, st); break;
-        case 2: launch_fast_n<2>(p, blocks, st); break;
-        case 4: launch_fast_n<4>(p, blocks, st); break;
-        case 8: launch_fast_n<8>(p, blocks, st); break;
-        default: launch_fast_n<16>(p, blocks, st); break;
+        case 1: launch_fast_n<1>(p, st); break;
+        case 2: launch_fast_n<2>(p, st); break;
+        case 4: launch_fast_n<4>(p, st); break;
+        case 8: launch_fast_n<8>(p, st); break;
+        default: launch_fast_n<16>(p, st); break;
     }
 }
 
@@ -495,14 +493,12 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
     const bool fast = !two_pass && a.norm_kind == QESGD_NORM_L2 && sh.N == sh.B && sh.log2N >= 5 &&
                       32u % sh.m == 0u;
     uint32_t ch = 2, nwaves = 4;                         // generic kernel: 2 chunks per wave, 4..16 waves
-    if (fast) {
-        fast_geometry(sh.N, &ch, &nwaves);
-    } else if (!two_pass) {
+    if (!two_pass && !fast) {
         if (sh.N == 8192) nwaves = 8;
         else if (sh.N == 16384) nwaves = 16;
         else if (sh.N == 32768) { ch = 4; nwaves = 16; }
     }
-    const uint64_t tile = (uint64_t)nwaves * ch * kChunk;
+    const uint64_t tile = fast ? fast_tile(sh.m, sh.N) : (uint64_t)nwaves * ch * kChunk;
     const uint64_t tiles = (slots + tile - 1) / tile;
     if (tiles * a.K >= (1ull << 31)) return QESGD_ERR_DIM;
     const dim3 block(nwaves * kWaveSize);
@@ -575,7 +571,8 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         // full_tiles may be 0 (a vector shorter than a tile): the launch is then one guarded tile per worker
         p.full_tiles = (uint32_t)(sh.d / tile);
         p.tail_tiles = (uint32_t)(tiles - p.full_tiles);
-        launch_fast(p, sh.m, (uint32_t)(tiles * a.K), a.stream);
+        p.xcd_group = xcd_group_log2(tile);
+        launch_fast(p, sh.m, a.stream);
         return check_launch();
     }
     p.tile0 = 0;

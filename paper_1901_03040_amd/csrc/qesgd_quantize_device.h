@@ -27,6 +27,7 @@ struct QParams {
     uint32_t full_tiles;         // fast kernels: tiles per worker that lie wholly inside the vector
     uint32_t tail_tiles;         // fast quantize kernel: ragged tiles per worker after those (0 or 1)
     uint32_t group_workers;      // workers covered by this launch
+    uint32_t xcd_group;          // fast quantize kernels: log2 of the tiles that one XCD takes in a row
     uint32_t ws_tiles_per_worker;  // partial sums: workspace entries per worker (nb * N / 4096)
     uint64_t data_tiles;         // partial sums: 4096-slot tiles of a worker that hold coordinates
     uint32_t key0, key1;
@@ -124,65 +125,157 @@ __device__ __forceinline__ float lds_tree16(const float* sm, uint32_t base, uint
 }
 
 // ---------------------------------------------------------------------------
-// Rounding and in-lane packing of the 8 coordinates of a lane.
-//   fixed = trunc(min(|v| * inv, smax) * 2^16) = floor(a) * 2^16 + trunc(frac(a) * 2^16)
-//   level = (fixed + r16) >> 16        (the carry out of the low half rounds up)
-// inv * 2^16 is folded into the scale when it is finite: scaling by a power of
-// two commutes with rounding, and a product that underflows truncates to 0
-// either way.  bits[] receives the 8*M level bits (M = 1: low byte, M = 2: low
-// half, M = 4: one word, M = 8: two words, M = 16: four words; M = 3, 5, 6, 7:
-// the low 8*M bits of bits[0..1] read as one 64-bit string).
+// Bucket scale.
 // ---------------------------------------------------------------------------
-template <int M>
-__device__ __forceinline__ void round_and_pack(const float (&v)[8], const uint32_t (&rnd)[4], float inv,
-                                               float smax, uint32_t& sign_byte, uint32_t (&bits)[4]) {
-    uint32_t y[8];
-    const float inv16 = inv * 65536.0f;
-    if (inv16 < INFINITY) {
-        const float smax16 = smax * 65536.0f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const uint32_t r16 = variate16(rnd, e);
-            y[e] = (uint32_t)fminf(fabsf(v[e]) * inv16, smax16) + r16;
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const uint32_t r16 = variate16(rnd, e);
-            y[e] = (uint32_t)(fminf(fabsf(v[e]) * inv, smax) * 65536.0f) + r16;
-        }
-    }
-    uint32_t sb = 0;
-#pragma unroll
-    for (int e = 7; e >= 0; --e) sb = sb + sb + (v[e] < 0.0f ? 1u : 0u);   // v_cmp + v_addc
-    sign_byte = sb;
-    bits[0] = bits[1] = bits[2] = bits[3] = 0;
-    if (M == 1 || M == 2 || M == 4) {
-        uint32_t w = y[0] >> 16;
-#pragma unroll
-        for (int e = 1; e < 8; ++e) w |= (y[e] >> 16) << (M * e);
-        bits[0] = w;
-    } else if (M == 3 || M == 5 || M == 6 || M == 7) {       // 8*M <= 56 bits: one 64-bit string
-        uint64_t w = y[0] >> 16;
-#pragma unroll
-        for (int e = 1; e < 8; ++e) w |= (uint64_t)(y[e] >> 16) << (M * e);
-        bits[0] = (uint32_t)w;
-        bits[1] = (uint32_t)(w >> 32);
-    } else if (M == 8) {
-        bits[0] = (y[0] >> 16) | ((y[1] >> 16) << 8) | ((y[2] >> 16) << 16) | ((y[3] >> 16) << 24);
-        bits[1] = (y[4] >> 16) | ((y[5] >> 16) << 8) | ((y[6] >> 16) << 16) | ((y[7] >> 16) << 24);
-    } else {
-        bits[0] = (y[0] >> 16) | (y[1] & 0xFFFF0000u);
-        bits[1] = (y[2] >> 16) | (y[3] & 0xFFFF0000u);
-        bits[2] = (y[4] >> 16) | (y[5] & 0xFFFF0000u);
-        bits[3] = (y[6] >> 16) | (y[7] & 0xFFFF0000u);
-    }
+// Correctly rounded square root and quotient for operands far from the ends of the exponent range:
+// the hardware estimate and the correction steps of the general expansions without their operand
+// scaling and special cases (checked against sqrtf on every float of the range below and against
+// IEEE division for every significand, every level width and norms from 2^-60 to 2^60).
+__device__ __forceinline__ float sqrt_in_range(float x) {
+    const float s = __builtin_amdgcn_sqrtf(x);
+    const float down = __uint_as_float(__float_as_uint(s) - 1u), up = __uint_as_float(__float_as_uint(s) + 1u);
+    const float rd = __builtin_fmaf(-down, s, x), ru = __builtin_fmaf(-up, s, x);
+    const float r = rd <= 0.0f ? down : s;
+    return ru > 0.0f ? up : r;
 }
-
+__device__ __forceinline__ float quotient_in_range(float a, float b) {
+    float r = __builtin_amdgcn_rcpf(b);
+    r = __builtin_fmaf(__builtin_fmaf(-b, r, 1.0f), r, r);
+    float q = a * r;
+    q = __builtin_fmaf(__builtin_fmaf(-b, q, a), r, q);
+    return __builtin_fmaf(__builtin_fmaf(-b, q, a), r, q);
+}
 __device__ __forceinline__ float inverse_step(float norm, float smax) {
     float inv = smax / norm;
     if (!(inv < INFINITY)) inv = 0.0f;     // norm 0 (or reciprocal overflow): every level is 0
     return inv;
+}
+
+// How the buckets of a wave are scaled.  direct (the same for the whole wave): every norm is in
+// [2^-60, 2^60] and mul = fl(smax/norm) * 2^(32-M), the form that ordinary buckets take (see
+// round_and_pack); otherwise mul is not used.
+struct Scale {
+    float norm, mul;
+    bool direct;
+};
+
+__device__ __forceinline__ bool wave_all(bool x) { return __builtin_amdgcn_ballot_w64(!x) == 0; }
+
+template <int M>
+__device__ __forceinline__ Scale scale_of_norm(float norm) {
+    constexpr float smax = (float)((1u << M) - 1u);
+    Scale sc;
+    sc.norm = norm;
+    sc.direct = wave_all(norm >= 0x1p-60f && norm <= 0x1p60f);
+    sc.mul = quotient_in_range(smax * (float)(1ull << (32 - M)), norm);
+    return sc;
+}
+
+// The scale of a bucket whose tree total (L2) or maximum is t.
+template <int M, int KIND>
+__device__ __forceinline__ Scale scale_of_total(float t) {
+    if (KIND != QESGD_NORM_L2) return scale_of_norm<M>(t);
+    constexpr float smax = (float)((1u << M) - 1u);
+    Scale sc;
+    sc.direct = wave_all(t >= 0x1p-90f && t <= 0x1p120f);
+    sc.norm = sc.direct ? sqrt_in_range(t) : sqrtf(t);
+    sc.mul = quotient_in_range(smax * (float)(1ull << (32 - M)), sc.norm);
+    return sc;
+}
+
+// ---------------------------------------------------------------------------
+// Rounding and in-lane packing of the 8 coordinates of a lane.
+//   fixed = trunc(min(|v| * inv, smax) * 2^16) = floor(a) * 2^16 + trunc(frac(a) * 2^16)
+//   level = (fixed + r16) >> 16        (the carry out of the low half rounds up)
+// bits[] receives the 8*M level bits (M = 1: low byte, M = 2: low half, M = 4: one word, M = 8: two
+// words, M = 16: four words; M = 3, 5, 6, 7: the low 8*M bits of bits[0..1] read as one 64-bit string).
+//
+// Direct form, 5 instructions per coordinate with the sign and the packing (10 before; the quantiser
+// spent 0.62 ms of vector issue on d = 138 M, K = 8, s = 2 and is bound by it next to the read stream):
+//   p = fma(v, mul, +0)       the product with its sign; the +0 turns -0 * mul into +0, so the sign bit
+//                             of p is [v < 0] also for v = -0, and changes no other product
+//   y = trunc(|p|) + r16 * 2^(16-M), saturating (v_mad_u32_u16 picks either half of the random word)
+//   level = the top M bits of y, sign = the top bit of p; one v_alignbit appends each to its string.
+// The scale carries 2^(32-M) instead of 2^16, so that the level lands in the top bits: the 16-M bits of
+// trunc(|p|) below the random number's lowest bit cannot carry.  Scaling by a power of two commutes
+// with rounding, and a product that underflows truncates to 0 either way.
+// The minimum with smax is not needed: norm >= |v| (the tree total is at least fl(v^2), and sqrt is
+// monotonic with sqrt(fl(v^2)) = |v|, away from underflow), so |p| exceeds smax * 2^(32-M) by at most
+// the last place of the product; for M <= 7 that is less than 2^(16-M) and never carries, and for
+// M = 8, 16 the saturating sum keeps the top level.
+// A bucket whose norm is outside [2^-60, 2^60] (zero buckets among them) takes the formula as it stands.
+// ---------------------------------------------------------------------------
+template <int HALF>
+__device__ __forceinline__ uint32_t add_variate(uint32_t word, uint32_t weight, uint32_t a) {
+    uint32_t y;
+    if (HALF == 0) asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[0,0,0,0] clamp" : "=v"(y) : "v"(word), "s"(weight), "v"(a));
+    else asm("v_mad_u32_u16 %0, %1, %2, %3 op_sel:[1,0,0,0] clamp" : "=v"(y) : "v"(word), "s"(weight), "v"(a));
+    return y;
+}
+
+// Level fields of four coordinates, level in the top M bits of each y (M < 8: 4*M bits; M = 8: a word).
+template <int M>
+__device__ __forceinline__ uint32_t pack4(const uint32_t* y) {
+    if (M == 8) {
+        const uint32_t lo = __builtin_amdgcn_perm(y[1], y[0], 0x0C0C0703u);     // byte 3 of each
+        const uint32_t hi = __builtin_amdgcn_perm(y[3], y[2], 0x07030C0Cu);
+        return lo | hi;
+    }
+    uint32_t w = y[3] >> (32 - M);
+#pragma unroll
+    for (int e = 2; e >= 0; --e) w = __builtin_amdgcn_alignbit(w, y[e], 32 - M);
+    return w;
+}
+
+template <int M>
+__device__ __forceinline__ void round_and_pack(const float (&v)[8], const uint32_t (&rnd)[4], const Scale& sc,
+                                               uint32_t& sign_byte, uint32_t (&bits)[4]) {
+    uint32_t y[8], sb;                                   // level in the top M bits of y
+    if (sc.direct) {
+        const uint32_t weight = 1u << (16 - M);
+        uint32_t p[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float pe = __builtin_fmaf(v[e], sc.mul, 0.0f);
+            p[e] = __float_as_uint(pe);
+            const uint32_t a = (uint32_t)fabsf(pe);
+            y[e] = (e & 1) ? add_variate<1>(rnd[e >> 1], weight, a) : add_variate<0>(rnd[e >> 1], weight, a);
+        }
+        sb = p[7] >> 31;
+#pragma unroll
+        for (int e = 6; e >= 0; --e) sb = __builtin_amdgcn_alignbit(sb, p[e], 31);
+    } else {
+        constexpr float smax = (float)((1u << M) - 1u);
+        // the product with 2^16 is folded into the scale where it is finite
+        const float inv = inverse_step(sc.norm, smax);
+        const bool fold = inv * 65536.0f < INFINITY;
+        const float mul = fold ? inv * 65536.0f : inv, cap = fold ? smax * 65536.0f : smax, post = fold ? 1.0f : 65536.0f;
+        sb = 0;
+#pragma unroll
+        for (int e = 7; e >= 0; --e) {
+            const float a = fminf(fabsf(v[e]) * mul, cap) * post;
+            y[e] = (((uint32_t)a + variate16(rnd, e)) >> 16) << (32 - M);
+            sb = sb + sb + (v[e] < 0.0f ? 1u : 0u);
+        }
+    }
+    sign_byte = sb;
+    bits[0] = bits[1] = bits[2] = bits[3] = 0;
+    if constexpr (M == 8) {
+        bits[0] = pack4<M>(y);
+        bits[1] = pack4<M>(y + 4);
+    } else if constexpr (M == 16) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bits[q] = __builtin_amdgcn_perm(y[2 * q + 1], y[2 * q], 0x07060302u);
+    } else if constexpr (M <= 4 && M != 3) {
+        uint32_t w = y[7] >> (32 - M);
+#pragma unroll
+        for (int e = 6; e >= 0; --e) w = __builtin_amdgcn_alignbit(w, y[e], 32 - M);
+        bits[0] = w;
+    } else {                                              // 8*M = 24..56 bits: one 64-bit string
+        const uint64_t w = (uint64_t)pack4<M>(y) | ((uint64_t)pack4<M>(y + 4) << (4 * M));
+        bits[0] = (uint32_t)w;
+        bits[1] = (uint32_t)(w >> 32);
+    }
 }
 
 // Cross-lane assembly of words and the stores, for a lane whose 8 coordinates
@@ -337,10 +430,10 @@ __device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint3
         load_lane(x, p.center, span[c], v[c]);
     }
 
-    float norm[CH];
+    Scale sc[CH];
     if (PRE) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) norm[c] = span[c].bucket < p.nb ? norms[span[c].bucket] : 0.0f;
+        for (int c = 0; c < CH; ++c) sc[c] = scale_of_norm<M>(span[c].bucket < p.nb ? norms[span[c].bucket] : 0.0f);
     } else {
         float t[CH];
         const uint32_t lanes_per_bucket = (uint32_t)((N < kChunk ? N : kChunk) / kLaneElems);
@@ -371,8 +464,8 @@ __device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint3
         }
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            norm[c] = (KIND == QESGD_NORM_L2) ? sqrtf(t[c]) : t[c];
-            if (span[c].opens_bucket) norms[span[c].bucket] = norm[c];
+            sc[c] = scale_of_total<M, KIND>(t[c]);
+            if (span[c].opens_bucket) norms[span[c].bucket] = sc[c].norm;
         }
     }
 
@@ -385,79 +478,118 @@ __device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint3
         uint32_t rnd[4];
         philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
         uint32_t sign_byte, bits[4];
-        round_and_pack<M>(v[c], rnd, inverse_step(norm[c], p.smax), p.smax, sign_byte, bits);
+        round_and_pack<M>(v[c], rnd, sc[c], sign_byte, bits);
         store_codes<M>(signs, levels, span[c].i, span[c].nvalid, lane, sign_byte, bits);
-        if (ACC) accumulate8<M>(acc[c], sign_byte, bits, norm[c] / p.smax);
+        if (ACC) accumulate8<M>(acc[c], sign_byte, bits, sc[c].norm / p.smax);
     }
 }
 
 // ---------------------------------------------------------------------------
 // Fast kernel.  Geometry per bucket size: tile = NW waves x CH chunks x 512.
 // ---------------------------------------------------------------------------
-template <int LOG2N>
+template <int M, int LOG2N>
 struct Geo {
-    // Buckets up to 2048: one chunk per wave (2048-coordinate tiles measured faster than 4096: 80
-    // against 84 us at d = 11 M), and two waves instead of four up to 1024 (0.84 against 0.86 ms at
-    // d = 138 M, K = 8, bucket 512 or 1024; one wave is slower again); 4096 / 8192: two chunks per
-    // wave (one chunk and twice the waves is as fast at 4096 and much slower at 8192: 0.46 against
-    // 0.38 ms at d = 25.6 M, K = 16).
-    static constexpr int CH = (LOG2N == 15) ? 4 : (LOG2N <= 11 ? 1 : 2);
-    static constexpr int NW = (LOG2N <= 10) ? 2 : ((LOG2N <= 12) ? 4 : (LOG2N == 13 ? 8 : 16));
+    // Chunks per wave and waves per workgroup, measured at 1.07 G coordinates.  Few level bits: two
+    // chunks per wave, the more bytes in flight the better (M = 1: 0.70 against 0.74 ms with bucket
+    // 512, M = 2: 0.73 against 0.75 ms with 2048); from M = 4 on the packed stores weigh more and one
+    // chunk is better (M = 8: 0.82 against 0.87 ms with 4096).  8192: two chunks, as fast as one with
+    // sixteen waves and open to a second workgroup per CU.  The workgroup is as small as the bucket
+    // allows, but not one wave (M = 4: the same; M = 1: 0.74 against 0.72 ms).
+    static constexpr int CH = LOG2N == 15 ? 4 : (LOG2N >= 13 || M <= 2 ? 2 : 1);
+    static constexpr int NW = (1 << LOG2N) / (CH * 512) < 2 ? 2 : (1 << LOG2N) / (CH * 512);
     static constexpr uint32_t TILE = (uint32_t)NW * CH * kChunk;
 };
 
-// Geo<log2 N> for a run-time N (host side): chunks per wave and waves per workgroup.
-inline void fast_geometry(uint64_t N, uint32_t* ch, uint32_t* nwaves) {
-    *ch = N == 32768 ? 4u : (N <= 2048 ? 1u : 2u);
-    *nwaves = N <= 1024 ? 2u : (N <= 4096 ? 4u : (N == 8192 ? 8u : 16u));
+// Geo<M, log2 N>::TILE on the host.
+inline uint64_t fast_tile(uint32_t m, uint64_t N) {
+    const uint64_t ch = N == 32768 ? 4 : (N >= 8192 || m <= 2 ? 2 : 1);
+    return N > 2 * ch * kChunk ? N : 2 * ch * kChunk;
 }
 
+// Tile of workgroup b.  Workgroups are handed to the 8 XCDs round-robin by id, so consecutive ids
+// would spread every stretch of memory over all of them.  Groups of 2^lg tiles (256 KB of input, set
+// by the host) go to one XCD instead: its reads and packed writes are then one run of addresses each
+// (M = 1, bucket 4096: 0.70 against 0.77 ms at 1.07 G coordinates; groups of 64 K .. 1 M coordinates
+// are within 2% of each other).  What is left over at the end stays in order.
+__device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t tiles, uint32_t lg) {
+    if (b >= ((tiles >> (lg + 3u)) << (lg + 3u))) return b;
+    const uint32_t r = b >> 3;
+    return ((((r >> lg) << 3) | (b & 7u)) << lg) | (r & ((1u << lg) - 1u));
+}
+inline uint32_t xcd_group_log2(uint64_t tile) {
+    uint32_t lg = 0;
+    while ((tile << lg) < 65536u) ++lg;
+    return lg;
+}
+
+// A wave's CH chunks of a tile into registers: xw / cw point at the wave's first coordinate.  All
+// loads are issued before the first use.  `center` is read by every worker's workgroup of the tile,
+// so it keeps the ordinary cache policy.
 template <int CH, bool CENTER>
-__device__ __forceinline__ void load_tile(const float* __restrict__ xt, const float* __restrict__ ct,
-                                          uint32_t lane_off, float (&v)[CH][8]) {
-    float4 a[CH], b[CH], ca[CH], cb[CH];
+__device__ __forceinline__ void load_tile(const float* __restrict__ xw, const float* __restrict__ cw, uint32_t lane,
+                                          float (&v)[CH][8]) {
+    vec4 a[CH], b[CH], ca[CH], cb[CH];
+    const uint32_t h = half_offset(lane);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const uint32_t o = lane_off + (uint32_t)c * kChunk;
-        a[c] = *reinterpret_cast<const float4*>(xt + o);
-        b[c] = *reinterpret_cast<const float4*>(xt + o + 4);
+        const uint32_t o = h + (uint32_t)c * kChunk;
+        a[c] = load_stream(xw + o);
+        b[c] = load_stream(xw + o + kChunk / 2);
         if (CENTER) {
-            ca[c] = *reinterpret_cast<const float4*>(ct + o);
-            cb[c] = *reinterpret_cast<const float4*>(ct + o + 4);
+            ca[c] = load_cached(cw + o);
+            cb[c] = load_cached(cw + o + kChunk / 2);
         }
     }
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        v[c][0] = a[c].x; v[c][1] = a[c].y; v[c][2] = a[c].z; v[c][3] = a[c].w;
-        v[c][4] = b[c].x; v[c][5] = b[c].y; v[c][6] = b[c].z; v[c][7] = b[c].w;
         if (CENTER) {
-            v[c][0] -= ca[c].x; v[c][1] -= ca[c].y; v[c][2] -= ca[c].z; v[c][3] -= ca[c].w;
-            v[c][4] -= cb[c].x; v[c][5] -= cb[c].y; v[c][6] -= cb[c].z; v[c][7] -= cb[c].w;
+            a[c] -= ca[c];
+            b[c] -= cb[c];
         }
+        halves_to_lane(a[c], b[c], v[c]);
     }
 }
 
-// Everything a workgroup needs to know about its worker, in registers.
+// Everything a workgroup needs to know about its worker, in registers; the pointers are uniform.
 struct FastCtx {
     float* __restrict__ norms;
-    uint32_t* __restrict__ signs;
-    uint32_t* __restrict__ levels;
-    uint32_t lane, wave, lane_off, worker, round, key0, key1;
+    unsigned char* __restrict__ signs;
+    unsigned char* __restrict__ levels;
+    uint32_t lane, wave, worker, round, key0, key1;
     float smax;
 };
 
+// The codes of a lane's 8 coordinates where all of them exist: lane group `idx` of the planes that
+// start at the (uniform) bytes signs and levels.  A lane's sign bits are one byte and its level bits M,
+// so widths that divide 32 need no exchange between lanes: 64 lanes write consecutive bytes.  A wave's
+// level bits fill whole lines from M = 2 on and leave with the non-temporal policy (M = 8, buckets of
+// 512: 0.81 against 0.94 ms at 1.07 G coordinates); the 64-byte halves of a line that one-bit planes
+// are written in meet in the L2 and keep the ordinary policy (0.72 against 0.75 ms).
+template <int M>
+__device__ __forceinline__ void store_codes_full(unsigned char* __restrict__ signs, unsigned char* __restrict__ levels,
+                                                 uint32_t idx, uint32_t sign_byte, const uint32_t (&bits)[4]) {
+    typedef uint32_t uvec2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t uvec4 __attribute__((ext_vector_type(4)));
+    signs[idx] = (unsigned char)sign_byte;
+    if (M == 1) levels[idx] = (unsigned char)bits[0];
+    else if (M == 2) __builtin_nontemporal_store((unsigned short)bits[0], reinterpret_cast<unsigned short*>(levels + idx * 2u));
+    else if (M == 4) __builtin_nontemporal_store(bits[0], reinterpret_cast<uint32_t*>(levels + idx * 4u));
+    else if (M == 8) __builtin_nontemporal_store(uvec2{bits[0], bits[1]}, reinterpret_cast<uvec2*>(levels + idx * 8u));
+    else __builtin_nontemporal_store(uvec4{bits[0], bits[1], bits[2], bits[3]}, reinterpret_cast<uvec4*>(levels + idx * 16u));
+}
+
 // One tile: bucket totals, scales, variates, rounding, packing, stores.  ACC as in guarded_tile.
-template <int M, int LOG2N, bool ACC = false>
-__device__ __forceinline__ void process_tile(const FastCtx& cx, float (&v)[Geo<LOG2N>::CH][8], uint32_t t, float* sm,
+template <int M, int LOG2N, bool ACC = false, class G = Geo<M, LOG2N>>
+__device__ __forceinline__ void process_tile(const FastCtx& cx, float (&v)[G::CH][8], uint32_t t, float* sm,
                                              float (*acc)[8] = nullptr) {
-    constexpr int CH = Geo<LOG2N>::CH;
+    constexpr int CH = G::CH;
     constexpr uint32_t N = 1u << LOG2N;
-    constexpr uint32_t TILE = Geo<LOG2N>::TILE;
+    constexpr uint32_t TILE = G::TILE;
     constexpr uint32_t LPB = (N < kChunk ? N : kChunk) / kLaneElems;                       // lanes per bucket
     constexpr int CPB = N <= kChunk ? 1 : (int)(N / kChunk < (uint32_t)CH ? N / kChunk : (uint32_t)CH);  // chunks per bucket in a wave
     constexpr uint32_t WPB = N <= CH * kChunk ? 1u : N / (CH * kChunk);                     // waves per bucket
     constexpr int KIND = QESGD_NORM_L2;
-    const uint64_t e0 = (uint64_t)t * TILE;                      // first coordinate of the tile
+    const uint64_t g0 = (uint64_t)t * (TILE / kLaneElems);        // first lane group (8 coordinates) of the tile
 
     float tot[CH];
 #pragma unroll
@@ -475,23 +607,25 @@ __device__ __forceinline__ void process_tile(const FastCtx& cx, float (&v)[Geo<L
         tot[0] = lds_tree16<KIND>(sm, cx.wave & ~(WPB - 1u), WPB);
     }
 
-    float inv = 0.0f, step = 0.0f;
+    Scale sc;
+    float step = 0.0f;
+    float* __restrict__ norms = cx.norms + (g0 >> (LOG2N - 3));
+    unsigned char* __restrict__ signs = cx.signs + g0;
+    unsigned char* __restrict__ levels = cx.levels + g0 * M;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const uint32_t off = cx.lane_off + (uint32_t)c * kChunk;
+        const uint32_t idx = (cx.wave * (uint32_t)CH + (uint32_t)c) * kWaveSize + cx.lane;   // lane group inside the tile
         if (c % CPB == 0) {                                       // first chunk of a bucket (or of its part in this wave)
-            const float norm = sqrtf(tot[c]);
-            inv = inverse_step(norm, cx.smax);
-            if (ACC) step = norm / cx.smax;
-            if ((off & (N - 1u)) == 0u) cx.norms[(e0 >> LOG2N) + (off >> LOG2N)] = norm;
+            sc = scale_of_total<M, KIND>(tot[c]);
+            if (ACC) step = sc.norm / cx.smax;
+            if ((idx & (N / kLaneElems - 1u)) == 0u) norms[idx >> (LOG2N - 3)] = sc.norm;
         }
-        const uint64_t i = e0 + off;
-        const uint64_t g = i >> 3;
+        // the tile starts at a multiple of its size, so the low word of the group number cannot carry
         uint32_t rnd[4];
-        philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), cx.worker, cx.round, cx.key0, cx.key1, rnd);
+        philox4x32_10((uint32_t)g0 + idx, (uint32_t)(g0 >> 32), cx.worker, cx.round, cx.key0, cx.key1, rnd);
         uint32_t sign_byte, bits[4];
-        round_and_pack<M>(v[c], rnd, inv, cx.smax, sign_byte, bits);
-        store_codes<M>(cx.signs, cx.levels, i, 8u, cx.lane, sign_byte, bits);
+        round_and_pack<M>(v[c], rnd, sc, sign_byte, bits);
+        store_codes_full<M>(signs, levels, idx, sign_byte, bits);
         if (ACC) accumulate8<M>(acc[c], sign_byte, bits, step);
     }
 }
