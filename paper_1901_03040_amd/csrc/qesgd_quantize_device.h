@@ -161,6 +161,15 @@ struct Scale {
 
 __device__ __forceinline__ bool wave_all(bool x) { return __builtin_amdgcn_ballot_w64(!x) == 0; }
 
+// No NaN among a lane's coordinates.  The L2 norm of a bucket with a NaN is a NaN itself, but a maximum
+// passes over it, so under the max norm the direct form has to look (4 compares per 8 coordinates).
+template <int KIND>
+__device__ __forceinline__ bool no_nan(const float (&v)[8]) {
+    if (KIND == QESGD_NORM_L2) return true;
+    return !(__builtin_isunordered(v[0], v[1]) || __builtin_isunordered(v[2], v[3]) ||
+             __builtin_isunordered(v[4], v[5]) || __builtin_isunordered(v[6], v[7]));
+}
+
 template <int M>
 __device__ __forceinline__ Scale scale_of_norm(float norm) {
     constexpr float smax = (float)((1u << M) - 1u);
@@ -203,7 +212,8 @@ __device__ __forceinline__ Scale scale_of_total(float t) {
 // monotonic with sqrt(fl(v^2)) = |v|, away from underflow), so |p| exceeds smax * 2^(32-M) by at most
 // the last place of the product; for M <= 7 that is less than 2^(16-M) and never carries, and for
 // M = 8, 16 the saturating sum keeps the top level.
-// A bucket whose norm is outside [2^-60, 2^60] (zero buckets among them) takes the formula as it stands.
+// A bucket whose norm is outside [2^-60, 2^60] (zero buckets among them) or a wave that holds a NaN takes
+// the formula as it stands.
 // ---------------------------------------------------------------------------
 template <int HALF>
 __device__ __forceinline__ uint32_t add_variate(uint32_t word, uint32_t weight, uint32_t a) {
@@ -478,6 +488,7 @@ __device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint3
         uint32_t rnd[4];
         philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
         uint32_t sign_byte, bits[4];
+        if (KIND != QESGD_NORM_L2) sc[c].direct = sc[c].direct && wave_all(no_nan<KIND>(v[c]));
         round_and_pack<M>(v[c], rnd, sc[c], sign_byte, bits);
         store_codes<M>(signs, levels, span[c].i, span[c].nvalid, lane, sign_byte, bits);
         if (ACC) accumulate8<M>(acc[c], sign_byte, bits, sc[c].norm / p.smax);

@@ -52,3 +52,25 @@ def test_tiles_dealt_in_groups(oracle, B, s, bucket, tail, centered):
     x = (torch.randn(K, d, generator=g) * 1e-3).cuda()
     center = (torch.randn(d, generator=g) * 1e-3).cuda() if centered else None
     run_and_compare(oracle, B, x, s, bucket, 4, 9, K=K, center=center)
+
+
+@pytest.mark.parametrize("bucket,d", [(96, 4000), (3008, 20_000), (4096, 16_384), (65_536, 200_000)])
+@pytest.mark.parametrize("s", [2, 8, 16, 256, 65536])
+def test_nan_and_infinity_keep_the_formula(oracle, B, s, bucket, d):
+    """A maximum passes over a NaN, so the scale stays finite: the level is the minimum's other operand,
+    s - 1, with the sign bit of no number, 0.  Infinities make the scale infinite under either norm."""
+    g = torch.Generator(device="cpu").manual_seed(s + d)
+    for norm in (0, 1):
+        for odd in (float("nan"), -float("nan"), float("inf"), -float("inf")):
+            x = torch.randn(d, generator=g) * 1e-2
+            x[torch.randint(d, (5,), generator=g)] = odd
+            lay = B.qesgd_layout_query(d, s, bucket)
+            packed = B.alloc_packed(lay, 1).zero_()
+            wsb = B.qesgd_workspace_bytes(d, s, bucket, 1)
+            ws = torch.empty(wsb // 4, device="cuda") if wsb else None
+            B.qesgd_quantize_pack(x.cuda(), None, d, s, bucket, norm, 3, 1, 0, packed[0], ws)
+            n, sg, lv = (t.cpu().numpy() for t in B.planes(packed[0], lay))
+            on, osw, olw = oracle.quantize_pack(x.numpy(), s, bucket, 3, 1, 0, norm_kind=norm)
+            assert np.array_equal(n, on, equal_nan=True), (norm, odd, "norms")
+            assert np.array_equal(sg.view(np.uint32), osw), (norm, odd, "signs")
+            assert np.array_equal(lv.view(np.uint32), olw), (norm, odd, "levels")
