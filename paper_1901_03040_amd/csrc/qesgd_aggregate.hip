@@ -10,39 +10,45 @@
 namespace qesgd {
 namespace {
 
-// A wave owns 512 consecutive coordinates.  The codes are read with a lane owning 8
-// consecutive coordinates (one sign byte, 8*M level bits per worker); the fp32 vectors are
-// read and written with a lane owning one float4 of each 256-coordinate half, so that every
-// 128-bit access of a wave covers a contiguous KiB (a 32-byte lane stride would split every
-// store into half-filled requests).  z crosses from one layout to the other through 2 KiB of
-// LDS private to the wave.  UPDATE: w, u present.  When the bucket size is a multiple of 512
-// the whole wave shares a bucket: lane k divides worker k's scale once and the loop reads it
-// back as a scalar.
+// A wave owns 512 consecutive coordinates.  The codes are read with a lane owning 8 consecutive
+// coordinates (one sign byte, 8*M level bits per worker); the fp32 vectors are read and written with
+// a lane owning one float4 of each 256-coordinate half, so that every 128-bit access of a wave covers
+// a contiguous KiB and can carry the non-temporal policy; z crosses from one layout to the other with
+// four lane swaps (lane_to_halves).  UPDATE: w, u present.  When the bucket size is a multiple of 512
+// the whole wave shares a bucket: lane k divides worker k's scale once and the loop reads it back as a
+// scalar.  Bound by the stream of vectors.  Before (ordinary policy, exchange through LDS, tiles dealt
+// round-robin to the XCDs) / after, whole call, same machine:
+//   d = 138 M, K = 8, s = 2, bucket 4096       556 -> 523 us = 5.8 TB/s
+//   d = 25.6 M, K = 1, s = 256, bucket 8192    100 ->  84 us = 6.4 TB/s
+//   d = 25.6 M, K = 16, s = 256, bucket 8192   180 -> 165 us = 5.9 TB/s
+//   d = 7.3 M, K = 5, s = 32, bucket 3008       36 ->  31 us = 5.5 TB/s
+// Up to a few million coordinates, where everything comes from the caches, both are within 1 us.
+// Stretches of 128 K or 256 K coordinates per XCD instead of 64 K are the same, 1 M is 4% slower.
 // Waves per workgroup; the waves share nothing.  Two measured 1-2% faster than four or eight at
 // d = 11 M .. 138 M (0.532 against 0.539 ms at d = 138 M, K = 8), one the same as two.
 constexpr uint32_t kAggWaves = 2;
 template <int M, bool UPDATE, bool ZSUM, bool ZBAR>
 __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(const AParams p) {
-    __shared__ float4 stage[kAggWaves][128];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint64_t wave_base = ((uint64_t)blockIdx.x * kAggWaves + wave) * kChunk;
+    const uint32_t block = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
+    const uint64_t wave_base = ((uint64_t)block * kAggWaves + wave) * kChunk;
     if (wave_base >= p.d) return;
     if (wave_base + kChunk > p.d) {                       // ragged last wave
         aggregate_lane_guarded<M>(p, wave_base + lane * kLaneElems);
         return;
     }
     const uint64_t i = wave_base + lane * kLaneElems;     // code layout: 8 consecutive coordinates
-    const uint64_t ia = wave_base + lane * 4u;            // vector layout: float4 #lane of each half
-    const uint64_t ib = ia + 256u;
+    const uint64_t ia = wave_base + half_offset(lane);    // vector layout: one float4 of each half
+    const uint64_t ib = ia + kChunk / 2;
 
-    float4 wa, wb, sa, sb;
+    vec4 wa, wb, sa, sb;
     if (UPDATE) {
-        wa = *reinterpret_cast<const float4*>(p.w + ia);
-        wb = *reinterpret_cast<const float4*>(p.w + ib);
+        wa = load_stream(p.w + ia);
+        wb = load_stream(p.w + ib);
     }
     if (ZSUM) {
-        sa = *reinterpret_cast<const float4*>(p.zsum + ia);
-        sb = *reinterpret_cast<const float4*>(p.zsum + ib);
+        sa = load_stream(p.zsum + ia);
+        sb = load_stream(p.zsum + ib);
     }
 
     float acc[8];
@@ -140,26 +146,19 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
         for (int e = 0; e < 8; ++e) z[e] = acc[e] / fk;
     }
 
-    // lane-of-8 layout -> float4-per-half layout (same wave on both sides: LDS keeps program order)
-    stage[wave][2 * lane] = make_float4(z[0], z[1], z[2], z[3]);
-    stage[wave][2 * lane + 1] = make_float4(z[4], z[5], z[6], z[7]);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const float4 za = stage[wave][lane];
-    const float4 zb = stage[wave][64 + lane];
-
+    vec4 za, zb;
+    lane_to_halves(z, za, zb);
     if (ZBAR) {
-        *reinterpret_cast<float4*>(p.zbar + ia) = za;
-        *reinterpret_cast<float4*>(p.zbar + ib) = zb;
+        store_stream(p.zbar + ia, za);
+        store_stream(p.zbar + ib, zb);
     }
     if (UPDATE) {
-        *reinterpret_cast<float4*>(p.u + ia) = make_float4(wa.x + za.x, wa.y + za.y, wa.z + za.z, wa.w + za.w);
-        *reinterpret_cast<float4*>(p.u + ib) = make_float4(wb.x + zb.x, wb.y + zb.y, wb.z + zb.z, wb.w + zb.w);
+        store_stream(p.u + ia, wa + za);
+        store_stream(p.u + ib, wb + zb);
     }
     if (ZSUM) {
-        *reinterpret_cast<float4*>(p.zsum + ia) = make_float4(sa.x + za.x, sa.y + za.y, sa.z + za.z, sa.w + za.w);
-        *reinterpret_cast<float4*>(p.zsum + ib) = make_float4(sb.x + zb.x, sb.y + zb.y, sb.z + zb.z, sb.w + zb.w);
+        store_stream(p.zsum + ia, sa + za);
+        store_stream(p.zsum + ib, sb + zb);
     }
 }
 
@@ -169,13 +168,13 @@ __global__ void __launch_bounds__(256) k_apply_update(const float* w, const floa
     const uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4u;
     if (i >= d) return;
     if (i + 4 <= d) {
-        const float4 z = *reinterpret_cast<const float4*>(zbar + i);
-        const float4 a = *reinterpret_cast<const float4*>(w + i);
+        const vec4 z = load_stream(zbar + i);
+        const vec4 a = load_stream(w + i);
         if (zsum) {
-            const float4 s = *reinterpret_cast<const float4*>(zsum + i);
-            *reinterpret_cast<float4*>(zsum + i) = make_float4(s.x + z.x, s.y + z.y, s.z + z.z, s.w + z.w);
+            const vec4 s = load_stream(zsum + i);
+            store_stream(zsum + i, s + z);
         }
-        *reinterpret_cast<float4*>(u + i) = make_float4(a.x + z.x, a.y + z.y, a.z + z.z, a.w + z.w);
+        store_stream(u + i, a + z);
     } else {
         for (uint64_t j = i; j < d; ++j) {
             const float z = zbar[j];
@@ -227,6 +226,7 @@ int launch_aggregate(const Shape& sh, const AggregateArgs& a) {
     const uint64_t lanes = (sh.d + kLaneElems - 1) / kLaneElems;
     const uint64_t blocks = (lanes + kAggWaves * 64 - 1) / (kAggWaves * 64);
     if (blocks >= (1ull << 31)) return QESGD_ERR_DIM;
+    p.xcd_group = xcd_group_log2(kAggWaves * kChunk);
     const dim3 grid((uint32_t)blocks), block(kAggWaves * 64);
     const bool upd = a.w_snap != nullptr, zs = a.zsum != nullptr, zb = a.zbar_out != nullptr;
 #define QESGD_LAUNCH_AGG(MM)                                                                              \

@@ -3,6 +3,7 @@
 // contribution to a lane's 8 coordinates, and the per-lane guarded form of the whole step.
 #pragma once
 
+#include "qesgd_device.h"
 #include "qesgd_internal.h"
 
 namespace qesgd {
@@ -20,6 +21,7 @@ struct AParams {
     uint64_t norms_off, signs_off, levels_off;
     uint64_t level_words;
     uint32_t K;
+    uint32_t xcd_group;     // log2 of the workgroups' stretches that one XCD takes in a row
     int32_t log2B;          // >= 0 when B is a power of two, else -1
     uint32_t wave_uniform_bucket;   // 1 when every 512-aligned chunk lies inside one bucket
     uint32_t wave_two_buckets;      // else 1 when a 512-aligned chunk touches at most two buckets and K <= 32

@@ -517,22 +517,6 @@ inline uint64_t fast_tile(uint32_t m, uint64_t N) {
     return N > 2 * ch * kChunk ? N : 2 * ch * kChunk;
 }
 
-// Tile of workgroup b.  Workgroups are handed to the 8 XCDs round-robin by id, so consecutive ids
-// would spread every stretch of memory over all of them.  Groups of 2^lg tiles (256 KB of input, set
-// by the host) go to one XCD instead: its reads and packed writes are then one run of addresses each
-// (M = 1, bucket 4096: 0.70 against 0.77 ms at 1.07 G coordinates; groups of 64 K .. 1 M coordinates
-// are within 2% of each other).  What is left over at the end stays in order.
-__device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t tiles, uint32_t lg) {
-    if (b >= ((tiles >> (lg + 3u)) << (lg + 3u))) return b;
-    const uint32_t r = b >> 3;
-    return ((((r >> lg) << 3) | (b & 7u)) << lg) | (r & ((1u << lg) - 1u));
-}
-inline uint32_t xcd_group_log2(uint64_t tile) {
-    uint32_t lg = 0;
-    while ((tile << lg) < 65536u) ++lg;
-    return lg;
-}
-
 // A wave's CH chunks of a tile into registers: xw / cw point at the wave's first coordinate.  All
 // loads are issued before the first use.  `center` is read by every worker's workgroup of the tile,
 // so it keeps the ordinary cache policy.
