@@ -41,15 +41,9 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
     const uint64_t ia = wave_base + half_offset(lane);    // vector layout: one float4 of each half
     const uint64_t ib = ia + kChunk / 2;
 
-    vec4 wa, wb, sa, sb;
-    if (UPDATE) {
-        wa = load_stream(p.w + ia);
-        wb = load_stream(p.w + ib);
-    }
-    if (ZSUM) {
-        sa = load_stream(p.zsum + ia);
-        sb = load_stream(p.zsum + ib);
-    }
+    vec4 wa[1], wb[1], sa[1], sb[1];
+    if (UPDATE) load_halves<1>(p.w + ia, p.vec_cached, wa, wb);
+    if (ZSUM) load_halves<1>(p.zsum + ia, p.vec_cached, sa, sb);
 
     float acc[8];
 #pragma unroll
@@ -153,12 +147,12 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
         store_stream(p.zbar + ib, zb);
     }
     if (UPDATE) {
-        store_stream(p.u + ia, wa + za);
-        store_stream(p.u + ib, wb + zb);
+        store_stream(p.u + ia, wa[0] + za);
+        store_stream(p.u + ib, wb[0] + zb);
     }
     if (ZSUM) {
-        store_stream(p.zsum + ia, sa + za);
-        store_stream(p.zsum + ib, sb + zb);
+        store_stream(p.zsum + ia, sa[0] + za);
+        store_stream(p.zsum + ib, sb[0] + zb);
     }
 }
 
@@ -227,6 +221,7 @@ int launch_aggregate(const Shape& sh, const AggregateArgs& a) {
     const uint64_t blocks = (lanes + kAggWaves * 64 - 1) / (kAggWaves * 64);
     if (blocks >= (1ull << 31)) return QESGD_ERR_DIM;
     p.xcd_group = xcd_group_log2(kAggWaves * kChunk);
+    p.vec_cached = update_bytes(sh, a.K) <= kCachedUpdateBytes;
     const dim3 grid((uint32_t)blocks), block(kAggWaves * 64);
     const bool upd = a.w_snap != nullptr, zs = a.zsum != nullptr, zb = a.zbar_out != nullptr;
 #define QESGD_LAUNCH_AGG(MM)                                                                              \

@@ -26,6 +26,7 @@ struct AParams {
     uint32_t wave_uniform_bucket;   // 1 when every 512-aligned chunk lies inside one bucket
     uint32_t wave_two_buckets;      // else 1 when a 512-aligned chunk touches at most two buckets and K <= 32
     float smax;
+    bool vec_cached;        // read w and zsum with the ordinary cache policy
     float rcpK;             // exact 1/K when K is a power of two, else 0
 };
 

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "qesgd_internal.h"
+
 namespace qesgd {
 
 // Three-way xor in one v_bitop3 (truth table of a ^ b ^ c).
@@ -66,6 +68,28 @@ __device__ __forceinline__ void store_stream(float* p, const vec4& v) {
     __builtin_nontemporal_store(v, reinterpret_cast<vec4*>(p));
 }
 __device__ __forceinline__ vec4 load_cached(const float* p) { return *reinterpret_cast<const vec4*>(p); }
+
+// CH x 512 coordinates of a vector, one float4 of each half chunk per lane, with either policy.  The
+// condition is uniform.  The empty asm statements keep the compiler from merging the two arms into one
+// set of loads, which would drop the policy.
+template <int CH>
+__device__ __forceinline__ void load_halves(const float* __restrict__ p, bool cached, vec4 (&a)[CH], vec4 (&b)[CH]) {
+    if (cached) {
+        asm volatile("; cached");
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            a[c] = load_cached(p + c * kChunk);
+            b[c] = load_cached(p + c * kChunk + kChunk / 2);
+        }
+        asm volatile("; cached end");
+    } else {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            a[c] = load_stream(p + c * kChunk);
+            b[c] = load_stream(p + c * kChunk + kChunk / 2);
+        }
+    }
+}
 
 // Offset of this lane's float4 inside a half chunk (256 coordinates).
 __device__ __forceinline__ uint32_t half_offset(uint32_t lane) { return (lane & 31u) * 8u + (lane >> 5) * 4u; }

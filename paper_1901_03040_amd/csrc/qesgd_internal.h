@@ -22,6 +22,18 @@ constexpr uint64_t kPartialTile = 4096;
 // Input bytes that the two-pass path lets the first pass read before the second pass re-reads
 // them: well inside the 256 MB memory-side cache, which also has to take the packed output.
 constexpr uint64_t kCacheBudgetBytes = 160ull << 20;
+// Cache policy of the streams.  The non-temporal one is right for what comes from HBM; what fits the
+// 256 MB memory-side cache from one round to the next, or from the workers' call to the server's, is
+// better read and written with the ordinary one.  Measured over d = 0.3 .. 12 M, K = 2 .. 16, with two
+// rounds' buffers in turn (whole two-call round, non-temporal / ordinary):
+//   input vectors                  d = 2 M, K = 8: 23.9 / 22.1 us;  d = 8 M, K = 8: 80.8 / 83.9 us
+//   level planes                   d = 5 M, K = 16, s = 256: 103 / 94 us;  12 M (216 MB): 234 / 237 us
+//   w and zsum of the update       d = 5 M, K = 4: 34.9 / 31.9 us;  12 M, K = 16, s = 256: 234 / 239 us
+// (the outputs z, u and zsum are best non-temporal at every size).
+constexpr uint64_t kCachedInputBytes = 96ull << 20;     // of the K input vectors ...
+constexpr uint64_t kCachedRoundBytes = 192ull << 20;    // ... and of all that a round touches
+constexpr uint64_t kCachedCodeBytes = 160ull << 20;     // of the K packed blocks, which the server reads next
+constexpr uint64_t kCachedUpdateBytes = 256ull << 20;   // of the packed blocks and the five vectors of the update
 // Floats of the per-GPU static scratch behind qesgd_quantize_pack_batched_noalloc (4 MiB): one
 // partial sum per 4096 padded coordinates, i.e. K * n_buckets * padded_bucket <= 2^32.
 constexpr size_t kStaticScratchFloats = QESGD_NOALLOC_SCRATCH_BYTES / sizeof(float);
@@ -39,6 +51,13 @@ struct Shape {
 
 // Validates (d, s, bucket) and fills the shape; returns QESGD_OK or an error.
 int make_shape(uint64_t d, uint32_t s, uint64_t bucket, Shape* out);
+
+// What the K workers' vectors, their packed blocks and the update's five vectors take.
+inline uint64_t update_bytes(const Shape& sh, uint32_t K) { return K * sh.lay.payload_bytes + 20u * sh.d; }
+inline bool input_cached(const Shape& sh, uint32_t K) {
+    const uint64_t in = 4u * (uint64_t)K * sh.d;
+    return in <= kCachedInputBytes && in + update_bytes(sh, K) <= kCachedRoundBytes;
+}
 
 struct QuantizeArgs {
     const float* x;
@@ -71,8 +90,17 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a);
 int static_scratch(float** out);
 int launch_aggregate(const Shape& sh, const AggregateArgs& a);
 // One launch for a whole round (quantise K workers, sum, update) where the shape allows it:
-// power-of-two bucket of 32..32768 coordinates, L2 scale, level width dividing 32.
+// power-of-two bucket of 32..16384 coordinates, L2 scale, level width dividing 32.
 bool round_fused_covers(const Shape& sh, uint32_t norm_kind);
+// One launch or two.  One launch takes the workers of a tile one after the other, about 1 us each (2.4 us
+// with buckets of 4096 and more, whose waves meet at a barrier per worker), which only a chip full of
+// tiles hides; two launches spread tiles and workers over the chip at once.  Measured, one / two:
+// d = 0.1 M, K = 8, bucket 4096: 23 / 10 us; 1 M, K = 16, bucket 8192: 44 / 25 us; 1 M, K = 16, bucket
+// 1024: 30 / 23 us; 2 M, K = 16, bucket 8192: 40 / 43 us; 1 M, K = 8, bucket 512: 14.0 / 14.2 us; 1 M,
+// K = 2, bucket 16384: 10.2 / 10.8 us.  Buckets of 32768 would need 300 registers per lane.
+inline bool round_fused_pays(const Shape& sh, uint32_t K) {
+    return sh.d >= (3u << 19) || K <= (sh.N <= 2048 ? 8u : 2u);
+}
 int launch_round_fused(const Shape& sh, const QuantizeArgs& a, const AggregateArgs& g);
 int launch_apply_update(const float* w, const float* zbar, float* u, float* zsum, uint64_t d,
                         hipStream_t stream);

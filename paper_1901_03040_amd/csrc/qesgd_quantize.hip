@@ -99,10 +99,11 @@ __global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_fast
     cx.key0 = p.key0;
     cx.key1 = p.key1;
     cx.smax = p.smax;
+    cx.codes_cached = p.codes_cached;
 
     float buf[CH][8];
     const uint64_t w0 = (uint64_t)t * TILE + cx.wave * (uint32_t)(CH * kChunk);
-    load_tile<CH, CENTER>(xk + w0, ck + w0, cx.lane, buf);
+    load_tile<CH, CENTER>(xk + w0, ck + w0, cx.lane, p.x_cached, buf);
     process_tile<M, LOG2N>(cx, buf, t, sm);
 }
 
@@ -127,6 +128,7 @@ __global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_cent
     cx.key0 = p.key0;
     cx.key1 = p.key1;
     cx.smax = p.smax;
+    cx.codes_cached = p.codes_cached;
     const uint64_t e0 = (uint64_t)t * TILE;
     const uint64_t w0 = e0 + cx.wave * (uint32_t)(CH * kChunk) + half_offset(cx.lane);
     vec4 ca[CH], cb[CH], a[CH], b[CH], na[CH], nb2[CH];
@@ -208,7 +210,7 @@ __global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
     }
     const uint64_t w0 = (uint64_t)t * kPartialTile + wave * (2u * kChunk);
     float v[2][8];
-    load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, v);
+    load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, p.x_cached, v);
     const float t0 = lane_butterfly<KIND>(lane_tree<KIND>(v[0]), 64);
     const float t1 = lane_butterfly<KIND>(lane_tree<KIND>(v[1]), 64);
     if (lane == 0) sm[wave] = t0 + t1;
@@ -232,21 +234,23 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
     const uint64_t e0 = (uint64_t)t * kPartialTile, g0 = e0 / kLaneElems;
     const uint64_t w0 = e0 + wave * (2u * kChunk);
     float v[2][8];
-    load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, v);
+    load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, p.x_cached, v);
     const Scale sc = scale_of_norm<M>(norms[e0 >> p.log2N]);
+    const uint32_t idx0 = wave * 2u * kWaveSize + lane;
+    uint32_t sign_byte[2], bits[2][4];
 #pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        const uint32_t idx = (wave * 2u + (uint32_t)c) * kWaveSize + lane;
+    for (uint32_t c = 0; c < 2; ++c) {
         uint32_t rnd[4];
-        philox4x32_10((uint32_t)g0 + idx, (uint32_t)(g0 >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
-        uint32_t sign_byte, bits[4];
-        round_and_pack<M>(v[c], rnd, sc, sign_byte, bits);
-        if (32 % M == 0) {
-            store_codes_full<M>(out + p.signs_off + g0, out + p.levels_off + g0 * M, idx, sign_byte, bits);
-        } else {
+        philox4x32_10((uint32_t)g0 + idx0 + c * kWaveSize, (uint32_t)(g0 >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        round_and_pack<M>(v[c], rnd, sc, sign_byte[c], bits[c]);
+    }
+    if constexpr (32 % M == 0) {
+        store_chunks<M, 2>(out + p.signs_off + g0, out + p.levels_off + g0 * M, idx0, p.codes_cached, sign_byte, bits);
+    } else {
+#pragma unroll
+        for (uint32_t c = 0; c < 2; ++c)
             store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off),
-                           (g0 + idx) * kLaneElems, 8u, lane, sign_byte, bits);
-        }
+                           (g0 + idx0 + c * kWaveSize) * kLaneElems, 8u, lane, sign_byte[c], bits[c]);
     }
 }
 
@@ -484,6 +488,8 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
     p.worker0 = a.worker0;
     p.smax = (float)(sh.s - 1);
     p.group_workers = a.K;
+    p.x_cached = input_cached(sh, a.K);
+    p.codes_cached = a.K * sh.lay.payload_bytes <= kCachedCodeBytes;
 
     const uint64_t slots = sh.nb * sh.N;                 // slot space of one worker
     const bool two_pass = sh.N > kMaxSinglePassBucket;

@@ -3,6 +3,8 @@
 // the guarded tile and the straight-line tile of the power-of-two-bucket kernels.
 #pragma once
 
+#include <type_traits>
+
 #include "qesgd_aggregate_device.h"
 #include "qesgd_device.h"
 #include "qesgd_internal.h"
@@ -34,6 +36,8 @@ struct QParams {
     uint32_t round;
     uint32_t worker0;
     float smax;
+    bool x_cached;               // read the vectors with the ordinary cache policy
+    bool codes_cached;           // write the level planes with the ordinary cache policy
 };
 
 
@@ -414,36 +418,39 @@ __device__ __forceinline__ void load_lane(const float* __restrict__ x, const flo
     }
 }
 
-// One tile of worker k with every access guarded per lane.  PRE = true: the scales were
-// computed by the partial-sum passes and are read from the norms plane.  sm: 32 floats of LDS.
+// The slots of this lane in a guarded tile (the same for every worker), and one worker's coordinates.
+template <int CH>
+__device__ __forceinline__ void guarded_spans(const QParams& p, uint32_t tile, LaneSpan (&span)[CH]) {
+    const uint64_t wave0 = (uint64_t)tile * (blockDim.x >> 6) + (threadIdx.x >> 6);
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+        span[c] = lane_span((wave0 * (uint64_t)CH + (uint64_t)c) * kChunk + (threadIdx.x & 63u) * kLaneElems, p);
+}
+template <int CH>
+__device__ __forceinline__ void guarded_load(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], float (&v)[CH][8]) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) load_lane(p.x + (uint64_t)k * p.x_stride, p.center, span[c], v[c]);
+}
+
+// One tile of worker k with every access guarded per lane, its coordinates loaded.  PRE = true: the scales
+// were computed by the partial-sum passes and are read from the norms plane.  sm: 32 floats of LDS.
 // ACC = true: the dequantised codes are also added to acc[chunk][0..8) (the server's sum over
 // workers, for the launch that runs a whole round).
 template <int M, int CH, int KIND, bool PRE, bool ACC = false>
-__device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint32_t tile, float* sm,
-                                             float (*acc)[8] = nullptr) {
+__device__ __forceinline__ void guarded_codes(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], const float (&v)[CH][8],
+                                              float* sm, float (*acc)[8] = nullptr) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = threadIdx.x >> 6;
-    const uint32_t nwaves = blockDim.x >> 6;
-    const float* __restrict__ x = p.x + (uint64_t)k * p.x_stride;
     unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
     float* __restrict__ norms = reinterpret_cast<float*>(out + p.norms_off);
     uint32_t* __restrict__ signs = reinterpret_cast<uint32_t*>(out + p.signs_off);
     uint32_t* __restrict__ levels = reinterpret_cast<uint32_t*>(out + p.levels_off);
     const uint64_t N = 1ull << p.log2N;
-    const uint64_t slot0 = ((uint64_t)tile * nwaves + wave) * (uint64_t)(CH * kChunk) + lane * kLaneElems;
-
-    LaneSpan span[CH];
-    float v[CH][8];
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        span[c] = lane_span(slot0 + (uint64_t)c * kChunk, p);
-        load_lane(x, p.center, span[c], v[c]);
-    }
 
     Scale sc[CH];
     if (PRE) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) sc[c] = scale_of_norm<M>(span[c].bucket < p.nb ? norms[span[c].bucket] : 0.0f);
+        for (int c = 0; c < CH; ++c) sc[c] = scale_of_norm<M>(span[c].nvalid ? norms[span[c].bucket] : 1.0f);
     } else {
         float t[CH];
         const uint32_t lanes_per_bucket = (uint32_t)((N < kChunk ? N : kChunk) / kLaneElems);
@@ -474,7 +481,8 @@ __device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint3
         }
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            sc[c] = scale_of_total<M, KIND>(t[c]);
+            // a lane without coordinates must not take its wave out of the short rounding: any ordinary scale
+            sc[c] = scale_of_total<M, KIND>(span[c].nvalid ? t[c] : 1.0f);
             if (span[c].opens_bucket) norms[span[c].bucket] = sc[c].norm;
         }
     }
@@ -493,6 +501,15 @@ __device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint3
         store_codes<M>(signs, levels, span[c].i, span[c].nvalid, lane, sign_byte, bits);
         if (ACC) accumulate8<M>(acc[c], sign_byte, bits, sc[c].norm / p.smax);
     }
+}
+
+template <int M, int CH, int KIND, bool PRE>
+__device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint32_t tile, float* sm) {
+    LaneSpan span[CH];
+    float v[CH][8];
+    guarded_spans<CH>(p, tile, span);
+    guarded_load<CH>(p, k, span, v);
+    guarded_codes<M, CH, KIND, PRE>(p, k, span, v, sm);
 }
 
 // ---------------------------------------------------------------------------
@@ -522,19 +539,11 @@ inline uint64_t fast_tile(uint32_t m, uint64_t N) {
 // so it keeps the ordinary cache policy.
 template <int CH, bool CENTER>
 __device__ __forceinline__ void load_tile(const float* __restrict__ xw, const float* __restrict__ cw, uint32_t lane,
-                                          float (&v)[CH][8]) {
+                                          bool x_cached, float (&v)[CH][8]) {
     vec4 a[CH], b[CH], ca[CH], cb[CH];
     const uint32_t h = half_offset(lane);
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const uint32_t o = h + (uint32_t)c * kChunk;
-        a[c] = load_stream(xw + o);
-        b[c] = load_stream(xw + o + kChunk / 2);
-        if (CENTER) {
-            ca[c] = load_cached(cw + o);
-            cb[c] = load_cached(cw + o + kChunk / 2);
-        }
-    }
+    load_halves<CH>(xw + h, x_cached, a, b);
+    if (CENTER) load_halves<CH>(cw + h, true, ca, cb);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         if (CENTER) {
@@ -552,6 +561,7 @@ struct FastCtx {
     unsigned char* __restrict__ levels;
     uint32_t lane, wave, worker, round, key0, key1;
     float smax;
+    bool codes_cached;
 };
 
 // The codes of a lane's 8 coordinates where all of them exist: lane group `idx` of the planes that
@@ -560,17 +570,41 @@ struct FastCtx {
 // level bits fill whole lines from M = 2 on and leave with the non-temporal policy (M = 8, buckets of
 // 512: 0.81 against 0.94 ms at 1.07 G coordinates); the 64-byte halves of a line that one-bit planes
 // are written in meet in the L2 and keep the ordinary policy (0.72 against 0.75 ms).
-template <int M>
+template <int M, bool CACHED>
 __device__ __forceinline__ void store_codes_full(unsigned char* __restrict__ signs, unsigned char* __restrict__ levels,
                                                  uint32_t idx, uint32_t sign_byte, const uint32_t (&bits)[4]) {
     typedef uint32_t uvec2 __attribute__((ext_vector_type(2)));
     typedef uint32_t uvec4 __attribute__((ext_vector_type(4)));
     signs[idx] = (unsigned char)sign_byte;
-    if (M == 1) levels[idx] = (unsigned char)bits[0];
-    else if (M == 2) __builtin_nontemporal_store((unsigned short)bits[0], reinterpret_cast<unsigned short*>(levels + idx * 2u));
-    else if (M == 4) __builtin_nontemporal_store(bits[0], reinterpret_cast<uint32_t*>(levels + idx * 4u));
-    else if (M == 8) __builtin_nontemporal_store(uvec2{bits[0], bits[1]}, reinterpret_cast<uvec2*>(levels + idx * 8u));
-    else __builtin_nontemporal_store(uvec4{bits[0], bits[1], bits[2], bits[3]}, reinterpret_cast<uvec4*>(levels + idx * 16u));
+    if constexpr (M == 1) {
+        levels[idx] = (unsigned char)bits[0];
+    } else {
+        typedef std::conditional_t<M == 2, unsigned short, std::conditional_t<M == 4, uint32_t, std::conditional_t<M == 8, uvec2, uvec4>>> field;
+        field f;
+        if constexpr (M == 8) f = uvec2{bits[0], bits[1]};
+        else if constexpr (M == 16) f = uvec4{bits[0], bits[1], bits[2], bits[3]};
+        else f = (field)bits[0];
+        field* dst = reinterpret_cast<field*>(levels + idx * (uint32_t)M);
+        if (CACHED) *dst = f;
+        else __builtin_nontemporal_store(f, dst);
+    }
+}
+
+// The same for the CH chunks of a wave that follow each other from lane group idx0 on.  One branch behind
+// all chunks: a branch per chunk would keep the chunks' arithmetic apart (528 against 504 us for the two
+// calls of a round at d = 25.6 M, K = 16, s = 256, bucket 8192).
+template <int M, int CH>
+__device__ __forceinline__ void store_chunks(unsigned char* __restrict__ signs, unsigned char* __restrict__ levels, uint32_t idx0,
+                                             bool cached, const uint32_t (&sign_byte)[CH], const uint32_t (&bits)[CH][4]) {
+    if (M > 1 && cached) {
+        asm volatile("; cached");                         // keeps the arms apart (see load_halves)
+#pragma unroll
+        for (int c = 0; c < CH; ++c) store_codes_full<M, true>(signs, levels, idx0 + (uint32_t)c * kWaveSize, sign_byte[c], bits[c]);
+        asm volatile("; cached end");
+    } else {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) store_codes_full<M, false>(signs, levels, idx0 + (uint32_t)c * kWaveSize, sign_byte[c], bits[c]);
+    }
 }
 
 // One tile: bucket totals, scales, variates, rounding, packing, stores.  ACC as in guarded_tile.
@@ -607,6 +641,7 @@ __device__ __forceinline__ void process_tile(const FastCtx& cx, float (&v)[G::CH
     float* __restrict__ norms = cx.norms + (g0 >> (LOG2N - 3));
     unsigned char* __restrict__ signs = cx.signs + g0;
     unsigned char* __restrict__ levels = cx.levels + g0 * M;
+    uint32_t sign_byte[CH], bits[CH][4];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         const uint32_t idx = (cx.wave * (uint32_t)CH + (uint32_t)c) * kWaveSize + cx.lane;   // lane group inside the tile
@@ -618,11 +653,10 @@ __device__ __forceinline__ void process_tile(const FastCtx& cx, float (&v)[G::CH
         // the tile starts at a multiple of its size, so the low word of the group number cannot carry
         uint32_t rnd[4];
         philox4x32_10((uint32_t)g0 + idx, (uint32_t)(g0 >> 32), cx.worker, cx.round, cx.key0, cx.key1, rnd);
-        uint32_t sign_byte, bits[4];
-        round_and_pack<M>(v[c], rnd, sc, sign_byte, bits);
-        store_codes_full<M>(signs, levels, idx, sign_byte, bits);
-        if (ACC) accumulate8<M>(acc[c], sign_byte, bits, step);
+        round_and_pack<M>(v[c], rnd, sc, sign_byte[c], bits[c]);
+        if (ACC) accumulate8<M>(acc[c], sign_byte[c], bits[c], step);
     }
+    store_chunks<M, CH>(signs, levels, cx.wave * (uint32_t)CH * kWaveSize + cx.lane, cx.codes_cached, sign_byte, bits);
 }
 
 }  // namespace

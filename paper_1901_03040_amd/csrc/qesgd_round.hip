@@ -8,8 +8,16 @@
 // z.  It takes the workers one after the other (the next worker's loads in flight while the
 // current one is rounded), keeps the running sum of the dequantised codes in registers, and writes
 // z, u and the running sum of z at the end.  The packed codes are written but never read back.
-// What this saves is one dependent launch per round and K*P bytes of reads; it exists for sizes at
-// which a round is launch-bound.
+// What this saves is one dependent launch per round and K*P bytes of reads.
+//
+// Bound by the stream of vectors where the tiles fill the chip, by the chain of K workers per tile
+// where they do not (see round_fused_pays).  All vectors move in halves of a KiB per instruction with
+// the non-temporal policy, in runs of 64 K coordinates per XCD; w and zsum are in flight while the last
+// worker is rounded.  Before (32 bytes per lane, ordinary policy, tiles dealt round-robin, update loads
+// after the last worker, z through LDS) / after:
+//   d = 11 M, K = 8, s = 4, bucket 2048       118 -> 102 us = 6.0 TB/s
+//   d = 12 M, K = 16, s = 256, bucket 8192    245 -> 220 us = 5.7 TB/s
+//   d = 12 M, K = 2, s = 256, bucket 4096      73 ->  60 us
 #include "qesgd_aggregate_device.h"
 #include "qesgd_quantize_device.h"
 
@@ -31,32 +39,20 @@ struct RParams {
 // chunks at bucket 2048, s = 4: 115 against 111 us at d = 11 M, K = 8).
 template <int LOG2N>
 struct RoundGeo {
-    static constexpr int CH = (LOG2N == 15) ? 4 : (LOG2N <= 11 ? 1 : 2);
+    static constexpr int CH = LOG2N <= 11 ? 1 : 2;
     static constexpr int NW = (LOG2N <= 10) ? 2 : ((LOG2N <= 12) ? 4 : (LOG2N == 13 ? 8 : 16));
     static constexpr uint32_t TILE = (uint32_t)NW * CH * kChunk;
 };
 inline uint64_t round_tile(uint64_t N) { return N > 2048 ? (N > 4096 ? N : 4096) : (N > 1024 ? N : 1024); }
-
-template <int CH>
-__device__ __forceinline__ void load_raw(const float* __restrict__ xt, uint32_t lane_off, float4 (&a)[CH], float4 (&b)[CH]) {
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const uint32_t o = lane_off + (uint32_t)c * kChunk;
-        a[c] = *reinterpret_cast<const float4*>(xt + o);
-        b[c] = *reinterpret_cast<const float4*>(xt + o + 4);
-    }
-}
 
 template <int M, int LOG2N, bool CENTER>
 __global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const RParams r) {
     constexpr int CH = RoundGeo<LOG2N>::CH;
     constexpr uint32_t TILE = RoundGeo<LOG2N>::TILE;
     __shared__ float sm[2][32];             // alternate per worker: one barrier per tile suffices
-    __shared__ float4 stage[RoundGeo<LOG2N>::NW][128];
     const QParams& p = r.q;
-    const uint32_t t = blockIdx.x;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t lane_off = wave * (uint32_t)(CH * kChunk) + lane * kLaneElems;
 
     float acc[CH][8];
 #pragma unroll
@@ -65,21 +61,23 @@ __global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const 
         for (int e = 0; e < 8; ++e) acc[c][e] = 0.0f;
 
     if (t < p.full_tiles) {
-        const uint64_t e0 = (uint64_t)t * TILE;
-        float4 ca[CH], cb[CH], a[CH], b[CH], na[CH], nbuf[CH];
-        if (CENTER) load_raw<CH>(p.center + e0, lane_off, ca, cb);
-        load_raw<CH>(p.x + e0, lane_off, a, b);
+        const uint64_t o = (uint64_t)t * TILE + wave * (uint32_t)(CH * kChunk) + half_offset(lane);
+        // one branch per worker for the policy is free with one chunk per wave (99 against 103 us at d = 11 M,
+        // K = 8, bucket 2048) and costs 8% with two
+        const bool cached = CH == 1 && p.x_cached;
+        vec4 ca[CH], cb[CH], a[CH], b[CH], na[CH], nb[CH], sa[CH], sb[CH];
+        if (CENTER) load_halves<CH>(p.center + o, false, ca, cb);
+        load_halves<CH>(p.x + o, cached, a, b);
         for (uint32_t k = 0; k < r.K; ++k) {
-            if (k + 1 < r.K) load_raw<CH>(p.x + (uint64_t)(k + 1) * p.x_stride + e0, lane_off, na, nbuf);
+            // in flight while worker k is rounded: the next worker's coordinates, after the last the update's
+            const bool last = k + 1 == r.K;
+            load_halves<CH>((last ? r.w : p.x + (uint64_t)(k + 1) * p.x_stride) + o, cached, na, nb);
+            if (last && r.zsum) load_halves<CH>(r.zsum + o, cached, sa, sb);
             float v[CH][8];
 #pragma unroll
             for (int c = 0; c < CH; ++c) {
-                v[c][0] = a[c].x; v[c][1] = a[c].y; v[c][2] = a[c].z; v[c][3] = a[c].w;
-                v[c][4] = b[c].x; v[c][5] = b[c].y; v[c][6] = b[c].z; v[c][7] = b[c].w;
-                if (CENTER) {
-                    v[c][0] -= ca[c].x; v[c][1] -= ca[c].y; v[c][2] -= ca[c].z; v[c][3] -= ca[c].w;
-                    v[c][4] -= cb[c].x; v[c][5] -= cb[c].y; v[c][6] -= cb[c].z; v[c][7] -= cb[c].w;
-                }
+                if (CENTER) halves_to_lane(a[c] - ca[c], b[c] - cb[c], v[c]);
+                else halves_to_lane(a[c], b[c], v[c]);
             }
             unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
             FastCtx cx;
@@ -93,59 +91,47 @@ __global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const 
             cx.key0 = p.key0;
             cx.key1 = p.key1;
             cx.smax = p.smax;
+            cx.codes_cached = false;                     // nothing reads them here
             process_tile<M, LOG2N, true, RoundGeo<LOG2N>>(cx, v, t, sm[k & 1u], acc);
-            if (k + 1 < r.K) {
 #pragma unroll
-                for (int c = 0; c < CH; ++c) { a[c] = na[c]; b[c] = nbuf[c]; }
-            }
+            for (int c = 0; c < CH; ++c) { a[c] = na[c]; b[c] = nb[c]; }
         }
-    } else {                                              // the ragged last tile
-        for (uint32_t k = 0; k < r.K; ++k)
-            guarded_tile<M, CH, QESGD_NORM_L2, false, true>(p, k, t, sm[k & 1u], acc);
-    }
-
-    const float fk = (float)r.K;
-    if (t < p.full_tiles) {
-        // z moves from the lane-of-8 layout of the codes to one float4 of each 256-coordinate half
-        // per lane, so that every 128-bit access of a wave covers a contiguous KiB, through 2 KiB
-        // of LDS private to the wave (same wave on both sides: LDS keeps program order).
+        const float fk = (float)r.K;
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             float z[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) z[e] = (r.rcpK != 0.0f) ? acc[c][e] * r.rcpK : acc[c][e] / fk;
-            stage[wave][2 * lane] = make_float4(z[0], z[1], z[2], z[3]);
-            stage[wave][2 * lane + 1] = make_float4(z[4], z[5], z[6], z[7]);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const float4 za = stage[wave][lane];
-            const float4 zb = stage[wave][64 + lane];
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();                       // the next chunk overwrites the staging area
-            const uint64_t ia = (uint64_t)t * TILE + wave * (uint32_t)(CH * kChunk) + (uint32_t)c * kChunk + lane * 4u;
-            const uint64_t ib = ia + 256u;
-            const float4 wa = *reinterpret_cast<const float4*>(r.w + ia);
-            const float4 wb = *reinterpret_cast<const float4*>(r.w + ib);
+            vec4 za, zb;
+            lane_to_halves(z, za, zb);
+            const uint64_t ia = o + (uint32_t)c * kChunk, ib = ia + kChunk / 2;
             if (r.zbar) {
-                *reinterpret_cast<float4*>(r.zbar + ia) = za;
-                *reinterpret_cast<float4*>(r.zbar + ib) = zb;
+                store_stream(r.zbar + ia, za);
+                store_stream(r.zbar + ib, zb);
             }
-            *reinterpret_cast<float4*>(r.u + ia) = make_float4(wa.x + za.x, wa.y + za.y, wa.z + za.z, wa.w + za.w);
-            *reinterpret_cast<float4*>(r.u + ib) = make_float4(wb.x + zb.x, wb.y + zb.y, wb.z + zb.z, wb.w + zb.w);
+            store_stream(r.u + ia, a[c] + za);
+            store_stream(r.u + ib, b[c] + zb);
             if (r.zsum) {
-                const float4 sa = *reinterpret_cast<const float4*>(r.zsum + ia);
-                const float4 sb = *reinterpret_cast<const float4*>(r.zsum + ib);
-                *reinterpret_cast<float4*>(r.zsum + ia) = make_float4(sa.x + za.x, sa.y + za.y, sa.z + za.z, sa.w + za.w);
-                *reinterpret_cast<float4*>(r.zsum + ib) = make_float4(sb.x + zb.x, sb.y + zb.y, sb.z + zb.z, sb.w + zb.w);
+                store_stream(r.zsum + ia, sa[c] + za);
+                store_stream(r.zsum + ib, sb[c] + zb);
             }
         }
         return;
     }
+
+    // the ragged last tile
+    LaneSpan span[CH];
+    float v[CH][8];
+    guarded_spans<CH>(p, t, span);
+    for (uint32_t k = 0; k < r.K; ++k) {
+        guarded_load<CH>(p, k, span, v);
+        guarded_codes<M, CH, QESGD_NORM_L2, false, true>(p, k, span, v, sm[k & 1u], acc);
+    }
+    const float fk = (float)r.K;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         // the ragged tile, lane by lane (power-of-two buckets: slot == coordinate)
-        const uint64_t i = (uint64_t)t * TILE + lane_off + (uint32_t)c * kChunk;
+        const uint64_t i = (uint64_t)t * TILE + (wave * (uint32_t)CH + (uint32_t)c) * kChunk + lane * kLaneElems;
         if (i >= p.d) continue;
         const uint64_t rem = p.d - i;
         const uint32_t nvalid = rem < 8 ? (uint32_t)rem : 8u;
@@ -170,10 +156,9 @@ __global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const 
 
 template <int M, int LOG2N>
 void launch_one(const RParams& r, uint32_t blocks, hipStream_t st) {
-    if (r.q.center)
-        hipLaunchKernelGGL((k_round_fused<M, LOG2N, true>), dim3(blocks), dim3(RoundGeo<LOG2N>::NW * 64), 0, st, r);
-    else
-        hipLaunchKernelGGL((k_round_fused<M, LOG2N, false>), dim3(blocks), dim3(RoundGeo<LOG2N>::NW * 64), 0, st, r);
+    const dim3 grid(blocks), block(RoundGeo<LOG2N>::NW * 64);
+    if (r.q.center) hipLaunchKernelGGL((k_round_fused<M, LOG2N, true>), grid, block, 0, st, r);
+    else hipLaunchKernelGGL((k_round_fused<M, LOG2N, false>), grid, block, 0, st, r);
 }
 
 template <int M>
@@ -188,15 +173,14 @@ void launch_n(const RParams& r, uint32_t blocks, hipStream_t st) {
         case 11: launch_one<M, 11>(r, blocks, st); break;
         case 12: launch_one<M, 12>(r, blocks, st); break;
         case 13: launch_one<M, 13>(r, blocks, st); break;
-        case 14: launch_one<M, 14>(r, blocks, st); break;
-        default: launch_one<M, 15>(r, blocks, st); break;
+        default: launch_one<M, 14>(r, blocks, st); break;
     }
 }
 
 }  // namespace
 
 bool round_fused_covers(const Shape& sh, uint32_t norm_kind) {
-    return norm_kind == QESGD_NORM_L2 && sh.N == sh.B && sh.log2N >= 5 && sh.N <= kMaxSinglePassBucket &&
+    return norm_kind == QESGD_NORM_L2 && sh.N == sh.B && sh.log2N >= 5 && sh.N <= 16384 &&
            32u % sh.m == 0u;
 }
 
@@ -221,11 +205,13 @@ int launch_round_fused(const Shape& sh, const QuantizeArgs& a, const AggregateAr
     p.worker0 = a.worker0;
     p.smax = (float)(sh.s - 1);
     p.group_workers = a.K;
+    p.x_cached = input_cached(sh, a.K);
     const uint64_t tile = round_tile(sh.N);
     const uint64_t tiles = (sh.nb * sh.N + tile - 1) / tile;
     if (tiles >= (1ull << 31)) return QESGD_ERR_DIM;
     p.full_tiles = (uint32_t)(sh.d / tile);
     p.tail_tiles = (uint32_t)(tiles - p.full_tiles);
+    p.xcd_group = xcd_group_log2(tile);
     r.w = g.w_snap;
     r.zbar = g.zbar_out;
     r.u = g.u_out;

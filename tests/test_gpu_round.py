@@ -67,6 +67,19 @@ def test_one_launch_shapes_equal_two_calls(B, log2n, s, K):
         assert_same(out)
 
 
+@pytest.mark.parametrize("bucket", [32, 1024, 2048, 4096, 8192, 16384])
+@pytest.mark.parametrize("s", [2, 16, 256])
+@pytest.mark.parametrize("d,K", [(1_572_864, 3), (1_572_863, 9), (1_600_037, 16), (4_800_000, 3)])
+def test_both_sides_of_the_one_launch_rule(B, bucket, s, d, K):
+    """Many workers take one launch only from 1.5 M coordinates on; the vectors' cache policy changes at
+    the last size.  (Buckets of 32768 never do.)"""
+    g = torch.Generator(device="cuda").manual_seed(d + K)
+    slab = torch.randn(K, (d + 63) // 64 * 64, generator=g, device="cuda") * 1e-3
+    w = torch.randn(d, generator=g, device="cuda")
+    _, out = both_forms(B, slab, None, d, s, bucket, 0, 99, 3, K, w, w * 1e-2)
+    assert_same(out)
+
+
 @pytest.mark.parametrize("d,bucket,s,K", [(4096 * 5 + 100, 512, 16, 4), (8192 * 3 + 8, 8192, 256, 3), (70_001, 4096, 2, 16)])
 def test_center_and_optional_outputs(B, d, bucket, s, K):
     slab, c, w, zsum0 = make_inputs(d, K, d, True)
