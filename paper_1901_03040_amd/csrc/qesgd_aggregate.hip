@@ -27,7 +27,7 @@ namespace {
 // Waves per workgroup; the waves share nothing.  Two measured 1-2% faster than four or eight at
 // d = 11 M .. 138 M (0.532 against 0.539 ms at d = 138 M, K = 8), one the same as two.
 constexpr uint32_t kAggWaves = 2;
-template <int M, bool UPDATE, bool ZSUM, bool ZBAR>
+template <int M, bool UPDATE, bool ZSUM, bool ZBAR, bool ZACC = false>
 __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(const AParams p) {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t block = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
@@ -41,7 +41,8 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
     const uint64_t ia = wave_base + half_offset(lane);    // vector layout: one float4 of each half
     const uint64_t ib = ia + kChunk / 2;
 
-    vec4 wa[1], wb[1], sa[1], sb[1];
+    vec4 wa[1], wb[1], sa[1], sb[1], ta[1], tb[1];
+    if (ZACC) load_halves<1>(p.z_acc + ia, p.vec_cached, ta, tb);
     if (UPDATE) load_halves<1>(p.w + ia, p.vec_cached, wa, wb);
     if (ZSUM) load_halves<1>(p.zsum + ia, p.vec_cached, sa, sb);
 
@@ -146,6 +147,12 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
         store_stream(p.zbar + ia, za);
         store_stream(p.zbar + ib, zb);
     }
+    if (ZACC) {
+        za = ta[0] + za;
+        zb = tb[0] + zb;
+        store_stream(p.z_acc + ia, za);
+        store_stream(p.z_acc + ib, zb);
+    }
     if (UPDATE) {
         store_stream(p.u + ia, wa[0] + za);
         store_stream(p.u + ib, wb[0] + zb);
@@ -197,6 +204,7 @@ int launch_aggregate(const Shape& sh, const AggregateArgs& a) {
     p.zbar = a.zbar_out;
     p.u = a.u_out;
     p.zsum = a.zsum;
+    p.z_acc = a.z_acc;
     p.packed_stride = a.packed_stride;
     p.d = sh.d;
     p.B = sh.B;
@@ -226,7 +234,9 @@ int launch_aggregate(const Shape& sh, const AggregateArgs& a) {
     const bool upd = a.w_snap != nullptr, zs = a.zsum != nullptr, zb = a.zbar_out != nullptr;
 #define QESGD_LAUNCH_AGG(MM)                                                                              \
     do {                                                                                                 \
-        if (upd && zs && zb) hipLaunchKernelGGL((k_unpack_aggregate_update<MM, true, true, true>), grid, block, 0, a.stream, p);        \
+        if (a.z_acc && zs) hipLaunchKernelGGL((k_unpack_aggregate_update<MM, true, true, true, true>), grid, block, 0, a.stream, p);     \
+        else if (a.z_acc) hipLaunchKernelGGL((k_unpack_aggregate_update<MM, true, false, true, true>), grid, block, 0, a.stream, p);     \
+        else if (upd && zs && zb) hipLaunchKernelGGL((k_unpack_aggregate_update<MM, true, true, true>), grid, block, 0, a.stream, p);        \
         else if (upd && zs) hipLaunchKernelGGL((k_unpack_aggregate_update<MM, true, true, false>), grid, block, 0, a.stream, p);        \
         else if (upd && zb) hipLaunchKernelGGL((k_unpack_aggregate_update<MM, true, false, true>), grid, block, 0, a.stream, p);        \
         else if (upd) hipLaunchKernelGGL((k_unpack_aggregate_update<MM, true, false, false>), grid, block, 0, a.stream, p);             \

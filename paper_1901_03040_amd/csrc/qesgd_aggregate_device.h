@@ -15,6 +15,7 @@ struct AParams {
     float* zbar;
     float* u;
     float* zsum;
+    float* z_acc;
     uint64_t packed_stride;
     uint64_t d;
     uint64_t B;
@@ -169,6 +170,13 @@ __device__ __forceinline__ void aggregate_lane_guarded(const AParams& p, uint64_
         for (int e = 0; e < 8; ++e) z[e] = acc[e] / fk;
     }
     if (p.zbar) store8(p.zbar, i, nvalid, z);
+    if (p.z_acc) {
+        float z8[8];
+        load8(p.z_acc, i, nvalid, z8);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) z[e] = z8[e] + z[e];
+        store8(p.z_acc, i, nvalid, z);
+    }
     if (p.w) {
         float w8[8], u8[8];
         load8(p.w, i, nvalid, w8);

@@ -242,6 +242,27 @@ int qesgd_round(const float* x_slab, uint64_t x_stride, const float* center, uin
     return rc != QESGD_OK ? rc : launch_aggregate(sh, g);
 }
 
+int qesgd_gradient_round(const float* x_slab, uint64_t x_stride, uint64_t d, uint32_t s, uint64_t bucket,
+                         uint32_t norm_kind, uint64_t seed, uint32_t round, uint32_t K, void* packed_slab,
+                         uint64_t packed_stride, void* workspace, size_t workspace_bytes, const float* w_snap,
+                         float* step_out, float* z_inout, float* u_out, float* zsum_inout, void* stream) {
+    if (!step_out || !z_inout) return QESGD_ERR_NULL;
+    Shape sh, sh2;
+    QuantizeArgs q;
+    AggregateArgs g;
+    int rc = quantize_check(x_slab, x_stride, nullptr, d, s, bucket, norm_kind, seed, round, 0, K, packed_slab,
+                            packed_stride, workspace, workspace_bytes, stream, false, &sh, &q);
+    if (rc != QESGD_OK) return rc;
+    rc = aggregate_check(packed_slab, packed_stride, K, d, s, bucket, w_snap, step_out, u_out, zsum_inout, true,
+                         stream, &sh2, &g);
+    if (rc != QESGD_OK) return rc;
+    if (!aligned(z_inout, 16)) return QESGD_ERR_ALIGN;
+    g.z_acc = z_inout;
+    if (sh.N > kMaxSinglePassBucket && round_fused_covers(sh, norm_kind) && round_fused_pays(sh, K)) return launch_round_fused(sh, q, g);
+    rc = launch_quantize(sh, q);
+    return rc != QESGD_OK ? rc : launch_aggregate(sh, g);
+}
+
 static bool fixed_bits_ok(uint32_t b) { return b == 2 || b == 4 || b == 8 || b == 16; }
 
 int qesgd_quantize_fixed(const float* x, const float* center, uint64_t d, float delta, uint32_t b,

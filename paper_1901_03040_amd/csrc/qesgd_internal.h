@@ -19,9 +19,6 @@ constexpr uint32_t kChunk = kLaneElems * kWaveSize;   // 512
 constexpr uint64_t kMaxSinglePassBucket = 32768;
 // Tile of the partial-sum pass used for larger buckets.
 constexpr uint64_t kPartialTile = 4096;
-// Input bytes that the two-pass path lets the first pass read before the second pass re-reads
-// them: well inside the 256 MB memory-side cache, which also has to take the packed output.
-constexpr uint64_t kCacheBudgetBytes = 160ull << 20;
 // Cache policy of the streams.  The non-temporal one is right for what comes from HBM; what fits the
 // 256 MB memory-side cache from one round to the next, or from the workers' call to the server's, is
 // better read and written with the ordinary one.  Measured over d = 0.3 .. 12 M, K = 2 .. 16, with two
@@ -82,6 +79,7 @@ struct AggregateArgs {
     float* zbar_out;         // nullable
     float* u_out;            // nullable iff w_snap is
     float* zsum;             // nullable
+    float* z_acc;            // nullable: z_acc += the mean, and z_acc takes the mean's place in u and zsum
     hipStream_t stream;
 };
 
@@ -89,8 +87,11 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a);
 // Device address of the current GPU's static scratch (kStaticScratchFloats floats).
 int static_scratch(float** out);
 int launch_aggregate(const Shape& sh, const AggregateArgs& a);
+// Wide buckets whose slot space equals coordinate space (a power of two, or a single bucket), L2 scale.
+bool dense_wide(const Shape& sh, uint32_t norm_kind);
 // One launch for a whole round (quantise K workers, sum, update) where the shape allows it:
-// power-of-two bucket of 32..16384 coordinates, L2 scale, level width dividing 32.
+// power-of-two bucket of 32..16384 coordinates, L2 scale, level width dividing 32; or, behind the launches
+// that find the scales, a dense wide bucket with the L2 scale.
 bool round_fused_covers(const Shape& sh, uint32_t norm_kind);
 // One launch or two.  One launch takes the workers of a tile one after the other, about 1 us each (2.4 us
 // with buckets of 4096 and more, whose waves meet at a barrier per worker), which only a chip full of
@@ -99,7 +100,7 @@ bool round_fused_covers(const Shape& sh, uint32_t norm_kind);
 // 1024: 30 / 23 us; 2 M, K = 16, bucket 8192: 40 / 43 us; 1 M, K = 8, bucket 512: 14.0 / 14.2 us; 1 M,
 // K = 2, bucket 16384: 10.2 / 10.8 us.  Buckets of 32768 would need 300 registers per lane.
 inline bool round_fused_pays(const Shape& sh, uint32_t K) {
-    return sh.d >= (3u << 19) || K <= (sh.N <= 2048 ? 8u : 2u);
+    return sh.d >= (3u << 19) || K <= (sh.N > 2048 && sh.N <= 32768 ? 2u : 8u);
 }
 int launch_round_fused(const Shape& sh, const QuantizeArgs& a, const AggregateArgs& g);
 int launch_apply_update(const float* w, const float* zbar, float* u, float* zsum, uint64_t d,

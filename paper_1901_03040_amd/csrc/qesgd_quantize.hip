@@ -37,17 +37,12 @@ static __device__ __align__(256) float scratch[qesgd::kStaticScratchFloats];
 namespace qesgd {
 namespace {
 
-// PRE (second pass of a wide bucket): workers and tiles are walked backwards, so that the launch
-// starts with what the partial-sum pass read last and most of it is still in the memory-side cache.
+// PRE: second pass of a wide bucket.
 template <int M, int CH, int KIND, bool PRE>
 __global__ void k_quantize_pack(const QParams p) {
     __shared__ float sm[32];
-    uint32_t k = blockIdx.x / p.tiles_per_worker;
-    uint32_t local = blockIdx.x - k * p.tiles_per_worker;
-    if (PRE) {
-        k = p.group_workers - 1u - k;
-        local = p.tiles_per_worker - 1u - local;
-    }
+    const uint32_t k = blockIdx.x / p.tiles_per_worker;
+    const uint32_t local = blockIdx.x - k * p.tiles_per_worker;
     guarded_tile<M, CH, KIND, PRE>(p, k, p.tile0 + local, sm);
 }
 
@@ -196,14 +191,14 @@ __device__ __forceinline__ void guarded_partial_tile(const QParams& p, uint32_t 
 // power-of-two bucket, or a single bucket).  First pass: tree sum of one 4096-coordinate tile into
 // the workspace.  Last pass: the quantiser with the bucket scale read from the norms plane; a tile
 // never straddles two such buckets, so the scale is one scalar per workgroup.
+// Both walk (tiles, workers) in the same order, so that a vector that fits the L2s is found in the same one.
 template <bool CENTER>
 __global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
     constexpr int KIND = QESGD_NORM_L2;
     __shared__ float sm[4];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t per_worker = p.full_tiles + p.tail_tiles;
-    const uint32_t k = blockIdx.x / per_worker;
-    const uint32_t t = blockIdx.x - k * per_worker;
+    const uint32_t k = blockIdx.y;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
     if (t >= p.full_tiles) {                              // the ragged last tile of the worker (at most one)
         guarded_partial_tile<KIND>(p, k, t, sm);
         return;
@@ -218,24 +213,41 @@ __global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
     if (threadIdx.x == 0) p.workspace[(uint64_t)k * p.ws_tiles_per_worker + t] = (sm[0] + sm[1]) + (sm[2] + sm[3]);
 }
 
+// merged: every wave finishes its bucket's tree by itself while its coordinates are on their way, which
+// saves the launch between the passes; the bucket's first tile writes the scale.
 template <int M, bool CENTER>
 __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p) {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t per_worker = p.full_tiles + p.tail_tiles;
-    const uint32_t kf = blockIdx.x / per_worker;
-    const uint32_t k = p.group_workers - 1u - kf;                       // backwards: see k_quantize_pack
-    const uint32_t t = per_worker - 1u - (blockIdx.x - kf * per_worker);
-    if (t >= p.full_tiles) {                              // the ragged last tile of the worker (at most one)
-        guarded_tile<M, 2, QESGD_NORM_L2, true>(p, k, t, nullptr);
+    const uint32_t k = blockIdx.y;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
+    unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
+    float* __restrict__ norms = reinterpret_cast<float*>(out + p.norms_off);
+    const uint64_t e0 = (uint64_t)t * kPartialTile, g0 = e0 / kLaneElems;
+    const uint64_t b = e0 >> p.log2N;
+    const bool full = t < p.full_tiles;
+    float v[2][8];
+    LaneSpan span[2];
+    if (full) {
+        const uint64_t w0 = e0 + wave * (2u * kChunk);
+        load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, p.x_cached, v);
+    } else {                                              // the ragged last tile of the worker (at most one)
+        guarded_spans<2>(p, t, span);
+        guarded_load<2>(p, k, span, v);
+    }
+    Scale sc;
+    if (p.merged) {
+        const uint32_t P = 1u << (p.log2N - 12u);
+        const uint64_t left = p.data_tiles - b * P;
+        const float* __restrict__ ws = p.workspace + (uint64_t)k * p.ws_tiles_per_worker + b * P;
+        sc = scale_of_total<M, QESGD_NORM_L2>(wave_total<QESGD_NORM_L2>(ws, P, left < P ? (uint32_t)left : P, lane));
+        if (threadIdx.x == 0 && (t & (P - 1u)) == 0u) norms[b] = sc.norm;
+    } else {
+        sc = scale_of_norm<M>(norms[b]);
+    }
+    if (!full) {
+        guarded_codes<M, 2, QESGD_NORM_L2, true>(p, k, span, v, nullptr, nullptr, true, sc.norm);
         return;
     }
-    unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
-    const float* __restrict__ norms = reinterpret_cast<const float*>(out + p.norms_off);
-    const uint64_t e0 = (uint64_t)t * kPartialTile, g0 = e0 / kLaneElems;
-    const uint64_t w0 = e0 + wave * (2u * kChunk);
-    float v[2][8];
-    load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, p.x_cached, v);
-    const Scale sc = scale_of_norm<M>(norms[e0 >> p.log2N]);
     const uint32_t idx0 = wave * 2u * kWaveSize + lane;
     uint32_t sign_byte[2], bits[2][4];
 #pragma unroll
@@ -408,12 +420,12 @@ void launch_fast(const QParams& p, uint32_t m, hipStream_t st) {
 }
 
 template <int M>
-void launch_pre_fast_m(const QParams& p, uint32_t blocks, hipStream_t st) {
-    if (p.center) hipLaunchKernelGGL((k_quantize_pack_pre_fast<M, true>), dim3(blocks), dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((k_quantize_pack_pre_fast<M, false>), dim3(blocks), dim3(256), 0, st, p);
+void launch_pre_fast_m(const QParams& p, dim3 blocks, hipStream_t st) {
+    if (p.center) hipLaunchKernelGGL((k_quantize_pack_pre_fast<M, true>), blocks, dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((k_quantize_pack_pre_fast<M, false>), blocks, dim3(256), 0, st, p);
 }
 
-void launch_pre_fast(const QParams& p, uint32_t m, uint32_t blocks, hipStream_t st) {
+void launch_pre_fast(const QParams& p, uint32_t m, dim3 blocks, hipStream_t st) {
     switch (m) {
         case 1: launch_pre_fast_m<1>(p, blocks, st); break;
         case 2: launch_pre_fast_m<2>(p, blocks, st); break;
@@ -467,7 +479,7 @@ int static_scratch(float** out) {
     return QESGD_OK;
 }
 
-int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
+QParams quantize_params(const Shape& sh, const QuantizeArgs& a) {
     QParams p{};
     p.x = a.x;
     p.center = a.center;
@@ -490,6 +502,40 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
     p.group_workers = a.K;
     p.x_cached = input_cached(sh, a.K);
     p.codes_cached = a.K * sh.lay.payload_bytes <= kCachedCodeBytes;
+    return p;
+}
+
+// First part of the dense two-pass path (slot space equals coordinate space: the bucket is a power of two or
+// there is one bucket; L2 scale): partial sums of all workers, and their trees where the last pass does not
+// finish them itself.  Up to 512 partial sums per bucket it does: reading them again in every wave then costs
+// less than the launch (quantise and aggregate, d = 0.1 M, K = 4, one bucket: 17.6 us with the launch, 14.8
+// without; at 25.6 M coordinates every wave would read 25 KB).
+int launch_dense_norms(QParams& p, const Shape& sh, const QuantizeArgs& a) {
+    const uint64_t P = sh.N / kPartialTile;
+    p.ws_tiles_per_worker = (uint32_t)(sh.nb * P);
+    p.data_tiles = (sh.d + kPartialTile - 1) / kPartialTile;
+    p.full_tiles = (uint32_t)(sh.d / kPartialTile);
+    p.tile0 = p.full_tiles;
+    p.tail_tiles = (uint32_t)(p.data_tiles - p.full_tiles);
+    p.xcd_group = xcd_group_log2(kPartialTile);
+    p.merged = P <= 512;                                 // <= kMergedLeaves
+    const dim3 grid((uint32_t)p.data_tiles, a.K);
+    if (p.center) hipLaunchKernelGGL(k_tile_partials_fast<true>, grid, dim3(256), 0, a.stream, p);
+    else hipLaunchKernelGGL(k_tile_partials_fast<false>, grid, dim3(256), 0, a.stream, p);
+    if (!p.merged) {
+        uint32_t waves = 1;
+        while (waves < 16 && (uint64_t)waves * 1024u < P) waves <<= 1;
+        hipLaunchKernelGGL(k_finish_norms<QESGD_NORM_L2>, dim3((uint32_t)(sh.nb * a.K)), dim3(waves * kWaveSize), 0, a.stream, p, P, 1u);
+    }
+    return check_launch();
+}
+
+bool dense_wide(const Shape& sh, uint32_t norm_kind) {
+    return sh.N > kMaxSinglePassBucket && norm_kind == QESGD_NORM_L2 && (sh.N == sh.B || sh.nb == 1) && sh.d >= kPartialTile;
+}
+
+int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
+    QParams p = quantize_params(sh, a);
 
     const uint64_t slots = sh.nb * sh.N;                 // slot space of one worker
     const bool two_pass = sh.N > kMaxSinglePassBucket;
@@ -509,68 +555,37 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
     if (tiles * a.K >= (1ull << 31)) return QESGD_ERR_DIM;
     const dim3 block(nwaves * kWaveSize);
 
+    if (dense_wide(sh, a.norm_kind)) {
+        // All workers at once in both passes: taking them in groups that fit the memory-side cache, with the
+        // second pass walking backwards, cost a launch gap per group and pass and gained no bandwidth.
+        const int rc = launch_dense_norms(p, sh, a);
+        if (rc != QESGD_OK) return rc;
+        launch_pre_fast(p, sh.m, dim3((uint32_t)p.data_tiles, a.K), a.stream);
+        return check_launch();
+    }
     if (two_pass) {
-        // Slot space equals coordinate space when the bucket is a power of two or there is a single
-        // bucket; then only the tiles that hold coordinates are visited, and the ones wholly inside
-        // the vector take the unguarded kernels.
+        // Buckets that are no power of two, and the max norm: guarded kernels over all of slot space (over the
+        // tiles that hold coordinates, where slot space equals coordinate space).
         const uint64_t P = sh.N / kPartialTile;          // tiles == nb * P
         uint32_t finish_waves = 1;
         while (finish_waves < 16 && (uint64_t)finish_waves * 1024u < P) finish_waves <<= 1;
-        const dim3 finish_block(finish_waves * kWaveSize);
         const bool dense = sh.N == sh.B || sh.nb == 1;
-        const uint64_t data_tiles = dense ? (sh.d + kPartialTile - 1) / kPartialTile : tiles;
-        const uint64_t full_tiles = (dense && a.norm_kind == QESGD_NORM_L2) ? sh.d / kPartialTile : 0;
         p.ws_tiles_per_worker = (uint32_t)tiles;
-        p.data_tiles = data_tiles;
-        p.full_tiles = (uint32_t)full_tiles;
-        p.tile0 = (uint32_t)full_tiles;
-        p.tiles_per_worker = (uint32_t)(data_tiles - full_tiles);
-        // The second pass re-reads what the first read.  Workers are taken in groups whose input
-        // fits the memory-side cache (all of them at once when everything fits), the partial sums,
-        // the rest of the tree and the quantiser one group after the other, and the quantiser walks
-        // its group backwards: what the first pass read last is read first.
-        const uint64_t worker_bytes = 4u * sh.d;
-        uint32_t group = a.K;
-        if ((uint64_t)a.K * worker_bytes > kCacheBudgetBytes) {
-            const uint64_t fit = kCacheBudgetBytes / worker_bytes;
-            group = fit < 1 ? 1u : (uint32_t)fit;
+        p.data_tiles = dense ? (sh.d + kPartialTile - 1) / kPartialTile : tiles;
+        p.tile0 = 0;
+        p.tiles_per_worker = (uint32_t)p.data_tiles;
+        const dim3 grid((uint32_t)(p.data_tiles * a.K)), finish_grid((uint32_t)(sh.nb * a.K)), finish_block(finish_waves * kWaveSize);
+        if (a.norm_kind == QESGD_NORM_L2) {
+            hipLaunchKernelGGL(k_tile_partials<QESGD_NORM_L2>, grid, block, 0, a.stream, p);
+            hipLaunchKernelGGL(k_finish_norms<QESGD_NORM_L2>, finish_grid, finish_block, 0, a.stream, p, P, dense ? 1u : 0u);
+        } else {
+            hipLaunchKernelGGL(k_tile_partials<QESGD_NORM_MAX>, grid, block, 0, a.stream, p);
+            hipLaunchKernelGGL(k_finish_norms<QESGD_NORM_MAX>, finish_grid, finish_block, 0, a.stream, p, P, dense ? 1u : 0u);
         }
-        for (uint32_t k0 = 0; k0 < a.K; k0 += group) {
-            const uint32_t kg = a.K - k0 < group ? a.K - k0 : group;
-            p.x = a.x + (uint64_t)k0 * a.x_stride;
-            p.packed = a.packed + (uint64_t)k0 * a.packed_stride;
-            p.workspace = a.workspace + (uint64_t)k0 * tiles;
-            p.worker0 = a.worker0 + k0;
-            p.group_workers = kg;
-            const dim3 finish_grid((uint32_t)(sh.nb * kg));
-            int rc;
-            if (full_tiles > 0) {
-                // dense tiles unguarded, the ragged last tile of each worker guarded in the same launches
-                p.tail_tiles = (uint32_t)(data_tiles - full_tiles);
-                const dim3 grid((uint32_t)(data_tiles * kg));
-                if (p.center) hipLaunchKernelGGL(k_tile_partials_fast<true>, grid, block, 0, a.stream, p);
-                else hipLaunchKernelGGL(k_tile_partials_fast<false>, grid, block, 0, a.stream, p);
-                hipLaunchKernelGGL(k_finish_norms<QESGD_NORM_L2>, finish_grid, finish_block, 0, a.stream, p, P, 1u);
-                rc = check_launch();
-                if (rc != QESGD_OK) return rc;
-                launch_pre_fast(p, sh.m, (uint32_t)(data_tiles * kg), a.stream);
-            } else {
-                const dim3 grid((uint32_t)(data_tiles * kg));
-                if (a.norm_kind == QESGD_NORM_L2) {
-                    hipLaunchKernelGGL(k_tile_partials<QESGD_NORM_L2>, grid, block, 0, a.stream, p);
-                    hipLaunchKernelGGL(k_finish_norms<QESGD_NORM_L2>, finish_grid, finish_block, 0, a.stream, p, P, dense ? 1u : 0u);
-                } else {
-                    hipLaunchKernelGGL(k_tile_partials<QESGD_NORM_MAX>, grid, block, 0, a.stream, p);
-                    hipLaunchKernelGGL(k_finish_norms<QESGD_NORM_MAX>, finish_grid, finish_block, 0, a.stream, p, P, dense ? 1u : 0u);
-                }
-                rc = check_launch();
-                if (rc != QESGD_OK) return rc;
-                launch_m<2, true>(p, sh.m, a.norm_kind, grid, block, a.stream);
-            }
-            rc = check_launch();
-            if (rc != QESGD_OK) return rc;
-        }
-        return QESGD_OK;
+        const int rc = check_launch();
+        if (rc != QESGD_OK) return rc;
+        launch_m<2, true>(p, sh.m, a.norm_kind, grid, block, a.stream);
+        return check_launch();
     }
 
     if (fast) {

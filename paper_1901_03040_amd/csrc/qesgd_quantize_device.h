@@ -10,7 +10,6 @@
 #include "qesgd_internal.h"
 
 namespace qesgd {
-namespace {
 
 struct QParams {
     const float* x;
@@ -31,6 +30,7 @@ struct QParams {
     uint32_t group_workers;      // workers covered by this launch
     uint32_t xcd_group;          // fast quantize kernels: log2 of the tiles that one XCD takes in a row
     uint32_t ws_tiles_per_worker;  // partial sums: workspace entries per worker (nb * N / 4096)
+    bool merged;                 // last pass: finish the tree from the partial sums (see wave_total)
     uint64_t data_tiles;         // partial sums: 4096-slot tiles of a worker that hold coordinates
     uint32_t key0, key1;
     uint32_t round;
@@ -39,6 +39,12 @@ struct QParams {
     bool x_cached;               // read the vectors with the ordinary cache policy
     bool codes_cached;           // write the level planes with the ordinary cache policy
 };
+
+// Kernel parameters of a quantise call, and the first launches of the dense two-pass path (qesgd_quantize.hip).
+QParams quantize_params(const Shape& sh, const QuantizeArgs& a);
+int launch_dense_norms(QParams& p, const Shape& sh, const QuantizeArgs& a);
+
+namespace {
 
 
 // ---------------------------------------------------------------------------
@@ -126,6 +132,29 @@ __device__ __forceinline__ float lds_tree16(const float* sm, uint32_t base, uint
         for (int r = 0; r < 16; r += 2 * w) a[r] = combine<KIND>(a[r], a[r + w]);
     }
     return a[0];
+}
+
+// The rest of a bucket's tree by one wave, for at most 1024 partial sums of which the first `valid` were
+// written (the others are +0, the identity of both combines): a lane takes 16 consecutive ones, index
+// bits 0-3, the lanes bits 4-9.  P, a power of two >= 16, entries are readable.
+constexpr uint32_t kMergedLeaves = 1024;
+template <int KIND>
+__device__ __forceinline__ float wave_total(const float* __restrict__ ws, uint32_t P, uint32_t valid, uint32_t lane) {
+    const uint32_t first = lane * 16u;
+    const float* __restrict__ src = ws + (first < P ? first : 0u);
+    float q[16];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const vec4 a = load_cached(src + 4 * i);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[4 * i + e] = first + (uint32_t)(4 * i + e) < valid ? a[e] : 0.0f;
+    }
+#pragma unroll
+    for (int w = 1; w < 16; w <<= 1) {
+#pragma unroll
+        for (int r = 0; r < 16; r += 2 * w) q[r] = combine<KIND>(q[r], q[r + w]);
+    }
+    return lane_butterfly<KIND>(q[0], 64);
 }
 
 // ---------------------------------------------------------------------------
@@ -433,12 +462,14 @@ __device__ __forceinline__ void guarded_load(const QParams& p, uint32_t k, const
 }
 
 // One tile of worker k with every access guarded per lane, its coordinates loaded.  PRE = true: the scales
-// were computed by the partial-sum passes and are read from the norms plane.  sm: 32 floats of LDS.
+// were computed by the partial-sum passes and are read from the norms plane, or the tile's one scale is
+// handed in (given).  sm: 32 floats of LDS, not used with PRE.
 // ACC = true: the dequantised codes are also added to acc[chunk][0..8) (the server's sum over
 // workers, for the launch that runs a whole round).
 template <int M, int CH, int KIND, bool PRE, bool ACC = false>
 __device__ __forceinline__ void guarded_codes(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], const float (&v)[CH][8],
-                                              float* sm, float (*acc)[8] = nullptr) {
+                                              float* sm, float (*acc)[8] = nullptr, bool given = false,
+                                              float given_norm = 0.0f) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = threadIdx.x >> 6;
     unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
@@ -450,7 +481,7 @@ __device__ __forceinline__ void guarded_codes(const QParams& p, uint32_t k, cons
     Scale sc[CH];
     if (PRE) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c) sc[c] = scale_of_norm<M>(span[c].nvalid ? norms[span[c].bucket] : 1.0f);
+        for (int c = 0; c < CH; ++c) sc[c] = scale_of_norm<M>(!span[c].nvalid ? 1.0f : given ? given_norm : norms[span[c].bucket]);
     } else {
         float t[CH];
         const uint32_t lanes_per_bucket = (uint32_t)((N < kChunk ? N : kChunk) / kLaneElems);

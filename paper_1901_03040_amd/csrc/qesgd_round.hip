@@ -30,6 +30,7 @@ struct RParams {
     float* zbar;
     float* u;
     float* zsum;
+    float* z_acc;    // nullable (wide buckets only): z_acc += the mean
     float rcpK;      // exact 1/K when K is a power of two, else 0
     uint32_t K;
 };
@@ -154,6 +155,156 @@ __global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const 
     }
 }
 
+// The same behind the launches that found the scales of wide buckets: no wave needs another, so a wave owns
+// 512 coordinates of every worker.  Lane k holds worker k's scale (from the norms plane, or finished from the
+// partial sums by the workgroup's waves in turn) and hands it out as a scalar.  ZACC: z_acc += the mean.
+// Bound by the stream of vectors; the codes are written but not read back.  Gradient round as four calls
+// (partial sums, trees and codes per group of workers, mean, two updates) / as one call:
+//   d = 25.6 M, K = 16, s = 256, one bucket    921 -> 771 us (both passes over x at 6.7 TB/s: 490 us)
+//   d = 853 K, K = 8, s = 256, one bucket     31.0 -> 21.3 us (partial sums, this; the chain of 8 workers)
+//   d = 30 M, K = 4, s = 8, one bucket         378 -> 288 us
+// One wave per workgroup would finish every scale by itself; four share that work.
+constexpr uint32_t kWideWaves = 4;
+template <int M, bool CENTER, bool ZACC>
+__global__ void __launch_bounds__(kWideWaves * 64) k_round_wide(const RParams r) {
+    __shared__ float total[64];
+    const QParams& p = r.q;
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group) * kWideWaves + wave;
+    const uint64_t c0 = (uint64_t)t * kChunk;             // first coordinate of the wave, in bucket b
+    const bool full = c0 + kChunk <= p.d;
+    const uint64_t o = c0 + half_offset(lane);
+    vec4 ca[1], cb[1], a[1], b1[1], na[1], nb[1], sa[1], sb[1], ta[1], tb[1];
+    if (full) {
+        if (CENTER) load_halves<1>(p.center + o, false, ca, cb);
+        load_halves<1>(p.x + o, p.x_cached, a, b1);
+    }
+
+    float norm = 1.0f;
+    if (p.merged) {                                       // the workgroup's waves lie in one bucket (a multiple of 32768, or the only one)
+        const uint64_t first = (uint64_t)(t - wave) * kChunk;
+        const uint32_t P = 1u << (p.log2N - 12u);
+        const uint64_t b = first >> p.log2N, left = p.data_tiles - b * P;
+        for (uint32_t k = wave; k < r.K; k += kWideWaves) {
+            const float sum = wave_total<QESGD_NORM_L2>(p.workspace + (uint64_t)k * p.ws_tiles_per_worker + b * P, P,
+                                                        left < P ? (uint32_t)left : P, lane);
+            if (lane == 0) total[k] = sum;
+        }
+        __syncthreads();
+        if (lane < r.K) {
+            norm = sqrtf(total[lane]);
+            if (wave == 0 && first == b << p.log2N)
+                reinterpret_cast<float*>(p.packed + (uint64_t)lane * p.packed_stride + p.norms_off)[b] = norm;
+        }
+    } else if (lane < r.K && c0 < p.d) {
+        norm = reinterpret_cast<const float*>(p.packed + (uint64_t)lane * p.packed_stride + p.norms_off)[c0 >> p.log2N];
+    }
+    if (c0 >= p.d) return;
+    const float my_step = norm / p.smax;
+
+    float acc[1][8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[0][e] = 0.0f;
+    const float fk = (float)r.K;
+
+    if (!full) {                                          // ragged last wave
+        const uint64_t i = c0 + lane * kLaneElems;
+        LaneSpan span[1];
+        span[0] = lane_span(i, p);
+        float v[1][8];
+        for (uint32_t k = 0; k < r.K; ++k) {
+            guarded_load<1>(p, k, span, v);
+            const float nk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(norm), k));
+            guarded_codes<M, 1, QESGD_NORM_L2, true, true>(p, k, span, v, nullptr, acc, true, nk);
+        }
+        if (i >= p.d) return;
+        float z[8], t8[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) z[e] = (r.rcpK != 0.0f) ? acc[0][e] * r.rcpK : acc[0][e] / fk;
+        const uint32_t nvalid = span[0].nvalid;
+        if (r.zbar) store8(r.zbar, i, nvalid, z);
+        if (ZACC) {
+            load8(r.z_acc, i, nvalid, t8);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) z[e] = t8[e] + z[e];
+            store8(r.z_acc, i, nvalid, z);
+        }
+        load8(r.w, i, nvalid, t8);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t8[e] = t8[e] + z[e];
+        store8(r.u, i, nvalid, t8);
+        if (r.zsum) {
+            load8(r.zsum, i, nvalid, t8);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t8[e] = t8[e] + z[e];
+            store8(r.zsum, i, nvalid, t8);
+        }
+        return;
+    }
+
+    const float my_mul = scale_of_norm<M>(norm).mul;
+    const uint64_t direct = __builtin_amdgcn_ballot_w64(norm >= 0x1p-60f && norm <= 0x1p60f);
+    const uint64_t g0 = c0 / kLaneElems;
+    for (uint32_t k = 0; k < r.K; ++k) {
+        const bool last = k + 1 == r.K;
+        load_halves<1>((last ? r.w : p.x + (uint64_t)(k + 1) * p.x_stride) + o, p.x_cached, na, nb);
+        if (last && r.zsum) load_halves<1>(r.zsum + o, p.x_cached, sa, sb);
+        if (last && ZACC) load_halves<1>(r.z_acc + o, p.x_cached, ta, tb);
+        float v[8];
+        if (CENTER) halves_to_lane(a[0] - ca[0], b1[0] - cb[0], v);
+        else halves_to_lane(a[0], b1[0], v);
+        Scale sc;
+        sc.norm = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(norm), k));
+        sc.mul = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_mul), k));
+        sc.direct = (direct >> k) & 1u;
+        const float step = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_step), k));
+        uint32_t rnd[4], sign_byte[1], bits[1][4];
+        philox4x32_10((uint32_t)g0 + lane, (uint32_t)(g0 >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        round_and_pack<M>(v, rnd, sc, sign_byte[0], bits[0]);
+        unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
+        if constexpr (32 % M == 0) {
+            store_chunks<M, 1>(out + p.signs_off + g0, out + p.levels_off + g0 * M, lane, false, sign_byte, bits);
+        } else {
+            store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off),
+                           c0 + lane * kLaneElems, 8u, lane, sign_byte[0], bits[0]);
+        }
+        accumulate8<M>(acc[0], sign_byte[0], bits[0], step);
+        a[0] = na[0];
+        b1[0] = nb[0];
+    }
+    float z[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) z[e] = (r.rcpK != 0.0f) ? acc[0][e] * r.rcpK : acc[0][e] / fk;
+    vec4 za, zb;
+    lane_to_halves(z, za, zb);
+    const uint64_t ob = o + kChunk / 2;
+    if (r.zbar) {
+        store_stream(r.zbar + o, za);
+        store_stream(r.zbar + ob, zb);
+    }
+    if (ZACC) {
+        za = ta[0] + za;
+        zb = tb[0] + zb;
+        store_stream(r.z_acc + o, za);
+        store_stream(r.z_acc + ob, zb);
+    }
+    store_stream(r.u + o, a[0] + za);
+    store_stream(r.u + ob, b1[0] + zb);
+    if (r.zsum) {
+        store_stream(r.zsum + o, sa[0] + za);
+        store_stream(r.zsum + ob, sb[0] + zb);
+    }
+}
+
+template <int M>
+void launch_wide(const RParams& r, hipStream_t st) {
+    const uint64_t blocks = (r.q.d + kWideWaves * kChunk - 1) / (kWideWaves * kChunk);
+    const dim3 grid((uint32_t)blocks), block(kWideWaves * 64);
+    if (r.z_acc) hipLaunchKernelGGL((k_round_wide<M, false, true>), grid, block, 0, st, r);
+    else if (r.q.center) hipLaunchKernelGGL((k_round_wide<M, true, false>), grid, block, 0, st, r);
+    else hipLaunchKernelGGL((k_round_wide<M, false, false>), grid, block, 0, st, r);
+}
+
 template <int M, int LOG2N>
 void launch_one(const RParams& r, uint32_t blocks, hipStream_t st) {
     const dim3 grid(blocks), block(RoundGeo<LOG2N>::NW * 64);
@@ -177,9 +328,19 @@ void launch_n(const RParams& r, uint32_t blocks, hipStream_t st) {
     }
 }
 
+int check_launch() {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) {
+        set_last_hip_error((int)e);
+        return QESGD_ERR_HIP;
+    }
+    return QESGD_OK;
+}
+
 }  // namespace
 
 bool round_fused_covers(const Shape& sh, uint32_t norm_kind) {
+    if (dense_wide(sh, norm_kind)) return true;
     return norm_kind == QESGD_NORM_L2 && sh.N == sh.B && sh.log2N >= 5 && sh.N <= 16384 &&
            32u % sh.m == 0u;
 }
@@ -187,37 +348,37 @@ bool round_fused_covers(const Shape& sh, uint32_t norm_kind) {
 int launch_round_fused(const Shape& sh, const QuantizeArgs& a, const AggregateArgs& g) {
     RParams r{};
     QParams& p = r.q;
-    p.x = a.x;
-    p.center = a.center;
-    p.packed = a.packed;
-    p.x_stride = a.x_stride;
-    p.packed_stride = a.packed_stride;
-    p.d = sh.d;
-    p.B = sh.B;
-    p.nb = sh.nb;
-    p.norms_off = sh.lay.norms_off;
-    p.signs_off = sh.lay.signs_off;
-    p.levels_off = sh.lay.levels_off;
-    p.log2N = sh.log2N;
-    p.key0 = (uint32_t)a.seed;
-    p.key1 = (uint32_t)(a.seed >> 32);
-    p.round = a.round;
-    p.worker0 = a.worker0;
-    p.smax = (float)(sh.s - 1);
-    p.group_workers = a.K;
-    p.x_cached = input_cached(sh, a.K);
+    p = quantize_params(sh, a);
+    r.w = g.w_snap;
+    r.zbar = g.zbar_out;
+    r.u = g.u_out;
+    r.zsum = g.zsum;
+    r.z_acc = g.z_acc;
+    r.K = a.K;
+    r.rcpK = ((a.K & (a.K - 1)) == 0) ? 1.0f / (float)a.K : 0.0f;
+    if (sh.N > kMaxSinglePassBucket) {
+        const int rc = launch_dense_norms(p, sh, a);
+        if (rc != QESGD_OK) return rc;
+        p.xcd_group = xcd_group_log2(kWideWaves * kChunk);
+        switch (sh.m) {
+            case 1: launch_wide<1>(r, a.stream); break;
+            case 2: launch_wide<2>(r, a.stream); break;
+            case 3: launch_wide<3>(r, a.stream); break;
+            case 4: launch_wide<4>(r, a.stream); break;
+            case 5: launch_wide<5>(r, a.stream); break;
+            case 6: launch_wide<6>(r, a.stream); break;
+            case 7: launch_wide<7>(r, a.stream); break;
+            case 8: launch_wide<8>(r, a.stream); break;
+            default: launch_wide<16>(r, a.stream); break;
+        }
+        return check_launch();
+    }
     const uint64_t tile = round_tile(sh.N);
     const uint64_t tiles = (sh.nb * sh.N + tile - 1) / tile;
     if (tiles >= (1ull << 31)) return QESGD_ERR_DIM;
     p.full_tiles = (uint32_t)(sh.d / tile);
     p.tail_tiles = (uint32_t)(tiles - p.full_tiles);
     p.xcd_group = xcd_group_log2(tile);
-    r.w = g.w_snap;
-    r.zbar = g.zbar_out;
-    r.u = g.u_out;
-    r.zsum = g.zsum;
-    r.K = a.K;
-    r.rcpK = ((a.K & (a.K - 1)) == 0) ? 1.0f / (float)a.K : 0.0f;
     switch (sh.m) {
         case 1: launch_n<1>(r, (uint32_t)tiles, a.stream); break;
         case 2: launch_n<2>(r, (uint32_t)tiles, a.stream); break;
@@ -225,12 +386,7 @@ int launch_round_fused(const Shape& sh, const QuantizeArgs& a, const AggregateAr
         case 8: launch_n<8>(r, (uint32_t)tiles, a.stream); break;
         default: launch_n<16>(r, (uint32_t)tiles, a.stream); break;
     }
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) {
-        set_last_hip_error((int)e);
-        return QESGD_ERR_HIP;
-    }
-    return QESGD_OK;
+    return check_launch();
 }
 
 }  // namespace qesgd

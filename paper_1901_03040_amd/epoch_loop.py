@@ -67,12 +67,10 @@ class QesgdEpochLoop:
         k's -eta * g_k, quantised with the scale of what is sent (per bucket, or one scale over the
         whole vector when bucket >= d).  z <- z + (1/K) sum_k Q(-eta g_k), u <- w_t + z.  Returns u."""
         assert step_slab.shape[0] == self.K and step_slab.stride(0) % 4 == 0
-        B.qesgd_quantize_pack_batched(step_slab, step_slab.stride(0), None, self.d, self.s, self.bucket,
-                                      B.NORM_L2, self.seed, self.round_id, self.K, self.packed,
-                                      self.packed.stride(0), self.ws)
-        B.qesgd_unpack_aggregate(self.packed, self.packed.stride(0), self.K, self.d, self.s, self.bucket, self.step)
-        B.qesgd_apply_update(self.z, self.step, self.z, None, self.d)              # z += mean step
-        B.qesgd_apply_update(self.w, self.z, self.u, self._zsum_arg(last), self.d)  # u = w_t + z, zsum += z
+        # step = mean of the quantised rows, z += step, u = w_t + z, zsum += z
+        B.qesgd_gradient_round(step_slab, step_slab.stride(0), self.d, self.s, self.bucket, B.NORM_L2, self.seed,
+                               self.round_id, self.K, self.packed, self.packed.stride(0), self.w, self.step, self.z,
+                               self.u, self._zsum_arg(last), workspace=self.ws)
         self.round_id += 1
         self.steps_in_epoch += 1
         return self.u
