@@ -3,6 +3,8 @@
 // range, stochastic floor/ceil inside; its inverse fused with u = w_t + z (Alg. 2); and the
 // end-of-epoch commit w_{t+1} = w_t + (1/K_t) sum_k z_{t,k} (Alg. 3, last step).
 // No reduction is needed, so these are plain streaming kernels.
+#include <type_traits>
+
 #include "qesgd_device.h"
 #include "qesgd_internal.h"
 
@@ -16,6 +18,8 @@ struct FParams {
     uint64_t d;
     uint64_t code_words;
     uint32_t full_tiles;   // tiles that lie wholly inside the vector
+    uint32_t xcd_group;    // log2 of the tiles that one XCD takes in a row
+    bool x_cached, codes_cached;   // ordinary cache policy for the vectors, for the codes
     float delta;
     float lo, hi;          // -2^(b-1), 2^(b-1)-1 as floats
     uint32_t key0, key1, round, worker;
@@ -65,25 +69,45 @@ struct Divider {
     }
 };
 
-// Variates, rounding and the stores for the 8 coordinates of a lane that start at coordinate i
-// (a multiple of 8), of which nvalid (0..8) exist.  Whole waves call this together: the 2-bit
-// form combines the two lanes of a pair.
+// Variates and rounding for the 8 coordinates of a lane that start at coordinate i (a multiple of 8), of
+// which nvalid (0..8) exist.
 template <int B, bool EXACT_DIV>
-__device__ __forceinline__ void fixed_chunk(const FParams& p, const Divider<EXACT_DIV>& div, const float (&v)[8],
-                                            uint64_t i, uint32_t nvalid, uint32_t lane) {
+__device__ __forceinline__ void fixed_codes(const FParams& p, const Divider<EXACT_DIV>& div, const float (&v)[8],
+                                            uint64_t i, uint32_t nvalid, uint32_t (&code)[8]) {
     constexpr uint32_t mask = (1u << B) - 1u;
     const uint64_t g = i >> 3;
     uint32_t rnd[4];
     philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker, p.round, p.key0, p.key1, rnd);
-
-    uint32_t code[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
         const uint32_t r16 = variate16(rnd, e);
         const int32_t k = round_on_grid(div(v[e]), r16);
         code[e] = ((uint32_t)e < nvalid) ? ((uint32_t)k & mask) : 0u;     // padding bits stay 0
     }
+}
 
+// Stores where all 8 coordinates exist: a lane's codes are B bytes, 64 lanes write consecutive bytes.
+template <int B, bool CACHED>
+__device__ __forceinline__ void store_fixed_full(const FParams& p, uint64_t i, const uint32_t (&code)[8]) {
+    typedef uint32_t uvec2 __attribute__((ext_vector_type(2)));
+    typedef uint32_t uvec4 __attribute__((ext_vector_type(4)));
+    typedef std::conditional_t<B == 2, unsigned short, std::conditional_t<B == 4, uint32_t, std::conditional_t<B == 8, uvec2, uvec4>>> field;
+    uint32_t w[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e * B / 32] |= code[e] << (e * B % 32);
+    field f;
+    if constexpr (B == 8) f = uvec2{w[0], w[1]};
+    else if constexpr (B == 16) f = uvec4{w[0], w[1], w[2], w[3]};
+    else f = (field)w[0];
+    field* dst = reinterpret_cast<field*>(reinterpret_cast<unsigned char*>(p.codes) + (i >> 3) * B);
+    if (CACHED) *dst = f;
+    else __builtin_nontemporal_store(f, dst);
+}
+
+// Stores at the ragged end.  Whole waves call this together: the 2-bit form combines the two lanes of a pair.
+template <int B>
+__device__ __forceinline__ void store_fixed_ragged(const FParams& p, uint64_t i, uint32_t nvalid, uint32_t lane,
+                                                   const uint32_t (&code)[8]) {
     uint32_t* __restrict__ out = p.codes;
     if (B == 2) {
         uint32_t h = 0;
@@ -120,65 +144,57 @@ __device__ __forceinline__ void fixed_chunk(const FParams& p, const Divider<EXAC
     }
 }
 
-// A workgroup owns a tile of kFixedWaves waves x kFixedChunks chunks x 512 coordinates; a lane
-// owns 8 consecutive coordinates of each of its wave's chunks (two 128-bit loads, one Philox call).
-// All loads of a tile are issued before the first variate is drawn.  Tiles wholly inside the
-// vector run without guards; the ragged last tile guards every access per lane.  The waves share
-// nothing, and the smallest unit measured fastest: at d = 138 M, b = 8, one wave x one chunk 0.144 ms,
-// four waves x one chunk 0.148 ms, four waves x two / four chunks 0.155 / 0.158 ms, persistent
-// workgroups that keep the next tile's loads in flight 0.165 ms or more.
-constexpr int kFixedChunks = 1;
+// A workgroup owns a tile of kFixedWaves waves x 512 coordinates; a lane owns 8 consecutive coordinates (one
+// Philox call), loaded as halves (see halves_to_lane).  Tiles wholly inside the vector run without guards;
+// the ragged last tile guards every access per lane.  The waves share nothing, and the smallest unit
+// measured fastest (d = 138 M, b = 8, both calls: one wave 572 us, two or four 577 us).  Bound by the read
+// stream with the vector issue next to it.  Quantise and dequantise before (32 bytes per lane, ordinary
+// policy, tiles dealt round-robin) / after: d = 138 M, b = 8: 624 -> 572 us = 6.3 TB/s; 25.6 M: 117 -> 106 us;
+// 12 M, b = 16: 59 -> 51 us; up to 3 M the same.
 constexpr uint32_t kFixedWaves = 1;
-constexpr uint32_t kFixedTile = kFixedWaves * kFixedChunks * kChunk;
+constexpr uint32_t kFixedTile = kFixedWaves * kChunk;
 
 template <int B, bool CENTER, bool EXACT_DIV>
 __global__ void __launch_bounds__(kFixedWaves * 64) k_quantize_fixed(const FParams p) {
-    constexpr int CH = kFixedChunks;
     const Divider<EXACT_DIV> div(p.delta, p.lo, p.hi);
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint64_t base = (uint64_t)blockIdx.x * kFixedTile + wave * (uint32_t)(CH * kChunk) + lane * kLaneElems;
-    float v[CH][8];
-    if (blockIdx.x < p.full_tiles) {
-        float4 a[CH], b[CH], ca[CH], cb[CH];
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const uint64_t i = base + (uint32_t)c * kChunk;
-            a[c] = *reinterpret_cast<const float4*>(p.x + i);
-            b[c] = *reinterpret_cast<const float4*>(p.x + i + 4);
-            if (CENTER) {
-                ca[c] = *reinterpret_cast<const float4*>(p.center + i);
-                cb[c] = *reinterpret_cast<const float4*>(p.center + i + 4);
-            }
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
+    const uint64_t w0 = (uint64_t)t * kFixedTile + wave * kChunk;
+    const uint64_t i = w0 + lane * kLaneElems;
+    float v[8];
+    uint32_t code[8];
+    if (t < p.full_tiles) {
+        vec4 a[1], b[1], ca[1], cb[1];
+        load_halves<1>(p.x + w0 + half_offset(lane), p.x_cached, a, b);
+        if (CENTER) {
+            load_halves<1>(p.center + w0 + half_offset(lane), p.x_cached, ca, cb);
+            halves_to_lane(a[0] - ca[0], b[0] - cb[0], v);
+        } else {
+            halves_to_lane(a[0], b[0], v);
         }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            v[c][0] = a[c].x; v[c][1] = a[c].y; v[c][2] = a[c].z; v[c][3] = a[c].w;
-            v[c][4] = b[c].x; v[c][5] = b[c].y; v[c][6] = b[c].z; v[c][7] = b[c].w;
-            if (CENTER) {
-                v[c][0] -= ca[c].x; v[c][1] -= ca[c].y; v[c][2] -= ca[c].z; v[c][3] -= ca[c].w;
-                v[c][4] -= cb[c].x; v[c][5] -= cb[c].y; v[c][6] -= cb[c].z; v[c][7] -= cb[c].w;
-            }
+        fixed_codes<B, EXACT_DIV>(p, div, v, i, 8u, code);
+        if (p.codes_cached) {
+            asm volatile("; cached");                     // keeps the arms apart (see load_halves)
+            store_fixed_full<B, true>(p, i, code);
+            asm volatile("; cached end");
+        } else {
+            store_fixed_full<B, false>(p, i, code);
         }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) fixed_chunk<B, EXACT_DIV>(p, div, v[c], base + (uint32_t)c * kChunk, 8u, lane);
         return;
     }
+    // whole waves stay together: the cross-lane step of the 2-bit form needs both lanes of a pair
+    const uint32_t nvalid = i >= p.d ? 0u : (p.d - i < 8 ? (uint32_t)(p.d - i) : 8u);
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const uint64_t i = base + (uint32_t)c * kChunk;
-        // whole waves stay together: the cross-lane step of the 2-bit form needs both lanes of a pair
-        const uint32_t nvalid = i >= p.d ? 0u : (p.d - i < 8 ? (uint32_t)(p.d - i) : 8u);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float t = 0.0f;
-            if ((uint32_t)e < nvalid) {
-                t = p.x[i + e];
-                if (CENTER) t -= p.center[i + e];
-            }
-            v[c][e] = t;
+    for (int e = 0; e < 8; ++e) {
+        float x = 0.0f;
+        if ((uint32_t)e < nvalid) {
+            x = p.x[i + e];
+            if (CENTER) x -= p.center[i + e];
         }
-        fixed_chunk<B, EXACT_DIV>(p, div, v[c], i, nvalid, lane);
+        v[e] = x;
     }
+    fixed_codes<B, EXACT_DIV>(p, div, v, i, nvalid, code);
+    store_fixed_ragged<B>(p, i, nvalid, lane, code);
 }
 
 struct DParams {
@@ -189,6 +205,8 @@ struct DParams {
     float* zsum;
     uint64_t d;
     uint64_t code_words;
+    uint32_t xcd_group;
+    bool vec_cached;       // read w and zsum with the ordinary cache policy
     float delta;
 };
 
@@ -197,13 +215,25 @@ __device__ __forceinline__ float decode(uint32_t field, int bits, float delta) {
     return (float)k * delta;
 }
 
-// One float4 per lane for the vectors, 4*B code bits per lane.
+// One float4 per lane for the vectors (a wave's accesses are contiguous KiB), 4*B code bits per lane.
 template <int B>
 __global__ void __launch_bounds__(256) k_dequantize_fixed_update(const DParams p) {
     constexpr uint32_t mask = (1u << B) - 1u;
-    const uint64_t i = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4u;
+    const uint64_t i = ((uint64_t)xcd_tile(blockIdx.x, gridDim.x, p.xcd_group) * blockDim.x + threadIdx.x) * 4u;
     if (i >= p.d) return;
     const uint32_t nvalid = p.d - i < 4 ? (uint32_t)(p.d - i) : 4u;
+    vec4 w4 = {0.0f, 0.0f, 0.0f, 0.0f}, s4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (nvalid == 4) {
+        if (p.vec_cached) {
+            asm volatile("; cached");                     // keeps the arms apart (see load_halves)
+            if (p.u) w4 = load_cached(p.w + i);
+            if (p.zsum) s4 = load_cached(p.zsum + i);
+            asm volatile("; cached end");
+        } else {
+            if (p.u) w4 = load_stream(p.w + i);
+            if (p.zsum) s4 = load_stream(p.zsum + i);
+        }
+    }
     const unsigned char* bytes = reinterpret_cast<const unsigned char*>(p.codes);
     uint32_t f[4];
     if (B == 2) {
@@ -228,15 +258,10 @@ __global__ void __launch_bounds__(256) k_dequantize_fixed_update(const DParams p
     for (int e = 0; e < 4; ++e) z[e] = decode(f[e], B, p.delta);
 
     if (nvalid == 4) {
-        if (p.z) *reinterpret_cast<float4*>(p.z + i) = make_float4(z[0], z[1], z[2], z[3]);
-        if (p.u) {
-            const float4 a = *reinterpret_cast<const float4*>(p.w + i);
-            *reinterpret_cast<float4*>(p.u + i) = make_float4(a.x + z[0], a.y + z[1], a.z + z[2], a.w + z[3]);
-        }
-        if (p.zsum) {
-            const float4 s = *reinterpret_cast<const float4*>(p.zsum + i);
-            *reinterpret_cast<float4*>(p.zsum + i) = make_float4(s.x + z[0], s.y + z[1], s.z + z[2], s.w + z[3]);
-        }
+        const vec4 z4 = {z[0], z[1], z[2], z[3]};
+        if (p.z) store_stream(p.z + i, z4);
+        if (p.u) store_stream(p.u + i, w4 + z4);
+        if (p.zsum) store_stream(p.zsum + i, s4 + z4);
     } else {
         for (uint32_t e = 0; e < nvalid; ++e) {
             const float ze = e == 0 ? z[0] : (e == 1 ? z[1] : z[2]);
@@ -296,6 +321,9 @@ int launch_quantize_fixed(const float* x, const float* center, uint64_t d, float
     const uint64_t blocks = (d + kFixedTile - 1) / kFixedTile;
     if (blocks >= (1ull << 31)) return QESGD_ERR_DIM;
     p.full_tiles = (uint32_t)(d / kFixedTile);
+    p.xcd_group = xcd_group_log2(kFixedTile);
+    p.x_cached = 4u * d <= kCachedInputBytes && 24u * d + 4u * p.code_words <= kCachedRoundBytes;
+    p.codes_cached = 4u * p.code_words <= kCachedCodeBytes;
     const dim3 grid((uint32_t)blocks), block(kFixedWaves * 64);
     // the short division is used where its scaling-free form is exact (see Divider)
     const bool exact_div = !(delta >= 0x1p-60f && delta <= 0x1p60f);
@@ -327,6 +355,8 @@ int launch_dequantize_fixed_update(const void* codes, uint64_t d, float delta, u
     p.d = d;
     p.code_words = (d * b + 31) / 32;
     p.delta = delta;
+    p.xcd_group = xcd_group_log2(256 * 4);
+    p.vec_cached = 20u * d + 4u * p.code_words <= kCachedUpdateBytes;
     const uint64_t lanes = (d + 3) / 4;
     const uint64_t blocks = (lanes + 255) / 256;
     if (blocks >= (1ull << 31)) return QESGD_ERR_DIM;
