@@ -112,12 +112,68 @@ __device__ __forceinline__ void lane_to_halves(const float (&v)[8], vec4& a, vec
     }
 }
 
+// The first `count` of those coordinates: a float4 that is not wholly inside is taken element by element
+// (stores leave the rest of it alone, loads give 0 there).
+__device__ __forceinline__ vec4 load_part(const float* __restrict__ p, uint32_t at, uint32_t count) {
+    vec4 r = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (at + 4u <= count) {
+        r = load_cached(p + at);
+    } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 3; ++e)
+            if (at + e < count) r[e] = p[at + e];
+    }
+    return r;
+}
+__device__ __forceinline__ void store_part(float* __restrict__ p, uint32_t at, uint32_t count, const vec4& v) {
+    if (at + 4u <= count) {
+        *reinterpret_cast<vec4*>(p + at) = v;
+    } else {
+#pragma unroll
+        for (uint32_t e = 0; e < 3; ++e)
+            if (at + e < count) p[at + e] = v[e];
+    }
+}
+// CH x 512 coordinates of a vector from p on, one float4 of each half chunk per lane; at the ragged end of the
+// vector (FULL = false) the first `count`, the rest 0.
+template <int CH, bool FULL>
+__device__ __forceinline__ void load_chunks(const float* __restrict__ p, uint32_t lane, uint32_t count, bool cached,
+                                            vec4 (&a)[CH], vec4 (&b)[CH]) {
+    const uint32_t h = half_offset(lane);
+    if (FULL) {
+        load_halves<CH>(p + h, cached, a, b);
+    } else {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            a[c] = load_part(p, h + c * kChunk, count);
+            b[c] = load_part(p, h + c * kChunk + kChunk / 2, count);
+        }
+    }
+}
+// One float4 of each half of 512 coordinates, back.
+template <bool FULL>
+__device__ __forceinline__ void store_chunk(float* __restrict__ p, uint32_t lane, uint32_t count, const vec4& a, const vec4& b) {
+    const uint32_t h = half_offset(lane);
+    if (FULL) {
+        store_stream(p + h, a);
+        store_stream(p + h + kChunk / 2, b);
+    } else {
+        store_part(p, h, count, a);
+        store_part(p, h + kChunk / 2, count, b);
+    }
+}
+
 // Tile of workgroup b.  Workgroups are handed to the 8 XCDs round-robin by id, so consecutive ids
 // would spread every stretch of memory over all of them.  Groups of 2^lg tiles (256 KB of input, set
 // by the host) go to one XCD instead: its reads and packed writes are then one run of addresses each
 // (M = 1, bucket 4096: 0.70 against 0.77 ms at 1.07 G coordinates; groups of 64 K .. 1 M coordinates
 // are within 2% of each other).  What is left over at the end stays in order.
+// Workgroup 0 takes the last tile, the ragged one where there is one: its guarded code is the longest
+// way through the kernel and would otherwise run on alone at the end.
 __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t tiles, uint32_t lg) {
+    --tiles;
+    if (b == 0) return tiles;
+    --b;
     if (b >= ((tiles >> (lg + 3u)) << (lg + 3u))) return b;
     const uint32_t r = b >> 3;
     return ((((r >> lg) << 3) | (b & 7u)) << lg) | (r & ((1u << lg) - 1u));

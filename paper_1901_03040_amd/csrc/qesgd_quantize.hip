@@ -41,9 +41,7 @@ namespace {
 template <int M, int CH, int KIND, bool PRE>
 __global__ void k_quantize_pack(const QParams p) {
     __shared__ float sm[32];
-    const uint32_t k = blockIdx.x / p.tiles_per_worker;
-    const uint32_t local = blockIdx.x - k * p.tiles_per_worker;
-    guarded_tile<M, CH, KIND, PRE>(p, k, p.tile0 + local, sm);
+    guarded_tile<M, CH, KIND, PRE>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
 }
 
 // One tile per workgroup; the ragged last tile of a worker, if any, runs the guarded code in
@@ -76,10 +74,6 @@ __global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_fast
         t = blockIdx.x;
     }
     t = xcd_tile(t, tiles, p.xcd_group);
-    if (t >= p.full_tiles) {                              // the ragged last tile of the worker (at most one)
-        guarded_tile<M, CH, QESGD_NORM_L2, false>(p, k, t, sm);
-        return;
-    }
     const float* __restrict__ xk = p.x + (uint64_t)k * p.x_stride;
     const float* __restrict__ ck = p.center;
     unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
@@ -98,6 +92,12 @@ __global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_fast
 
     float buf[CH][8];
     const uint64_t w0 = (uint64_t)t * TILE + cx.wave * (uint32_t)(CH * kChunk);
+    if (t >= p.full_tiles) {                              // the ragged last tile of the worker (at most one)
+        const uint32_t count = (uint32_t)(p.d - (uint64_t)t * TILE);
+        load_tile<CH, CENTER, false>(xk + w0, ck + w0, cx.lane, true, buf, count_from(count, cx.wave * (uint32_t)(CH * kChunk)));
+        process_tile<M, LOG2N, false, Geo<M, LOG2N>, false>(cx, buf, t, sm, nullptr, count);
+        return;
+    }
     load_tile<CH, CENTER>(xk + w0, ck + w0, cx.lane, p.x_cached, buf);
     process_tile<M, LOG2N>(cx, buf, t, sm);
 }
@@ -110,12 +110,8 @@ __global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_cent
     constexpr int CH = Geo<M, LOG2N>::CH;
     constexpr uint32_t TILE = Geo<M, LOG2N>::TILE;
     __shared__ float sm[2][32];             // alternate per worker: one barrier per tile suffices
-    const uint32_t t = blockIdx.x;
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
     const uint32_t K = p.group_workers;
-    if (t >= p.full_tiles) {                              // the ragged last tile
-        for (uint32_t k = 0; k < K; ++k) guarded_tile<M, CH, QESGD_NORM_L2, false>(p, k, t, sm[k & 1u]);
-        return;
-    }
     FastCtx cx;
     cx.lane = threadIdx.x & 63u;
     cx.wave = threadIdx.x >> 6;
@@ -125,6 +121,21 @@ __global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_cent
     cx.smax = p.smax;
     cx.codes_cached = p.codes_cached;
     const uint64_t e0 = (uint64_t)t * TILE;
+    if (t >= p.full_tiles) {                              // the ragged last tile
+        const uint32_t count = (uint32_t)(p.d - e0), first = cx.wave * (uint32_t)(CH * kChunk);
+        for (uint32_t k = 0; k < K; ++k) {
+            unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
+            cx.norms = reinterpret_cast<float*>(out + p.norms_off);
+            cx.signs = out + p.signs_off;
+            cx.levels = out + p.levels_off;
+            cx.worker = p.worker0 + k;
+            float v[CH][8];
+            load_tile<CH, true, false>(p.x + (uint64_t)k * p.x_stride + e0 + first, p.center + e0 + first, cx.lane, true, v,
+                                       count_from(count, first));
+            process_tile<M, LOG2N, false, Geo<M, LOG2N>, false>(cx, v, t, sm[k & 1u], nullptr, count);
+        }
+        return;
+    }
     const uint64_t w0 = e0 + cx.wave * (uint32_t)(CH * kChunk) + half_offset(cx.lane);
     vec4 ca[CH], cb[CH], a[CH], b[CH], na[CH], nb2[CH];
 #pragma unroll
@@ -168,16 +179,12 @@ __device__ __forceinline__ void guarded_partial_tile(const QParams& p, uint32_t 
     constexpr int CH = 2;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = threadIdx.x >> 6;
-    const float* __restrict__ x = p.x + (uint64_t)k * p.x_stride;
-    const uint64_t slot0 = ((uint64_t)tile * 4 + wave) * (uint64_t)(CH * kChunk) + lane * kLaneElems;
-    float t[CH];
+    LaneSpan span[CH];
+    float v[CH][8], t[CH];
+    guarded_spans<CH>(p, tile, span);
+    guarded_load<CH>(p, k, span, v);
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        float v[8];
-        const LaneSpan s = lane_span(slot0 + (uint64_t)c * kChunk, p);
-        load_lane(x, p.center, s, v);
-        t[c] = lane_butterfly<KIND>(lane_tree<KIND>(v), 64);
-    }
+    for (int c = 0; c < CH; ++c) t[c] = lane_butterfly<KIND>(lane_tree<KIND>(v[c]), 64);
     t[0] = combine<KIND>(t[0], t[1]);
     if (lane == 0) sm[wave] = t[0];
     __syncthreads();
@@ -245,7 +252,7 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
         sc = scale_of_norm<M>(norms[b]);
     }
     if (!full) {
-        guarded_codes<M, 2, QESGD_NORM_L2, true>(p, k, span, v, nullptr, nullptr, true, sc.norm);
+        guarded_codes<M, 2, QESGD_NORM_L2, true>(p, k, span, v, nullptr, true, sc.norm);
         return;
     }
     const uint32_t idx0 = wave * 2u * kWaveSize + lane;
@@ -261,8 +268,7 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
     } else {
 #pragma unroll
         for (uint32_t c = 0; c < 2; ++c)
-            store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off),
-                           (g0 + idx0 + c * kWaveSize) * kLaneElems, 8u, lane, sign_byte[c], bits[c]);
+            store_whole<M>(out + p.signs_off, out + p.levels_off, e0 + (wave * 2u + c) * kChunk, lane, p.codes_cached, sign_byte[c], bits[c]);
     }
 }
 
@@ -275,9 +281,7 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
 template <int KIND>
 __global__ void k_tile_partials(const QParams p) {
     __shared__ float sm[4];
-    const uint32_t k = blockIdx.x / p.tiles_per_worker;
-    const uint32_t tile = p.tile0 + (blockIdx.x - k * p.tiles_per_worker);
-    guarded_partial_tile<KIND>(p, k, tile, sm);
+    guarded_partial_tile<KIND>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
 }
 
 // Finishes the tree of one bucket: P leaves (a power of two, >= 16), of which only the first
@@ -515,7 +519,6 @@ int launch_dense_norms(QParams& p, const Shape& sh, const QuantizeArgs& a) {
     p.ws_tiles_per_worker = (uint32_t)(sh.nb * P);
     p.data_tiles = (sh.d + kPartialTile - 1) / kPartialTile;
     p.full_tiles = (uint32_t)(sh.d / kPartialTile);
-    p.tile0 = p.full_tiles;
     p.tail_tiles = (uint32_t)(p.data_tiles - p.full_tiles);
     p.xcd_group = xcd_group_log2(kPartialTile);
     p.merged = P <= 512;                                 // <= kMergedLeaves
@@ -572,9 +575,8 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         const bool dense = sh.N == sh.B || sh.nb == 1;
         p.ws_tiles_per_worker = (uint32_t)tiles;
         p.data_tiles = dense ? (sh.d + kPartialTile - 1) / kPartialTile : tiles;
-        p.tile0 = 0;
-        p.tiles_per_worker = (uint32_t)p.data_tiles;
-        const dim3 grid((uint32_t)(p.data_tiles * a.K)), finish_grid((uint32_t)(sh.nb * a.K)), finish_block(finish_waves * kWaveSize);
+        p.xcd_group = xcd_group_log2(kPartialTile);
+        const dim3 grid((uint32_t)p.data_tiles, a.K), finish_grid((uint32_t)(sh.nb * a.K)), finish_block(finish_waves * kWaveSize);
         if (a.norm_kind == QESGD_NORM_L2) {
             hipLaunchKernelGGL(k_tile_partials<QESGD_NORM_L2>, grid, block, 0, a.stream, p);
             hipLaunchKernelGGL(k_finish_norms<QESGD_NORM_L2>, finish_grid, finish_block, 0, a.stream, p, P, dense ? 1u : 0u);
@@ -596,9 +598,8 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         launch_fast(p, sh.m, a.stream);
         return check_launch();
     }
-    p.tile0 = 0;
-    p.tiles_per_worker = (uint32_t)tiles;
-    const dim3 grid((uint32_t)(tiles * a.K));
+    p.xcd_group = xcd_group_log2(tile);
+    const dim3 grid((uint32_t)tiles, a.K);
     if (ch == 2) launch_m<2, false>(p, sh.m, a.norm_kind, grid, block, a.stream);
     else launch_m<4, false>(p, sh.m, a.norm_kind, grid, block, a.stream);
     return check_launch();

@@ -23,8 +23,6 @@ struct QParams {
     uint64_t nb;
     uint64_t norms_off, signs_off, levels_off;
     uint32_t log2N;
-    uint32_t tile0;              // generic kernel: first tile it covers
-    uint32_t tiles_per_worker;   // generic kernel: tiles it covers per worker
     uint32_t full_tiles;         // fast kernels: tiles per worker that lie wholly inside the vector
     uint32_t tail_tiles;         // fast quantize kernel: ragged tiles per worker after those (0 or 1)
     uint32_t group_workers;      // workers covered by this launch
@@ -393,208 +391,6 @@ __device__ __forceinline__ void store_codes(uint32_t* __restrict__ sign_words, u
     }
 }
 
-// ---------------------------------------------------------------------------
-// Guarded tile: the shared body of the generic kernel and of the ragged last tile.
-// ---------------------------------------------------------------------------
-// Where the 8 slots of this lane fall: bucket, first coordinate, how many of
-// them are real coordinates (0..8), and whether they open the bucket.
-struct LaneSpan {
-    uint64_t bucket;
-    uint64_t i;        // first coordinate (a multiple of 8)
-    uint32_t nvalid;
-    bool opens_bucket;
-};
-
-__device__ __forceinline__ LaneSpan lane_span(uint64_t slot, const QParams& p) {
-    LaneSpan s;
-    const uint64_t N = 1ull << p.log2N;
-    s.bucket = slot >> p.log2N;
-    const uint64_t j = slot & (N - 1);
-    uint64_t len = 0;
-    if (s.bucket < p.nb) {
-        const uint64_t rem = p.d - s.bucket * p.B;
-        len = rem < p.B ? rem : p.B;
-    }
-    s.nvalid = j < len ? (uint32_t)((len - j) < 8 ? (len - j) : 8) : 0u;
-    s.i = s.bucket * p.B + j;
-    s.opens_bucket = (j == 0) && (s.bucket < p.nb);
-    return s;
-}
-
-__device__ __forceinline__ void load_lane(const float* __restrict__ x, const float* __restrict__ center,
-                                          const LaneSpan& s, float (&v)[8]) {
-    if (s.nvalid == 8) {
-        const float4 a = *reinterpret_cast<const float4*>(x + s.i);
-        const float4 b = *reinterpret_cast<const float4*>(x + s.i + 4);
-        v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-        v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-        if (center) {
-            const float4 ca = *reinterpret_cast<const float4*>(center + s.i);
-            const float4 cb = *reinterpret_cast<const float4*>(center + s.i + 4);
-            v[0] -= ca.x; v[1] -= ca.y; v[2] -= ca.z; v[3] -= ca.w;
-            v[4] -= cb.x; v[5] -= cb.y; v[6] -= cb.z; v[7] -= cb.w;
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float t = 0.0f;
-            if ((uint32_t)e < s.nvalid) {
-                t = x[s.i + e];
-                if (center) t -= center[s.i + e];
-            }
-            v[e] = t;
-        }
-    }
-}
-
-// The slots of this lane in a guarded tile (the same for every worker), and one worker's coordinates.
-template <int CH>
-__device__ __forceinline__ void guarded_spans(const QParams& p, uint32_t tile, LaneSpan (&span)[CH]) {
-    const uint64_t wave0 = (uint64_t)tile * (blockDim.x >> 6) + (threadIdx.x >> 6);
-#pragma unroll
-    for (int c = 0; c < CH; ++c)
-        span[c] = lane_span((wave0 * (uint64_t)CH + (uint64_t)c) * kChunk + (threadIdx.x & 63u) * kLaneElems, p);
-}
-template <int CH>
-__device__ __forceinline__ void guarded_load(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], float (&v)[CH][8]) {
-#pragma unroll
-    for (int c = 0; c < CH; ++c) load_lane(p.x + (uint64_t)k * p.x_stride, p.center, span[c], v[c]);
-}
-
-// One tile of worker k with every access guarded per lane, its coordinates loaded.  PRE = true: the scales
-// were computed by the partial-sum passes and are read from the norms plane, or the tile's one scale is
-// handed in (given).  sm: 32 floats of LDS, not used with PRE.
-// ACC = true: the dequantised codes are also added to acc[chunk][0..8) (the server's sum over
-// workers, for the launch that runs a whole round).
-template <int M, int CH, int KIND, bool PRE, bool ACC = false>
-__device__ __forceinline__ void guarded_codes(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], const float (&v)[CH][8],
-                                              float* sm, float (*acc)[8] = nullptr, bool given = false,
-                                              float given_norm = 0.0f) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = threadIdx.x >> 6;
-    unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
-    float* __restrict__ norms = reinterpret_cast<float*>(out + p.norms_off);
-    uint32_t* __restrict__ signs = reinterpret_cast<uint32_t*>(out + p.signs_off);
-    uint32_t* __restrict__ levels = reinterpret_cast<uint32_t*>(out + p.levels_off);
-    const uint64_t N = 1ull << p.log2N;
-
-    Scale sc[CH];
-    if (PRE) {
-#pragma unroll
-        for (int c = 0; c < CH; ++c) sc[c] = scale_of_norm<M>(!span[c].nvalid ? 1.0f : given ? given_norm : norms[span[c].bucket]);
-    } else {
-        float t[CH];
-        const uint32_t lanes_per_bucket = (uint32_t)((N < kChunk ? N : kChunk) / kLaneElems);
-#pragma unroll
-        for (int c = 0; c < CH; ++c) t[c] = lane_butterfly<KIND>(lane_tree<KIND>(v[c]), lanes_per_bucket);
-        if (N > kChunk) {
-            const uint32_t chunks_per_bucket = (uint32_t)(N / kChunk < (uint64_t)CH ? N / kChunk : (uint64_t)CH);
-#pragma unroll
-            for (int w = 1; w < CH; w <<= 1) {
-                if (chunks_per_bucket > (uint32_t)w) {
-#pragma unroll
-                    for (int c = 0; c < CH; c += 2 * w) t[c] = combine<KIND>(t[c], t[c + w]);
-                }
-            }
-            if (N > (uint64_t)(CH * kChunk)) {          // the bucket spans several waves
-                const uint32_t waves_per_bucket = (uint32_t)(N / (CH * kChunk));
-                if (lane == 0) sm[wave] = t[0];
-                __syncthreads();
-                t[0] = lds_tree16<KIND>(sm, wave & ~(waves_per_bucket - 1u), waves_per_bucket);
-            }
-#pragma unroll
-            for (int w = CH / 2; w >= 1; w >>= 1) {
-                if (chunks_per_bucket > (uint32_t)w) {
-#pragma unroll
-                    for (int c = 0; c < CH; c += 2 * w) t[c + w] = t[c];
-                }
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            // a lane without coordinates must not take its wave out of the short rounding: any ordinary scale
-            sc[c] = scale_of_total<M, KIND>(span[c].nvalid ? t[c] : 1.0f);
-            if (span[c].opens_bucket) norms[span[c].bucket] = sc[c].norm;
-        }
-    }
-
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        // Lanes are in slot order, so a chunk whose first lane holds no coordinate is all padding
-        // (the tail of a bucket that is not a power of two, or of the vector): nothing to encode.
-        if (__builtin_amdgcn_readfirstlane(span[c].nvalid) == 0u) continue;
-        const uint64_t g = span[c].i >> 3;
-        uint32_t rnd[4];
-        philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
-        uint32_t sign_byte, bits[4];
-        if (KIND != QESGD_NORM_L2) sc[c].direct = sc[c].direct && wave_all(no_nan<KIND>(v[c]));
-        round_and_pack<M>(v[c], rnd, sc[c], sign_byte, bits);
-        store_codes<M>(signs, levels, span[c].i, span[c].nvalid, lane, sign_byte, bits);
-        if (ACC) accumulate8<M>(acc[c], sign_byte, bits, sc[c].norm / p.smax);
-    }
-}
-
-template <int M, int CH, int KIND, bool PRE>
-__device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint32_t tile, float* sm) {
-    LaneSpan span[CH];
-    float v[CH][8];
-    guarded_spans<CH>(p, tile, span);
-    guarded_load<CH>(p, k, span, v);
-    guarded_codes<M, CH, KIND, PRE>(p, k, span, v, sm);
-}
-
-// ---------------------------------------------------------------------------
-// Fast kernel.  Geometry per bucket size: tile = NW waves x CH chunks x 512.
-// ---------------------------------------------------------------------------
-template <int M, int LOG2N>
-struct Geo {
-    // Chunks per wave and waves per workgroup, measured at 1.07 G coordinates.  Few level bits: two
-    // chunks per wave, the more bytes in flight the better (M = 1: 0.70 against 0.74 ms with bucket
-    // 512, M = 2: 0.73 against 0.75 ms with 2048); from M = 4 on the packed stores weigh more and one
-    // chunk is better (M = 8: 0.82 against 0.87 ms with 4096).  8192: two chunks, as fast as one with
-    // sixteen waves and open to a second workgroup per CU.  The workgroup is as small as the bucket
-    // allows, but not one wave (M = 4: the same; M = 1: 0.74 against 0.72 ms).
-    static constexpr int CH = LOG2N == 15 ? 4 : (LOG2N >= 13 || M <= 2 ? 2 : 1);
-    static constexpr int NW = (1 << LOG2N) / (CH * 512) < 2 ? 2 : (1 << LOG2N) / (CH * 512);
-    static constexpr uint32_t TILE = (uint32_t)NW * CH * kChunk;
-};
-
-// Geo<M, log2 N>::TILE on the host.
-inline uint64_t fast_tile(uint32_t m, uint64_t N) {
-    const uint64_t ch = N == 32768 ? 4 : (N >= 8192 || m <= 2 ? 2 : 1);
-    return N > 2 * ch * kChunk ? N : 2 * ch * kChunk;
-}
-
-// A wave's CH chunks of a tile into registers: xw / cw point at the wave's first coordinate.  All
-// loads are issued before the first use.  `center` is read by every worker's workgroup of the tile,
-// so it keeps the ordinary cache policy.
-template <int CH, bool CENTER>
-__device__ __forceinline__ void load_tile(const float* __restrict__ xw, const float* __restrict__ cw, uint32_t lane,
-                                          bool x_cached, float (&v)[CH][8]) {
-    vec4 a[CH], b[CH], ca[CH], cb[CH];
-    const uint32_t h = half_offset(lane);
-    load_halves<CH>(xw + h, x_cached, a, b);
-    if (CENTER) load_halves<CH>(cw + h, true, ca, cb);
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        if (CENTER) {
-            a[c] -= ca[c];
-            b[c] -= cb[c];
-        }
-        halves_to_lane(a[c], b[c], v[c]);
-    }
-}
-
-// Everything a workgroup needs to know about its worker, in registers; the pointers are uniform.
-struct FastCtx {
-    float* __restrict__ norms;
-    unsigned char* __restrict__ signs;
-    unsigned char* __restrict__ levels;
-    uint32_t lane, wave, worker, round, key0, key1;
-    float smax;
-    bool codes_cached;
-};
-
 // The codes of a lane's 8 coordinates where all of them exist: lane group `idx` of the planes that
 // start at the (uniform) bytes signs and levels.  A lane's sign bits are one byte and its level bits M,
 // so widths that divide 32 need no exchange between lanes: 64 lanes write consecutive bytes.  A wave's
@@ -638,10 +434,309 @@ __device__ __forceinline__ void store_chunks(unsigned char* __restrict__ signs, 
     }
 }
 
-// One tile: bucket totals, scales, variates, rounding, packing, stores.  ACC as in guarded_tile.
-template <int M, int LOG2N, bool ACC = false, class G = Geo<M, LOG2N>>
+// Level words of 512 consecutive coordinates for the widths that do not divide 32: the lanes' M bytes each
+// meet in LDS private to the wave and leave as consecutive words (M = 5: about 15 instructions against 55 for
+// shifting every lane's string into the words of its quad, as store_codes does).  words: the first of 16 * M.
+template <int M>
+__device__ __forceinline__ void store_levels_lds(uint32_t* __restrict__ words, uint32_t lane, const uint32_t (&bits)[4]) {
+    __shared__ uint32_t stage[16][16 * M];
+    uint32_t* mine = stage[threadIdx.x >> 6];
+    unsigned char* bytes = reinterpret_cast<unsigned char*>(mine) + lane * (uint32_t)M;
+#pragma unroll
+    for (int j = 0; j < M; ++j) bytes[j] = (unsigned char)(bits[j >> 2] >> (8 * (j & 3)));
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const uint32_t first = lane < 16u * M ? mine[lane] : 0u;
+    const uint32_t second = lane + 64u < 16u * M ? mine[lane + 64u] : 0u;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();                      // the next chunk overwrites the area
+    if (lane < 16u * M) words[lane] = first;
+    if (lane + 64u < 16u * M) words[lane + 64u] = second;
+}
+
+// The codes of a wave's 512 consecutive coordinates from coordinate i0 (a multiple of 32) on.
+template <int M>
+__device__ __forceinline__ void store_whole(unsigned char* __restrict__ signs, unsigned char* __restrict__ levels, uint64_t i0,
+                                            uint32_t lane, bool cached, uint32_t sign_byte, const uint32_t (&bits)[4]) {
+    const uint64_t g0 = i0 / kLaneElems;
+    if constexpr (32 % M == 0) {
+        const uint32_t sb[1] = {sign_byte}, bt[1][4] = {{bits[0], bits[1], bits[2], bits[3]}};
+        store_chunks<M, 1>(signs + g0, levels + g0 * M, lane, cached, sb, bt);
+    } else {
+        (signs + g0)[lane] = (unsigned char)sign_byte;
+        store_levels_lds<M>(reinterpret_cast<uint32_t*>(levels + g0 * M), lane, bits);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Guarded tile: the body of the generic kernel and of the last pass's ragged tile.
+// ---------------------------------------------------------------------------
+// Where the 8 slots of this lane fall: bucket, first coordinate, how many of
+// them are real coordinates (0..8), and whether they open the bucket.
+struct LaneSpan {
+    uint64_t bucket;
+    uint64_t i;        // first coordinate (a multiple of 8)
+    uint32_t nvalid;
+    bool opens_bucket;
+    bool whole;        // the wave's 512 slots are 512 consecutive coordinates
+};
+
+__device__ __forceinline__ LaneSpan lane_span(uint64_t slot, const QParams& p) {
+    LaneSpan s;
+    const uint64_t N = 1ull << p.log2N;
+    s.bucket = slot >> p.log2N;
+    const uint64_t j = slot & (N - 1);
+    uint64_t len = 0;
+    if (s.bucket < p.nb) {
+        const uint64_t rem = p.d - s.bucket * p.B;
+        len = rem < p.B ? rem : p.B;
+    }
+    s.nvalid = j < len ? (uint32_t)((len - j) < 8 ? (len - j) : 8) : 0u;
+    s.i = s.bucket * p.B + j;
+    s.opens_bucket = (j == 0) && (s.bucket < p.nb);
+    s.whole = false;
+    return s;
+}
+
+// The slots of this lane in the chunk that starts at `slot` (a multiple of 512, the same for the wave).
+// Where a bucket fills whole chunks the place of the chunk is worked out once per wave, in scalar registers.
+__device__ __forceinline__ LaneSpan chunk_span(uint64_t slot, uint32_t lane, const QParams& p) {
+    if ((1ull << p.log2N) < kChunk) return lane_span(slot + lane * kLaneElems, p);
+    LaneSpan s;
+    s.bucket = slot >> p.log2N;
+    const uint64_t j = slot & ((1ull << p.log2N) - 1u);
+    uint32_t count = 0;                                   // coordinates in the chunk
+    if (s.bucket < p.nb) {
+        const uint64_t rem = p.d - s.bucket * p.B;
+        const uint64_t len = rem < p.B ? rem : p.B;
+        count = j < len ? (uint32_t)((len - j) < kChunk ? (len - j) : kChunk) : 0u;
+    }
+    const uint32_t before = lane * kLaneElems;
+    s.nvalid = before < count ? (count - before < 8u ? count - before : 8u) : 0u;
+    s.i = s.bucket * p.B + j + before;
+    s.opens_bucket = j == 0 && lane == 0 && s.bucket < p.nb;
+    s.whole = false;
+    return s;
+}
+
+// The slots of this lane in a guarded tile (the same for every worker).
+template <int CH>
+__device__ __forceinline__ void guarded_spans(const QParams& p, uint32_t tile, LaneSpan (&span)[CH]) {
+    const uint64_t wave0 = (uint64_t)tile * (blockDim.x >> 6) + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        span[c] = chunk_span((wave0 * (uint64_t)CH + (uint64_t)c) * kChunk, threadIdx.x & 63u, p);
+        const uint32_t i = (uint32_t)span[c].i;
+        span[c].whole = wave_all(span[c].nvalid == 8) &&
+                        __builtin_amdgcn_readlane(i, 63) - __builtin_amdgcn_readlane(i, 0) == 63u * kLaneElems;
+    }
+}
+
+// One vector's coordinates of those slots, still in the layout they were loaded in.  A chunk whose slots are
+// 512 consecutive coordinates is loaded like a full tile (halves, see halves_to_lane); otherwise a lane loads
+// its own: 8, none, or at the end of the vector the first few.
+template <int CH>
+__device__ __forceinline__ void guarded_load_raw(const float* __restrict__ x, const LaneSpan (&span)[CH],
+                                                 bool cached, vec4 (&a)[CH], vec4 (&b)[CH]) {
+    const uint32_t lane = threadIdx.x & 63u;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const float* __restrict__ src = x + span[c].i;
+        if (span[c].whole) {
+            vec4 ha[1], hb[1];
+            load_halves<1>(src - lane * kLaneElems + half_offset(lane), cached, ha, hb);
+            a[c] = ha[0];
+            b[c] = hb[0];
+        } else {
+            a[c] = vec4{0.0f, 0.0f, 0.0f, 0.0f};
+            b[c] = a[c];
+            if (span[c].nvalid == 8) {
+                a[c] = load_cached(src);
+                b[c] = load_cached(src + 4);
+            } else if (span[c].nvalid > 0) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    if ((uint32_t)e < span[c].nvalid) a[c][e] = src[e];
+                    if ((uint32_t)e + 4u < span[c].nvalid) b[c][e] = src[e + 4];
+                }
+            }
+        }
+    }
+}
+template <int CH>
+__device__ __forceinline__ void guarded_load(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], float (&v)[CH][8]) {
+    vec4 a[CH], b[CH];
+    guarded_load_raw<CH>(p.x + (uint64_t)k * p.x_stride, span, p.x_cached, a, b);
+    if (p.center) {
+        vec4 ca[CH], cb[CH];
+        guarded_load_raw<CH>(p.center, span, true, ca, cb);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            a[c] -= ca[c];
+            b[c] -= cb[c];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        if (span[c].whole) {
+            halves_to_lane(a[c], b[c], v[c]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[c][e] = a[c][e];
+                v[c][4 + e] = b[c][e];
+            }
+        }
+    }
+}
+
+// One tile of worker k with every access guarded per lane, its coordinates loaded.  PRE = true: the scales
+// were computed by the partial-sum passes and are read from the norms plane, or the tile's one scale is
+// handed in (given).  sm: 32 floats of LDS, not used with PRE.
+template <int M, int CH, int KIND, bool PRE>
+__device__ __forceinline__ void guarded_codes(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], const float (&v)[CH][8],
+                                              float* sm, bool given = false, float given_norm = 0.0f) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = threadIdx.x >> 6;
+    unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
+    float* __restrict__ norms = reinterpret_cast<float*>(out + p.norms_off);
+    uint32_t* __restrict__ signs = reinterpret_cast<uint32_t*>(out + p.signs_off);
+    uint32_t* __restrict__ levels = reinterpret_cast<uint32_t*>(out + p.levels_off);
+    const uint64_t N = 1ull << p.log2N;
+
+    Scale sc[CH];
+    if (PRE) {
+#pragma unroll
+        for (int c = 0; c < CH; ++c) sc[c] = scale_of_norm<M>(!span[c].nvalid ? 1.0f : given ? given_norm : norms[span[c].bucket]);
+    } else {
+        float t[CH];
+        const uint32_t lanes_per_bucket = (uint32_t)((N < kChunk ? N : kChunk) / kLaneElems);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) t[c] = lane_butterfly<KIND>(lane_tree<KIND>(v[c]), lanes_per_bucket);
+        if (N > kChunk) {
+            const uint32_t chunks_per_bucket = (uint32_t)(N / kChunk < (uint64_t)CH ? N / kChunk : (uint64_t)CH);
+#pragma unroll
+            for (int w = 1; w < CH; w <<= 1) {
+                if (chunks_per_bucket > (uint32_t)w) {
+#pragma unroll
+                    for (int c = 0; c < CH; c += 2 * w) t[c] = combine<KIND>(t[c], t[c + w]);
+                }
+            }
+            if (N > (uint64_t)(CH * kChunk)) {          // the bucket spans several waves
+                const uint32_t waves_per_bucket = (uint32_t)(N / (CH * kChunk));
+                if (lane == 0) sm[wave] = t[0];
+                __syncthreads();
+                t[0] = lds_tree16<KIND>(sm, wave & ~(waves_per_bucket - 1u), waves_per_bucket);
+            }
+#pragma unroll
+            for (int w = CH / 2; w >= 1; w >>= 1) {
+                if (chunks_per_bucket > (uint32_t)w) {
+#pragma unroll
+                    for (int c = 0; c < CH; c += 2 * w) t[c + w] = t[c];
+                }
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            // a lane without coordinates must not take its wave out of the short rounding: any ordinary scale
+            if (c > 0 && N >= 2 * kChunk && N >= (uint64_t)CH * kChunk) sc[c] = sc[0];
+            else sc[c] = scale_of_total<M, KIND>(span[c].nvalid || N >= kChunk ? t[c] : 1.0f);
+            if (span[c].opens_bucket) norms[span[c].bucket] = sc[c].norm;
+        }
+    }
+
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        // Lanes are in slot order, so a chunk whose first lane holds no coordinate is all padding
+        // (the tail of a bucket that is not a power of two, or of the vector): nothing to encode.
+        if (__builtin_amdgcn_readfirstlane(span[c].nvalid) == 0u) continue;
+        const uint64_t g = span[c].i >> 3;
+        uint32_t rnd[4];
+        philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        uint32_t sign_byte, bits[4];
+        if (KIND != QESGD_NORM_L2) sc[c].direct = sc[c].direct && wave_all(no_nan<KIND>(v[c]));
+        round_and_pack<M>(v[c], rnd, sc[c], sign_byte, bits);
+        if (span[c].whole) {
+            const uint64_t i0 = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)span[c].i) |
+                                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(span[c].i >> 32)) << 32;
+            store_whole<M>(out + p.signs_off, out + p.levels_off, i0, lane, p.codes_cached, sign_byte, bits);
+        } else {
+            store_codes<M>(signs, levels, span[c].i, span[c].nvalid, lane, sign_byte, bits);
+        }
+    }
+}
+
+template <int M, int CH, int KIND, bool PRE>
+__device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint32_t tile, float* sm) {
+    LaneSpan span[CH];
+    float v[CH][8];
+    guarded_spans<CH>(p, tile, span);
+    guarded_load<CH>(p, k, span, v);
+    guarded_codes<M, CH, KIND, PRE>(p, k, span, v, sm);
+}
+
+// ---------------------------------------------------------------------------
+// Fast kernel.  Geometry per bucket size: tile = NW waves x CH chunks x 512.
+// ---------------------------------------------------------------------------
+template <int M, int LOG2N>
+struct Geo {
+    // Chunks per wave and waves per workgroup, measured at 1.07 G coordinates.  Few level bits: two
+    // chunks per wave, the more bytes in flight the better (M = 1: 0.70 against 0.74 ms with bucket
+    // 512, M = 2: 0.73 against 0.75 ms with 2048); from M = 4 on the packed stores weigh more and one
+    // chunk is better (M = 8: 0.82 against 0.87 ms with 4096).  8192: two chunks, as fast as one with
+    // sixteen waves and open to a second workgroup per CU.  The workgroup is as small as the bucket
+    // allows, but not one wave (M = 4: the same; M = 1: 0.74 against 0.72 ms).
+    static constexpr int CH = LOG2N == 15 ? 4 : (LOG2N >= 13 || M <= 2 ? 2 : 1);
+    static constexpr int NW = (1 << LOG2N) / (CH * 512) < 2 ? 2 : (1 << LOG2N) / (CH * 512);
+    static constexpr uint32_t TILE = (uint32_t)NW * CH * kChunk;
+};
+
+// Geo<M, log2 N>::TILE on the host.
+inline uint64_t fast_tile(uint32_t m, uint64_t N) {
+    const uint64_t ch = N == 32768 ? 4 : (N >= 8192 || m <= 2 ? 2 : 1);
+    return N > 2 * ch * kChunk ? N : 2 * ch * kChunk;
+}
+
+// A wave's CH chunks of a tile into registers: xw / cw point at the wave's first coordinate.  All
+// loads are issued before the first use.  `center` is read by every worker's workgroup of the tile,
+// so it keeps the ordinary cache policy.
+template <int CH, bool CENTER, bool FULL = true>
+__device__ __forceinline__ void load_tile(const float* __restrict__ xw, const float* __restrict__ cw, uint32_t lane,
+                                          bool x_cached, float (&v)[CH][8], uint32_t count = CH * kChunk) {
+    vec4 a[CH], b[CH], ca[CH], cb[CH];
+    load_chunks<CH, FULL>(xw, lane, count, x_cached, a, b);
+    if (CENTER) load_chunks<CH, FULL>(cw, lane, count, true, ca, cb);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        if (CENTER) {
+            a[c] -= ca[c];
+            b[c] -= cb[c];
+        }
+        halves_to_lane(a[c], b[c], v[c]);
+    }
+}
+
+// Of the tile's `count` coordinates those from the wave's first on.
+__device__ __forceinline__ uint32_t count_from(uint32_t count, uint32_t first) { return count > first ? count - first : 0u; }
+
+// Everything a workgroup needs to know about its worker, in registers; the pointers are uniform.
+struct FastCtx {
+    float* __restrict__ norms;
+    unsigned char* __restrict__ signs;
+    unsigned char* __restrict__ levels;
+    uint32_t lane, wave, worker, round, key0, key1;
+    float smax;
+    bool codes_cached;
+};
+
+// One tile: bucket totals, scales, variates, rounding, packing, stores.  ACC: the dequantised codes are also
+// added to acc[chunk][0..8) (the server's sum over workers, for the launch that runs a whole round).
+// FULL = false: the ragged last tile of a vector, of which the first `count` coordinates exist and the rest
+// of v is 0.
+template <int M, int LOG2N, bool ACC = false, class G = Geo<M, LOG2N>, bool FULL = true>
 __device__ __forceinline__ void process_tile(const FastCtx& cx, float (&v)[G::CH][8], uint32_t t, float* sm,
-                                             float (*acc)[8] = nullptr) {
+                                             float (*acc)[8] = nullptr, uint32_t count = G::TILE) {
     constexpr int CH = G::CH;
     constexpr uint32_t N = 1u << LOG2N;
     constexpr uint32_t TILE = G::TILE;
@@ -677,17 +772,24 @@ __device__ __forceinline__ void process_tile(const FastCtx& cx, float (&v)[G::CH
     for (int c = 0; c < CH; ++c) {
         const uint32_t idx = (cx.wave * (uint32_t)CH + (uint32_t)c) * kWaveSize + cx.lane;   // lane group inside the tile
         if (c % CPB == 0) {                                       // first chunk of a bucket (or of its part in this wave)
-            sc = scale_of_total<M, KIND>(tot[c]);
+            // a lane beyond the last bucket must not take its wave out of the short rounding: any ordinary scale
+            const bool live = FULL || ((idx * kLaneElems) & ~(N - 1u)) < count;
+            sc = scale_of_total<M, KIND>(live ? tot[c] : 1.0f);
             if (ACC) step = sc.norm / cx.smax;
-            if ((idx & (N / kLaneElems - 1u)) == 0u) norms[idx >> (LOG2N - 3)] = sc.norm;
+            if ((idx & (N / kLaneElems - 1u)) == 0u && live) norms[idx >> (LOG2N - 3)] = sc.norm;
         }
         // the tile starts at a multiple of its size, so the low word of the group number cannot carry
         uint32_t rnd[4];
         philox4x32_10((uint32_t)g0 + idx, (uint32_t)(g0 >> 32), cx.worker, cx.round, cx.key0, cx.key1, rnd);
         round_and_pack<M>(v[c], rnd, sc, sign_byte[c], bits[c]);
         if (ACC) accumulate8<M>(acc[c], sign_byte[c], bits[c], step);
+        if (!FULL) {
+            const uint32_t rest = count_from(count, idx * kLaneElems);
+            store_codes<M>(reinterpret_cast<uint32_t*>(cx.signs), reinterpret_cast<uint32_t*>(cx.levels),
+                           (g0 + idx) * kLaneElems, rest < 8u ? rest : 8u, cx.lane, sign_byte[c], bits[c]);
+        }
     }
-    store_chunks<M, CH>(signs, levels, cx.wave * (uint32_t)CH * kWaveSize + cx.lane, cx.codes_cached, sign_byte, bits);
+    if (FULL) store_chunks<M, CH>(signs, levels, cx.wave * (uint32_t)CH * kWaveSize + cx.lane, cx.codes_cached, sign_byte, bits);
 }
 
 }  // namespace

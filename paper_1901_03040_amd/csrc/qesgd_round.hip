@@ -46,113 +46,76 @@ struct RoundGeo {
 };
 inline uint64_t round_tile(uint64_t N) { return N > 2048 ? (N > 4096 ? N : 4096) : (N > 1024 ? N : 1024); }
 
-template <int M, int LOG2N, bool CENTER>
-__global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const RParams r) {
+template <int M, int LOG2N, bool CENTER, bool FULL>
+__device__ __forceinline__ void round_one_tile(const RParams& r, uint32_t t, float (&sm)[2][32]) {
     constexpr int CH = RoundGeo<LOG2N>::CH;
     constexpr uint32_t TILE = RoundGeo<LOG2N>::TILE;
-    __shared__ float sm[2][32];             // alternate per worker: one barrier per tile suffices
     const QParams& p = r.q;
-    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    FastCtx cx;
+    cx.lane = threadIdx.x & 63u;
+    cx.wave = threadIdx.x >> 6;
+    cx.round = p.round;
+    cx.key0 = p.key0;
+    cx.key1 = p.key1;
+    cx.smax = p.smax;
+    cx.codes_cached = false;                              // nothing reads them here
+    const uint32_t lane = cx.lane, first = cx.wave * (uint32_t)(CH * kChunk);
+    const uint64_t o = (uint64_t)t * TILE + first;
+    const uint32_t count = FULL ? TILE : (uint32_t)(p.d - (uint64_t)t * TILE), mine = FULL ? TILE : count_from(count, first);
+    // one branch per worker for the policy is free with one chunk per wave (99 against 103 us at d = 11 M,
+    // K = 8, bucket 2048) and costs 8% with two
+    const bool cached = CH == 1 && p.x_cached;
 
     float acc[CH][8];
 #pragma unroll
     for (int c = 0; c < CH; ++c)
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[c][e] = 0.0f;
-
-    if (t < p.full_tiles) {
-        const uint64_t o = (uint64_t)t * TILE + wave * (uint32_t)(CH * kChunk) + half_offset(lane);
-        // one branch per worker for the policy is free with one chunk per wave (99 against 103 us at d = 11 M,
-        // K = 8, bucket 2048) and costs 8% with two
-        const bool cached = CH == 1 && p.x_cached;
-        vec4 ca[CH], cb[CH], a[CH], b[CH], na[CH], nb[CH], sa[CH], sb[CH];
-        if (CENTER) load_halves<CH>(p.center + o, false, ca, cb);
-        load_halves<CH>(p.x + o, cached, a, b);
-        for (uint32_t k = 0; k < r.K; ++k) {
-            // in flight while worker k is rounded: the next worker's coordinates, after the last the update's
-            const bool last = k + 1 == r.K;
-            load_halves<CH>((last ? r.w : p.x + (uint64_t)(k + 1) * p.x_stride) + o, cached, na, nb);
-            if (last && r.zsum) load_halves<CH>(r.zsum + o, cached, sa, sb);
-            float v[CH][8];
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                if (CENTER) halves_to_lane(a[c] - ca[c], b[c] - cb[c], v[c]);
-                else halves_to_lane(a[c], b[c], v[c]);
-            }
-            unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
-            FastCtx cx;
-            cx.norms = reinterpret_cast<float*>(out + p.norms_off);
-            cx.signs = out + p.signs_off;
-            cx.levels = out + p.levels_off;
-            cx.lane = lane;
-            cx.wave = wave;
-            cx.worker = p.worker0 + k;
-            cx.round = p.round;
-            cx.key0 = p.key0;
-            cx.key1 = p.key1;
-            cx.smax = p.smax;
-            cx.codes_cached = false;                     // nothing reads them here
-            process_tile<M, LOG2N, true, RoundGeo<LOG2N>>(cx, v, t, sm[k & 1u], acc);
-#pragma unroll
-            for (int c = 0; c < CH; ++c) { a[c] = na[c]; b[c] = nb[c]; }
-        }
-        const float fk = (float)r.K;
+    vec4 ca[CH], cb[CH], a[CH], b[CH], na[CH], nb[CH], sa[CH], sb[CH];
+    if (CENTER) load_chunks<CH, FULL>(p.center + o, lane, mine, false, ca, cb);
+    load_chunks<CH, FULL>(p.x + o, lane, mine, cached, a, b);
+    for (uint32_t k = 0; k < r.K; ++k) {
+        // in flight while worker k is rounded: the next worker's coordinates, after the last the update's
+        const bool last = k + 1 == r.K;
+        load_chunks<CH, FULL>((last ? r.w : p.x + (uint64_t)(k + 1) * p.x_stride) + o, lane, mine, cached, na, nb);
+        if (last && r.zsum) load_chunks<CH, FULL>(r.zsum + o, lane, mine, cached, sa, sb);
+        float v[CH][8];
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            float z[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) z[e] = (r.rcpK != 0.0f) ? acc[c][e] * r.rcpK : acc[c][e] / fk;
-            vec4 za, zb;
-            lane_to_halves(z, za, zb);
-            const uint64_t ia = o + (uint32_t)c * kChunk, ib = ia + kChunk / 2;
-            if (r.zbar) {
-                store_stream(r.zbar + ia, za);
-                store_stream(r.zbar + ib, zb);
-            }
-            store_stream(r.u + ia, a[c] + za);
-            store_stream(r.u + ib, b[c] + zb);
-            if (r.zsum) {
-                store_stream(r.zsum + ia, sa[c] + za);
-                store_stream(r.zsum + ib, sb[c] + zb);
-            }
+            if (CENTER) halves_to_lane(a[c] - ca[c], b[c] - cb[c], v[c]);
+            else halves_to_lane(a[c], b[c], v[c]);
         }
-        return;
-    }
-
-    // the ragged last tile
-    LaneSpan span[CH];
-    float v[CH][8];
-    guarded_spans<CH>(p, t, span);
-    for (uint32_t k = 0; k < r.K; ++k) {
-        guarded_load<CH>(p, k, span, v);
-        guarded_codes<M, CH, QESGD_NORM_L2, false, true>(p, k, span, v, sm[k & 1u], acc);
+        unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
+        cx.norms = reinterpret_cast<float*>(out + p.norms_off);
+        cx.signs = out + p.signs_off;
+        cx.levels = out + p.levels_off;
+        cx.worker = p.worker0 + k;
+        process_tile<M, LOG2N, true, RoundGeo<LOG2N>, FULL>(cx, v, t, sm[k & 1u], acc, count);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) { a[c] = na[c]; b[c] = nb[c]; }
     }
     const float fk = (float)r.K;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        // the ragged tile, lane by lane (power-of-two buckets: slot == coordinate)
-        const uint64_t i = (uint64_t)t * TILE + (wave * (uint32_t)CH + (uint32_t)c) * kChunk + lane * kLaneElems;
-        if (i >= p.d) continue;
-        const uint64_t rem = p.d - i;
-        const uint32_t nvalid = rem < 8 ? (uint32_t)rem : 8u;
         float z[8];
 #pragma unroll
         for (int e = 0; e < 8; ++e) z[e] = (r.rcpK != 0.0f) ? acc[c][e] * r.rcpK : acc[c][e] / fk;
-        if (r.zbar) store8(r.zbar, i, nvalid, z);
-        float w8[8], u8[8];
-        load8(r.w, i, nvalid, w8);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u8[e] = w8[e] + z[e];
-        store8(r.u, i, nvalid, u8);
-        if (r.zsum) {
-            float s8[8];
-            load8(r.zsum, i, nvalid, s8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s8[e] = s8[e] + z[e];
-            store8(r.zsum, i, nvalid, s8);
-        }
+        vec4 za, zb;
+        lane_to_halves(z, za, zb);
+        const uint64_t oc = o + (uint32_t)c * kChunk;
+        const uint32_t left = FULL ? kChunk : count_from(mine, (uint32_t)c * kChunk);
+        if (r.zbar) store_chunk<FULL>(r.zbar + oc, lane, left, za, zb);
+        store_chunk<FULL>(r.u + oc, lane, left, a[c] + za, b[c] + zb);
+        if (r.zsum) store_chunk<FULL>(r.zsum + oc, lane, left, sa[c] + za, sb[c] + zb);
     }
+}
+
+template <int M, int LOG2N, bool CENTER>
+__global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const RParams r) {
+    __shared__ float sm[2][32];             // alternate per worker: one barrier per tile suffices
+    const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, r.q.xcd_group);
+    if (t < r.q.full_tiles) round_one_tile<M, LOG2N, CENTER, true>(r, t, sm);
+    else round_one_tile<M, LOG2N, CENTER, false>(r, t, sm);   // the ragged last tile (at most one)
 }
 
 // The same behind the launches that found the scales of wide buckets: no wave needs another, so a wave owns
@@ -165,19 +128,78 @@ __global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const 
 //   d = 30 M, K = 4, s = 8, one bucket         378 -> 288 us
 // One wave per workgroup would finish every scale by itself; four share that work.
 constexpr uint32_t kWideWaves = 4;
+
+// norm: lane k holds worker k's (lanes from K on: 1).  ca, cb, a, b: the center's and the first worker's.
+template <int M, bool CENTER, bool ZACC, bool FULL>
+__device__ __forceinline__ void wide_chunk(const RParams& r, uint64_t c0, uint32_t lane, float norm, const vec4 (&ca)[1],
+                                           const vec4 (&cb)[1], vec4 (&a)[1], vec4 (&b)[1]) {
+    const QParams& p = r.q;
+    const uint32_t count = FULL ? kChunk : (uint32_t)(p.d - c0);
+    const bool cached = p.x_cached;
+    const float my_step = norm / p.smax, my_mul = scale_of_norm<M>(norm).mul;
+    const uint64_t direct = __builtin_amdgcn_ballot_w64(norm >= 0x1p-60f && norm <= 0x1p60f);
+    const uint64_t g0 = c0 / kLaneElems;
+    vec4 na[1], nb[1], sa[1], sb[1], ta[1], tb[1];
+    float acc[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+    for (uint32_t k = 0; k < r.K; ++k) {
+        const bool last = k + 1 == r.K;
+        load_chunks<1, FULL>((last ? r.w : p.x + (uint64_t)(k + 1) * p.x_stride) + c0, lane, count, cached, na, nb);
+        if (last && r.zsum) load_chunks<1, FULL>(r.zsum + c0, lane, count, cached, sa, sb);
+        if (last && ZACC) load_chunks<1, FULL>(r.z_acc + c0, lane, count, cached, ta, tb);
+        float v[8];
+        if (CENTER) halves_to_lane(a[0] - ca[0], b[0] - cb[0], v);
+        else halves_to_lane(a[0], b[0], v);
+        Scale sc;
+        sc.norm = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(norm), k));
+        sc.mul = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_mul), k));
+        sc.direct = (direct >> k) & 1u;
+        const float step = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_step), k));
+        uint32_t rnd[4], sign_byte, bits[4];
+        philox4x32_10((uint32_t)g0 + lane, (uint32_t)(g0 >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        round_and_pack<M>(v, rnd, sc, sign_byte, bits);
+        unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
+        if (FULL) {
+            store_whole<M>(out + p.signs_off, out + p.levels_off, c0, lane, false, sign_byte, bits);
+        } else {
+            const uint32_t before = lane * kLaneElems;
+            const uint32_t nvalid = before < count ? (count - before < 8u ? count - before : 8u) : 0u;
+            store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off),
+                           c0 + before, nvalid, lane, sign_byte, bits);
+        }
+        accumulate8<M>(acc, sign_byte, bits, step);
+        a[0] = na[0];
+        b[0] = nb[0];
+    }
+    const float fk = (float)r.K;
+    float z[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) z[e] = (r.rcpK != 0.0f) ? acc[e] * r.rcpK : acc[e] / fk;
+    vec4 za, zb;
+    lane_to_halves(z, za, zb);
+    if (r.zbar) store_chunk<FULL>(r.zbar + c0, lane, count, za, zb);
+    if (ZACC) {
+        za = ta[0] + za;
+        zb = tb[0] + zb;
+        store_chunk<FULL>(r.z_acc + c0, lane, count, za, zb);
+    }
+    store_chunk<FULL>(r.u + c0, lane, count, a[0] + za, b[0] + zb);
+    if (r.zsum) store_chunk<FULL>(r.zsum + c0, lane, count, sa[0] + za, sb[0] + zb);
+}
+
 template <int M, bool CENTER, bool ZACC>
 __global__ void __launch_bounds__(kWideWaves * 64) k_round_wide(const RParams r) {
     __shared__ float total[64];
     const QParams& p = r.q;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group) * kWideWaves + wave;
-    const uint64_t c0 = (uint64_t)t * kChunk;             // first coordinate of the wave, in bucket b
+    const uint64_t c0 = (uint64_t)t * kChunk;             // first coordinate of the wave
     const bool full = c0 + kChunk <= p.d;
-    const uint64_t o = c0 + half_offset(lane);
-    vec4 ca[1], cb[1], a[1], b1[1], na[1], nb[1], sa[1], sb[1], ta[1], tb[1];
+    vec4 ca[1], cb[1], a[1], b1[1];
     if (full) {
-        if (CENTER) load_halves<1>(p.center + o, false, ca, cb);
-        load_halves<1>(p.x + o, p.x_cached, a, b1);
+        if (CENTER) load_chunks<1, true>(p.center + c0, lane, kChunk, false, ca, cb);
+        load_chunks<1, true>(p.x + c0, lane, kChunk, p.x_cached, a, b1);
     }
 
     float norm = 1.0f;
@@ -199,100 +221,13 @@ __global__ void __launch_bounds__(kWideWaves * 64) k_round_wide(const RParams r)
     } else if (lane < r.K && c0 < p.d) {
         norm = reinterpret_cast<const float*>(p.packed + (uint64_t)lane * p.packed_stride + p.norms_off)[c0 >> p.log2N];
     }
-    if (c0 >= p.d) return;
-    const float my_step = norm / p.smax;
-
-    float acc[1][8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[0][e] = 0.0f;
-    const float fk = (float)r.K;
-
-    if (!full) {                                          // ragged last wave
-        const uint64_t i = c0 + lane * kLaneElems;
-        LaneSpan span[1];
-        span[0] = lane_span(i, p);
-        float v[1][8];
-        for (uint32_t k = 0; k < r.K; ++k) {
-            guarded_load<1>(p, k, span, v);
-            const float nk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(norm), k));
-            guarded_codes<M, 1, QESGD_NORM_L2, true, true>(p, k, span, v, nullptr, acc, true, nk);
-        }
-        if (i >= p.d) return;
-        float z[8], t8[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) z[e] = (r.rcpK != 0.0f) ? acc[0][e] * r.rcpK : acc[0][e] / fk;
-        const uint32_t nvalid = span[0].nvalid;
-        if (r.zbar) store8(r.zbar, i, nvalid, z);
-        if (ZACC) {
-            load8(r.z_acc, i, nvalid, t8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) z[e] = t8[e] + z[e];
-            store8(r.z_acc, i, nvalid, z);
-        }
-        load8(r.w, i, nvalid, t8);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) t8[e] = t8[e] + z[e];
-        store8(r.u, i, nvalid, t8);
-        if (r.zsum) {
-            load8(r.zsum, i, nvalid, t8);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) t8[e] = t8[e] + z[e];
-            store8(r.zsum, i, nvalid, t8);
-        }
-        return;
-    }
-
-    const float my_mul = scale_of_norm<M>(norm).mul;
-    const uint64_t direct = __builtin_amdgcn_ballot_w64(norm >= 0x1p-60f && norm <= 0x1p60f);
-    const uint64_t g0 = c0 / kLaneElems;
-    for (uint32_t k = 0; k < r.K; ++k) {
-        const bool last = k + 1 == r.K;
-        load_halves<1>((last ? r.w : p.x + (uint64_t)(k + 1) * p.x_stride) + o, p.x_cached, na, nb);
-        if (last && r.zsum) load_halves<1>(r.zsum + o, p.x_cached, sa, sb);
-        if (last && ZACC) load_halves<1>(r.z_acc + o, p.x_cached, ta, tb);
-        float v[8];
-        if (CENTER) halves_to_lane(a[0] - ca[0], b1[0] - cb[0], v);
-        else halves_to_lane(a[0], b1[0], v);
-        Scale sc;
-        sc.norm = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(norm), k));
-        sc.mul = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_mul), k));
-        sc.direct = (direct >> k) & 1u;
-        const float step = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_step), k));
-        uint32_t rnd[4], sign_byte[1], bits[1][4];
-        philox4x32_10((uint32_t)g0 + lane, (uint32_t)(g0 >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
-        round_and_pack<M>(v, rnd, sc, sign_byte[0], bits[0]);
-        unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
-        if constexpr (32 % M == 0) {
-            store_chunks<M, 1>(out + p.signs_off + g0, out + p.levels_off + g0 * M, lane, false, sign_byte, bits);
-        } else {
-            store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off),
-                           c0 + lane * kLaneElems, 8u, lane, sign_byte[0], bits[0]);
-        }
-        accumulate8<M>(acc[0], sign_byte[0], bits[0], step);
-        a[0] = na[0];
-        b1[0] = nb[0];
-    }
-    float z[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) z[e] = (r.rcpK != 0.0f) ? acc[0][e] * r.rcpK : acc[0][e] / fk;
-    vec4 za, zb;
-    lane_to_halves(z, za, zb);
-    const uint64_t ob = o + kChunk / 2;
-    if (r.zbar) {
-        store_stream(r.zbar + o, za);
-        store_stream(r.zbar + ob, zb);
-    }
-    if (ZACC) {
-        za = ta[0] + za;
-        zb = tb[0] + zb;
-        store_stream(r.z_acc + o, za);
-        store_stream(r.z_acc + ob, zb);
-    }
-    store_stream(r.u + o, a[0] + za);
-    store_stream(r.u + ob, b1[0] + zb);
-    if (r.zsum) {
-        store_stream(r.zsum + o, sa[0] + za);
-        store_stream(r.zsum + ob, sb[0] + zb);
+    if (full) {
+        wide_chunk<M, CENTER, ZACC, true>(r, c0, lane, norm, ca, cb, a, b1);
+    } else if (c0 < p.d) {                                // ragged last wave
+        const uint32_t count = (uint32_t)(p.d - c0);
+        if (CENTER) load_chunks<1, false>(p.center + c0, lane, count, true, ca, cb);
+        load_chunks<1, false>(p.x + c0, lane, count, true, a, b1);
+        wide_chunk<M, CENTER, ZACC, false>(r, c0, lane, norm, ca, cb, a, b1);
     }
 }
 
