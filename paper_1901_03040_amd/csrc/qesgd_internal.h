@@ -99,7 +99,13 @@ bool round_fused_covers(const Shape& sh, uint32_t norm_kind);
 // d = 0.1 M, K = 8, bucket 4096: 23 / 10 us; 1 M, K = 16, bucket 8192: 44 / 25 us; 1 M, K = 16, bucket
 // 1024: 30 / 23 us; 2 M, K = 16, bucket 8192: 40 / 43 us; 1 M, K = 8, bucket 512: 14.0 / 14.2 us; 1 M,
 // K = 2, bucket 16384: 10.2 / 10.8 us.  Buckets of 32768 would need 300 registers per lane.
+// A wave that owns one chunk of every worker (buckets up to 4096, and wide ones) falls behind two launches
+// where a round no longer fits about 1.2 GB: d = 20 M, K = 8, s = 16, bucket 512 178 / 190 us; 30 M 313 /
+// 289 us; 138 M, K = 4, s = 16, one bucket 1298 / 1235 us; with two chunks it does not (60 M, K = 8, bucket
+// 8192: 584 / 604 us).
 inline bool round_fused_pays(const Shape& sh, uint32_t K) {
+    const bool narrow = sh.N <= 4096 || sh.N > 32768;
+    if (narrow && 4u * (uint64_t)K * sh.d + update_bytes(sh, K) > (1250ull << 20)) return false;
     return sh.d >= (3u << 19) || K <= (sh.N > 2048 && sh.N <= 32768 ? 2u : 8u);
 }
 int launch_round_fused(const Shape& sh, const QuantizeArgs& a, const AggregateArgs& g);

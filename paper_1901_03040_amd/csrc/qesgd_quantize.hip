@@ -55,9 +55,9 @@ __global__ void k_quantize_pack(const QParams p) {
 //   d = 11 M, K = 8, s = 4, bucket 2048       77 ->  63 us = 6.24 TB/s
 //   d = 1 M, K = 8, s = 16, bucket 512      10.1 -> 9.3 us (launch and one round of loads)
 template <int M, int LOG2N, bool CENTER>
-__global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_fast(const QParams p) {
-    constexpr int CH = Geo<M, LOG2N>::CH;
-    constexpr uint32_t TILE = Geo<M, LOG2N>::TILE;
+__global__ void __launch_bounds__((Geo<M, LOG2N, CENTER>::NW * 64)) k_quantize_pack_fast(const QParams p) {
+    constexpr int CH = Geo<M, LOG2N, CENTER>::CH;
+    constexpr uint32_t TILE = Geo<M, LOG2N, CENTER>::TILE;
     __shared__ float sm[32];
 
     // Grid: (tiles, workers), so that nothing has to be divided; with a center (8 * workers, y, z).
@@ -95,20 +95,20 @@ __global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_fast
     if (t >= p.full_tiles) {                              // the ragged last tile of the worker (at most one)
         const uint32_t count = (uint32_t)(p.d - (uint64_t)t * TILE);
         load_tile<CH, CENTER, false>(xk + w0, ck + w0, cx.lane, true, buf, count_from(count, cx.wave * (uint32_t)(CH * kChunk)));
-        process_tile<M, LOG2N, false, Geo<M, LOG2N>, false>(cx, buf, t, sm, nullptr, count);
+        process_tile<M, LOG2N, false, Geo<M, LOG2N, CENTER>, false>(cx, buf, t, sm, nullptr, count);
         return;
     }
     load_tile<CH, CENTER>(xk + w0, ck + w0, cx.lane, p.x_cached, buf);
-    process_tile<M, LOG2N>(cx, buf, t, sm);
+    process_tile<M, LOG2N, false, Geo<M, LOG2N, CENTER>>(cx, buf, t, sm);
 }
 
 // The center form for several workers: a workgroup owns one tile of every worker, keeps the tile
 // of `center` in registers and takes the workers one after the other with the next worker's loads
 // in flight, so `center` is read once per tile instead of once per tile and worker.
 template <int M, int LOG2N>
-__global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_center(const QParams p) {
-    constexpr int CH = Geo<M, LOG2N>::CH;
-    constexpr uint32_t TILE = Geo<M, LOG2N>::TILE;
+__global__ void __launch_bounds__((Geo<M, LOG2N, true>::NW * 64)) k_quantize_pack_center(const QParams p) {
+    constexpr int CH = Geo<M, LOG2N, true>::CH;
+    constexpr uint32_t TILE = Geo<M, LOG2N, true>::TILE;
     __shared__ float sm[2][32];             // alternate per worker: one barrier per tile suffices
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
     const uint32_t K = p.group_workers;
@@ -132,7 +132,7 @@ __global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_cent
             float v[CH][8];
             load_tile<CH, true, false>(p.x + (uint64_t)k * p.x_stride + e0 + first, p.center + e0 + first, cx.lane, true, v,
                                        count_from(count, first));
-            process_tile<M, LOG2N, false, Geo<M, LOG2N>, false>(cx, v, t, sm[k & 1u], nullptr, count);
+            process_tile<M, LOG2N, false, Geo<M, LOG2N, true>, false>(cx, v, t, sm[k & 1u], nullptr, count);
         }
         return;
     }
@@ -163,7 +163,7 @@ __global__ void __launch_bounds__((Geo<M, LOG2N>::NW * 64)) k_quantize_pack_cent
         cx.signs = out + p.signs_off;
         cx.levels = out + p.levels_off;
         cx.worker = p.worker0 + k;
-        process_tile<M, LOG2N>(cx, v, t, sm[k & 1u]);
+        process_tile<M, LOG2N, false, Geo<M, LOG2N, true>>(cx, v, t, sm[k & 1u]);
         if (k + 1 < K) {
 #pragma unroll
             for (int c = 0; c < CH; ++c) { a[c] = na[c]; b[c] = nb2[c]; }
@@ -382,14 +382,14 @@ void launch_fast_one(const QParams& p, hipStream_t st) {
     const uint32_t tiles = p.full_tiles + p.tail_tiles;
     // With a center and enough tiles to fill the chip many times over (measured: it pays from about
     // 64 waves per SIMD on), a workgroup takes one tile of every worker and reads `center` once.
-    if (p.center && p.group_workers > 1 && (uint64_t)p.full_tiles * Geo<M, LOG2N>::NW >= 65536u) {
-        hipLaunchKernelGGL((k_quantize_pack_center<M, LOG2N>), dim3(tiles), dim3((Geo<M, LOG2N>::NW * 64)), 0, st, p);
+    if (p.center && p.group_workers > 1 && (uint64_t)p.full_tiles * Geo<M, LOG2N, true>::NW >= 65536u) {
+        hipLaunchKernelGGL((k_quantize_pack_center<M, LOG2N>), dim3(tiles), dim3((Geo<M, LOG2N, true>::NW * 64)), 0, st, p);
         return;
     }
     if (p.center) {
         const uint32_t octets = (tiles + 7u) / 8u, gz = (octets + 65534u) / 65535u, gy = (octets + gz - 1u) / gz;
         hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, true>), dim3(8u * p.group_workers, gy, gz),
-                           dim3((Geo<M, LOG2N>::NW * 64)), 0, st, p);
+                           dim3((Geo<M, LOG2N, true>::NW * 64)), 0, st, p);
         return;
     }
     hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, false>), dim3(tiles, p.group_workers),
@@ -553,7 +553,7 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         else if (sh.N == 16384) nwaves = 16;
         else if (sh.N == 32768) { ch = 4; nwaves = 16; }
     }
-    const uint64_t tile = fast ? fast_tile(sh.m, sh.N) : (uint64_t)nwaves * ch * kChunk;
+    const uint64_t tile = fast ? fast_tile(sh.m, sh.N, a.center != nullptr) : (uint64_t)nwaves * ch * kChunk;
     const uint64_t tiles = (slots + tile - 1) / tile;
     if (tiles * a.K >= (1ull << 31)) return QESGD_ERR_DIM;
     const dim3 block(nwaves * kWaveSize);

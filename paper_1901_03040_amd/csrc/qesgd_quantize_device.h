@@ -679,22 +679,22 @@ __device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint3
 // ---------------------------------------------------------------------------
 // Fast kernel.  Geometry per bucket size: tile = NW waves x CH chunks x 512.
 // ---------------------------------------------------------------------------
-template <int M, int LOG2N>
+template <int M, int LOG2N, bool CENTER = false>
 struct Geo {
-    // Chunks per wave and waves per workgroup, measured at 1.07 G coordinates.  Few level bits: two
-    // chunks per wave, the more bytes in flight the better (M = 1: 0.70 against 0.74 ms with bucket
-    // 512, M = 2: 0.73 against 0.75 ms with 2048); from M = 4 on the packed stores weigh more and one
-    // chunk is better (M = 8: 0.82 against 0.87 ms with 4096).  8192: two chunks, as fast as one with
-    // sixteen waves and open to a second workgroup per CU.  The workgroup is as small as the bucket
-    // allows, but not one wave (M = 4: the same; M = 1: 0.74 against 0.72 ms).
-    static constexpr int CH = LOG2N == 15 ? 4 : (LOG2N >= 13 || M <= 2 ? 2 : 1);
+    // Chunks per wave and waves per workgroup, measured at 480 M coordinates with the non-temporal streams.  Two
+    // chunks per wave, the more bytes in flight the better (one / two: M = 2, bucket 2048 361 / 341 us; M = 4,
+    // 512 377 / 358; M = 8, 128 421 / 393; M = 8, 4096 408 / 394; four are slower, M = 1, bucket 4096 at 1.1 G
+    // 860 / 811).  With a center its coordinates are held as well, and from M = 4 on one is better (58 M, K = 4,
+    // M = 4, whole round: 415 / 427 us).  The workgroup is as small as the bucket allows, but not one wave
+    // (M = 4: the same; M = 1: slower).
+    static constexpr int CH = LOG2N == 15 ? 4 : (CENTER && M > 2 && LOG2N < 13 ? 1 : 2);
     static constexpr int NW = (1 << LOG2N) / (CH * 512) < 2 ? 2 : (1 << LOG2N) / (CH * 512);
     static constexpr uint32_t TILE = (uint32_t)NW * CH * kChunk;
 };
 
-// Geo<M, log2 N>::TILE on the host.
-inline uint64_t fast_tile(uint32_t m, uint64_t N) {
-    const uint64_t ch = N == 32768 ? 4 : (N >= 8192 || m <= 2 ? 2 : 1);
+// Geo<m, log2 N, center>::TILE on the host.
+inline uint64_t fast_tile(uint32_t m, uint64_t N, bool center) {
+    const uint64_t ch = N == 32768 ? 4 : (center && m > 2 && N < 8192 ? 1 : 2);
     return N > 2 * ch * kChunk ? N : 2 * ch * kChunk;
 }
 

@@ -36,15 +36,16 @@ struct RParams {
 };
 
 // Tile of a workgroup: chunks per wave and waves.  The running sum and the next worker's coordinates are
-// held in registers next to the current ones, so fewer chunks fit than in the plain quantiser (two
-// chunks at bucket 2048, s = 4: 115 against 111 us at d = 11 M, K = 8).
+// held in registers next to the current ones, so fewer chunks fit than in the plain quantiser (two / one at
+// d = 12 M, K = 8, bucket 4096, s = 256: 128 / 119 us; but 8192, s = 4: 128 / 141 us, where one would need
+// sixteen waves).
 template <int LOG2N>
 struct RoundGeo {
-    static constexpr int CH = LOG2N <= 11 ? 1 : 2;
-    static constexpr int NW = (LOG2N <= 10) ? 2 : ((LOG2N <= 12) ? 4 : (LOG2N == 13 ? 8 : 16));
+    static constexpr int CH = LOG2N <= 12 ? 1 : 2;
+    static constexpr int NW = LOG2N <= 10 ? 2 : (1 << LOG2N) / (CH * 512);
     static constexpr uint32_t TILE = (uint32_t)NW * CH * kChunk;
 };
-inline uint64_t round_tile(uint64_t N) { return N > 2048 ? (N > 4096 ? N : 4096) : (N > 1024 ? N : 1024); }
+inline uint64_t round_tile(uint64_t N) { return N > 1024 ? N : 1024; }
 
 template <int M, int LOG2N, bool CENTER, bool FULL>
 __device__ __forceinline__ void round_one_tile(const RParams& r, uint32_t t, float (&sm)[2][32]) {
