@@ -13,18 +13,16 @@
 // with its bucket's total, so the scale never goes through memory.
 //
 // The kernels share the arithmetic:
-//   k_quantize_pack_fast  power-of-two buckets, L2 scale, level width dividing
-//                         32, tiles that lie wholly inside the vector.  N is a
-//                         template parameter, so the whole tile is straight-line
-//                         code without guards; the ragged last tile of a worker
-//                         runs the guarded body in the same launch.
-//   k_quantize_pack       everything else: buckets that are not a power of two,
-//                         max-norm, level widths 3/5/6/7, tiny vectors, and the
-//                         last pass of buckets too wide for one workgroup.
+//   k_quantize_pack_fast  power-of-two buckets, L2 scale, level width dividing 32.  N is a template
+//                         parameter, so a tile is straight-line code without guards; the ragged last
+//                         tile of a worker runs the same code with masked loads and stores.
+//   k_quantize_pack_center  the same with a center and several workers, one tile of every worker.
+//   k_quantize_pack       everything else: buckets that are not a power of two, max-norm, level
+//                         widths 3/5/6/7, and the last pass of the buckets among them that are too
+//                         wide for one workgroup.
 //   k_tile_partials(_fast), k_finish_norms, k_quantize_pack_pre_fast
-//                         buckets wider than kMaxSinglePassBucket: per-tile tree
-//                         sums into the workspace, the rest of each bucket's
-//                         tree, then the quantiser with the scale read back.
+//                         buckets wider than kMaxSinglePassBucket: per-tile tree sums into the
+//                         workspace, the rest of each bucket's tree, then the quantiser.
 #include <mutex>
 
 #include "qesgd_quantize_device.h"
@@ -44,16 +42,16 @@ __global__ void k_quantize_pack(const QParams p) {
     guarded_tile<M, CH, KIND, PRE>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
 }
 
-// One tile per workgroup; the ragged last tile of a worker, if any, runs the guarded code in
-// the same launch.  (Walking several tiles per workgroup with the next tile's loads
-// in flight was measured and is slower: the packed stores of a long-lived workgroup spread
-// out in time and the mixed read/write stream to HBM loses more than the prefetch gains.)
-// Bound by the read stream, with vector issue at about two thirds of it.  Before / after non-temporal
-// whole-line loads, the short rounding and the XCD-wise tile order (same machine, median of 25):
-//   d = 138 M, K = 8, s = 2, bucket 4096     851 -> 762 us = 6.18 TB/s
-//   d = 25.6 M, K = 16, s = 256, bucket 8192 380 -> 329 us = 6.38 TB/s
-//   d = 11 M, K = 8, s = 4, bucket 2048       77 ->  63 us = 6.24 TB/s
-//   d = 1 M, K = 8, s = 16, bucket 512      10.1 -> 9.3 us (launch and one round of loads)
+// One tile per workgroup.  (Walking several tiles per workgroup with the next tile's loads in flight was
+// measured and is slower: the packed stores of a long-lived workgroup spread out in time and the mixed
+// read/write stream to HBM loses more than the prefetch gains.)
+// Bound by the mix of reads and writes: at d = 138 M, K = 8, s = 2, bucket 4096 it takes 811 us, 610 us with
+// the stores left out (7.3 TB/s) and 813 us without Philox.  Before (32 bytes per lane, ordinary policy,
+// general rounding, tiles dealt round-robin) / now, same machine, two inputs in turn:
+//   d = 138 M, K = 8, s = 2, bucket 4096     850 -> 811 us = 5.8 TB/s (one input again and again: 741 us)
+//   d = 25.6 M, K = 16, s = 256, bucket 8192 380 -> 334 us = 6.3 TB/s
+//   d = 60 M, K = 8, s = 4, bucket 2048      364 -> 341 us = 6.2 TB/s
+//   d = 60 M, K = 8, s = 256, bucket 1024    402 -> 396 us = 6.2 TB/s
 template <int M, int LOG2N, bool CENTER>
 __global__ void __launch_bounds__((Geo<M, LOG2N, CENTER>::NW * 64)) k_quantize_pack_fast(const QParams p) {
     constexpr int CH = Geo<M, LOG2N, CENTER>::CH;

@@ -230,8 +230,8 @@ __device__ __forceinline__ Scale scale_of_total(float t) {
 // bits[] receives the 8*M level bits (M = 1: low byte, M = 2: low half, M = 4: one word, M = 8: two
 // words, M = 16: four words; M = 3, 5, 6, 7: the low 8*M bits of bits[0..1] read as one 64-bit string).
 //
-// Direct form, 5 instructions per coordinate with the sign and the packing (10 before; the quantiser
-// spent 0.62 ms of vector issue on d = 138 M, K = 8, s = 2 and is bound by it next to the read stream):
+// Direct form, 5 instructions per coordinate with the sign and the packing (10 before, which showed as
+// 0.62 ms of vector issue on d = 138 M, K = 8, s = 2):
 //   p = fma(v, mul, +0)       the product with its sign; the +0 turns -0 * mul into +0, so the sign bit
 //                             of p is [v < 0] also for v = -0, and changes no other product
 //   y = trunc(|p|) + r16 * 2^(16-M), saturating (v_mad_u32_u16 picks either half of the random word)
