@@ -69,25 +69,27 @@ __device__ __forceinline__ void store_stream(float* p, const vec4& v) {
 }
 __device__ __forceinline__ vec4 load_cached(const float* p) { return *reinterpret_cast<const vec4*>(p); }
 
-// CH x 512 coordinates of a vector, one float4 of each half chunk per lane, with either policy.  The
-// condition is uniform.  The empty asm statements keep the compiler from merging the two arms into one
-// set of loads, which would drop the policy.
+// CH x 512 coordinates of a vector, one float4 of each half chunk per lane, with either policy.
+template <int CH, bool CACHED>
+__device__ __forceinline__ void load_halves_as(const float* __restrict__ p, vec4 (&a)[CH], vec4 (&b)[CH]) {
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        a[c] = CACHED ? load_cached(p + c * kChunk) : load_stream(p + c * kChunk);
+        b[c] = CACHED ? load_cached(p + c * kChunk + kChunk / 2) : load_stream(p + c * kChunk + kChunk / 2);
+    }
+}
+// The policy chosen at run time; the condition is uniform.  The empty asm statements keep the compiler from
+// merging the two arms into one set of loads, which would drop the policy.  Not for loads that are to stay in
+// flight over other work: behind the arms the compiler no longer knows how many loads are younger than the
+// ones it needs, and waits for all of them.
 template <int CH>
 __device__ __forceinline__ void load_halves(const float* __restrict__ p, bool cached, vec4 (&a)[CH], vec4 (&b)[CH]) {
     if (cached) {
         asm volatile("; cached");
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            a[c] = load_cached(p + c * kChunk);
-            b[c] = load_cached(p + c * kChunk + kChunk / 2);
-        }
+        load_halves_as<CH, true>(p, a, b);
         asm volatile("; cached end");
     } else {
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            a[c] = load_stream(p + c * kChunk);
-            b[c] = load_stream(p + c * kChunk + kChunk / 2);
-        }
+        load_halves_as<CH, false>(p, a, b);
     }
 }
 
@@ -135,20 +137,26 @@ __device__ __forceinline__ void store_part(float* __restrict__ p, uint32_t at, u
     }
 }
 // CH x 512 coordinates of a vector from p on, one float4 of each half chunk per lane; at the ragged end of the
-// vector (FULL = false) the first `count`, the rest 0.
+// vector (FULL = false) the first `count`, the rest 0, with the ordinary policy.
+template <int CH>
+__device__ __forceinline__ void load_ragged(const float* __restrict__ p, uint32_t lane, uint32_t count, vec4 (&a)[CH], vec4 (&b)[CH]) {
+    const uint32_t h = half_offset(lane);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        a[c] = load_part(p, h + c * kChunk, count);
+        b[c] = load_part(p, h + c * kChunk + kChunk / 2, count);
+    }
+}
 template <int CH, bool FULL>
 __device__ __forceinline__ void load_chunks(const float* __restrict__ p, uint32_t lane, uint32_t count, bool cached,
                                             vec4 (&a)[CH], vec4 (&b)[CH]) {
-    const uint32_t h = half_offset(lane);
-    if (FULL) {
-        load_halves<CH>(p + h, cached, a, b);
-    } else {
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            a[c] = load_part(p, h + c * kChunk, count);
-            b[c] = load_part(p, h + c * kChunk + kChunk / 2, count);
-        }
-    }
+    if (FULL) load_halves<CH>(p + half_offset(lane), cached, a, b);
+    else load_ragged<CH>(p, lane, count, a, b);
+}
+template <int CH, bool FULL, bool CACHED>
+__device__ __forceinline__ void load_chunks_as(const float* __restrict__ p, uint32_t lane, uint32_t count, vec4 (&a)[CH], vec4 (&b)[CH]) {
+    if (FULL) load_halves_as<CH, CACHED>(p + half_offset(lane), a, b);
+    else load_ragged<CH>(p, lane, count, a, b);
 }
 // One float4 of each half of 512 coordinates, back.
 template <bool FULL>

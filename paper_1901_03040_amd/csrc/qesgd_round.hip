@@ -11,13 +11,16 @@
 // What this saves is one dependent launch per round and K*P bytes of reads.
 //
 // Bound by the stream of vectors where the tiles fill the chip, by the chain of K workers per tile
-// where they do not (see round_fused_pays).  All vectors move in halves of a KiB per instruction with
-// the non-temporal policy, in runs of 64 K coordinates per XCD; w and zsum are in flight while the last
-// worker is rounded.  Before (32 bytes per lane, ordinary policy, tiles dealt round-robin, update loads
-// after the last worker, z through LDS) / after:
+// where they do not (see round_fused_pays).  All vectors move in halves of a KiB per instruction, in runs
+// of 64 K coordinates per XCD, with the non-temporal policy unless the round fits the memory-side cache and
+// a wave owns one chunk; w and zsum are in flight while the last worker is rounded.  Before (32 bytes per
+// lane, ordinary policy, tiles dealt round-robin, update loads after the last worker, z through LDS) / after:
 //   d = 11 M, K = 8, s = 4, bucket 2048       118 -> 102 us = 6.0 TB/s
 //   d = 12 M, K = 16, s = 256, bucket 8192    245 -> 220 us = 5.7 TB/s
 //   d = 12 M, K = 2, s = 256, bucket 4096      73 ->  60 us
+// The policy is chosen outside the loop over the workers: a branch inside it made every worker wait for the
+// next one's coordinates (d = 2048, K = 8, s = 256, bucket 128: 7.65 us, 6.9 without, 6.7 with the ordinary
+// policy alone).
 #include "qesgd_aggregate_device.h"
 #include "qesgd_quantize_device.h"
 
@@ -47,7 +50,7 @@ struct RoundGeo {
 };
 inline uint64_t round_tile(uint64_t N) { return N > 1024 ? N : 1024; }
 
-template <int M, int LOG2N, bool CENTER, bool FULL>
+template <int M, int LOG2N, bool CENTER, bool FULL, bool CACHED>
 __device__ __forceinline__ void round_one_tile(const RParams& r, uint32_t t, float (&sm)[2][32]) {
     constexpr int CH = RoundGeo<LOG2N>::CH;
     constexpr uint32_t TILE = RoundGeo<LOG2N>::TILE;
@@ -63,50 +66,57 @@ __device__ __forceinline__ void round_one_tile(const RParams& r, uint32_t t, flo
     const uint32_t lane = cx.lane, first = cx.wave * (uint32_t)(CH * kChunk);
     const uint64_t o = (uint64_t)t * TILE + first;
     const uint32_t count = FULL ? TILE : (uint32_t)(p.d - (uint64_t)t * TILE), mine = FULL ? TILE : count_from(count, first);
-    // one branch per worker for the policy is free with one chunk per wave (99 against 103 us at d = 11 M,
-    // K = 8, bucket 2048) and costs 8% with two
-    const bool cached = CH == 1 && p.x_cached;
 
-    float acc[CH][8];
+    float acc[CH][8], v[CH][8];
 #pragma unroll
     for (int c = 0; c < CH; ++c)
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[c][e] = 0.0f;
-    vec4 ca[CH], cb[CH], a[CH], b[CH], na[CH], nb[CH], sa[CH], sb[CH];
-    if (CENTER) load_chunks<CH, FULL>(p.center + o, lane, mine, false, ca, cb);
-    load_chunks<CH, FULL>(p.x + o, lane, mine, cached, a, b);
+    vec4 ca[CH], cb[CH], a[CH], b[CH], sa[CH], sb[CH];
+    load_chunks_as<CH, FULL, CACHED>(p.x + o, lane, mine, a, b);
+    if (CENTER) load_chunks_as<CH, FULL, false>(p.center + o, lane, mine, ca, cb);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        if (CENTER) halves_to_lane(a[c] - ca[c], b[c] - cb[c], v[c]);
+        else halves_to_lane(a[c], b[c], v[c]);
+    }
     for (uint32_t k = 0; k < r.K; ++k) {
         // in flight while worker k is rounded: the next worker's coordinates, after the last the update's
         const bool last = k + 1 == r.K;
-        load_chunks<CH, FULL>((last ? r.w : p.x + (uint64_t)(k + 1) * p.x_stride) + o, lane, mine, cached, na, nb);
-        if (last && r.zsum) load_chunks<CH, FULL>(r.zsum + o, lane, mine, cached, sa, sb);
-        float v[CH][8];
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            if (CENTER) halves_to_lane(a[c] - ca[c], b[c] - cb[c], v[c]);
-            else halves_to_lane(a[c], b[c], v[c]);
-        }
+        if (last && r.zsum) load_chunks_as<CH, FULL, CACHED>(r.zsum + o, lane, mine, sa, sb);
+        load_chunks_as<CH, FULL, CACHED>((last ? r.w : p.x + (uint64_t)(k + 1) * p.x_stride) + o, lane, mine, a, b);
         unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
         cx.norms = reinterpret_cast<float*>(out + p.norms_off);
         cx.signs = out + p.signs_off;
         cx.levels = out + p.levels_off;
         cx.worker = p.worker0 + k;
         process_tile<M, LOG2N, true, RoundGeo<LOG2N>, FULL>(cx, v, t, sm[k & 1u], acc, count);
+        // the exchange stands at the end of the worker's work: it is what waits for the loads
 #pragma unroll
-        for (int c = 0; c < CH; ++c) { a[c] = na[c]; b[c] = nb[c]; }
+        for (int c = 0; c < CH; ++c) {
+            if (CENTER && !last) {
+                a[c] -= ca[c];
+                b[c] -= cb[c];
+            }
+            halves_to_lane(a[c], b[c], v[c]);
+        }
     }
     const float fk = (float)r.K;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        float z[8];
+        float z[8], u[8];                                 // v holds w
 #pragma unroll
-        for (int e = 0; e < 8; ++e) z[e] = (r.rcpK != 0.0f) ? acc[c][e] * r.rcpK : acc[c][e] / fk;
-        vec4 za, zb;
+        for (int e = 0; e < 8; ++e) {
+            z[e] = (r.rcpK != 0.0f) ? acc[c][e] * r.rcpK : acc[c][e] / fk;
+            u[e] = v[c][e] + z[e];
+        }
+        vec4 za, zb, ua, ub;
         lane_to_halves(z, za, zb);
+        lane_to_halves(u, ua, ub);
         const uint64_t oc = o + (uint32_t)c * kChunk;
         const uint32_t left = FULL ? kChunk : count_from(mine, (uint32_t)c * kChunk);
         if (r.zbar) store_chunk<FULL>(r.zbar + oc, lane, left, za, zb);
-        store_chunk<FULL>(r.u + oc, lane, left, a[c] + za, b[c] + zb);
+        store_chunk<FULL>(r.u + oc, lane, left, ua, ub);
         if (r.zsum) store_chunk<FULL>(r.zsum + oc, lane, left, sa[c] + za, sb[c] + zb);
     }
 }
@@ -115,8 +125,11 @@ template <int M, int LOG2N, bool CENTER>
 __global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const RParams r) {
     __shared__ float sm[2][32];             // alternate per worker: one barrier per tile suffices
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, r.q.xcd_group);
-    if (t < r.q.full_tiles) round_one_tile<M, LOG2N, CENTER, true>(r, t, sm);
-    else round_one_tile<M, LOG2N, CENTER, false>(r, t, sm);   // the ragged last tile (at most one)
+    // the policy is chosen once, outside the loop over the workers (see load_halves); with two chunks per wave
+    // there is one form
+    if (t >= r.q.full_tiles) round_one_tile<M, LOG2N, CENTER, false, true>(r, t, sm);   // the ragged last tile (at most one)
+    else if (RoundGeo<LOG2N>::CH == 1 && r.q.x_cached) round_one_tile<M, LOG2N, CENTER, true, RoundGeo<LOG2N>::CH == 1>(r, t, sm);
+    else round_one_tile<M, LOG2N, CENTER, true, false>(r, t, sm);
 }
 
 // The same behind the launches that found the scales of wide buckets: no wave needs another, so a wave owns
@@ -124,9 +137,9 @@ __global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const 
 // partial sums by the workgroup's waves in turn) and hands it out as a scalar.  ZACC: z_acc += the mean.
 // Bound by the stream of vectors; the codes are written but not read back.  Gradient round as four calls
 // (partial sums, trees and codes per group of workers, mean, two updates) / as one call:
-//   d = 25.6 M, K = 16, s = 256, one bucket    921 -> 771 us (both passes over x at 6.7 TB/s: 490 us)
 //   d = 853 K, K = 8, s = 256, one bucket     31.0 -> 21.3 us (partial sums, this; the chain of 8 workers)
 //   d = 30 M, K = 4, s = 8, one bucket         378 -> 288 us
+// (beyond about 1.2 GB, d = 25.6 M, K = 16 among them, the round takes two launches: see round_fused_pays)
 // One wave per workgroup would finish every scale by itself; four share that work.
 constexpr uint32_t kWideWaves = 4;
 
@@ -146,6 +159,8 @@ __device__ __forceinline__ void wide_chunk(const RParams& r, uint64_t c0, uint32
     for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
     for (uint32_t k = 0; k < r.K; ++k) {
         const bool last = k + 1 == r.K;
+        // (a choice in the loop, unlike in round_one_tile: two copies of the loop were slower here, 19.6 against
+        // 18.6 us at d = 853 K, K = 8, s = 256)
         load_chunks<1, FULL>((last ? r.w : p.x + (uint64_t)(k + 1) * p.x_stride) + c0, lane, count, cached, na, nb);
         if (last && r.zsum) load_chunks<1, FULL>(r.zsum + c0, lane, count, cached, sa, sb);
         if (last && ZACC) load_chunks<1, FULL>(r.z_acc + c0, lane, count, cached, ta, tb);
