@@ -95,18 +95,32 @@ bool dense_wide(const Shape& sh, uint32_t norm_kind);
 bool round_fused_covers(const Shape& sh, uint32_t norm_kind);
 // One launch or two.  One launch takes the workers of a tile one after the other, about 1 us each (2.4 us
 // with buckets of 4096 and more, whose waves meet at a barrier per worker), which only a chip full of
-// tiles hides; two launches spread tiles and workers over the chip at once.  Measured, one / two:
-// d = 0.1 M, K = 8, bucket 4096: 23 / 10 us; 1 M, K = 16, bucket 8192: 44 / 25 us; 1 M, K = 16, bucket
-// 1024: 30 / 23 us; 2 M, K = 16, bucket 8192: 40 / 43 us; 1 M, K = 8, bucket 512: 14.0 / 14.2 us; 1 M,
-// K = 2, bucket 16384: 10.2 / 10.8 us.  Buckets of 32768 would need 300 registers per lane.
-// A wave that owns one chunk of every worker (buckets up to 4096, and wide ones) falls behind two launches
-// where a round no longer fits about 1.2 GB: d = 20 M, K = 8, s = 16, bucket 512 178 / 190 us; 30 M 313 /
-// 289 us; 138 M, K = 4, s = 16, one bucket 1298 / 1235 us; with two chunks it does not (60 M, K = 8, bucket
-// 8192: 584 / 604 us).
-inline bool round_fused_pays(const Shape& sh, uint32_t K) {
-    const bool narrow = sh.N <= 4096 || sh.N > 32768;
-    if (narrow && 4u * (uint64_t)K * sh.d + update_bytes(sh, K) > (1250ull << 20)) return false;
-    return sh.d >= (3u << 19) || K <= (sh.N > 2048 && sh.N <= 32768 ? 2u : 8u);
+// tiles hides; two launches spread tiles and workers over the chip at once.  Measured, one / two, whole round:
+//   from 1.5 M coordinates on       1.7 M, K = 16, bucket 512: 32.1 / 34.8 us; 1.7 M, K = 4, bucket 8192: 14.1 / 15.9;
+//                                   12 M, K = 16, bucket 8192: 183 / 187; 12 M, K = 8, bucket 16384: 126 / 129
+//     (with 8192 and 16384 two would be better up to about 10 M: 2.4 M, K = 8, bucket 8192 34.8 / 26.1; 5 M, K = 8,
+//     54 / 48; 1.7 M, K = 8, bucket 16384 31.5 / 22.4; not so with K = 1, 2: 2.4 M, K = 2, bucket 16384 14.2 / 17.4)
+//   below, up to 8 workers          1 M, K = 8, bucket 512: 11.0 / 14.6; 0.1 M, K = 8, bucket 64: 7.6 / 7.2
+//     up to 16 from 0.65 M (buckets up to 1024) or 1 M (2048) on, where there is no ragged tile, whose chain is longer
+//                                   1 M, K = 16, bucket 128: 16.5 / 22.6; 0.7 M, K = 12, bucket 512: 13.5 / 15.2;
+//                                   0.4 M, K = 12: 13.0 / 12.4; 1 M, K = 16, bucket 2048: 18.9 / 22.8; 0.7 M, K = 9,
+//                                   2048: 14.7 / 13.5; 1 M, K = 32, bucket 128: 47.5 / 37.6; ragged, 1 M, K = 16,
+//                                   bucket 512: 22.4 / 21.5, with a center 25.2 / 21.2
+//     up to 2 with 4096 and 8192    0.5 M, K = 1, bucket 8192: 5.7 / 6.9; 0.2 M, K = 8, 4096: 11.8 / 8.1
+//     none with 16384               0.5 M, K = 1: 9.3 / 8.3; 20 K, K = 1: 8.7 / 7.0; 0.5 M, K = 2: 12.8 / 8.5
+// Buckets of 32768 would need 300 registers per lane.
+// A wave that owns one chunk of every worker (buckets up to 4096, and wide ones) falls behind two launches where a
+// round no longer fits about 1.2 GB, unless the workers' side is the dearer for it: level widths of 8 and more, whose
+// codes cost the most to read back, or a center.  K = 16, 25 M, bucket 512: s = 4 415 / 388 us, s = 16 443 / 425, with a
+// center 426 / 482; s = 65536 577 / 634; bucket 4096, s = 256 465 / 492, with a center 484 / 600; one bucket, 138 M,
+// K = 4, s = 16 1298 / 1235.
+inline bool round_fused_pays(const Shape& sh, uint32_t K, bool center) {
+    const bool wide = sh.N > 32768, narrow = sh.N <= 4096 && sh.m < 8 && !center;
+    if ((wide || narrow) && 4u * (uint64_t)K * sh.d + update_bytes(sh, K) > (1250ull << 20)) return false;
+    if (sh.d >= (3u << 19)) return true;
+    const uint64_t tile = sh.N <= 1024 ? 1024 : sh.N;
+    if (sh.N <= 2048 && K <= 16 && sh.d >= (sh.N <= 1024 ? 5u << 17 : 15u << 16) && sh.d % tile == 0) return true;
+    return K <= (sh.N <= 2048 || wide ? 8u : sh.N <= 8192 ? 2u : 0u);
 }
 int launch_round_fused(const Shape& sh, const QuantizeArgs& a, const AggregateArgs& g);
 int launch_apply_update(const float* w, const float* zbar, float* u, float* zsum, uint64_t d,

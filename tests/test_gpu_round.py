@@ -71,12 +71,28 @@ def test_one_launch_shapes_equal_two_calls(B, log2n, s, K):
 @pytest.mark.parametrize("s", [2, 16, 256])
 @pytest.mark.parametrize("d,K", [(1_572_864, 3), (1_572_863, 9), (1_600_037, 16), (4_800_000, 3)])
 def test_both_sides_of_the_one_launch_rule(B, bucket, s, d, K):
-    """Many workers take one launch only from 1.5 M coordinates on; the vectors' cache policy changes at
-    the last size.  (Buckets of 32768 never do.)"""
+    """All these buckets take one launch from 1.5 M coordinates on, many workers with short vectors two.  The
+    vectors of (1_600_037, 16) are beyond the ordinary cache policy.  (Buckets of 32768 never take one launch.)"""
     g = torch.Generator(device="cuda").manual_seed(d + K)
     slab = torch.randn(K, (d + 63) // 64 * 64, generator=g, device="cuda") * 1e-3
     w = torch.randn(d, generator=g, device="cuda")
     _, out = both_forms(B, slab, None, d, s, bucket, 0, 99, 3, K, w, w * 1e-2)
+    assert_same(out)
+
+
+@pytest.mark.parametrize("d,K,bucket,s,centered", [
+    (654_336, 12, 512, 4, False), (655_360, 12, 512, 4, True), (655_361, 12, 512, 4, True), (981_000, 16, 2048, 256, False),
+    (983_040, 16, 2048, 256, True), (983_040, 17, 128, 16, False), (500_003, 1, 16_384, 256, True),
+    (500_000, 2, 8192, 4, False), (500_000, 3, 8192, 4, False),
+    (11_000_003, 32, 512, 4, False), (11_000_003, 32, 512, 4, True), (11_000_003, 32, 512, 256, False),  # beyond 1.25 GB
+    (11_000_000, 32, 8192, 16, False)])
+def test_sides_of_the_one_launch_rule_by_workers_and_size(B, d, K, bucket, s, centered):
+    """The lines between one launch and two: workers and length by bucket; beyond 1.25 GB level width and center."""
+    g = torch.Generator(device="cuda").manual_seed(d + K)
+    slab = torch.randn(K, (d + 63) // 64 * 64, generator=g, device="cuda") * 1e-3
+    w = torch.randn(d, generator=g, device="cuda")
+    center = torch.randn(d, generator=g, device="cuda") * 1e-3 if centered else None
+    _, out = both_forms(B, slab, center, d, s, bucket, 0, 99, 3, K, w, w * 1e-2)
     assert_same(out)
 
 
