@@ -35,11 +35,11 @@ static __device__ __align__(256) float scratch[qesgd::kStaticScratchFloats];
 namespace qesgd {
 namespace {
 
-// PRE: second pass of a wide bucket.
-template <int M, int CH, int KIND, bool PRE>
+// PRE: second pass of a wide bucket.  CONTIG: see LaneSpan.
+template <int M, int CH, int KIND, bool PRE, bool CONTIG, bool CENTER>
 __global__ void k_quantize_pack(const QParams p) {
     __shared__ float sm[32];
-    guarded_tile<M, CH, KIND, PRE>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
+    guarded_tile<M, CH, KIND, PRE, CONTIG, CENTER>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
 }
 
 // One tile per workgroup.  (Walking several tiles per workgroup with the next tile's loads in flight was
@@ -172,15 +172,15 @@ __global__ void __launch_bounds__((Geo<M, LOG2N, true>::NW * 64)) k_quantize_pac
 // Tree sum (or max) of one 4096-slot tile of worker k with every access guarded per lane, left in
 // the workspace.  Tiles of a bucket are consecutive in slot space, so the workspace index of
 // (bucket, tile in bucket) is the tile index.  sm: 4 floats of LDS.
-template <int KIND>
+template <int KIND, bool CENTER>
 __device__ __forceinline__ void guarded_partial_tile(const QParams& p, uint32_t k, uint32_t tile, float* sm) {
     constexpr int CH = 2;
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = threadIdx.x >> 6;
     LaneSpan span[CH];
     float v[CH][8], t[CH];
-    guarded_spans<CH>(p, tile, span);
-    guarded_load<CH>(p, k, span, v);
+    guarded_spans<CH, true, true>(p, tile, span);
+    guarded_load<CH, true, CENTER>(p, k, span, v);
 #pragma unroll
     for (int c = 0; c < CH; ++c) t[c] = lane_butterfly<KIND>(lane_tree<KIND>(v[c]), 64);
     t[0] = combine<KIND>(t[0], t[1]);
@@ -205,7 +205,7 @@ __global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
     const uint32_t k = blockIdx.y;
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
     if (t >= p.full_tiles) {                              // the ragged last tile of the worker (at most one)
-        guarded_partial_tile<KIND>(p, k, t, sm);
+        guarded_partial_tile<KIND, CENTER>(p, k, t, sm);
         return;
     }
     const uint64_t w0 = (uint64_t)t * kPartialTile + wave * (2u * kChunk);
@@ -236,8 +236,8 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
         const uint64_t w0 = e0 + wave * (2u * kChunk);
         load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, p.x_cached, v);
     } else {                                              // the ragged last tile of the worker (at most one)
-        guarded_spans<2>(p, t, span);
-        guarded_load<2>(p, k, span, v);
+        guarded_spans<2, true, true>(p, t, span);
+        guarded_load<2, true, CENTER>(p, k, span, v);
     }
     Scale sc;
     if (p.merged) {
@@ -250,7 +250,7 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
         sc = scale_of_norm<M>(norms[b]);
     }
     if (!full) {
-        guarded_codes<M, 2, QESGD_NORM_L2, true>(p, k, span, v, nullptr, true, sc.norm);
+        guarded_codes<M, 2, QESGD_NORM_L2, true, true>(p, k, span, v, nullptr, true, sc.norm);
         return;
     }
     const uint32_t idx0 = wave * 2u * kWaveSize + lane;
@@ -276,10 +276,10 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
 // bucket and writes the scale, then k_quantize_pack<.., PRE = true> reads it.
 // workspace[(k*nb + b)*P + t], P = N / 4096.
 // ---------------------------------------------------------------------------
-template <int KIND>
+template <int KIND, bool CENTER>
 __global__ void k_tile_partials(const QParams p) {
     __shared__ float sm[4];
-    guarded_partial_tile<KIND>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
+    guarded_partial_tile<KIND, CENTER>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
 }
 
 // Finishes the tree of one bucket: P leaves (a power of two, >= 16), of which only the first
@@ -352,26 +352,36 @@ __global__ void __launch_bounds__(1024) k_finish_norms(const QParams p, uint64_t
 // ---------------------------------------------------------------------------
 // Launch plumbing.
 // ---------------------------------------------------------------------------
-template <int M, int CH, bool PRE>
-void launch_kind(const QParams& p, uint32_t norm_kind, dim3 grid, dim3 block, hipStream_t st) {
-    if (norm_kind == QESGD_NORM_L2)
-        hipLaunchKernelGGL((k_quantize_pack<M, CH, QESGD_NORM_L2, PRE>), grid, block, 0, st, p);
-    else
-        hipLaunchKernelGGL((k_quantize_pack<M, CH, QESGD_NORM_MAX, PRE>), grid, block, 0, st, p);
+template <int M, int CH, int KIND, bool PRE, bool CONTIG>
+void launch_center(const QParams& p, dim3 grid, dim3 block, hipStream_t st) {
+    if (p.center) hipLaunchKernelGGL((k_quantize_pack<M, CH, KIND, PRE, CONTIG, true>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((k_quantize_pack<M, CH, KIND, PRE, CONTIG, false>), grid, block, 0, st, p);
 }
 
-template <int CH, bool PRE>
+template <int M, int CH, bool PRE, bool CONTIG>
+void launch_kind(const QParams& p, uint32_t norm_kind, dim3 grid, dim3 block, hipStream_t st) {
+    if (norm_kind == QESGD_NORM_L2) launch_center<M, CH, QESGD_NORM_L2, PRE, CONTIG>(p, grid, block, st);
+    else launch_center<M, CH, QESGD_NORM_MAX, PRE, CONTIG>(p, grid, block, st);
+}
+
+template <int KIND>
+void launch_partials(const QParams& p, dim3 grid, hipStream_t st) {
+    if (p.center) hipLaunchKernelGGL((k_tile_partials<KIND, true>), grid, dim3(256), 0, st, p);
+    else hipLaunchKernelGGL((k_tile_partials<KIND, false>), grid, dim3(256), 0, st, p);
+}
+
+template <int CH, bool PRE, bool CONTIG = true>
 void launch_m(const QParams& p, uint32_t m, uint32_t norm_kind, dim3 grid, dim3 block, hipStream_t st) {
     switch (m) {
-        case 1: launch_kind<1, CH, PRE>(p, norm_kind, grid, block, st); break;
-        case 2: launch_kind<2, CH, PRE>(p, norm_kind, grid, block, st); break;
-        case 3: launch_kind<3, CH, PRE>(p, norm_kind, grid, block, st); break;
-        case 4: launch_kind<4, CH, PRE>(p, norm_kind, grid, block, st); break;
-        case 5: launch_kind<5, CH, PRE>(p, norm_kind, grid, block, st); break;
-        case 6: launch_kind<6, CH, PRE>(p, norm_kind, grid, block, st); break;
-        case 7: launch_kind<7, CH, PRE>(p, norm_kind, grid, block, st); break;
-        case 8: launch_kind<8, CH, PRE>(p, norm_kind, grid, block, st); break;
-        default: launch_kind<16, CH, PRE>(p, norm_kind, grid, block, st); break;
+        case 1: launch_kind<1, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
+        case 2: launch_kind<2, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
+        case 3: launch_kind<3, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
+        case 4: launch_kind<4, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
+        case 5: launch_kind<5, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
+        case 6: launch_kind<6, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
+        case 7: launch_kind<7, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
+        case 8: launch_kind<8, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
+        default: launch_kind<16, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
     }
 }
 
@@ -496,6 +506,7 @@ QParams quantize_params(const Shape& sh, const QuantizeArgs& a) {
     p.signs_off = sh.lay.signs_off;
     p.levels_off = sh.lay.levels_off;
     p.log2N = sh.log2N;
+    p.log2_waves = 2;
     p.key0 = (uint32_t)a.seed;
     p.key1 = (uint32_t)(a.seed >> 32);
     p.round = a.round;
@@ -555,6 +566,7 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
     const uint64_t tiles = (slots + tile - 1) / tile;
     if (tiles * a.K >= (1ull << 31)) return QESGD_ERR_DIM;
     const dim3 block(nwaves * kWaveSize);
+    p.log2_waves = nwaves == 16 ? 4 : nwaves == 8 ? 3 : 2;
 
     if (dense_wide(sh, a.norm_kind)) {
         // All workers at once in both passes: taking them in groups that fit the memory-side cache, with the
@@ -576,10 +588,10 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         p.xcd_group = xcd_group_log2(kPartialTile);
         const dim3 grid((uint32_t)p.data_tiles, a.K), finish_grid((uint32_t)(sh.nb * a.K)), finish_block(finish_waves * kWaveSize);
         if (a.norm_kind == QESGD_NORM_L2) {
-            hipLaunchKernelGGL(k_tile_partials<QESGD_NORM_L2>, grid, block, 0, a.stream, p);
+            launch_partials<QESGD_NORM_L2>(p, grid, a.stream);
             hipLaunchKernelGGL(k_finish_norms<QESGD_NORM_L2>, finish_grid, finish_block, 0, a.stream, p, P, dense ? 1u : 0u);
         } else {
-            hipLaunchKernelGGL(k_tile_partials<QESGD_NORM_MAX>, grid, block, 0, a.stream, p);
+            launch_partials<QESGD_NORM_MAX>(p, grid, a.stream);
             hipLaunchKernelGGL(k_finish_norms<QESGD_NORM_MAX>, finish_grid, finish_block, 0, a.stream, p, P, dense ? 1u : 0u);
         }
         const int rc = check_launch();
@@ -598,7 +610,8 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
     }
     p.xcd_group = xcd_group_log2(tile);
     const dim3 grid((uint32_t)tiles, a.K);
-    if (ch == 2) launch_m<2, false>(p, sh.m, a.norm_kind, grid, block, a.stream);
+    if (ch == 2 && (sh.N >= 2 * kChunk || sh.N == sh.B)) launch_m<2, false>(p, sh.m, a.norm_kind, grid, block, a.stream);
+    else if (ch == 2) launch_m<2, false, false>(p, sh.m, a.norm_kind, grid, block, a.stream);
     else launch_m<4, false>(p, sh.m, a.norm_kind, grid, block, a.stream);
     return check_launch();
 }

@@ -23,6 +23,7 @@ struct QParams {
     uint64_t nb;
     uint64_t norms_off, signs_off, levels_off;
     uint32_t log2N;
+    uint32_t log2_waves;         // guarded tiles: waves per workgroup
     uint32_t full_tiles;         // fast kernels: tiles per worker that lie wholly inside the vector
     uint32_t tail_tiles;         // fast quantize kernel: ragged tiles per worker after those (0 or 1)
     uint32_t group_workers;      // workers covered by this launch
@@ -472,18 +473,23 @@ __device__ __forceinline__ void store_whole(unsigned char* __restrict__ signs, u
 // ---------------------------------------------------------------------------
 // Guarded tile: the body of the generic kernel and of the last pass's ragged tile.
 // ---------------------------------------------------------------------------
-// Where the 8 slots of this lane fall: bucket, first coordinate, how many of
-// them are real coordinates (0..8), and whether they open the bucket.
+// Where the 8 slots of this lane in a chunk of 512 fall: bucket, first coordinate, how many of them are real
+// coordinates (0..8), and whether they open the bucket.  CONTIG: the chunk's slots are consecutive coordinates
+// as far as they hold any, `count` from coordinate i0 on, the same for the wave and worked out in scalar
+// registers: buckets padded to 1024 or more, and power-of-two buckets.  (Buckets of 256 to 512 are faster lane by
+// lane, every wave of theirs holding padding: d = 15 M, K = 5, s = 16, bucket 320 84.0 / 76.0 us.)
 struct LaneSpan {
     uint64_t bucket;
     uint64_t i;        // first coordinate (a multiple of 8)
+    uint64_t i0;       // CONTIG only
+    uint64_t safe;     // not CONTIG: 4 coordinates that exist (d >= 4)
+    uint32_t count;    // CONTIG only
     uint32_t nvalid;
     bool opens_bucket;
-    bool whole;        // the wave's 512 slots are 512 consecutive coordinates
 };
 
 __device__ __forceinline__ LaneSpan lane_span(uint64_t slot, const QParams& p) {
-    LaneSpan s;
+    LaneSpan s{};
     const uint64_t N = 1ull << p.log2N;
     s.bucket = slot >> p.log2N;
     const uint64_t j = slot & (N - 1);
@@ -494,92 +500,164 @@ __device__ __forceinline__ LaneSpan lane_span(uint64_t slot, const QParams& p) {
     }
     s.nvalid = j < len ? (uint32_t)((len - j) < 8 ? (len - j) : 8) : 0u;
     s.i = s.bucket * p.B + j;
+    s.safe = len >= 4 ? s.i - j : 0;
     s.opens_bucket = (j == 0) && (s.bucket < p.nb);
-    s.whole = false;
     return s;
 }
 
-// The slots of this lane in the chunk that starts at `slot` (a multiple of 512, the same for the wave).
-// Where a bucket fills whole chunks the place of the chunk is worked out once per wave, in scalar registers.
-__device__ __forceinline__ LaneSpan chunk_span(uint64_t slot, uint32_t lane, const QParams& p) {
-    if ((1ull << p.log2N) < kChunk) return lane_span(slot + lane * kLaneElems, p);
-    LaneSpan s;
-    s.bucket = slot >> p.log2N;
-    const uint64_t j = slot & ((1ull << p.log2N) - 1u);
-    uint32_t count = 0;                                   // coordinates in the chunk
-    if (s.bucket < p.nb) {
-        const uint64_t rem = p.d - s.bucket * p.B;
-        const uint64_t len = rem < p.B ? rem : p.B;
-        count = j < len ? (uint32_t)((len - j) < kChunk ? (len - j) : kChunk) : 0u;
-    }
-    const uint32_t before = lane * kLaneElems;
-    s.nvalid = before < count ? (count - before < 8u ? count - before : 8u) : 0u;
-    s.i = s.bucket * p.B + j + before;
-    s.opens_bucket = j == 0 && lane == 0 && s.bucket < p.nb;
-    s.whole = false;
-    return s;
-}
-
-// The slots of this lane in a guarded tile (the same for every worker).
-template <int CH>
+// The slots of this lane in a guarded tile (the same for every worker).  ONE: the wave's chunks lie in one bucket.
+template <int CH, bool CONTIG, bool ONE>
 __device__ __forceinline__ void guarded_spans(const QParams& p, uint32_t tile, LaneSpan (&span)[CH]) {
-    const uint64_t wave0 = (uint64_t)tile * (blockDim.x >> 6) + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t lane = threadIdx.x & 63u, before = lane * kLaneElems;
+    const uint64_t wave0 = ((uint64_t)tile << p.log2_waves) + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t slot0 = wave0 * (uint64_t)(CH * kChunk), N = 1ull << p.log2N;
+    const bool one = ONE || N >= (uint64_t)CH * kChunk;   // otherwise B == N
+    uint64_t bucket = 0, j = 0, i0 = 0;
+    uint32_t rest = 0;                                    // coordinates from i0 to the end of the bucket, at most CH * 512
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        span[c] = chunk_span((wave0 * (uint64_t)CH + (uint64_t)c) * kChunk, threadIdx.x & 63u, p);
-        const uint32_t i = (uint32_t)span[c].i;
-        span[c].whole = wave_all(span[c].nvalid == 8) &&
-                        __builtin_amdgcn_readlane(i, 63) - __builtin_amdgcn_readlane(i, 0) == 63u * kLaneElems;
-    }
-}
-
-// One vector's coordinates of those slots, still in the layout they were loaded in.  A chunk whose slots are
-// 512 consecutive coordinates is loaded like a full tile (halves, see halves_to_lane); otherwise a lane loads
-// its own: 8, none, or at the end of the vector the first few.
-template <int CH>
-__device__ __forceinline__ void guarded_load_raw(const float* __restrict__ x, const LaneSpan (&span)[CH],
-                                                 bool cached, vec4 (&a)[CH], vec4 (&b)[CH]) {
-    const uint32_t lane = threadIdx.x & 63u;
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        const float* __restrict__ src = x + span[c].i;
-        if (span[c].whole) {
-            vec4 ha[1], hb[1];
-            load_halves<1>(src - lane * kLaneElems + half_offset(lane), cached, ha, hb);
-            a[c] = ha[0];
-            b[c] = hb[0];
-        } else {
-            a[c] = vec4{0.0f, 0.0f, 0.0f, 0.0f};
-            b[c] = a[c];
-            if (span[c].nvalid == 8) {
-                a[c] = load_cached(src);
-                b[c] = load_cached(src + 4);
-            } else if (span[c].nvalid > 0) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    if ((uint32_t)e < span[c].nvalid) a[c][e] = src[e];
-                    if ((uint32_t)e + 4u < span[c].nvalid) b[c][e] = src[e + 4];
-                }
+        const uint64_t slot = slot0 + (uint32_t)c * kChunk;
+        if (!CONTIG) {
+            span[c] = lane_span(slot + before, p);
+            continue;
+        }
+        if (c == 0 || !one) {
+            uint64_t end = p.d;
+            i0 = slot;
+            if (one) {
+                bucket = slot >> p.log2N;
+                j = slot & (N - 1);
+                i0 = bucket * p.B + j;
+                end = bucket >= p.nb ? 0 : bucket * p.B + p.B < p.d ? bucket * p.B + p.B : p.d;
             }
+            const uint64_t left = i0 < end ? end - i0 : 0;
+            rest = left < CH * kChunk ? (uint32_t)left : CH * kChunk;
+        } else {
+            i0 += kChunk;
+            rest = rest > kChunk ? rest - kChunk : 0;
+        }
+        span[c].i0 = i0;
+        span[c].count = rest < kChunk ? rest : kChunk;
+        span[c].i = i0 + before;
+        span[c].nvalid = before < span[c].count ? (span[c].count - before < 8u ? span[c].count - before : 8u) : 0u;
+        if (one) {
+            span[c].bucket = bucket;
+            span[c].opens_bucket = c == 0 && j == 0 && lane == 0 && bucket < p.nb;
+        } else {
+            span[c].bucket = (slot + before) >> p.log2N;
+            span[c].opens_bucket = ((slot + before) & (N - 1)) == 0 && span[c].nvalid > 0;
         }
     }
 }
-template <int CH>
-__device__ __forceinline__ void guarded_load(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], float (&v)[CH][8]) {
-    vec4 a[CH], b[CH];
-    guarded_load_raw<CH>(p.x + (uint64_t)k * p.x_stride, span, p.x_cached, a, b);
-    if (p.center) {
-        vec4 ca[CH], cb[CH];
-        guarded_load_raw<CH>(p.center, span, true, ca, cb);
+
+// How many coordinates the two float4 that this lane loads of a chunk hold (0..4 and more), and the place of the
+// first.  CONTIG: like a full tile, one of each half (see halves_to_lane); otherwise the lane's own 8.
+template <bool CONTIG>
+struct GuardedLoad {
+    static constexpr uint32_t step = CONTIG ? kChunk / 2 : 4u;      // from the first to the second
+    uint32_t na, nb;
+    uint64_t at;
+    __device__ __forceinline__ explicit GuardedLoad(const LaneSpan& s) {
+        const uint32_t h = CONTIG ? half_offset(threadIdx.x & 63u) : 0u, count = CONTIG ? s.count : s.nvalid;
+        na = count > h ? count - h : 0u;
+        nb = count > h + step ? count - h - step : 0u;
+        at = CONTIG ? s.i0 + h : s.i;
+    }
+};
+// A float4 that the vector ends in.
+template <bool CENTER>
+__device__ __forceinline__ void load_end(const float* __restrict__ x, const float* __restrict__ center, uint64_t at, uint32_t n, vec4& a) {
+    if (n == 0u || n >= 4u) return;
+#pragma unroll
+    for (uint32_t e = 0; e < 3; ++e)
+        if (e < n) a[e] = CENTER ? x[at + e] - center[at + e] : x[at + e];
+}
+
+// One vector's coordinates of those slots, in the layout they are loaded in.  FULL: all slots of the wave hold some.
+// Otherwise a float4 that is not wholly inside means nothing; it is read where the wave or the bucket reads anyway
+// (CONTIG: the wave's first four coordinates, or the four before it where it holds fewer: a vector in this form has 8
+// or more).  Nothing here waits: the loads of all chunks, and of the center behind them, are in flight together
+// (a wait between the chunks: d = 15 M, K = 5, s = 4, max norm, bucket 23648 119.7 us, without 83.7; with a center, L2
+// 146.5 / 126.7; d = 3.5 M, K = 8, s = 256, bucket 23648 47.4 / 37.0).
+template <int CH, bool CONTIG, bool FULL, bool CACHED>
+__device__ __forceinline__ void guarded_load_raw(const float* __restrict__ x, const LaneSpan (&span)[CH], vec4 (&a)[CH], vec4 (&b)[CH]) {
+    const uint64_t first = span[0].count >= 4u ? span[0].i0 : span[0].i0 - 4u;
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const GuardedLoad<CONTIG> l(span[c]);
+        const float *pa, *pb;
+        if (CONTIG) {                                     // a scalar base and 32-bit offsets
+            const float* __restrict__ base = x + (FULL || span[c].count >= 4u ? span[c].i0 : first);
+            const uint32_t h = half_offset(threadIdx.x & 63u);
+            pa = base + (FULL || l.na >= 4u ? h : 0u);
+            pb = base + (FULL || l.nb >= 4u ? h + l.step : 0u);
+        } else {
+            pa = x + (l.na >= 4u ? l.at : span[c].safe);
+            pb = x + (l.nb >= 4u ? l.at + l.step : span[c].safe);
+        }
+        a[c] = CACHED ? load_cached(pa) : load_stream(pa);
+        b[c] = CACHED ? load_cached(pb) : load_stream(pb);
+    }
+}
+template <int CH, bool CONTIG, bool CENTER, bool FULL>
+__device__ __forceinline__ void guarded_load_diff(const QParams& p, const float* __restrict__ x, const LaneSpan (&span)[CH], vec4 (&a)[CH], vec4 (&b)[CH]) {
+    vec4 ca[CH], cb[CH];
+    if (!CONTIG || p.x_cached) {
+        asm volatile("; cached");                         // keeps the arms apart (see load_halves)
+        guarded_load_raw<CH, CONTIG, FULL, true>(x, span, a, b);
+        if (CENTER) guarded_load_raw<CH, CONTIG, FULL, true>(p.center, span, ca, cb);
+        asm volatile("; cached end");
+    } else {
+        guarded_load_raw<CH, CONTIG, FULL, false>(x, span, a, b);
+        if (CENTER) guarded_load_raw<CH, CONTIG, FULL, true>(p.center, span, ca, cb);
+    }
+    if (CENTER) {
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
             a[c] -= ca[c];
             b[c] -= cb[c];
         }
     }
+}
+template <int CH, bool CONTIG, bool CENTER>
+__device__ __forceinline__ void guarded_load(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], float (&v)[CH][8]) {
+    if (CONTIG && span[0].count == 0u) {                  // a wave of padding
+#pragma unroll
+        for (int c = 0; c < CH; ++c)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[c][e] = 0.0f;
+        return;
+    }
+    const float* __restrict__ x = p.x + (uint64_t)k * p.x_stride;
+    vec4 a[CH], b[CH];
+    bool full = CONTIG, end = false;                      // the same for the wave: no padding; the vector ends here, off a float4
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        if (span[c].whole) {
+        full = full && span[c].count == kChunk;
+        end = end || (CONTIG ? (span[c].count & 3u) != 0u : !wave_all(span[c].nvalid == 0u || span[c].nvalid == 8u));
+    }
+    if (full) {
+        guarded_load_diff<CH, CONTIG, CENTER, true>(p, x, span, a, b);
+    } else {
+        const bool some = CONTIG || p.d >= 4u;            // a float4 to read
+        if (some) guarded_load_diff<CH, CONTIG, CENTER, false>(p, x, span, a, b);
+#pragma unroll
+        for (int c = 0; c < CH; ++c) {
+            const GuardedLoad<CONTIG> l(span[c]);
+#pragma unroll
+            for (uint32_t e = 0; e < 4; ++e) {
+                if (!some || l.na < 4u) a[c][e] = 0.0f;
+                if (!some || l.nb < 4u) b[c][e] = 0.0f;
+            }
+            if (end) {
+                load_end<CENTER>(x, p.center, l.at, l.na, a[c]);
+                load_end<CENTER>(x, p.center, l.at + l.step, l.nb, b[c]);
+            }
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        if (CONTIG) {
             halves_to_lane(a[c], b[c], v[c]);
         } else {
 #pragma unroll
@@ -594,7 +672,7 @@ __device__ __forceinline__ void guarded_load(const QParams& p, uint32_t k, const
 // One tile of worker k with every access guarded per lane, its coordinates loaded.  PRE = true: the scales
 // were computed by the partial-sum passes and are read from the norms plane, or the tile's one scale is
 // handed in (given).  sm: 32 floats of LDS, not used with PRE.
-template <int M, int CH, int KIND, bool PRE>
+template <int M, int CH, int KIND, bool PRE, bool CONTIG>
 __device__ __forceinline__ void guarded_codes(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], const float (&v)[CH][8],
                                               float* sm, bool given = false, float given_norm = 0.0f) {
     const uint32_t lane = threadIdx.x & 63u;
@@ -606,9 +684,10 @@ __device__ __forceinline__ void guarded_codes(const QParams& p, uint32_t k, cons
     const uint64_t N = 1ull << p.log2N;
 
     Scale sc[CH];
-    if (PRE) {
+    if (PRE) {                                            // the tile lies in one bucket; if in none, nothing is encoded
+        const Scale one = scale_of_norm<M>(given ? given_norm : span[0].bucket < p.nb ? norms[span[0].bucket] : 1.0f);
 #pragma unroll
-        for (int c = 0; c < CH; ++c) sc[c] = scale_of_norm<M>(!span[c].nvalid ? 1.0f : given ? given_norm : norms[span[c].bucket]);
+        for (int c = 0; c < CH; ++c) sc[c] = one;
     } else {
         float t[CH];
         const uint32_t lanes_per_bucket = (uint32_t)((N < kChunk ? N : kChunk) / kLaneElems);
@@ -650,30 +729,26 @@ __device__ __forceinline__ void guarded_codes(const QParams& p, uint32_t k, cons
     for (int c = 0; c < CH; ++c) {
         // Lanes are in slot order, so a chunk whose first lane holds no coordinate is all padding
         // (the tail of a bucket that is not a power of two, or of the vector): nothing to encode.
-        if (__builtin_amdgcn_readfirstlane(span[c].nvalid) == 0u) continue;
+        if (CONTIG ? span[c].count == 0u : __builtin_amdgcn_readfirstlane(span[c].nvalid) == 0u) continue;
         const uint64_t g = span[c].i >> 3;
         uint32_t rnd[4];
         philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
         uint32_t sign_byte, bits[4];
-        if (KIND != QESGD_NORM_L2) sc[c].direct = sc[c].direct && wave_all(no_nan<KIND>(v[c]));
-        round_and_pack<M>(v[c], rnd, sc[c], sign_byte, bits);
-        if (span[c].whole) {
-            const uint64_t i0 = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)span[c].i) |
-                                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(span[c].i >> 32)) << 32;
-            store_whole<M>(out + p.signs_off, out + p.levels_off, i0, lane, p.codes_cached, sign_byte, bits);
-        } else {
-            store_codes<M>(signs, levels, span[c].i, span[c].nvalid, lane, sign_byte, bits);
-        }
+        Scale own = sc[c];
+        if (KIND != QESGD_NORM_L2) own.direct = own.direct && wave_all(no_nan<KIND>(v[c]));
+        round_and_pack<M>(v[c], rnd, own, sign_byte, bits);
+        if (CONTIG && span[c].count == kChunk) store_whole<M>(out + p.signs_off, out + p.levels_off, span[c].i0, lane, p.codes_cached, sign_byte, bits);
+        else store_codes<M>(signs, levels, span[c].i, span[c].nvalid, lane, sign_byte, bits);
     }
 }
 
-template <int M, int CH, int KIND, bool PRE>
+template <int M, int CH, int KIND, bool PRE, bool CONTIG, bool CENTER>
 __device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint32_t tile, float* sm) {
     LaneSpan span[CH];
     float v[CH][8];
-    guarded_spans<CH>(p, tile, span);
-    guarded_load<CH>(p, k, span, v);
-    guarded_codes<M, CH, KIND, PRE>(p, k, span, v, sm);
+    guarded_spans<CH, CONTIG, PRE || CH == 4>(p, tile, span);     // four chunks per wave: buckets of 32768
+    guarded_load<CH, CONTIG, CENTER>(p, k, span, v);
+    guarded_codes<M, CH, KIND, PRE, CONTIG>(p, k, span, v, sm);
 }
 
 // ---------------------------------------------------------------------------
