@@ -120,8 +120,26 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
         }
     } else {
         const uint64_t b = bucket_of(i, p);
+        uint32_t k = 0;
+        if constexpr (ZACC && M == 16) {
+            // Left to itself the scheduler takes the workers one after the other here, the only instance that does
+            // (d = 28,672, K = 64, bucket 128, the whole gradient round: 32.7 us, 18.7 with their loads together).
+            for (; k + 4 <= p.K; k += 4) {
+                float norm[4];
+                uint32_t sbyte[4], w[4][4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const unsigned char* __restrict__ blk = p.packed + (uint64_t)(k + j) * p.packed_stride;
+                    norm[j] = reinterpret_cast<const float*>(blk + p.norms_off)[b];
+                    sbyte[j] = (blk + p.signs_off)[i >> 3];
+                    load_level_bits<M>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, 8u, p.level_words, w[j]);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) accumulate8<M>(acc, sbyte[j], w[j], norm[j] / p.smax);
+            }
+        }
 #pragma unroll 4
-        for (uint32_t k = 0; k < p.K; ++k) {
+        for (; k < p.K; ++k) {
             const unsigned char* __restrict__ blk = p.packed + (uint64_t)k * p.packed_stride;
             const float norm = reinterpret_cast<const float*>(blk + p.norms_off)[b];
             const uint32_t sbyte = (blk + p.signs_off)[i >> 3];
