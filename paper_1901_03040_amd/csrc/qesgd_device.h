@@ -68,6 +68,13 @@ __device__ __forceinline__ void store_stream(float* p, const vec4& v) {
     __builtin_nontemporal_store(v, reinterpret_cast<vec4*>(p));
 }
 __device__ __forceinline__ vec4 load_cached(const float* p) { return *reinterpret_cast<const vec4*>(p); }
+template <bool CACHED>
+__device__ __forceinline__ vec4 load_as(const float* p) { return CACHED ? load_cached(p) : load_stream(p); }
+template <bool CACHED>
+__device__ __forceinline__ void store_as(float* p, const vec4& v) {
+    if (CACHED) *reinterpret_cast<vec4*>(p) = v;
+    else store_stream(p, v);
+}
 
 // CH x 512 coordinates of a vector, one float4 of each half chunk per lane, with either policy.
 template <int CH, bool CACHED>

@@ -327,6 +327,20 @@ def test_unpack_aggregate_update_matches_oracle(oracle, B, S, s, K, d, bucket):
     assert torch.equal(u3, u)
 
 
+@pytest.mark.parametrize("d,with_zsum", [(8_388_608, True), (8_388_609, True), (11_184_810, False), (11_184_813, False)])
+def test_apply_update_on_both_sides_of_the_cache_policy(B, d, with_zsum):
+    """The update alone around 128 MiB of vectors, u apart and on w: each sum is one float32 addition, so bit for bit."""
+    g = torch.Generator(device="cuda").manual_seed(d)
+    w, z, zsum0 = (torch.randn(d, generator=g, device="cuda") for _ in range(3))
+    for in_place in (False, True):
+        target = w.clone() if in_place else torch.full((d,), float("nan"), device="cuda")
+        zsum = zsum0.clone() if with_zsum else None
+        B.qesgd_apply_update(target if in_place else w, z, target, zsum, d)
+        torch.cuda.synchronize()
+        assert torch.equal(target, w + z)
+        assert zsum is None or torch.equal(zsum, zsum0 + z)
+
+
 @pytest.mark.parametrize("s,K", [(2, 8), (16, 3), (256, 16), (4, 32), (4, 33), (8, 5)])
 @pytest.mark.parametrize("d,bucket", [(50_000, 3008), (200_003, 48_000), (20_000, 544), (70_001, 512 + 32)])
 def test_aggregate_with_buckets_that_straddle_waves(oracle, B, S, s, K, d, bucket):
