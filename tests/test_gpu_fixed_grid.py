@@ -198,3 +198,15 @@ def test_fixed_grid_full_size_sampled(oracle, B):
         oz, ou, _ = oracle.dequantize_fixed_update(rhost[a // 4:(a + 5000) // 4], 5000, delta, b,
                                                    w_snap=w[a:a + 5000].cpu().numpy())
         assert np.array_equal(z[a:a + 5000].cpu().numpy(), oz) and np.array_equal(u[a:a + 5000].cpu().numpy(), ou)
+
+
+def test_fixed_grid_16_bits_beyond_the_cached_codes(oracle, B):
+    """90 M coordinates in 16 bits: 180 MB of codes, more than are stored with the ordinary cache policy."""
+    d, b, delta = 90_000_004, 16, float(np.float32(4e-3 / 32768))
+    x = torch.randn(d, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda") * 1e-3
+    _, host = gpu_quantize_fixed(B, x, delta, b, 21, 1, 4)
+    for a in (0, 33_554_432 - 512, 77_777_776, d - 1028):
+        seg = x[a:a + 1028].cpu().numpy()
+        codes = [oracle.fixed_round(v, delta, b, oracle.uniform16(21, 1, 4, a + j)) & 0xFFFF for j, v in enumerate(seg)]
+        want = np.array(codes, np.uint16).view(np.uint32)
+        assert np.array_equal(host[a // 2:a // 2 + want.size], want), a

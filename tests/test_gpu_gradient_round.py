@@ -54,6 +54,16 @@ def test_gradient_round_is_the_four_calls(B, d, bucket, K, norm_kind, s):
             assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
 
 
+@pytest.mark.parametrize("d,bucket,K,s", [
+    (20_000_003, WHOLE, 16, 16),                                 # beyond 1250 MiB, and its vectors beyond the ordinary policy
+    (1_600_001, WHOLE, 64, 4), (300_004, 65_536, 64, 256),       # the most workers, one launch and two
+    (28_675, 128, 64, 65536), (1_600_003, 128, 64, 65536)])
+def test_gradient_round_of_many_workers(B, d, bucket, K, s):
+    slab, w, z0, zsum0 = inputs(d, K)
+    for a, b in zip(*gradient_forms(B, slab, d, s, bucket, 0, K, w, z0, zsum0)):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
 @pytest.mark.parametrize("s", [2, 4, 8, 16, 32, 64, 128, 256, 65536])
 @pytest.mark.parametrize("d,bucket,K", [(40_001, WHOLE, 3), (131_072 * 2, 131_072, 8), (300_004, 65_536, 2),
                                         (2_100_001, WHOLE, 2)])

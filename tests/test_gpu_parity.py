@@ -222,14 +222,13 @@ def test_wide_buckets_batched(oracle, B, d, bucket, s, K, norm_kind, with_center
 
 
 @pytest.mark.parametrize("d,bucket,s,K,norm_kind,with_center", [
-    (6_000_037, 1 << 30, 2, 8, 0, False),     # one bucket over the vector: 8 x 24 MB of input, groups of 6 + 2 workers
-    (5_500_000, 65_536, 16, 9, 0, True),      # wide power-of-two buckets with a center: groups of 7 + 2
-    (5_300_011, 48_000, 256, 8, 1, False)])   # not a power of two, max norm (guarded passes): groups of 7 + 1
-def test_wide_buckets_input_beyond_one_group(oracle, B, d, bucket, s, K, norm_kind, with_center):
-    """The wide-bucket path takes the workers of a call in groups whose input stays within a fixed
-    byte budget (160 MB).  Here one call needs two groups: every scale and code word of every worker
-    against the oracle, so the per-group offsets of input, output, workspace and worker index are
-    all exercised; the entry point without a workspace gives the same bytes."""
+    (6_000_037, 1 << 30, 2, 8, 0, False),     # one bucket over the vector
+    (5_500_000, 65_536, 16, 9, 0, True),      # wide power-of-two buckets with a center
+    (5_300_011, 48_000, 256, 8, 1, False)])   # not a power of two, max norm (guarded passes)
+def test_wide_buckets_many_workers_of_many_tiles(oracle, B, d, bucket, s, K, norm_kind, with_center):
+    """Each pass of the wide-bucket path takes all workers in one launch, here with more than 160 MB of
+    input: every scale and code word of every worker against the oracle, so the offsets of input, output,
+    workspace and worker index are all exercised; the entry point without a workspace gives the same bytes."""
     g = torch.Generator(device="cpu").manual_seed(d + K)
     stride = (d + 63) // 64 * 64
     assert K * 4 * d > 160 << 20 and 4 * d < 160 << 20

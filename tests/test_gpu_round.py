@@ -109,7 +109,9 @@ def test_center_and_optional_outputs(B, d, bucket, s, K):
     (50_000, 96, 16, 3, 0),          # bucket not a power of two
     (50_000, 512, 16, 3, 1),         # max norm
     (50_000, 512, 8, 3, 0),          # level width that does not divide a word
-    (150_000, 65_536, 4, 3, 0),      # wide bucket (needs the workspace)
+    (150_000, 65_536, 4, 3, 1),      # max norm, wide bucket (needs the workspace)
+    (150_000, 48_000, 4, 3, 0),      # wide bucket, not a power of two
+    (150_000, 65_536, 4, 3, 0),      # the wide bucket that does take one launch, behind those that find the scales
     (9_000, 1 << 20, 4, 2, 0)])      # one bucket, not a power of two
 def test_other_shapes_fall_back_to_two_launches(B, d, bucket, s, K, norm_kind):
     slab, _, w, zsum0 = make_inputs(d, K, d + s, False)
