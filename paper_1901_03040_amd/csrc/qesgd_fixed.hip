@@ -16,7 +16,6 @@ struct FParams {
     const float* center;
     uint32_t* codes;
     uint64_t d;
-    uint64_t code_words;
     uint32_t full_tiles;   // tiles that lie wholly inside the vector
     uint32_t xcd_group;    // log2 of the tiles that one XCD takes in a row
     bool x_cached, codes_cached;   // ordinary cache policy for the vectors, for the codes
@@ -310,7 +309,7 @@ int launch_quantize_fixed(const float* x, const float* center, uint64_t d, float
     p.center = center;
     p.codes = (uint32_t*)codes;
     p.d = d;
-    p.code_words = (d * b + 31) / 32;
+    const uint64_t code_words = (d * b + 31) / 32;
     p.delta = delta;
     p.lo = -(float)(1u << (b - 1));
     p.hi = (float)((1u << (b - 1)) - 1u);
@@ -322,8 +321,8 @@ int launch_quantize_fixed(const float* x, const float* center, uint64_t d, float
     if (blocks >= (1ull << 31)) return QESGD_ERR_DIM;
     p.full_tiles = (uint32_t)(d / kFixedTile);
     p.xcd_group = xcd_group_log2(kFixedTile);
-    p.x_cached = 4u * d <= kCachedInputBytes && 24u * d + 4u * p.code_words <= kCachedRoundBytes;
-    p.codes_cached = 4u * p.code_words <= kCachedCodeBytes;
+    p.x_cached = 4u * d <= kCachedInputBytes && 24u * d + 4u * code_words <= kCachedRoundBytes;
+    p.codes_cached = 4u * code_words <= kCachedCodeBytes;
     const dim3 grid((uint32_t)blocks), block(kFixedWaves * 64);
     // the short division is used where its scaling-free form is exact (see Divider)
     const bool exact_div = !(delta >= 0x1p-60f && delta <= 0x1p60f);

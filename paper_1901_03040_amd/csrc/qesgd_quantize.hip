@@ -102,7 +102,8 @@ __global__ void __launch_bounds__((Geo<M, LOG2N, CENTER>::NW * 64)) k_quantize_p
 
 // The center form for several workers: a workgroup owns one tile of every worker, keeps the tile
 // of `center` in registers and takes the workers one after the other with the next worker's loads
-// in flight, so `center` is read once per tile instead of once per tile and worker.
+// in flight, so `center` is read once per tile instead of once per tile and worker.  Buckets of 32768 spill (200 to
+// 272 bytes per lane at the 128 registers that 1024 threads leave).
 template <int M, int LOG2N>
 __global__ void __launch_bounds__((Geo<M, LOG2N, true>::NW * 64)) k_quantize_pack_center(const QParams p) {
     constexpr int CH = Geo<M, LOG2N, true>::CH;
@@ -523,6 +524,8 @@ QParams quantize_params(const Shape& sh, const QuantizeArgs& a) {
 // finish them itself.  Up to 512 partial sums per bucket it does: reading them again in every wave then costs
 // less than the launch (quantise and aggregate, d = 0.1 M, K = 4, one bucket: 17.6 us with the launch, 14.8
 // without; at 25.6 M coordinates every wave would read 25 KB).
+constexpr uint64_t kMergePartials = 512;
+static_assert(kMergePartials <= kMergedLeaves, "wave_total takes the partial sums of a bucket in one go");
 int launch_dense_norms(QParams& p, const Shape& sh, const QuantizeArgs& a) {
     const uint64_t P = sh.N / kPartialTile;
     p.ws_tiles_per_worker = (uint32_t)(sh.nb * P);
@@ -530,7 +533,7 @@ int launch_dense_norms(QParams& p, const Shape& sh, const QuantizeArgs& a) {
     p.full_tiles = (uint32_t)(sh.d / kPartialTile);
     p.tail_tiles = (uint32_t)(p.data_tiles - p.full_tiles);
     p.xcd_group = xcd_group_log2(kPartialTile);
-    p.merged = P <= 512;                                 // <= kMergedLeaves
+    p.merged = P <= kMergePartials;
     const dim3 grid((uint32_t)p.data_tiles, a.K);
     if (p.center) hipLaunchKernelGGL(k_tile_partials_fast<true>, grid, dim3(256), 0, a.stream, p);
     else hipLaunchKernelGGL(k_tile_partials_fast<false>, grid, dim3(256), 0, a.stream, p);
@@ -543,7 +546,7 @@ int launch_dense_norms(QParams& p, const Shape& sh, const QuantizeArgs& a) {
 }
 
 bool dense_wide(const Shape& sh, uint32_t norm_kind) {
-    return sh.N > kMaxSinglePassBucket && norm_kind == QESGD_NORM_L2 && (sh.N == sh.B || sh.nb == 1) && sh.d >= kPartialTile;
+    return sh.N > kMaxSinglePassBucket && norm_kind == QESGD_NORM_L2 && (sh.N == sh.B || sh.nb == 1);
 }
 
 int launch_quantize(const Shape& sh, const QuantizeArgs& a) {

@@ -161,8 +161,8 @@ __device__ __forceinline__ float wave_total(const float* __restrict__ ws, uint32
 // ---------------------------------------------------------------------------
 // Correctly rounded square root and quotient for operands far from the ends of the exponent range:
 // the hardware estimate and the correction steps of the general expansions without their operand
-// scaling and special cases (checked against sqrtf on every float of the range below and against
-// IEEE division for every significand, every level width and norms from 2^-60 to 2^60).
+// scaling and special cases, which the ranges of their callers leave out (norms of 2^-60 to 2^60, totals
+// of 2^-90 to 2^120); the tests compare codes and scales with IEEE arithmetic at both ends of these ranges.
 __device__ __forceinline__ float sqrt_in_range(float x) {
     const float s = __builtin_amdgcn_sqrtf(x);
     const float down = __uint_as_float(__float_as_uint(s) - 1u), up = __uint_as_float(__float_as_uint(s) + 1u);
@@ -759,8 +759,10 @@ struct Geo {
     // Chunks per wave and waves per workgroup, measured at 480 M coordinates with the non-temporal streams.  Two
     // chunks per wave, the more bytes in flight the better (one / two: M = 2, bucket 2048 361 / 341 us; M = 4,
     // 512 377 / 358; M = 8, 128 421 / 393; M = 8, 4096 408 / 394; four are slower, M = 1, bucket 4096 at 1.1 G
-    // 860 / 811).  With a center its coordinates are held as well, and from M = 4 on one is better (58 M, K = 4,
-    // M = 4, whole round: 415 / 427 us).  The workgroup is as small as the bucket allows, but not one wave
+    // 860 / 811).  With a center its coordinates are held as well, and from M = 4 on neither is always better
+    // (quantiser, one / two: 30 M, K = 8, M = 8, bucket 2048 248 / 259 us; 57 M, K = 2, M = 4, 4096 127 / 130; 58 M,
+    // K = 4, M = 4, 4096 228 / 236; but 57 M, K = 8, M = 8, 512 490 / 450; 120 M, K = 4, M = 4, 4096 496 / 481; 16 M,
+    // K = 16, M = 4, 4096 255 / 251): one.  The workgroup is as small as the bucket allows, but not one wave
     // (M = 4: the same; M = 1: slower).
     static constexpr int CH = LOG2N == 15 ? 4 : (CENTER && M > 2 && LOG2N < 13 ? 1 : 2);
     static constexpr int NW = (1 << LOG2N) / (CH * 512) < 2 ? 2 : (1 << LOG2N) / (CH * 512);

@@ -41,7 +41,8 @@ struct RParams {
 // Tile of a workgroup: chunks per wave and waves.  The running sum and the next worker's coordinates are
 // held in registers next to the current ones, so fewer chunks fit than in the plain quantiser (two / one at
 // d = 12 M, K = 8, bucket 4096, s = 256: 128 / 119 us; but 8192, s = 4: 128 / 141 us, where one would need
-// sixteen waves).
+// sixteen waves).  Buckets of 16384 have 128 registers per lane and spill 44 to 80 bytes of them, 128 to 148 with a center: see round_fused_pays
+// for where they take this kernel all the same.
 template <int LOG2N>
 struct RoundGeo {
     static constexpr int CH = LOG2N <= 12 ? 1 : 2;
