@@ -15,12 +15,12 @@
 // of 64 K coordinates per XCD, with the non-temporal policy unless the round fits the memory-side cache and
 // a wave owns one chunk; w and zsum are in flight while the last worker is rounded.  Before (32 bytes per
 // lane, ordinary policy, tiles dealt round-robin, update loads after the last worker, z through LDS) / after:
-//   d = 11 M, K = 8, s = 4, bucket 2048       118 -> 102 us = 6.0 TB/s
-//   d = 12 M, K = 16, s = 256, bucket 8192    245 -> 220 us = 5.7 TB/s
-//   d = 12 M, K = 2, s = 256, bucket 4096      73 ->  60 us
+//   d = 11 M, K = 8, s = 4, bucket 2048       118 ->  93 us = 6.6 TB/s
+//   d = 12 M, K = 16, s = 256, bucket 8192    240 -> 199 us = 6.1 TB/s
+//   d = 12 M, K = 2, s = 256, bucket 4096      70 ->  54 us
 // The policy is chosen outside the loop over the workers: a branch inside it made every worker wait for the
-// next one's coordinates (d = 2048, K = 8, s = 256, bucket 128: 7.65 us, 6.9 without, 6.7 with the ordinary
-// policy alone).
+// next one's coordinates (the three shapes above 102, 214 and 61 us; d = 2048, K = 8, s = 256, bucket 128 7.6 us,
+// 6.9 without, 6.7 with the ordinary policy alone).
 #include "qesgd_aggregate_device.h"
 #include "qesgd_quantize_device.h"
 
