@@ -64,7 +64,7 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
             for (int j = 0; j < 4; ++j) {
                 const unsigned char* __restrict__ blk = p.packed + (uint64_t)(k + j) * p.packed_stride;
                 sbyte[j] = (blk + p.signs_off)[i >> 3];
-                load_level_bits<M>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, 8u, p.level_words, w[j]);
+                load_level_bits<M, true>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, p.level_words, w[j]);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -76,7 +76,7 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
             const unsigned char* __restrict__ blk = p.packed + (uint64_t)k * p.packed_stride;
             const uint32_t sbyte = (blk + p.signs_off)[i >> 3];
             uint32_t w[4];
-            load_level_bits<M>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, 8u, p.level_words, w);
+            load_level_bits<M, true>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, p.level_words, w);
             const float step = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_step), k));
             accumulate8<M>(acc, sbyte, w, step);
         }
@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
             for (int j = 0; j < 4; ++j) {
                 const unsigned char* __restrict__ blk = p.packed + (uint64_t)(k + j) * p.packed_stride;
                 sbyte[j] = (blk + p.signs_off)[i >> 3];
-                load_level_bits<M>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, 8u, p.level_words, w[j]);
+                load_level_bits<M, true>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, p.level_words, w[j]);
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -113,7 +113,7 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
             const unsigned char* __restrict__ blk = p.packed + (uint64_t)k * p.packed_stride;
             const uint32_t sbyte = (blk + p.signs_off)[i >> 3];
             uint32_t w[4];
-            load_level_bits<M>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, 8u, p.level_words, w);
+            load_level_bits<M, true>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, p.level_words, w);
             const float s0 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_step), k));
             const float s1 = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(my_step), 32u + k));
             accumulate8<M>(acc, sbyte, w, second ? s1 : s0);
@@ -132,7 +132,7 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
                     const unsigned char* __restrict__ blk = p.packed + (uint64_t)(k + j) * p.packed_stride;
                     norm[j] = reinterpret_cast<const float*>(blk + p.norms_off)[b];
                     sbyte[j] = (blk + p.signs_off)[i >> 3];
-                    load_level_bits<M>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, 8u, p.level_words, w[j]);
+                    load_level_bits<M, true>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, p.level_words, w[j]);
                 }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) accumulate8<M>(acc, sbyte[j], w[j], norm[j] / p.smax);
@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(kAggWaves * 64) k_unpack_aggregate_update(cons
             const float norm = reinterpret_cast<const float*>(blk + p.norms_off)[b];
             const uint32_t sbyte = (blk + p.signs_off)[i >> 3];
             uint32_t w[4];
-            load_level_bits<M>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, 8u, p.level_words, w);
+            load_level_bits<M, true>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, p.level_words, w);
             accumulate8<M>(acc, sbyte, w, norm / p.smax);
         }
     }

@@ -68,10 +68,11 @@ __device__ __forceinline__ void load8(const float* __restrict__ src, uint64_t i,
 // The 8*M level bits of the lane's coordinates, as up to four words.  For a
 // width that does not divide 32 the lane's M bytes start at byte (i/8)*M of the
 // plane, at any alignment: the two or three words that hold them are read and
-// shifted down so that coordinate i's field starts at bit 0 of w[0].
-template <int M>
-__device__ __forceinline__ void load_level_bits(const uint32_t* __restrict__ levels, uint64_t i, uint32_t nvalid,
-                                                uint64_t level_words, uint32_t (&w)[4]) {
+// shifted down so that coordinate i's field starts at bit 0 of w[0].  WHOLE: all 8 coordinates exist; otherwise the
+// lane's first word stands for one beyond the plane, whose fields nothing uses, so that nothing branches.
+template <int M, bool WHOLE>
+__device__ __forceinline__ void load_level_bits(const uint32_t* __restrict__ levels, uint64_t i, uint64_t level_words,
+                                                uint32_t (&w)[4]) {
     w[0] = w[1] = w[2] = w[3] = 0;
     const unsigned char* bytes = reinterpret_cast<const unsigned char*>(levels);
     if (M == 3 || M == 5 || M == 6 || M == 7) {
@@ -93,21 +94,22 @@ __device__ __forceinline__ void load_level_bits(const uint32_t* __restrict__ lev
     } else if (M == 4) {
         w[0] = levels[i >> 3];
     } else if (M == 8) {
-        if (nvalid == 8) {
+        if (WHOLE) {
             const uint2 t = *reinterpret_cast<const uint2*>(levels + (i >> 2));
             w[0] = t.x; w[1] = t.y;
         } else {
-            w[0] = levels[i >> 2];
-            if ((i >> 2) + 1 < level_words) w[1] = levels[(i >> 2) + 1];
+            const uint64_t a = i >> 2;
+            w[0] = levels[a];
+            w[1] = levels[a + 1 < level_words ? a + 1 : a];
         }
     } else {
-        if (nvalid == 8) {
+        if (WHOLE) {
             const uint4 t = *reinterpret_cast<const uint4*>(levels + (i >> 1));
             w[0] = t.x; w[1] = t.y; w[2] = t.z; w[3] = t.w;
         } else {
+            const uint64_t a = i >> 1;
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if ((i >> 1) + q < level_words) w[q] = levels[(i >> 1) + q];
+            for (int q = 0; q < 4; ++q) w[q] = levels[a + q < level_words ? a + q : a];
         }
     }
 }
@@ -140,7 +142,10 @@ __device__ __forceinline__ void accumulate8(float (&acc)[8], uint32_t sbyte, con
 }
 
 // Ragged end of the vector (and shapes the wave-uniform path below does not cover): every
-// access guarded per lane, 8 consecutive coordinates per lane for all streams.
+// access guarded per lane, 8 consecutive coordinates per lane for all streams, four workers' codes in flight at a
+// time: one after the other, the whole call waits for the K reads of this one wave, the longer the farther the codes
+// are (the quantiser may have run on another XCD).  d = 7933, K = 24, s = 256, bucket 1024, right behind the quantiser
+// 17.7 us, now 9.7, over and over 10.9 / 6.3; d = 1 M + 3, K = 16, s = 256, bucket 1024 13.3 / 7.6.
 template <int M>
 __device__ __forceinline__ void aggregate_lane_guarded(const AParams& p, uint64_t i) {
     if (i >= p.d) return;
@@ -151,13 +156,30 @@ __device__ __forceinline__ void aggregate_lane_guarded(const AParams& p, uint64_
     float acc[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
-#pragma unroll 4
-    for (uint32_t k = 0; k < p.K; ++k) {
+    uint32_t k = 0;
+    if constexpr (M >= 8) {                               // the narrower widths' loads stay together by themselves
+        for (; k + 4 <= p.K; k += 4) {
+            float norm[4];
+            uint32_t sbyte[4], w[4][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const unsigned char* __restrict__ blk = p.packed + (uint64_t)(k + j) * p.packed_stride;
+                norm[j] = reinterpret_cast<const float*>(blk + p.norms_off)[b];
+                sbyte[j] = (blk + p.signs_off)[i >> 3];
+                load_level_bits<M, false>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, p.level_words, w[j]);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) accumulate8<M>(acc, sbyte[j], w[j], norm[j] / p.smax);
+        }
+    }
+    constexpr int together = M >= 8 ? 1 : 4;
+#pragma unroll together
+    for (; k < p.K; ++k) {
         const unsigned char* __restrict__ blk = p.packed + (uint64_t)k * p.packed_stride;
         const float norm = reinterpret_cast<const float*>(blk + p.norms_off)[b];
         const uint32_t sbyte = (blk + p.signs_off)[i >> 3];
         uint32_t w[4];
-        load_level_bits<M>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, nvalid, p.level_words, w);
+        load_level_bits<M, false>(reinterpret_cast<const uint32_t*>(blk + p.levels_off), i, p.level_words, w);
         accumulate8<M>(acc, sbyte, w, norm / p.smax);
     }
     float z[8];

@@ -361,6 +361,20 @@ def test_aggregate_with_buckets_that_straddle_waves(oracle, B, S, s, K, d, bucke
         assert np.array_equal(got.cpu().numpy().view(np.uint32), want.view(np.uint32)), f"{what} not bit-exact"
 
 
+@pytest.mark.parametrize("s", [4, 128, 256, 65536])
+@pytest.mark.parametrize("K", [3, 4, 11, 64])
+def test_aggregate_of_the_ragged_end(oracle, B, S, s, K):
+    """Every length of the last lane, with workers in fours and left over.  The words behind a plane hold other bits."""
+    for d in [512 + 200 + e for e in range(1, 9)] + [1, 2, 3, 5]:
+        lay, packed = random_packed(B, S, d, s, 256, K, seed=s + K + d)
+        zbar = torch.full((d + 8,), -7.0, device="cuda")
+        B.qesgd_unpack_aggregate(packed, packed.stride(0), K, d, s, 256, zbar)
+        torch.cuda.synchronize()
+        want = oracle.unpack_aggregate(*oracle_planes(B, packed, lay, K), d, s, 256)
+        assert np.array_equal(zbar[:d].cpu().numpy().view(np.uint32), want.view(np.uint32)), d
+        assert bool((zbar[d:] == -7.0).all())
+
+
 def test_full_round_small(oracle, B, S):
     """quantize -> aggregate -> update for several rounds, each side on its own intermediates."""
     cfg = S.by_name("cfg3").scaled(d=41_034, K=4)
