@@ -17,9 +17,9 @@
 //                         parameter, so a tile is straight-line code without guards; the ragged last
 //                         tile of a worker runs the same code with masked loads and stores.
 //   k_quantize_pack_center  the same with a center and several workers, one tile of every worker.
-//   k_quantize_pack       everything else: buckets that are not a power of two, max-norm, level
-//                         widths 3/5/6/7, and the last pass of the buckets among them that are too
-//                         wide for one workgroup.
+//   k_quantize_pack_bucket  buckets that are not a power of two, max-norm, level widths 3/5/6/7, and the
+//                         last pass of the buckets among them that are too wide for one workgroup.
+//   k_quantize_pack_lanes  of those the ones padded to 512 or less, lane by lane.
 //   k_tile_partials(_fast), k_finish_norms, k_quantize_pack_pre_fast
 //                         buckets wider than kMaxSinglePassBucket: per-tile tree sums into the
 //                         workspace, the rest of each bucket's tree, then the quantiser.
@@ -35,11 +35,103 @@ static __device__ __align__(256) float scratch[qesgd::kStaticScratchFloats];
 namespace qesgd {
 namespace {
 
-// PRE: second pass of a wide bucket.  CONTIG: see LaneSpan.
-template <int M, int CH, int KIND, bool PRE, bool CONTIG, bool CENTER>
-__global__ void k_quantize_pack(const QParams p) {
-    __shared__ float sm[32];
-    guarded_tile<M, CH, KIND, PRE, CONTIG, CENTER>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
+// Buckets that the fast kernel does not take but whose coordinates a wave finds side by side: the max norm, level widths
+// 3, 5, 6 and 7, sizes that are no power of two.  What depends on the size is scalar work, so one kernel serves all sizes.
+//   kBuckets  padded to 1024 .. 32768: a bucket is a few waves, whose totals meet in LDS; a workgroup holds whole buckets
+//   kNarrow   up to 512, a power of two or the only one: slot == coordinate, several buckets in a wave
+//   kPre      last pass of buckets wider than kMaxSinglePassBucket: the scale is read from the norms plane
+// A wave is whole, ragged, or all padding (then it only meets the others); only a ragged one guards its lanes.
+// Bound by vector issue (d = 7.3 M, K = 5, s = 32, bucket 3008, max norm: 339 vector instructions per 1024 coordinates,
+// 428 and 1.5 times the scalar ones where every wave guarded itself).  Guarded / this, quantiser alone:
+//   d = 7.3 M, K = 5, s = 32, bucket 3008, max    48.5 -> 40.7 us
+//   d = 20 M, K = 8, s = 4, bucket 2400, max      BENCH_B
+//   d = 15 M, K = 5, s = 4, bucket 23648, max     BENCH_C
+//   d = 30 M, K = 8, s = 64, bucket 32768         271 -> 214 us
+enum Mode { kBuckets, kNarrow, kPre };
+template <int M, int CH, int KIND, bool CENTER, Mode MODE>
+__global__ void __launch_bounds__(MODE == kBuckets ? 1024 : 256) k_quantize_pack_bucket(const QParams p) {
+    __shared__ float sm[16];
+    extern __shared__ __align__(16) unsigned char strings[];
+    const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), k = blockIdx.y;
+    const uint64_t unit = ((uint64_t)xcd_tile(blockIdx.x, gridDim.x, p.xcd_group) << p.log2_waves) + wave;
+    const uint32_t lg = p.log2N - (CH == 4 ? 11u : 10u);                         // log2 of a bucket's waves
+    static_assert(CH == 2 || CH == 4, "");
+    const WaveSpan s = MODE == kNarrow ? wave_span_dense<CH>(p, unit) : wave_span<CH>(p, unit, lg);
+    float v[CH][8];
+    load_span<CH, CENTER>(p, k, s, lane, v);
+    float* __restrict__ norms = reinterpret_cast<float*>(p.packed + (uint64_t)k * p.packed_stride + p.norms_off);
+
+    Scale sc[CH];
+    if (MODE == kPre) {
+        if (s.mine == 0) return;
+        sc[0] = scale_of_norm<M>(norms[s.bucket]);
+    } else {
+        const uint32_t lanes = MODE == kNarrow ? 1u << (p.log2N - 3u) : 64u;     // that share a bucket
+        float tot[CH];
+#pragma unroll
+        for (int c = 0; c < CH; ++c) tot[c] = lane_butterfly<KIND>(lane_tree<KIND>(v[c]), lanes);
+        if (MODE == kNarrow) {
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                // a lane beyond the last bucket must not take its wave out of the short rounding: any ordinary scale
+                const uint32_t at = (uint32_t)c * kChunk + lane * kLaneElems;
+                const bool live = (at & ~(lanes * kLaneElems - 1u)) < s.mine;
+                sc[c] = scale_of_total<M, KIND>(live ? tot[c] : 1.0f);
+                if ((lane & (lanes - 1u)) == 0u && live) norms[(s.i0 + at) >> p.log2N] = sc[c].norm;
+            }
+        } else {
+#pragma unroll
+            for (int w = 1; w < CH; w <<= 1)
+#pragma unroll
+                for (int c = 0; c < CH; c += 2 * w) tot[c] = combine<KIND>(tot[c], tot[c + w]);
+            if (lg > 0) {                                                        // the same for the workgroup
+                const uint32_t waves = 1u << lg;
+                if (lane == 0) sm[wave] = tot[0];
+                __syncthreads();
+                tot[0] = lane_butterfly<KIND>(sm[(wave & ~(waves - 1u)) + (lane & (waves - 1u))], waves);
+            }
+            if (s.mine == 0) return;
+            sc[0] = scale_of_total<M, KIND>(tot[0]);
+            if (s.sub == 0 && lane == 0) norms[s.bucket] = sc[0].norm;
+        }
+    }
+    if (MODE != kNarrow) {
+#pragma unroll
+        for (int c = 1; c < CH; ++c) sc[c] = sc[0];
+    }
+    encode_span<M, CH, KIND>(p, k, s, lane, strings + wave * kStringBytes<M>, v, sc);
+}
+
+// The buckets that neither takes (see LaneSpan).  (Through whole-line loads and an exchange: d = 15 M, K = 5, s = 16,
+// bucket 320 84.0 us, lane by lane 76.0.)
+template <int M, int KIND, bool CENTER>
+__global__ void __launch_bounds__(256) k_quantize_pack_lanes(const QParams p) {
+    constexpr int CH = 2;
+    const uint32_t lane = threadIdx.x & 63u, k = blockIdx.y;
+    const uint64_t N = 1ull << p.log2N;
+    const uint64_t slot0 = ((uint64_t)xcd_tile(blockIdx.x, gridDim.x, p.xcd_group) * 4u + (threadIdx.x >> 6)) * (CH * kChunk);
+    LaneSpan span[CH];
+    float v[CH][8];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) span[c] = lane_span(slot0 + (uint32_t)c * kChunk + lane * kLaneElems, p);
+    load_lanes<CH, CENTER>(p, k, span, v);
+    unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
+    float* __restrict__ norms = reinterpret_cast<float*>(out + p.norms_off);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const float tot = lane_butterfly<KIND>(lane_tree<KIND>(v[c]), (uint32_t)(N / kLaneElems));
+        Scale sc = scale_of_total<M, KIND>(span[c].nvalid || N == kChunk ? tot : 1.0f);      // (see kNarrow)
+        if (span[c].opens_bucket) norms[span[c].bucket] = sc.norm;
+        // a chunk opens a bucket: if that holds no coordinate, the vector has ended
+        if (__builtin_amdgcn_readfirstlane(span[c].nvalid) == 0u) continue;
+        const uint64_t g = span[c].i / kLaneElems;
+        uint32_t rnd[4], sign_byte, bits[4];
+        philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        if (KIND != QESGD_NORM_L2) sc.direct = sc.direct && wave_all(no_nan<KIND>(v[c]));
+        round_and_pack<M>(v[c], rnd, sc, sign_byte, bits);
+        store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off), span[c].i,
+                       span[c].nvalid, lane, sign_byte, bits);
+    }
 }
 
 // One tile per workgroup.  (Walking several tiles per workgroup with the next tile's loads in flight was
@@ -170,22 +262,16 @@ __global__ void __launch_bounds__((Geo<M, LOG2N, true>::NW * 64)) k_quantize_pac
     }
 }
 
-// Tree sum (or max) of one 4096-slot tile of worker k with every access guarded per lane, left in
-// the workspace.  Tiles of a bucket are consecutive in slot space, so the workspace index of
-// (bucket, tile in bucket) is the tile index.  sm: 4 floats of LDS.
+// Tree sum (or max) of one 4096-slot tile of worker k, left in the workspace.  Tiles of a bucket are consecutive in
+// slot space, so the workspace index of (bucket, tile in bucket) is the tile index.  sm: 4 floats of LDS.
 template <int KIND, bool CENTER>
-__device__ __forceinline__ void guarded_partial_tile(const QParams& p, uint32_t k, uint32_t tile, float* sm) {
-    constexpr int CH = 2;
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = threadIdx.x >> 6;
-    LaneSpan span[CH];
-    float v[CH][8], t[CH];
-    guarded_spans<CH, true, true>(p, tile, span);
-    guarded_load<CH, true, CENTER>(p, k, span, v);
-#pragma unroll
-    for (int c = 0; c < CH; ++c) t[c] = lane_butterfly<KIND>(lane_tree<KIND>(v[c]), 64);
-    t[0] = combine<KIND>(t[0], t[1]);
-    if (lane == 0) sm[wave] = t[0];
+__device__ __forceinline__ void partial_tile(const QParams& p, uint32_t k, uint32_t tile, float* sm) {
+    const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const WaveSpan s = wave_span<2>(p, (uint64_t)tile * 4u + wave, p.log2N - 10u);
+    float v[2][8];
+    load_span<2, CENTER>(p, k, s, lane, v);
+    const float t = combine<KIND>(lane_butterfly<KIND>(lane_tree<KIND>(v[0]), 64), lane_butterfly<KIND>(lane_tree<KIND>(v[1]), 64));
+    if (lane == 0) sm[wave] = t;
     __syncthreads();
     if (threadIdx.x == 0) {
         const float total = combine<KIND>(combine<KIND>(sm[0], sm[1]), combine<KIND>(sm[2], sm[3]));
@@ -206,7 +292,7 @@ __global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
     const uint32_t k = blockIdx.y;
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
     if (t >= p.full_tiles) {                              // the ragged last tile of the worker (at most one)
-        guarded_partial_tile<KIND, CENTER>(p, k, t, sm);
+        partial_tile<KIND, CENTER>(p, k, t, sm);
         return;
     }
     const uint64_t w0 = (uint64_t)t * kPartialTile + wave * (2u * kChunk);
@@ -223,23 +309,16 @@ __global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
 // saves the launch between the passes; the bucket's first tile writes the scale.
 template <int M, bool CENTER>
 __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p) {
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    __shared__ __align__(16) unsigned char strings[4][kStringBytes<M> + 16];
+    const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t k = blockIdx.y;
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group);
     unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
     float* __restrict__ norms = reinterpret_cast<float*>(out + p.norms_off);
-    const uint64_t e0 = (uint64_t)t * kPartialTile, g0 = e0 / kLaneElems;
-    const uint64_t b = e0 >> p.log2N;
-    const bool full = t < p.full_tiles;
+    const uint64_t b = (uint64_t)t * kPartialTile >> p.log2N;
+    const WaveSpan s = wave_span_dense<2>(p, (uint64_t)t * 4u + wave);
     float v[2][8];
-    LaneSpan span[2];
-    if (full) {
-        const uint64_t w0 = e0 + wave * (2u * kChunk);
-        load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, p.x_cached, v);
-    } else {                                              // the ragged last tile of the worker (at most one)
-        guarded_spans<2, true, true>(p, t, span);
-        guarded_load<2, true, CENTER>(p, k, span, v);
-    }
+    load_span<2, CENTER>(p, k, s, lane, v);
     Scale sc;
     if (p.merged) {
         const uint32_t P = 1u << (p.log2N - 12u);
@@ -250,37 +329,20 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
     } else {
         sc = scale_of_norm<M>(norms[b]);
     }
-    if (!full) {
-        guarded_codes<M, 2, QESGD_NORM_L2, true, true>(p, k, span, v, nullptr, true, sc.norm);
-        return;
-    }
-    const uint32_t idx0 = wave * 2u * kWaveSize + lane;
-    uint32_t sign_byte[2], bits[2][4];
-#pragma unroll
-    for (uint32_t c = 0; c < 2; ++c) {
-        uint32_t rnd[4];
-        philox4x32_10((uint32_t)g0 + idx0 + c * kWaveSize, (uint32_t)(g0 >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
-        round_and_pack<M>(v[c], rnd, sc, sign_byte[c], bits[c]);
-    }
-    if constexpr (32 % M == 0) {
-        store_chunks<M, 2>(out + p.signs_off + g0, out + p.levels_off + g0 * M, idx0, p.codes_cached, sign_byte, bits);
-    } else {
-#pragma unroll
-        for (uint32_t c = 0; c < 2; ++c)
-            store_whole<M>(out + p.signs_off, out + p.levels_off, e0 + (wave * 2u + c) * kChunk, lane, p.codes_cached, sign_byte[c], bits[c]);
-    }
+    const Scale both[2] = {sc, sc};
+    encode_span<M, 2, QESGD_NORM_L2>(p, k, s, lane, strings[wave], v, both);
 }
 
 // ---------------------------------------------------------------------------
-// Buckets wider than kMaxSinglePassBucket, guarded versions: pass A leaves the
-// tree sum of a 4096-slot tile in the workspace, pass B finishes the tree per
-// bucket and writes the scale, then k_quantize_pack<.., PRE = true> reads it.
+// Buckets wider than kMaxSinglePassBucket that are no power of two, and the max norm: pass A leaves
+// the tree sum of a 4096-slot tile in the workspace, pass B finishes the tree per bucket and writes
+// the scale, then k_quantize_pack_bucket<.., kPre> reads it.
 // workspace[(k*nb + b)*P + t], P = N / 4096.
 // ---------------------------------------------------------------------------
 template <int KIND, bool CENTER>
 __global__ void k_tile_partials(const QParams p) {
     __shared__ float sm[4];
-    guarded_partial_tile<KIND, CENTER>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
+    partial_tile<KIND, CENTER>(p, blockIdx.y, xcd_tile(blockIdx.x, gridDim.x, p.xcd_group), sm);
 }
 
 // Finishes the tree of one bucket: P leaves (a power of two, >= 16), of which only the first
@@ -353,37 +415,43 @@ __global__ void __launch_bounds__(1024) k_finish_norms(const QParams p, uint64_t
 // ---------------------------------------------------------------------------
 // Launch plumbing.
 // ---------------------------------------------------------------------------
-template <int M, int CH, int KIND, bool PRE, bool CONTIG>
-void launch_center(const QParams& p, dim3 grid, dim3 block, hipStream_t st) {
-    if (p.center) hipLaunchKernelGGL((k_quantize_pack<M, CH, KIND, PRE, CONTIG, true>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((k_quantize_pack<M, CH, KIND, PRE, CONTIG, false>), grid, block, 0, st, p);
+// CH, MODE: of k_quantize_pack_bucket; CH = 0: k_quantize_pack_lanes.
+template <int M, int CH, Mode MODE, int KIND, bool CENTER>
+void launch_general_one(const QParams& p, dim3 grid, dim3 block, hipStream_t st) {
+    if constexpr (CH == 0) hipLaunchKernelGGL((k_quantize_pack_lanes<M, KIND, CENTER>), grid, block, 0, st, p);
+    else hipLaunchKernelGGL((k_quantize_pack_bucket<M, CH, KIND, CENTER, MODE>), grid, block, ((block.x >> 6) * kStringBytes<M>), st, p);
 }
 
-template <int M, int CH, bool PRE, bool CONTIG>
-void launch_kind(const QParams& p, uint32_t norm_kind, dim3 grid, dim3 block, hipStream_t st) {
-    if (norm_kind == QESGD_NORM_L2) launch_center<M, CH, QESGD_NORM_L2, PRE, CONTIG>(p, grid, block, st);
-    else launch_center<M, CH, QESGD_NORM_MAX, PRE, CONTIG>(p, grid, block, st);
+template <int M, int CH, Mode MODE>
+void launch_general_m(const QParams& p, uint32_t norm_kind, dim3 grid, dim3 block, hipStream_t st) {
+    if (norm_kind == QESGD_NORM_L2) {
+        if (p.center) launch_general_one<M, CH, MODE, QESGD_NORM_L2, true>(p, grid, block, st);
+        else launch_general_one<M, CH, MODE, QESGD_NORM_L2, false>(p, grid, block, st);
+    } else {
+        if (p.center) launch_general_one<M, CH, MODE, QESGD_NORM_MAX, true>(p, grid, block, st);
+        else launch_general_one<M, CH, MODE, QESGD_NORM_MAX, false>(p, grid, block, st);
+    }
+}
+
+template <int CH, Mode MODE>
+void launch_general(const QParams& p, uint32_t m, uint32_t norm_kind, dim3 grid, dim3 block, hipStream_t st) {
+    switch (m) {
+        case 1: launch_general_m<1, CH, MODE>(p, norm_kind, grid, block, st); break;
+        case 2: launch_general_m<2, CH, MODE>(p, norm_kind, grid, block, st); break;
+        case 3: launch_general_m<3, CH, MODE>(p, norm_kind, grid, block, st); break;
+        case 4: launch_general_m<4, CH, MODE>(p, norm_kind, grid, block, st); break;
+        case 5: launch_general_m<5, CH, MODE>(p, norm_kind, grid, block, st); break;
+        case 6: launch_general_m<6, CH, MODE>(p, norm_kind, grid, block, st); break;
+        case 7: launch_general_m<7, CH, MODE>(p, norm_kind, grid, block, st); break;
+        case 8: launch_general_m<8, CH, MODE>(p, norm_kind, grid, block, st); break;
+        default: launch_general_m<16, CH, MODE>(p, norm_kind, grid, block, st); break;
+    }
 }
 
 template <int KIND>
 void launch_partials(const QParams& p, dim3 grid, hipStream_t st) {
     if (p.center) hipLaunchKernelGGL((k_tile_partials<KIND, true>), grid, dim3(256), 0, st, p);
     else hipLaunchKernelGGL((k_tile_partials<KIND, false>), grid, dim3(256), 0, st, p);
-}
-
-template <int CH, bool PRE, bool CONTIG = true>
-void launch_m(const QParams& p, uint32_t m, uint32_t norm_kind, dim3 grid, dim3 block, hipStream_t st) {
-    switch (m) {
-        case 1: launch_kind<1, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
-        case 2: launch_kind<2, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
-        case 3: launch_kind<3, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
-        case 4: launch_kind<4, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
-        case 5: launch_kind<5, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
-        case 6: launch_kind<6, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
-        case 7: launch_kind<7, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
-        case 8: launch_kind<8, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
-        default: launch_kind<16, CH, PRE, CONTIG>(p, norm_kind, grid, block, st); break;
-    }
 }
 
 template <int M, int LOG2N>
@@ -556,10 +624,10 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
     const bool two_pass = sh.N > kMaxSinglePassBucket;
     // Tiles that lie wholly inside the vector go to the fast kernel when the bucket is a
     // power of two (slot == coordinate), the scale is the L2 norm and the level width
-    // divides a word (the other widths are served by the generic kernel alone).
+    // divides a word (the other widths are served by the general kernels alone).
     const bool fast = !two_pass && a.norm_kind == QESGD_NORM_L2 && sh.N == sh.B && sh.log2N >= 5 &&
                       32u % sh.m == 0u;
-    uint32_t ch = 2, nwaves = 4;                         // generic kernel: 2 chunks per wave, 4..16 waves
+    uint32_t ch = 2, nwaves = 4;                         // general kernels: 2 chunks per wave, 4..16 waves
     if (!two_pass && !fast) {
         if (sh.N == 8192) nwaves = 8;
         else if (sh.N == 16384) nwaves = 16;
@@ -580,7 +648,7 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         return check_launch();
     }
     if (two_pass) {
-        // Buckets that are no power of two, and the max norm: guarded kernels over all of slot space (over the
+        // Buckets that are no power of two, and the max norm: all of slot space (over the
         // tiles that hold coordinates, where slot space equals coordinate space).
         const uint64_t P = sh.N / kPartialTile;          // tiles == nb * P
         uint32_t finish_waves = 1;
@@ -599,7 +667,7 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         }
         const int rc = check_launch();
         if (rc != QESGD_OK) return rc;
-        launch_m<2, true>(p, sh.m, a.norm_kind, grid, block, a.stream);
+        launch_general<2, kPre>(p, sh.m, a.norm_kind, grid, block, a.stream);
         return check_launch();
     }
 
@@ -613,9 +681,10 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
     }
     p.xcd_group = xcd_group_log2(tile);
     const dim3 grid((uint32_t)tiles, a.K);
-    if (ch == 2 && (sh.N >= 2 * kChunk || sh.N == sh.B)) launch_m<2, false>(p, sh.m, a.norm_kind, grid, block, a.stream);
-    else if (ch == 2) launch_m<2, false, false>(p, sh.m, a.norm_kind, grid, block, a.stream);
-    else launch_m<4, false>(p, sh.m, a.norm_kind, grid, block, a.stream);
+    if (ch == 4) launch_general<4, kBuckets>(p, sh.m, a.norm_kind, grid, block, a.stream);
+    else if (sh.N >= 2 * kChunk) launch_general<2, kBuckets>(p, sh.m, a.norm_kind, grid, block, a.stream);
+    else if (sh.N == sh.B || sh.nb == 1) launch_general<2, kNarrow>(p, sh.m, a.norm_kind, grid, block, a.stream);
+    else launch_general<0, kNarrow>(p, sh.m, a.norm_kind, grid, block, a.stream);
     return check_launch();
 }
 

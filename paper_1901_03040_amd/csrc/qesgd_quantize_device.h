@@ -1,6 +1,6 @@
 // Device code of the quantiser shared by the translation units that launch it (not installed):
 // the kernel parameter block, the cross-lane tree, rounding and packing of a lane's 8 coordinates,
-// the guarded tile and the straight-line tile of the power-of-two-bucket kernels.
+// a wave on any bucket and the straight-line tile of the power-of-two-bucket kernels.
 #pragma once
 
 #include <type_traits>
@@ -23,7 +23,7 @@ struct QParams {
     uint64_t nb;
     uint64_t norms_off, signs_off, levels_off;
     uint32_t log2N;
-    uint32_t log2_waves;         // guarded tiles: waves per workgroup
+    uint32_t log2_waves;         // general kernels: waves per workgroup
     uint32_t full_tiles;         // fast kernels: tiles per worker that lie wholly inside the vector
     uint32_t tail_tiles;         // fast quantize kernel: ragged tiles per worker after those (0 or 1)
     uint32_t group_workers;      // workers covered by this launch
@@ -435,30 +435,28 @@ __device__ __forceinline__ void store_chunks(unsigned char* __restrict__ signs, 
     }
 }
 
-// Level words of 512 consecutive coordinates for the widths that do not divide 32: the lanes' M bytes each
-// meet in LDS private to the wave and leave as consecutive words (M = 5: about 15 instructions against 55 for
-// shifting every lane's string into the words of its quad, as store_codes does).  words: the first of 16 * M.
+// Level strings of 512 consecutive coordinates for the widths that do not divide 32: the lanes' M bytes each meet in
+// LDS private to the wave and leave as consecutive 16-byte pieces.  words: the first of 16 * M, on any word.  mine: the
+// wave's kStringBytes of LDS.  Chunk by chunk and with the ordinary policy (two chunks at a time: d = 3.5 M, K = 8, s = 128,
+// bucket 8192 27.7 us, 25.7 one by one; non-temporal: d = 10 M, K = 8, s = 64, one bucket, gradient round 164 us, 157).
 template <int M>
-__device__ __forceinline__ void store_levels_lds(uint32_t* __restrict__ words, uint32_t lane, const uint32_t (&bits)[4]) {
-    __shared__ uint32_t stage[16][16 * M];
-    uint32_t* mine = stage[threadIdx.x >> 6];
-    unsigned char* bytes = reinterpret_cast<unsigned char*>(mine) + lane * (uint32_t)M;
-#pragma unroll
-    for (int j = 0; j < M; ++j) bytes[j] = (unsigned char)(bits[j >> 2] >> (8 * (j & 3)));
+constexpr uint32_t kStringBytes = 32 % M == 0 ? 0 : kWaveSize * M;
+template <int M>
+__device__ __forceinline__ void store_levels_lds(unsigned char* mine, uint32_t* __restrict__ words, uint32_t lane, const uint32_t (&bits)[4]) {
+    typedef uint32_t uvec4 __attribute__((ext_vector_type(4)));
+    typedef uvec4 anywhere __attribute__((aligned(4)));
+    __builtin_memcpy(mine + lane * (uint32_t)M, bits, M);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const uint32_t first = lane < 16u * M ? mine[lane] : 0u;
-    const uint32_t second = lane + 64u < 16u * M ? mine[lane + 64u] : 0u;
+    if (lane < 4u * M) reinterpret_cast<anywhere*>(words)[lane] = *reinterpret_cast<const uvec4*>(mine + lane * 16u);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();                      // the next chunk overwrites the area
-    if (lane < 16u * M) words[lane] = first;
-    if (lane + 64u < 16u * M) words[lane + 64u] = second;
 }
 
 // The codes of a wave's 512 consecutive coordinates from coordinate i0 (a multiple of 32) on.
 template <int M>
-__device__ __forceinline__ void store_whole(unsigned char* __restrict__ signs, unsigned char* __restrict__ levels, uint64_t i0,
+__device__ __forceinline__ void store_whole(unsigned char* string, unsigned char* __restrict__ signs, unsigned char* __restrict__ levels, uint64_t i0,
                                             uint32_t lane, bool cached, uint32_t sign_byte, const uint32_t (&bits)[4]) {
     const uint64_t g0 = i0 / kLaneElems;
     if constexpr (32 % M == 0) {
@@ -466,24 +464,120 @@ __device__ __forceinline__ void store_whole(unsigned char* __restrict__ signs, u
         store_chunks<M, 1>(signs + g0, levels + g0 * M, lane, cached, sb, bt);
     } else {
         (signs + g0)[lane] = (unsigned char)sign_byte;
-        store_levels_lds<M>(reinterpret_cast<uint32_t*>(levels + g0 * M), lane, bits);
+        store_levels_lds<M>(string, reinterpret_cast<uint32_t*>(levels + g0 * M), lane, bits);
+    }
+}
+
+// Of the tile's `count` coordinates those from the wave's first on.
+__device__ __forceinline__ uint32_t count_from(uint32_t count, uint32_t first) { return count > first ? count - first : 0u; }
+
+// A wave's CH chunks of a tile into registers: xw / cw point at the wave's first coordinate.  All
+// loads are issued before the first use.  `center` is read by every worker's workgroup of the tile,
+// so it keeps the ordinary cache policy.
+template <int CH, bool CENTER, bool FULL = true>
+__device__ __forceinline__ void load_tile(const float* __restrict__ xw, const float* __restrict__ cw, uint32_t lane,
+                                          bool x_cached, float (&v)[CH][8], uint32_t count = CH * kChunk) {
+    vec4 a[CH], b[CH], ca[CH], cb[CH];
+    load_chunks<CH, FULL>(xw, lane, count, x_cached, a, b);
+    if (CENTER) load_chunks<CH, FULL>(cw, lane, count, true, ca, cb);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        if (CENTER) {
+            a[c] -= ca[c];
+            b[c] -= cb[c];
+        }
+        halves_to_lane(a[c], b[c], v[c]);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Guarded tile: the body of the generic kernel and of the last pass's ragged tile.
+// A wave on CH x 512 slots that hold consecutive coordinates, whatever the bucket's size.
 // ---------------------------------------------------------------------------
-// Where the 8 slots of this lane in a chunk of 512 fall: bucket, first coordinate, how many of them are real
-// coordinates (0..8), and whether they open the bucket.  CONTIG: the chunk's slots are consecutive coordinates
-// as far as they hold any, `count` from coordinate i0 on, the same for the wave and worked out in scalar
-// registers: buckets padded to 1024 or more, and power-of-two buckets.  (Buckets of 256 to 512 are faster lane by
-// lane, every wave of theirs holding padding: d = 15 M, K = 5, s = 16, bucket 320 84.0 / 76.0 us.)
+// Where the wave's slots fall, worked out in scalar registers: `mine` coordinates (0: all padding) from coordinate
+// i0 (a multiple of 32) on, in bucket `bucket`, in whose slots the wave is number `sub`.
+struct WaveSpan {
+    uint64_t bucket, i0;
+    uint32_t sub, mine;
+};
+
+// max(0, min(left, most)).  In 32-bit comparisons: a uniform 64-bit one runs on the vector unit, and where its result
+// served a branch and a selection the compiler lost the latter's condition (the selection took whatever carry was last).
+__device__ __forceinline__ uint32_t clamp_left(int64_t left, uint32_t most) {
+    const int32_t high = (int32_t)(left >> 32);
+    const uint32_t low = (uint32_t)left;
+    return high < 0 ? 0u : high > 0 || low > most ? most : low;
+}
+
+// unit: the wave's number in slot space.  Buckets are 2^lg waves.
+template <int CH>
+__device__ __forceinline__ WaveSpan wave_span(const QParams& p, uint64_t unit, uint32_t lg) {
+    WaveSpan s;
+    s.bucket = unit >> lg;
+    s.sub = (uint32_t)unit & ((1u << lg) - 1u);
+    const uint64_t j = (unit & ((1ull << lg) - 1u)) * (CH * kChunk), at = s.bucket * p.B + j;
+    const uint32_t in_bucket = clamp_left((int64_t)(p.B - j), CH * kChunk), in_vector = clamp_left((int64_t)(p.d - at), CH * kChunk);
+    s.mine = in_bucket < in_vector ? in_bucket : in_vector;
+    s.i0 = s.mine ? at : 0;
+    return s;
+}
+// The same where slots are coordinates (a bucket that is a power of two, or the only one); the bucket is left out.
+template <int CH>
+__device__ __forceinline__ WaveSpan wave_span_dense(const QParams& p, uint64_t unit) {
+    WaveSpan s{};
+    const uint64_t at = unit * (CH * kChunk);
+    s.mine = clamp_left((int64_t)(p.d - at), CH * kChunk);
+    s.i0 = s.mine ? at : 0;
+    return s;
+}
+
+// Worker k's coordinates of the span, 0 beyond it.
+template <int CH, bool CENTER>
+__device__ __forceinline__ void load_span(const QParams& p, uint32_t k, const WaveSpan& s, uint32_t lane, float (&v)[CH][8]) {
+    const float* __restrict__ x = p.x + (uint64_t)k * p.x_stride + s.i0;
+    if (s.mine == CH * kChunk) load_tile<CH, CENTER>(x, p.center + s.i0, lane, p.x_cached, v);
+    else load_tile<CH, CENTER, false>(x, p.center + s.i0, lane, true, v, s.mine);
+}
+
+// Their codes.  string: kStringBytes<M> of LDS that are the wave's.
+template <int M, int CH, int KIND>
+__device__ __forceinline__ void encode_span(const QParams& p, uint32_t k, const WaveSpan& s, uint32_t lane, unsigned char* string,
+                                            const float (&v)[CH][8], const Scale (&sc)[CH]) {
+    unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
+    const bool whole = s.mine == CH * kChunk;
+    uint32_t sign_byte[CH], bits[CH][4];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        if (!whole && s.mine <= (uint32_t)c * kChunk) break;                     // no coordinate left
+        const uint64_t g = s.i0 / kLaneElems + (uint32_t)c * kWaveSize;
+        const uint32_t low = (uint32_t)g + lane, high = (uint32_t)(g >> 32);
+        uint32_t rnd[4];
+        // the group number's high word is the same for the wave, and scalar, unless the low one wraps among its lanes
+        if ((uint32_t)g <= 0xFFFFFFC0u) philox4x32_10(low, high, p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        else philox4x32_10(low, high + (low < (uint32_t)g ? 1u : 0u), p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        Scale own = sc[c];
+        if (KIND != QESGD_NORM_L2) own.direct = own.direct && wave_all(no_nan<KIND>(v[c]));
+        round_and_pack<M>(v[c], rnd, own, sign_byte[c], bits[c]);
+        if (!whole) {
+            const uint32_t at = (uint32_t)c * kChunk + lane * kLaneElems, rest = count_from(s.mine, at);
+            store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off), s.i0 + at,
+                           rest < 8u ? rest : 8u, lane, sign_byte[c], bits[c]);
+        } else if constexpr (32 % M != 0) {
+            store_whole<M>(string, out + p.signs_off, out + p.levels_off, s.i0 + (uint32_t)c * kChunk, lane, p.codes_cached, sign_byte[c], bits[c]);
+        }
+    }
+    const uint64_t g0 = s.i0 / kLaneElems;
+    if constexpr (32 % M == 0)
+        if (whole) store_chunks<M, CH>(out + p.signs_off + g0, out + p.levels_off + g0 * M, lane, p.codes_cached, sign_byte, bits);
+}
+
+// ---------------------------------------------------------------------------
+// Lane by lane: buckets padded to 512 or less that are neither a power of two nor the only one, every wave of which
+// holds padding.
+// ---------------------------------------------------------------------------
+// Where the 8 slots of a lane fall: bucket, first coordinate (a multiple of 8), 4 coordinates that exist, how many of
+// the 8 are real coordinates (0..8), and whether they open the bucket.
 struct LaneSpan {
-    uint64_t bucket;
-    uint64_t i;        // first coordinate (a multiple of 8)
-    uint64_t i0;       // CONTIG only
-    uint64_t safe;     // not CONTIG: 4 coordinates that exist (d >= 4)
-    uint32_t count;    // CONTIG only
+    uint64_t bucket, i, safe;
     uint32_t nvalid;
     bool opens_bucket;
 };
@@ -505,250 +599,44 @@ __device__ __forceinline__ LaneSpan lane_span(uint64_t slot, const QParams& p) {
     return s;
 }
 
-// The slots of this lane in a guarded tile (the same for every worker).  ONE: the wave's chunks lie in one bucket.
-template <int CH, bool CONTIG, bool ONE>
-__device__ __forceinline__ void guarded_spans(const QParams& p, uint32_t tile, LaneSpan (&span)[CH]) {
-    const uint32_t lane = threadIdx.x & 63u, before = lane * kLaneElems;
-    const uint64_t wave0 = ((uint64_t)tile << p.log2_waves) + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint64_t slot0 = wave0 * (uint64_t)(CH * kChunk), N = 1ull << p.log2N;
-    const bool one = ONE || N >= (uint64_t)CH * kChunk;   // otherwise B == N
-    uint64_t bucket = 0, j = 0, i0 = 0;
-    uint32_t rest = 0;                                    // coordinates from i0 to the end of the bucket, at most CH * 512
+// The coordinates of a lane's slots, 0 beyond them: two float4, read from s.safe where they are not wholly inside, so that
+// the loads of all chunks, and of the center behind them, are in flight together.  (A vector of several
+// such buckets has more than 4.)
+template <int CH, bool CENTER>
+__device__ __forceinline__ void load_lanes(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], float (&v)[CH][8]) {
+    const float* __restrict__ x = p.x + (uint64_t)k * p.x_stride;
+    vec4 a[CH], b[CH], ca[CH], cb[CH];
+    bool end = false;                                     // the vector ends here, off a float4 (the same for the wave)
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const uint64_t slot = slot0 + (uint32_t)c * kChunk;
-        if (!CONTIG) {
-            span[c] = lane_span(slot + before, p);
-            continue;
+        const uint64_t ia = span[c].nvalid >= 4u ? span[c].i : span[c].safe, ib = span[c].nvalid == 8u ? span[c].i + 4u : span[c].safe;
+        a[c] = load_cached(x + ia);
+        b[c] = load_cached(x + ib);
+        if (CENTER) {
+            ca[c] = load_cached(p.center + ia);
+            cb[c] = load_cached(p.center + ib);
         }
-        if (c == 0 || !one) {
-            uint64_t end = p.d;
-            i0 = slot;
-            if (one) {
-                bucket = slot >> p.log2N;
-                j = slot & (N - 1);
-                i0 = bucket * p.B + j;
-                end = bucket >= p.nb ? 0 : bucket * p.B + p.B < p.d ? bucket * p.B + p.B : p.d;
-            }
-            const uint64_t left = i0 < end ? end - i0 : 0;
-            rest = left < CH * kChunk ? (uint32_t)left : CH * kChunk;
-        } else {
-            i0 += kChunk;
-            rest = rest > kChunk ? rest - kChunk : 0;
-        }
-        span[c].i0 = i0;
-        span[c].count = rest < kChunk ? rest : kChunk;
-        span[c].i = i0 + before;
-        span[c].nvalid = before < span[c].count ? (span[c].count - before < 8u ? span[c].count - before : 8u) : 0u;
-        if (one) {
-            span[c].bucket = bucket;
-            span[c].opens_bucket = c == 0 && j == 0 && lane == 0 && bucket < p.nb;
-        } else {
-            span[c].bucket = (slot + before) >> p.log2N;
-            span[c].opens_bucket = ((slot + before) & (N - 1)) == 0 && span[c].nvalid > 0;
-        }
+        end = end || !wave_all(span[c].nvalid == 0u || span[c].nvalid == 8u);
     }
-}
-
-// How many coordinates the two float4 that this lane loads of a chunk hold (0..4 and more), and the place of the
-// first.  CONTIG: like a full tile, one of each half (see halves_to_lane); otherwise the lane's own 8.
-template <bool CONTIG>
-struct GuardedLoad {
-    static constexpr uint32_t step = CONTIG ? kChunk / 2 : 4u;      // from the first to the second
-    uint32_t na, nb;
-    uint64_t at;
-    __device__ __forceinline__ explicit GuardedLoad(const LaneSpan& s) {
-        const uint32_t h = CONTIG ? half_offset(threadIdx.x & 63u) : 0u, count = CONTIG ? s.count : s.nvalid;
-        na = count > h ? count - h : 0u;
-        nb = count > h + step ? count - h - step : 0u;
-        at = CONTIG ? s.i0 + h : s.i;
-    }
-};
-// A float4 that the vector ends in.
-template <bool CENTER>
-__device__ __forceinline__ void load_end(const float* __restrict__ x, const float* __restrict__ center, uint64_t at, uint32_t n, vec4& a) {
-    if (n == 0u || n >= 4u) return;
-#pragma unroll
-    for (uint32_t e = 0; e < 3; ++e)
-        if (e < n) a[e] = CENTER ? x[at + e] - center[at + e] : x[at + e];
-}
-
-// One vector's coordinates of those slots, in the layout they are loaded in.  FULL: all slots of the wave hold some.
-// Otherwise a float4 that is not wholly inside means nothing; it is read where the wave or the bucket reads anyway
-// (CONTIG: the wave's first four coordinates, or the four before it where it holds fewer: a vector in this form has 8
-// or more).  Nothing here waits: the loads of all chunks, and of the center behind them, are in flight together
-// (a wait between the chunks: d = 15 M, K = 5, s = 4, max norm, bucket 23648 119.7 us, without 83.7; with a center, L2
-// 146.5 / 126.7; d = 3.5 M, K = 8, s = 256, bucket 23648 47.4 / 37.0).
-template <int CH, bool CONTIG, bool FULL, bool CACHED>
-__device__ __forceinline__ void guarded_load_raw(const float* __restrict__ x, const LaneSpan (&span)[CH], vec4 (&a)[CH], vec4 (&b)[CH]) {
-    const uint64_t first = span[0].count >= 4u ? span[0].i0 : span[0].i0 - 4u;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        const GuardedLoad<CONTIG> l(span[c]);
-        const float *pa, *pb;
-        if (CONTIG) {                                     // a scalar base and 32-bit offsets
-            const float* __restrict__ base = x + (FULL || span[c].count >= 4u ? span[c].i0 : first);
-            const uint32_t h = half_offset(threadIdx.x & 63u);
-            pa = base + (FULL || l.na >= 4u ? h : 0u);
-            pb = base + (FULL || l.nb >= 4u ? h + l.step : 0u);
-        } else {
-            pa = x + (l.na >= 4u ? l.at : span[c].safe);
-            pb = x + (l.nb >= 4u ? l.at + l.step : span[c].safe);
-        }
-        a[c] = CACHED ? load_cached(pa) : load_stream(pa);
-        b[c] = CACHED ? load_cached(pb) : load_stream(pb);
-    }
-}
-template <int CH, bool CONTIG, bool CENTER, bool FULL>
-__device__ __forceinline__ void guarded_load_diff(const QParams& p, const float* __restrict__ x, const LaneSpan (&span)[CH], vec4 (&a)[CH], vec4 (&b)[CH]) {
-    vec4 ca[CH], cb[CH];
-    if (!CONTIG || p.x_cached) {
-        asm volatile("; cached");                         // keeps the arms apart (see load_halves)
-        guarded_load_raw<CH, CONTIG, FULL, true>(x, span, a, b);
-        if (CENTER) guarded_load_raw<CH, CONTIG, FULL, true>(p.center, span, ca, cb);
-        asm volatile("; cached end");
-    } else {
-        guarded_load_raw<CH, CONTIG, FULL, false>(x, span, a, b);
-        if (CENTER) guarded_load_raw<CH, CONTIG, FULL, true>(p.center, span, ca, cb);
-    }
-    if (CENTER) {
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
+        if (CENTER) {
             a[c] -= ca[c];
             b[c] -= cb[c];
         }
-    }
-}
-template <int CH, bool CONTIG, bool CENTER>
-__device__ __forceinline__ void guarded_load(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], float (&v)[CH][8]) {
-    if (CONTIG && span[0].count == 0u) {                  // a wave of padding
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
+        for (uint32_t e = 0; e < 4; ++e) {
+            v[c][e] = span[c].nvalid >= 4u ? a[c][e] : 0.0f;
+            v[c][4 + e] = span[c].nvalid == 8u ? b[c][e] : 0.0f;
+        }
+        if (end) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[c][e] = 0.0f;
-        return;
-    }
-    const float* __restrict__ x = p.x + (uint64_t)k * p.x_stride;
-    vec4 a[CH], b[CH];
-    bool full = CONTIG, end = false;                      // the same for the wave: no padding; the vector ends here, off a float4
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        full = full && span[c].count == kChunk;
-        end = end || (CONTIG ? (span[c].count & 3u) != 0u : !wave_all(span[c].nvalid == 0u || span[c].nvalid == 8u));
-    }
-    if (full) {
-        guarded_load_diff<CH, CONTIG, CENTER, true>(p, x, span, a, b);
-    } else {
-        const bool some = CONTIG || p.d >= 4u;            // a float4 to read
-        if (some) guarded_load_diff<CH, CONTIG, CENTER, false>(p, x, span, a, b);
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const GuardedLoad<CONTIG> l(span[c]);
-#pragma unroll
-            for (uint32_t e = 0; e < 4; ++e) {
-                if (!some || l.na < 4u) a[c][e] = 0.0f;
-                if (!some || l.nb < 4u) b[c][e] = 0.0f;
-            }
-            if (end) {
-                load_end<CENTER>(x, p.center, l.at, l.na, a[c]);
-                load_end<CENTER>(x, p.center, l.at + l.step, l.nb, b[c]);
+            for (uint32_t e = 0; e < 8; ++e) {
+                const bool last = span[c].nvalid < 8u && e < span[c].nvalid && e >= (span[c].nvalid & 4u);
+                if (last) v[c][e] = CENTER ? x[span[c].i + e] - p.center[span[c].i + e] : x[span[c].i + e];
             }
         }
     }
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        if (CONTIG) {
-            halves_to_lane(a[c], b[c], v[c]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                v[c][e] = a[c][e];
-                v[c][4 + e] = b[c][e];
-            }
-        }
-    }
-}
-
-// One tile of worker k with every access guarded per lane, its coordinates loaded.  PRE = true: the scales
-// were computed by the partial-sum passes and are read from the norms plane, or the tile's one scale is
-// handed in (given).  sm: 32 floats of LDS, not used with PRE.
-template <int M, int CH, int KIND, bool PRE, bool CONTIG>
-__device__ __forceinline__ void guarded_codes(const QParams& p, uint32_t k, const LaneSpan (&span)[CH], const float (&v)[CH][8],
-                                              float* sm, bool given = false, float given_norm = 0.0f) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = threadIdx.x >> 6;
-    unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
-    float* __restrict__ norms = reinterpret_cast<float*>(out + p.norms_off);
-    uint32_t* __restrict__ signs = reinterpret_cast<uint32_t*>(out + p.signs_off);
-    uint32_t* __restrict__ levels = reinterpret_cast<uint32_t*>(out + p.levels_off);
-    const uint64_t N = 1ull << p.log2N;
-
-    Scale sc[CH];
-    if (PRE) {                                            // the tile lies in one bucket; if in none, nothing is encoded
-        const Scale one = scale_of_norm<M>(given ? given_norm : span[0].bucket < p.nb ? norms[span[0].bucket] : 1.0f);
-#pragma unroll
-        for (int c = 0; c < CH; ++c) sc[c] = one;
-    } else {
-        float t[CH];
-        const uint32_t lanes_per_bucket = (uint32_t)((N < kChunk ? N : kChunk) / kLaneElems);
-#pragma unroll
-        for (int c = 0; c < CH; ++c) t[c] = lane_butterfly<KIND>(lane_tree<KIND>(v[c]), lanes_per_bucket);
-        if (N > kChunk) {
-            const uint32_t chunks_per_bucket = (uint32_t)(N / kChunk < (uint64_t)CH ? N / kChunk : (uint64_t)CH);
-#pragma unroll
-            for (int w = 1; w < CH; w <<= 1) {
-                if (chunks_per_bucket > (uint32_t)w) {
-#pragma unroll
-                    for (int c = 0; c < CH; c += 2 * w) t[c] = combine<KIND>(t[c], t[c + w]);
-                }
-            }
-            if (N > (uint64_t)(CH * kChunk)) {          // the bucket spans several waves
-                const uint32_t waves_per_bucket = (uint32_t)(N / (CH * kChunk));
-                if (lane == 0) sm[wave] = t[0];
-                __syncthreads();
-                t[0] = lds_tree16<KIND>(sm, wave & ~(waves_per_bucket - 1u), waves_per_bucket);
-            }
-#pragma unroll
-            for (int w = CH / 2; w >= 1; w >>= 1) {
-                if (chunks_per_bucket > (uint32_t)w) {
-#pragma unroll
-                    for (int c = 0; c < CH; c += 2 * w) t[c + w] = t[c];
-                }
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            // a lane without coordinates must not take its wave out of the short rounding: any ordinary scale
-            if (c > 0 && N >= 2 * kChunk && N >= (uint64_t)CH * kChunk) sc[c] = sc[0];
-            else sc[c] = scale_of_total<M, KIND>(span[c].nvalid || N >= kChunk ? t[c] : 1.0f);
-            if (span[c].opens_bucket) norms[span[c].bucket] = sc[c].norm;
-        }
-    }
-
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        // Lanes are in slot order, so a chunk whose first lane holds no coordinate is all padding
-        // (the tail of a bucket that is not a power of two, or of the vector): nothing to encode.
-        if (CONTIG ? span[c].count == 0u : __builtin_amdgcn_readfirstlane(span[c].nvalid) == 0u) continue;
-        const uint64_t g = span[c].i >> 3;
-        uint32_t rnd[4];
-        philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
-        uint32_t sign_byte, bits[4];
-        Scale own = sc[c];
-        if (KIND != QESGD_NORM_L2) own.direct = own.direct && wave_all(no_nan<KIND>(v[c]));
-        round_and_pack<M>(v[c], rnd, own, sign_byte, bits);
-        if (CONTIG && span[c].count == kChunk) store_whole<M>(out + p.signs_off, out + p.levels_off, span[c].i0, lane, p.codes_cached, sign_byte, bits);
-        else store_codes<M>(signs, levels, span[c].i, span[c].nvalid, lane, sign_byte, bits);
-    }
-}
-
-template <int M, int CH, int KIND, bool PRE, bool CONTIG, bool CENTER>
-__device__ __forceinline__ void guarded_tile(const QParams& p, uint32_t k, uint32_t tile, float* sm) {
-    LaneSpan span[CH];
-    float v[CH][8];
-    guarded_spans<CH, CONTIG, PRE || CH == 4>(p, tile, span);     // four chunks per wave: buckets of 32768
-    guarded_load<CH, CONTIG, CENTER>(p, k, span, v);
-    guarded_codes<M, CH, KIND, PRE, CONTIG>(p, k, span, v, sm);
 }
 
 // ---------------------------------------------------------------------------
@@ -774,28 +662,6 @@ inline uint64_t fast_tile(uint32_t m, uint64_t N, bool center) {
     const uint64_t ch = N == 32768 ? 4 : (center && m > 2 && N < 8192 ? 1 : 2);
     return N > 2 * ch * kChunk ? N : 2 * ch * kChunk;
 }
-
-// A wave's CH chunks of a tile into registers: xw / cw point at the wave's first coordinate.  All
-// loads are issued before the first use.  `center` is read by every worker's workgroup of the tile,
-// so it keeps the ordinary cache policy.
-template <int CH, bool CENTER, bool FULL = true>
-__device__ __forceinline__ void load_tile(const float* __restrict__ xw, const float* __restrict__ cw, uint32_t lane,
-                                          bool x_cached, float (&v)[CH][8], uint32_t count = CH * kChunk) {
-    vec4 a[CH], b[CH], ca[CH], cb[CH];
-    load_chunks<CH, FULL>(xw, lane, count, x_cached, a, b);
-    if (CENTER) load_chunks<CH, FULL>(cw, lane, count, true, ca, cb);
-#pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        if (CENTER) {
-            a[c] -= ca[c];
-            b[c] -= cb[c];
-        }
-        halves_to_lane(a[c], b[c], v[c]);
-    }
-}
-
-// Of the tile's `count` coordinates those from the wave's first on.
-__device__ __forceinline__ uint32_t count_from(uint32_t count, uint32_t first) { return count > first ? count - first : 0u; }
 
 // Everything a workgroup needs to know about its worker, in registers; the pointers are uniform.
 struct FastCtx {

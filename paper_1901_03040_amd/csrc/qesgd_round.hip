@@ -144,9 +144,9 @@ __global__ void __launch_bounds__(RoundGeo<LOG2N>::NW * 64) k_round_fused(const 
 // One wave per workgroup would finish every scale by itself; four share that work.
 constexpr uint32_t kWideWaves = 4;
 
-// norm: lane k holds worker k's (lanes from K on: 1).  ca, cb, a, b: the center's and the first worker's.
+// string: kStringBytes<M> of LDS that are the wave's.  norm: lane k holds worker k's (lanes from K on: 1).  ca, cb, a, b: the center's and the first worker's.
 template <int M, bool CENTER, bool ZACC, bool FULL>
-__device__ __forceinline__ void wide_chunk(const RParams& r, uint64_t c0, uint32_t lane, float norm, const vec4 (&ca)[1],
+__device__ __forceinline__ void wide_chunk(const RParams& r, unsigned char* string, uint64_t c0, uint32_t lane, float norm, const vec4 (&ca)[1],
                                            const vec4 (&cb)[1], vec4 (&a)[1], vec4 (&b)[1]) {
     const QParams& p = r.q;
     const uint32_t count = FULL ? kChunk : (uint32_t)(p.d - c0);
@@ -178,7 +178,7 @@ __device__ __forceinline__ void wide_chunk(const RParams& r, uint64_t c0, uint32
         round_and_pack<M>(v, rnd, sc, sign_byte, bits);
         unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
         if (FULL) {
-            store_whole<M>(out + p.signs_off, out + p.levels_off, c0, lane, false, sign_byte, bits);
+            store_whole<M>(string, out + p.signs_off, out + p.levels_off, c0, lane, false, sign_byte, bits);
         } else {
             const uint32_t before = lane * kLaneElems;
             const uint32_t nvalid = before < count ? (count - before < 8u ? count - before : 8u) : 0u;
@@ -208,6 +208,7 @@ __device__ __forceinline__ void wide_chunk(const RParams& r, uint64_t c0, uint32
 template <int M, bool CENTER, bool ZACC>
 __global__ void __launch_bounds__(kWideWaves * 64) k_round_wide(const RParams r) {
     __shared__ float total[64];
+    __shared__ __align__(16) unsigned char strings[kWideWaves][kStringBytes<M> + 16];
     const QParams& p = r.q;
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t t = xcd_tile(blockIdx.x, gridDim.x, p.xcd_group) * kWideWaves + wave;
@@ -239,12 +240,12 @@ __global__ void __launch_bounds__(kWideWaves * 64) k_round_wide(const RParams r)
         norm = reinterpret_cast<const float*>(p.packed + (uint64_t)lane * p.packed_stride + p.norms_off)[c0 >> p.log2N];
     }
     if (full) {
-        wide_chunk<M, CENTER, ZACC, true>(r, c0, lane, norm, ca, cb, a, b1);
+        wide_chunk<M, CENTER, ZACC, true>(r, strings[wave], c0, lane, norm, ca, cb, a, b1);
     } else if (c0 < p.d) {                                // ragged last wave
         const uint32_t count = (uint32_t)(p.d - c0);
         if (CENTER) load_chunks<1, false>(p.center + c0, lane, count, true, ca, cb);
         load_chunks<1, false>(p.x + c0, lane, count, true, a, b1);
-        wide_chunk<M, CENTER, ZACC, false>(r, c0, lane, norm, ca, cb, a, b1);
+        wide_chunk<M, CENTER, ZACC, false>(r, strings[wave], c0, lane, norm, ca, cb, a, b1);
     }
 }
 
