@@ -438,14 +438,16 @@ __device__ __forceinline__ void store_chunks(unsigned char* __restrict__ signs, 
 // Level strings of 512 consecutive coordinates for the widths that do not divide 32: the lanes' M bytes each meet in
 // LDS private to the wave and leave as consecutive 16-byte pieces.  words: the first of 16 * M, on any word.  mine: the
 // wave's kStringBytes of LDS.  Chunk by chunk and with the ordinary policy (two chunks at a time: d = 3.5 M, K = 8, s = 128,
-// bucket 8192 27.7 us, 25.7 one by one; non-temporal: d = 10 M, K = 8, s = 64, one bucket, gradient round 164 us, 157).
+// bucket 8192 27.7 us, 26.3 one by one; byte by byte: as
+// unaligned words d = 49 M, K = 8, s = 128, bucket 8192 336 us, 326 as bytes; non-temporal: d = 10 M, K = 8, s = 64, one bucket, gradient round 164 us, 157).
 template <int M>
 constexpr uint32_t kStringBytes = 32 % M == 0 ? 0 : kWaveSize * M;
 template <int M>
 __device__ __forceinline__ void store_levels_lds(unsigned char* mine, uint32_t* __restrict__ words, uint32_t lane, const uint32_t (&bits)[4]) {
     typedef uint32_t uvec4 __attribute__((ext_vector_type(4)));
     typedef uvec4 anywhere __attribute__((aligned(4)));
-    __builtin_memcpy(mine + lane * (uint32_t)M, bits, M);
+#pragma unroll
+    for (int j = 0; j < M; ++j) mine[lane * (uint32_t)M + j] = (unsigned char)(bits[j >> 2] >> (8 * (j & 3)));
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
