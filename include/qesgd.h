@@ -179,11 +179,10 @@ int qesgd_unpack_aggregate_update(const void* packed_slab, uint64_t packed_strid
  * followed by qesgd_unpack_aggregate_update, same arguments, same results bit for bit (the packed
  * blocks are written too).  Buckets are independent on the worker side (Sec. 3) and coordinates
  * on the server side (Alg. 3, server task), so one workgroup can own one tile of every worker and
- * of z: for a power-of-two bucket of 32..16384 coordinates, the L2 scale and a level width that
- * divides 32 the round is a single launch that never reads the packed codes back, and for a single
- * bucket or power-of-two buckets wider than 32768 (L2 scale) one launch behind those that find the
- * scales; every other shape, and many workers with a short vector, run the two calls one after the
- * other.  In the method the two halves run on different machines. */
+ * of z: for a power-of-two bucket of 32..16384 coordinates and the L2 scale the round can be a
+ * single launch that never reads the packed codes back, and for a single bucket or power-of-two
+ * buckets wider than 32768 (L2 scale) one launch behind those that find the scales; every other
+ * shape, and sizes at which two launches are faster, run the two calls one after the other.  In the method the two halves run on different machines. */
 int qesgd_round(const float* x_slab, uint64_t x_stride, const float* center,
                 uint64_t d, uint32_t s, uint64_t bucket, uint32_t norm_kind,
                 uint64_t seed, uint32_t round, uint32_t K,

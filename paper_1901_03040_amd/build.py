@@ -12,7 +12,9 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libqesgd.so")
 OBJDIR = os.path.join(HERE, "_build")
-SOURCES = ["qesgd_api.cpp", "qesgd_quantize.hip", "qesgd_aggregate.hip", "qesgd_fixed.hip", "qesgd_round.hip"]
+SOURCES = ["qesgd_api.cpp", "qesgd_quantize.hip", "qesgd_aggregate.hip", "qesgd_fixed.hip", "qesgd_round.hip",
+           "qesgd_round_1_2.hip", "qesgd_round_3_5.hip", "qesgd_round_6_7.hip",
+           "qesgd_round_4.hip", "qesgd_round_8.hip", "qesgd_round_16.hip"]
 PROBE_SRC = "bench_probe.hip"
 PROBE_LIB = os.path.join(HERE, "libqesgd_bench_probe.so")
 

@@ -94,37 +94,70 @@ int launch_aggregate(const Shape& sh, const AggregateArgs& a);
 // Wide buckets whose slot space equals coordinate space (a power of two, or a single bucket), L2 scale.
 bool dense_wide(const Shape& sh, uint32_t norm_kind);
 // One launch for a whole round (quantise K workers, sum, update) where the shape allows it:
-// power-of-two bucket of 32..16384 coordinates, L2 scale, level width dividing 32; or, behind the launches
-// that find the scales, a dense wide bucket with the L2 scale.
+// power-of-two bucket of 32..16384 coordinates, L2 scale; or, behind the launches that find the scales, a dense
+// wide bucket with the L2 scale.
 bool round_fused_covers(const Shape& sh, uint32_t norm_kind);
-// One launch or two.  One launch takes the workers of a tile one after the other, about 1 us each (2.4 us
-// with buckets of 4096 and more, whose waves meet at a barrier per worker), which only a chip full of
-// tiles hides; two launches spread tiles and workers over the chip at once.  Measured, one / two, whole round:
-//   from 1.5 M coordinates on       1.7 M, K = 16, bucket 512: 32.1 / 34.8 us; 1.7 M, K = 4, bucket 8192: 14.1 / 15.9;
-//                                   12 M, K = 16, bucket 8192: 183 / 187; 12 M, K = 8, bucket 16384: 126 / 129
-//     (with 8192 and 16384 two would be better up to about 10 M: 2.4 M, K = 8, bucket 8192 34.8 / 26.1; 5 M, K = 8,
-//     54 / 48; 1.7 M, K = 8, bucket 16384 31.5 / 22.4; not so with K = 1, 2: 2.4 M, K = 2, bucket 16384 14.2 / 17.4)
-//   below, up to 8 workers          1 M, K = 8, bucket 512: 11.0 / 14.6; 0.1 M, K = 8, bucket 64: 7.6 / 7.2
-//     up to 16 from 0.65 M (buckets up to 1024) or 1 M (2048) on, where there is no ragged tile, whose chain is longer
-//                                   1 M, K = 16, bucket 128: 16.5 / 22.6; 0.7 M, K = 12, bucket 512: 13.5 / 15.2;
-//                                   0.4 M, K = 12: 13.0 / 12.4; 1 M, K = 16, bucket 2048: 18.9 / 22.8; 0.7 M, K = 9,
-//                                   2048: 14.7 / 13.5; 1 M, K = 32, bucket 128: 47.5 / 37.6; ragged, 1 M, K = 16,
-//                                   bucket 512: 22.4 / 21.5, with a center 25.2 / 21.2
-//     up to 2 with 4096 and 8192    0.5 M, K = 1, bucket 8192: 5.7 / 6.9; 0.2 M, K = 8, 4096: 11.8 / 8.1
-//     none with 16384               0.5 M, K = 1: 9.3 / 8.3; 20 K, K = 1: 8.7 / 7.0; 0.5 M, K = 2: 12.8 / 8.5
-// Buckets of 32768 would need 300 registers per lane.
-// A wave that owns one chunk of every worker (buckets up to 4096, and wide ones) falls behind two launches where a
-// round no longer fits about 1.2 GB, unless the workers' side is the dearer for it: level widths of 8 and more, whose
-// codes cost the most to read back, or a center.  K = 16, 25 M, bucket 512: s = 4 415 / 388 us, s = 16 443 / 425, with a
-// center 426 / 482; s = 65536 577 / 634; bucket 4096, s = 256 465 / 492, with a center 484 / 600; one bucket, 138 M,
-// K = 4, s = 16 1298 / 1235.
-inline bool round_fused_pays(const Shape& sh, uint32_t K, bool center) {
-    const bool wide = sh.N > 32768, narrow = sh.N <= 4096 && sh.m < 8 && !center;
-    if ((wide || narrow) && 4u * (uint64_t)K * sh.d + update_bytes(sh, K) > (1250ull << 20)) return false;
-    if (sh.d >= (3u << 19)) return true;
-    const uint64_t tile = sh.N <= 1024 ? 1024 : sh.N;
-    if (sh.N <= 2048 && K <= 16 && sh.d >= (sh.N <= 1024 ? 5u << 17 : 15u << 16) && sh.d % tile == 0) return true;
-    return K <= (sh.N <= 2048 || wide ? 8u : sh.N <= 8192 ? 2u : 0u);
+// Tile of the one-launch round for buckets up to 16384.
+inline uint64_t round_tile(uint64_t N, uint32_t chunks) { return N > 2u * chunks * kChunk ? N : 2u * chunks * kChunk; }
+// One launch or two, and the chunks per wave of the one: 0 two launches, else 1 or 2 (always 2 from 8192 on; the
+// wide buckets' kernel has 1).  One launch takes the workers of a tile one after the other, about 1 us each (2.4 us with
+// buckets of 4096 and more, whose waves meet at a barrier per worker), which only a chip full of tiles hides; two
+// launches spread tiles and workers over the chip at once, and read the codes back.  Two sets of buffers in turn, us,
+// two launches / one.  "Bytes" are the K vectors', the packed blocks' and the update's; "odd" level widths are 3, 5, 6, 7,
+// which the two launches store and read the dearest.
+//   wide: up to 1250 MiB (138 M, K = 4, s = 16 1244 / 1320), from 1.5 M coordinates or up to 8 workers
+//   8192 and 16384, whose chain is the longest
+//     one generation of workgroups, K = 1, 2   0.5 M, K = 1, 8192 6.9 / 5.7; 1.5 M, K = 2, 8192 11.4 / 9.5; 2.4 M, K = 2,
+//                               16384 16.8 / 14.6; but 5000, K = 2, 8192 8.6 / 8.8; 1.5 M, 16384 11.6 / 13.7
+//     8 bits and more, K >= 8 from 8 M on, K >= 5 from 40 M on (K >= 16 with z_acc)   8 M, K = 8, 8192 89 / 81; 25 M, K = 16, 16384 480 / 468;
+//                               5 M, K = 8 56 / 56; but 25 M, K = 4 171 / 171; 12 M, K = 8, 16384, z_acc 143 / 145
+//     4 bits, K >= 16, 8192, from 20 M on      25 M 435 / 412; but 16384 430 / 443
+//     odd, K >= 4, from 10 M on (8192 alone with z_acc)   12 M, K = 8, s = 128 137 / 124; 25 M, K = 4, s = 32, 16384 185 / 175;
+//                               but 5 M, K = 4, s = 32 36 / 41; 25 M, K = 8, s = 32, 16384, z_acc 320 / 346
+//     center, K >= 8 (8 bits, 8192: K >= 4), from 8 M on   12 M, K = 16, s = 4 231 / 203; 12 M, K = 4, s = 256 96 / 90, s = 4 80 / 86
+//   up to 4096, below 1.5 M
+//     whole tiles, from 0.65 M on (2048, not odd: 0.98 M; 4096: odd alone), up to 16 workers
+//                               0.65 M, K = 16, s = 32, 128 21.5 / 18.4; 1 M, K = 16, bucket 128 22.6 / 16.5; 0.7 M, K = 9,
+//                               2048 13.5 / 14.7; 1 M, K = 32, bucket 128 37.6 / 47.5
+//     up to 5 workers           256, K = 5, bucket 128 8.6 / 7.3; 0.1 M, K = 5, 2048 8.7 / 8.6, K = 6 8.8 / 9.5; 0.3 M, K = 8, 512 8.8 / 10.5
+//     8 up to 1024 with whole tiles, not odd, no z_acc   47104, K = 8, s = 4, bucket 128 7.7 / 7.4, with a ragged tile 7.7 / 8.7
+//     8 from 0.9 M, 12 from 1.25 M on   1 M, K = 8, 512 15.0 / 14.4, K = 12 18.1 / 19.2; 1.3 M, K = 12, 512 20.8 / 19.5
+//     with 4096 2 workers, 4 from 0.9 M on   0.4 M, K = 4 8.5 / 9.5; 1 M, K = 4 11.5 / 9.7
+//   up to 4096, from 1.5 M on
+//     odd, but not K = 1, 2 beyond 1000 MiB   12 M, K = 8, s = 128, 512 133 / 115; 50 M, K = 16, s = 8, 512 935 / 845; 50 M, K = 2, s = 8 238 / 247
+//     up to 950 MiB, 1250 with 1 and 2 bits, 1100 with a center   25 M, K = 2, s = 16 122 / 109; 12 M, K = 16, s = 4 184 / 177;
+//                               25 M, K = 2, s = 256 126 / 127; 12 M, K = 16, s = 16 198 / 210
+//     beyond, two chunks (one / two): from 8 bits on with K * m >= 32, with 4 bits from 12 workers on, and with a center
+//                               25 M, K = 16, s = 256, 512 503 / 505 / 467; 50 M, K = 8, s = 256, 256 575 / 563 / 536; 25 M, K = 16,
+//                               s = 16, 256 430 / 460 / 418; center, 25 M, K = 16, s = 256 617 / 521 / 485; but 25 M, K = 8, s = 16
+//                               238 / 261 / 248; 50 M, K = 2, s = 256 242 / 254 / 249; 12 M, K = 8, s = 4 110 / 101 / 114
+//     center with 1 and 2 bits: one chunk      25 M, K = 16, s = 4 509 / 449
+inline uint32_t round_chunks(const Shape& sh, uint32_t K, bool center, bool z_acc) {
+    const uint64_t bytes = 4u * (uint64_t)K * sh.d + update_bytes(sh, K), mib = bytes >> 20;
+    const uint64_t M = 1000000;
+    const bool odd = 32u % sh.m != 0u;
+    if (sh.N > kMaxSinglePassBucket) return bytes <= (1250ull << 20) && (sh.d >= (3u << 19) || K <= 8) ? 1 : 0;
+    if (sh.N > 4096) {
+        const bool narrow = sh.N == 8192;
+        bool pays;
+        if (center) pays = sh.d >= 8 * M && (K >= 8 || (K >= 4 && sh.m >= 8 && narrow));
+        else if (odd) pays = sh.d >= 10 * M && K >= 4 && (narrow || !z_acc);
+        else if (sh.m >= 8) pays = sh.d >= 8 * M && K >= (z_acc ? 16u : sh.d >= 40 * M ? 5u : 8u);
+        else pays = sh.m == 4 && sh.d >= 20 * M && K >= 16 && narrow;
+        const bool one_generation = K <= 2 && sh.d <= 256u * sh.N && sh.d >= (narrow ? (K - 1u) * 650000u : 1800000u);
+        return pays || one_generation ? 2 : 0;
+    }
+    if (sh.d < (3u << 19)) {
+        const uint64_t tile = round_tile(sh.N, 1);
+        if ((odd || sh.N <= 2048) && K <= 16 && sh.d % tile == 0 && sh.d >= (odd || sh.N <= 1024 ? 5u << 17 : 15u << 16)) return 1;
+        if (sh.N == 4096) return K <= (sh.d < 900000 ? 2u : 4u) ? 1 : 0;
+        if (sh.N <= 1024 && !odd && !z_acc && K <= 8 && sh.d % tile == 0) return 1;
+        return K <= (sh.d < 900000 ? 5u : sh.d < 1250000 ? 8u : 12u) ? 1 : 0;
+    }
+    if (odd) return K <= 2 && mib > 1000 ? 0 : 1;
+    if (mib <= (sh.m < 4 ? 1250u : center ? 1100u : 950u)) return 1;
+    if (center) return sh.m < 4 ? 1 : 2;
+    return sh.m >= 4 && K * sh.m >= (sh.m == 4 ? 48u : 32u) ? 2 : 0;
 }
 int launch_round_fused(const Shape& sh, const QuantizeArgs& a, const AggregateArgs& g);
 int launch_apply_update(const float* w, const float* zbar, float* u, float* zsum, uint64_t d,

@@ -673,6 +673,7 @@ struct FastCtx {
     uint32_t lane, wave, worker, round, key0, key1;
     float smax;
     bool codes_cached;
+    unsigned char* string;       // kStringBytes<M> of LDS that are the wave's (level widths 3, 5, 6, 7)
 };
 
 // One tile: bucket totals, scales, variates, rounding, packing, stores.  ACC: the dequantised codes are also
@@ -732,9 +733,12 @@ __device__ __forceinline__ void process_tile(const FastCtx& cx, float (&v)[G::CH
             const uint32_t rest = count_from(count, idx * kLaneElems);
             store_codes<M>(reinterpret_cast<uint32_t*>(cx.signs), reinterpret_cast<uint32_t*>(cx.levels),
                            (g0 + idx) * kLaneElems, rest < 8u ? rest : 8u, cx.lane, sign_byte[c], bits[c]);
+        } else if constexpr (32 % M != 0) {
+            store_whole<M>(cx.string, cx.signs, cx.levels, (g0 + idx - cx.lane) * kLaneElems, cx.lane, cx.codes_cached, sign_byte[c], bits[c]);
         }
     }
-    if (FULL) store_chunks<M, CH>(signs, levels, cx.wave * (uint32_t)CH * kWaveSize + cx.lane, cx.codes_cached, sign_byte, bits);
+    if constexpr (FULL && 32 % M == 0)
+        store_chunks<M, CH>(signs, levels, cx.wave * (uint32_t)CH * kWaveSize + cx.lane, cx.codes_cached, sign_byte, bits);
 }
 
 }  // namespace

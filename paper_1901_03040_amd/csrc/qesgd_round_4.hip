@@ -1,0 +1,6 @@
+// The round kernels for level widths of 4 bits.
+#include "qesgd_round_device.h"
+
+namespace qesgd {
+template void launch_round<4>(const RParams&, uint32_t, uint32_t, hipStream_t);
+}  // namespace qesgd

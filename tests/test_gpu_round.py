@@ -71,7 +71,7 @@ def test_one_launch_shapes_equal_two_calls(B, log2n, s, K):
 @pytest.mark.parametrize("s", [2, 16, 256])
 @pytest.mark.parametrize("d,K", [(1_572_864, 3), (1_572_863, 9), (1_600_037, 16), (4_800_000, 3)])
 def test_both_sides_of_the_one_launch_rule(B, bucket, s, d, K):
-    """All these buckets take one launch from 1.5 M coordinates on, many workers with short vectors two.  The
+    """Buckets up to 4096 take one launch from 1.5 M coordinates on, many workers with short vectors two.  The
     vectors of (1_600_037, 16) are beyond the ordinary cache policy.  (Buckets of 32768 never take one launch.)"""
     g = torch.Generator(device="cuda").manual_seed(d + K)
     slab = torch.randn(K, (d + 63) // 64 * 64, generator=g, device="cuda") * 1e-3
@@ -108,7 +108,7 @@ def test_center_and_optional_outputs(B, d, bucket, s, K):
 @pytest.mark.parametrize("d,bucket,s,K,norm_kind", [
     (50_000, 96, 16, 3, 0),          # bucket not a power of two
     (50_000, 512, 16, 3, 1),         # max norm
-    (50_000, 512, 8, 3, 0),          # level width that does not divide a word
+    (50_000, 512, 8, 3, 0),          # level width that does not divide a word (takes one launch)
     (150_000, 65_536, 4, 3, 1),      # max norm, wide bucket (needs the workspace)
     (150_000, 48_000, 4, 3, 0),      # wide bucket, not a power of two
     (150_000, 65_536, 4, 3, 0),      # the wide bucket that does take one launch, behind those that find the scales
