@@ -44,8 +44,8 @@ namespace {
 // Bound by vector issue (d = 7.3 M, K = 5, s = 32, bucket 3008, max norm: 339 vector instructions per 1024 coordinates,
 // 428 and 1.5 times the scalar ones where every wave guarded itself).  Guarded / this, quantiser alone:
 //   d = 7.3 M, K = 5, s = 32, bucket 3008, max    48.5 -> 40.7 us
-//   d = 20 M, K = 8, s = 4, bucket 2400, max      BENCH_B
-//   d = 15 M, K = 5, s = 4, bucket 23648, max     BENCH_C
+//   d = 20 M, K = 8, s = 4, bucket 2400, max      174 -> 141 us
+//   d = 15 M, K = 5, s = 4, bucket 23648, max     84.7 -> 60.0 us
 //   d = 30 M, K = 8, s = 64, bucket 32768         271 -> 214 us
 enum Mode { kBuckets, kNarrow, kPre };
 template <int M, int CH, int KIND, bool CENTER, Mode MODE>
@@ -117,10 +117,15 @@ __global__ void __launch_bounds__(256) k_quantize_pack_lanes(const QParams p) {
     load_lanes<CH, CENTER>(p, k, span, v);
     unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
     float* __restrict__ norms = reinterpret_cast<float*>(out + p.norms_off);
+    Scale scale[CH];                                      // of all chunks before the first store
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         const float tot = lane_butterfly<KIND>(lane_tree<KIND>(v[c]), (uint32_t)(N / kLaneElems));
-        Scale sc = scale_of_total<M, KIND>(span[c].nvalid || N == kChunk ? tot : 1.0f);      // (see kNarrow)
+        scale[c] = scale_of_total<M, KIND>(span[c].nvalid || N == kChunk ? tot : 1.0f);      // (see kNarrow)
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        Scale sc = scale[c];
         if (span[c].opens_bucket) norms[span[c].bucket] = sc.norm;
         // a chunk opens a bucket: if that holds no coordinate, the vector has ended
         if (__builtin_amdgcn_readfirstlane(span[c].nvalid) == 0u) continue;
@@ -316,9 +321,16 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
     unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
     float* __restrict__ norms = reinterpret_cast<float*>(out + p.norms_off);
     const uint64_t b = (uint64_t)t * kPartialTile >> p.log2N;
-    const WaveSpan s = wave_span_dense<2>(p, (uint64_t)t * 4u + wave);
+    const bool full = t < p.full_tiles;                   // one condition for the workgroup, no other for its waves
+    const uint64_t w0 = (uint64_t)t * kPartialTile + wave * (2u * kChunk);
+    WaveSpan s{};
     float v[2][8];
-    load_span<2, CENTER>(p, k, s, lane, v);
+    if (full) {
+        load_tile<2, CENTER>(p.x + (uint64_t)k * p.x_stride + w0, p.center + w0, lane, p.x_cached, v);
+    } else {                                              // the ragged last tile of the worker (at most one)
+        s = wave_span_dense<2>(p, (uint64_t)t * 4u + wave);
+        load_span<2, CENTER>(p, k, s, lane, v);
+    }
     Scale sc;
     if (p.merged) {
         const uint32_t P = 1u << (p.log2N - 12u);
@@ -330,7 +342,8 @@ __global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p)
         sc = scale_of_norm<M>(norms[b]);
     }
     const Scale both[2] = {sc, sc};
-    encode_span<M, 2, QESGD_NORM_L2>(p, k, s, lane, strings[wave], v, both);
+    if (full) encode_whole<M, 2, QESGD_NORM_L2>(p, k, w0, lane, strings[wave], v, both);
+    else encode_span<M, 2, QESGD_NORM_L2>(p, k, s, lane, strings[wave], v, both);
 }
 
 // ---------------------------------------------------------------------------

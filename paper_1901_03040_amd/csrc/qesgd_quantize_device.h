@@ -540,36 +540,51 @@ __device__ __forceinline__ void load_span(const QParams& p, uint32_t k, const Wa
     else load_tile<CH, CENTER, false>(x, p.center + s.i0, lane, true, v, s.mine);
 }
 
-// Their codes.  string: kStringBytes<M> of LDS that are the wave's.
+// The codes of CH x 512 coordinates that all exist, from coordinate i0 on, whose group numbers share their high word.
+// string: kStringBytes<M> of LDS that are the wave's.
 template <int M, int CH, int KIND>
-__device__ __forceinline__ void encode_span(const QParams& p, uint32_t k, const WaveSpan& s, uint32_t lane, unsigned char* string,
-                                            const float (&v)[CH][8], const Scale (&sc)[CH]) {
+__device__ __forceinline__ void encode_whole(const QParams& p, uint32_t k, uint64_t i0, uint32_t lane, unsigned char* string,
+                                             const float (&v)[CH][8], const Scale (&sc)[CH]) {
     unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
-    const bool whole = s.mine == CH * kChunk;
+    const uint64_t g0 = i0 / kLaneElems;
     uint32_t sign_byte[CH], bits[CH][4];
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        if (!whole && s.mine <= (uint32_t)c * kChunk) break;                     // no coordinate left
-        const uint64_t g = s.i0 / kLaneElems + (uint32_t)c * kWaveSize;
-        const uint32_t low = (uint32_t)g + lane, high = (uint32_t)(g >> 32);
         uint32_t rnd[4];
-        // the group number's high word is the same for the wave, and scalar, unless the low one wraps among its lanes
-        if ((uint32_t)g <= 0xFFFFFFC0u) philox4x32_10(low, high, p.worker0 + k, p.round, p.key0, p.key1, rnd);
-        else philox4x32_10(low, high + (low < (uint32_t)g ? 1u : 0u), p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        philox4x32_10((uint32_t)g0 + (uint32_t)c * kWaveSize + lane, (uint32_t)(g0 >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
         Scale own = sc[c];
         if (KIND != QESGD_NORM_L2) own.direct = own.direct && wave_all(no_nan<KIND>(v[c]));
         round_and_pack<M>(v[c], rnd, own, sign_byte[c], bits[c]);
-        if (!whole) {
-            const uint32_t at = (uint32_t)c * kChunk + lane * kLaneElems, rest = count_from(s.mine, at);
-            store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off), s.i0 + at,
-                           rest < 8u ? rest : 8u, lane, sign_byte[c], bits[c]);
-        } else if constexpr (32 % M != 0) {
-            store_whole<M>(string, out + p.signs_off, out + p.levels_off, s.i0 + (uint32_t)c * kChunk, lane, p.codes_cached, sign_byte[c], bits[c]);
-        }
+        if constexpr (32 % M != 0)
+            store_whole<M>(string, out + p.signs_off, out + p.levels_off, i0 + (uint32_t)c * kChunk, lane, p.codes_cached, sign_byte[c], bits[c]);
     }
+    if constexpr (32 % M == 0) store_chunks<M, CH>(out + p.signs_off + g0, out + p.levels_off + g0 * M, lane, p.codes_cached, sign_byte, bits);
+}
+
+// The codes of a span.
+template <int M, int CH, int KIND>
+__device__ __forceinline__ void encode_span(const QParams& p, uint32_t k, const WaveSpan& s, uint32_t lane, unsigned char* string,
+                                            const float (&v)[CH][8], const Scale (&sc)[CH]) {
     const uint64_t g0 = s.i0 / kLaneElems;
-    if constexpr (32 % M == 0)
-        if (whole) store_chunks<M, CH>(out + p.signs_off + g0, out + p.levels_off + g0 * M, lane, p.codes_cached, sign_byte, bits);
+    if (s.mine == CH * kChunk && (uint32_t)g0 <= 0u - (uint32_t)CH * kWaveSize) {
+        encode_whole<M, CH, KIND>(p, k, s.i0, lane, string, v, sc);
+        return;
+    }
+    unsigned char* __restrict__ out = p.packed + (uint64_t)k * p.packed_stride;
+    uint32_t sign_byte[CH], bits[CH][4];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        if (s.mine <= (uint32_t)c * kChunk) break;                               // no coordinate left
+        const uint64_t g = g0 + (uint32_t)c * kWaveSize + lane;
+        uint32_t rnd[4];
+        philox4x32_10((uint32_t)g, (uint32_t)(g >> 32), p.worker0 + k, p.round, p.key0, p.key1, rnd);
+        Scale own = sc[c];
+        if (KIND != QESGD_NORM_L2) own.direct = own.direct && wave_all(no_nan<KIND>(v[c]));
+        round_and_pack<M>(v[c], rnd, own, sign_byte[c], bits[c]);
+        const uint32_t at = (uint32_t)c * kChunk + lane * kLaneElems, rest = count_from(s.mine, at);
+        store_codes<M>(reinterpret_cast<uint32_t*>(out + p.signs_off), reinterpret_cast<uint32_t*>(out + p.levels_off), s.i0 + at,
+                       rest < 8u ? rest : 8u, lane, sign_byte[c], bits[c]);
+    }
 }
 
 // ---------------------------------------------------------------------------
