@@ -139,6 +139,15 @@ __global__ void __launch_bounds__(256) k_quantize_pack_lanes(const QParams p) {
     }
 }
 
+// At most six waves per SIMD for the kernels that stream whole tiles: their registers would allow eight, which are more
+// streams than the memory takes at full rate.  Quantiser, eight / six / four waves:
+//   d = 138 M, K = 8, s = 2, bucket 4096          800 / 780 / 846 us
+//   d = 60 M, K = 8, s = 4, bucket 2048           335 / 326 / 345 us
+//   d = 25.6 M, K = 16, s = 256, one bucket       551 / 533 / 570 us
+//   d = 25.6 M, K = 16, s = 256, bucket 8192      328 / 330 / 329 us
+//   d = 1 M, K = 8, s = 16, bucket 512            9.0 / 8.7 / 8.8 us
+#define kSixWaves __attribute__((amdgpu_waves_per_eu(1, 6)))
+
 // One tile per workgroup.  (Walking several tiles per workgroup with the next tile's loads in flight was
 // measured and is slower: the packed stores of a long-lived workgroup spread out in time and the mixed
 // read/write stream to HBM loses more than the prefetch gains.)
@@ -150,7 +159,7 @@ __global__ void __launch_bounds__(256) k_quantize_pack_lanes(const QParams p) {
 //   d = 60 M, K = 8, s = 4, bucket 2048      364 -> 341 us = 6.2 TB/s
 //   d = 60 M, K = 8, s = 256, bucket 1024    402 -> 396 us = 6.2 TB/s
 template <int M, int LOG2N, bool CENTER>
-__global__ void __launch_bounds__((Geo<M, LOG2N, CENTER>::NW * 64)) k_quantize_pack_fast(const QParams p) {
+__global__ void __launch_bounds__((Geo<M, LOG2N, CENTER>::NW * 64)) kSixWaves k_quantize_pack_fast(const QParams p) {
     constexpr int CH = Geo<M, LOG2N, CENTER>::CH;
     constexpr uint32_t TILE = Geo<M, LOG2N, CENTER>::TILE;
     __shared__ float sm[32];
@@ -290,7 +299,7 @@ __device__ __forceinline__ void partial_tile(const QParams& p, uint32_t k, uint3
 // never straddles two such buckets, so the scale is one scalar per workgroup.
 // Both walk (tiles, workers) in the same order, so that a vector that fits the L2s is found in the same one.
 template <bool CENTER>
-__global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
+__global__ void __launch_bounds__(256) kSixWaves k_tile_partials_fast(const QParams p) {
     constexpr int KIND = QESGD_NORM_L2;
     __shared__ float sm[4];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
@@ -313,7 +322,7 @@ __global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
 // merged: every wave finishes its bucket's tree by itself while its coordinates are on their way, which
 // saves the launch between the passes; the bucket's first tile writes the scale.
 template <int M, bool CENTER>
-__global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p) {
+__global__ void __launch_bounds__(256) kSixWaves k_quantize_pack_pre_fast(const QParams p) {
     __shared__ __align__(16) unsigned char strings[4][kStringBytes<M> + 16];
     const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t k = blockIdx.y;
