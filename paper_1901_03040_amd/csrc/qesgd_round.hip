@@ -1,5 +1,5 @@
 // Launches of a whole round: the scales of wide buckets where there are any, then the round (qesgd_round_device.h).
-#include "qesgd_round_device.h"
+#include "qesgd_round.h"
 
 namespace qesgd {
 

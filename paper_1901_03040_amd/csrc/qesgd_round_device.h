@@ -29,25 +29,9 @@
 #pragma once
 
 #include "qesgd_aggregate_device.h"
-#include "qesgd_quantize_device.h"
+#include "qesgd_round.h"
 
 namespace qesgd {
-
-struct RParams {
-    QParams q;
-    const float* w;
-    float* zbar;
-    float* u;
-    float* zsum;
-    float* z_acc;    // nullable (wide buckets only): z_acc += the mean
-    float rcpK;      // exact 1/K when K is a power of two, else 0
-    uint32_t K;
-};
-
-// Queues the round's last launch for level width M: chunks of a wave (0: the wide buckets' kernel), workgroups.
-// Instantiated in qesgd_round_*.hip, a few widths each, since they take long to compile.
-template <int M>
-void launch_round(const RParams& r, uint32_t chunks, uint32_t blocks, hipStream_t st);
 
 namespace {
 
@@ -166,8 +150,7 @@ __global__ void __launch_bounds__((RoundGeo<LOG2N, CH>::NW * 64)) k_round_fused(
 //   d = 853 K, K = 8, s = 256, one bucket     31.0 -> 21.3 us (partial sums, this; the chain of 8 workers)
 //   d = 30 M, K = 4, s = 8, one bucket         378 -> 288 us
 // (beyond about 1.2 GB, d = 25.6 M, K = 16 among them, the round takes two launches: see round_chunks)
-// One wave per workgroup would finish every scale by itself; four share that work.
-constexpr uint32_t kWideWaves = 4;
+// One wave per workgroup would finish every scale by itself; four (kWideWaves) share that work.
 
 // string: kStringBytes<M> of LDS that are the wave's.  norm: lane k holds worker k's (lanes from K on: 1).  ca, cb, a, b: the center's and the first worker's.
 template <int M, bool CENTER, bool ZACC, bool FULL>
