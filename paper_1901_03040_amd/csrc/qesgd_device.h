@@ -123,10 +123,11 @@ __device__ __forceinline__ void lane_to_halves(const float (&v)[8], vec4& a, vec
 
 // The first `count` of those coordinates: a float4 that is not wholly inside is taken element by element
 // (stores leave the rest of it alone, loads give 0 there).
+template <bool CACHED>
 __device__ __forceinline__ vec4 load_part(const float* __restrict__ p, uint32_t at, uint32_t count) {
     vec4 r = {0.0f, 0.0f, 0.0f, 0.0f};
     if (at + 4u <= count) {
-        r = load_cached(p + at);
+        r = CACHED ? load_cached(p + at) : load_stream(p + at);
     } else {
 #pragma unroll
         for (uint32_t e = 0; e < 3; ++e)
@@ -145,13 +146,13 @@ __device__ __forceinline__ void store_part(float* __restrict__ p, uint32_t at, u
 }
 // CH x 512 coordinates of a vector from p on, one float4 of each half chunk per lane; at the ragged end of the
 // vector (FULL = false) the first `count`, the rest 0, with the ordinary policy.
-template <int CH>
+template <int CH, bool CACHED = true>
 __device__ __forceinline__ void load_ragged(const float* __restrict__ p, uint32_t lane, uint32_t count, vec4 (&a)[CH], vec4 (&b)[CH]) {
     const uint32_t h = half_offset(lane);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
-        a[c] = load_part(p, h + c * kChunk, count);
-        b[c] = load_part(p, h + c * kChunk + kChunk / 2, count);
+        a[c] = load_part<CACHED>(p, h + c * kChunk, count);
+        b[c] = load_part<CACHED>(p, h + c * kChunk + kChunk / 2, count);
     }
 }
 template <int CH, bool FULL>

@@ -606,6 +606,14 @@ QParams quantize_params(const Shape& sh, const QuantizeArgs& a) {
     p.group_workers = a.K;
     p.x_cached = input_cached(sh, a.K);
     p.codes_cached = a.K * sh.lay.payload_bytes <= kCachedCodeBytes;
+    // The ragged waves of buckets that are no power of two are up to all of the input, so they follow the policy of the
+    // whole ones: an ordinary stream drives the center out of the memory-side cache, from which the second worker on
+    // reads it (quantiser, ordinary / this: d = 60 M, K = 8, s = 4, with a center, bucket 992 707 / 548 us, 2016 682 / 554, 3008
+    // 650 / 556; without one d = 25.6 M, K = 4, s = 256, bucket 2016 88.7 / 82.0, 992 88.7 / 85.3).
+    // But with codes that go out non-temporally, no center and a ragged wave behind each one to three whole ones the
+    // ordinary policy is better (non-temporal / this: K = 16, d = 25.6 M, s = 256, bucket 2016 396 / 351 us, 3008 381 / 350; K = 8,
+    // d = 60 M, s = 16, 2016 417 / 379; wider, s = 16, 5024 372 / 370; all ragged, s = 16, 992 375 / 392).
+    p.ragged_cached = p.x_cached || (!p.center && !p.codes_cached && sh.N > 2 * kChunk && sh.N <= 4096);
     return p;
 }
 

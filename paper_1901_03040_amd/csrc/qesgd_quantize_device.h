@@ -35,7 +35,8 @@ struct QParams {
     uint32_t round;
     uint32_t worker0;
     float smax;
-    bool x_cached;               // read the vectors with the ordinary cache policy
+    bool x_cached;               // read the vectors with the ordinary cache policy ...
+    bool ragged_cached;          // ... where a wave of the general kernels is ragged
     bool codes_cached;           // write the level planes with the ordinary cache policy
 };
 
@@ -536,8 +537,28 @@ __device__ __forceinline__ WaveSpan wave_span_dense(const QParams& p, uint64_t u
 template <int CH, bool CENTER>
 __device__ __forceinline__ void load_span(const QParams& p, uint32_t k, const WaveSpan& s, uint32_t lane, float (&v)[CH][8]) {
     const float* __restrict__ x = p.x + (uint64_t)k * p.x_stride + s.i0;
-    if (s.mine == CH * kChunk) load_tile<CH, CENTER>(x, p.center + s.i0, lane, p.x_cached, v);
-    else load_tile<CH, CENTER, false>(x, p.center + s.i0, lane, true, v, s.mine);
+    const float* __restrict__ center = p.center + s.i0;
+    if (s.mine == CH * kChunk) {
+        load_tile<CH, CENTER>(x, center, lane, p.x_cached, v);
+        return;
+    }
+    vec4 a[CH], b[CH], ca[CH], cb[CH];
+    if (p.ragged_cached) {
+        asm volatile("; cached");                         // keeps the arms apart (see load_halves)
+        load_ragged<CH, true>(x, lane, s.mine, a, b);
+        asm volatile("; cached end");
+    } else {
+        load_ragged<CH, false>(x, lane, s.mine, a, b);
+    }
+    if (CENTER) load_ragged<CH, true>(center, lane, s.mine, ca, cb);
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        if (CENTER) {
+            a[c] -= ca[c];
+            b[c] -= cb[c];
+        }
+        halves_to_lane(a[c], b[c], v[c]);
+    }
 }
 
 // The codes of CH x 512 coordinates that all exist, from coordinate i0 on, whose group numbers share their high word.

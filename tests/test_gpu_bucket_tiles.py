@@ -39,3 +39,24 @@ def test_edges_of_waves(oracle, B, bucket, last, s, norm_kind, with_center):
         for end, upto in ((lay.norms_off + 4 * lay.n_buckets, lay.signs_off), (lay.signs_off + 4 * lay.sign_words, lay.levels_off),
                           (lay.levels_off + 4 * lay.level_words, lay.bytes_per_worker)):
             assert bool((packed[k, end:upto] == 0xA5).all()), (k, "a gap between planes was written")
+
+
+@pytest.mark.parametrize("bucket,s,norm_kind,K,with_center", [
+    (992, 4, 0, 3, True), (992, 256, 1, 3, False), (2016, 128, 0, 3, True), (2016, 65536, 0, 10, False), (3008, 65536, 1, 10, False),
+    (5024, 16, 0, 3, True), (12_000, 32, 1, 3, True), (20_000, 8, 0, 3, True), (48_000, 64, 0, 3, False), (48_000, 4, 1, 3, True)])
+def test_streams_beyond_the_caches(B, bucket, s, norm_kind, K, with_center):
+    """More than 96 MiB of input (and with 10 workers 160 MiB of codes) against one call per worker, which stays below:
+    the policy of the streams and the order of the workers change no bit."""
+    d = 8_400_003
+    g = torch.Generator(device="cuda").manual_seed(bucket + s)
+    stride = (d + 3) // 4 * 4
+    x = torch.randn(K, stride, generator=g, device="cuda") * 1e-2
+    center = torch.randn(d, generator=g, device="cuda") * 1e-2 if with_center else None
+    lay = B.qesgd_layout_query(d, s, bucket)
+    wsb = B.qesgd_workspace_bytes(d, s, bucket, K)
+    ws = torch.empty(wsb // 4, device="cuda") if wsb else None
+    packed, want = B.alloc_packed(lay, K).fill_(0xA5), B.alloc_packed(lay, K).fill_(0xA5)
+    B.qesgd_quantize_pack_batched(x, stride, center, d, s, bucket, norm_kind, 77, 5, K, packed, packed.stride(0), ws)
+    for k in range(K):
+        B.qesgd_quantize_pack(x[k], center, d, s, bucket, norm_kind, 77, 5, k, want[k], ws)
+    assert torch.equal(packed, want)
