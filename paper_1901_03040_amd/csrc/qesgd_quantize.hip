@@ -35,6 +35,13 @@ static __device__ __align__(256) float scratch[qesgd::kStaticScratchFloats];
 namespace qesgd {
 namespace {
 
+// Worker and tile of a workgroup in the grid of center_grid.  All workers read the same `center`: the K workgroups of one
+// tile get ids 8 apart, so they run on one XCD one after the other, and all but the first find the tile of `center` in its L2.
+__device__ __forceinline__ void center_order(uint32_t& k, uint32_t& t) {
+    k = blockIdx.x >> 3;
+    t = (blockIdx.z * gridDim.y + blockIdx.y) * 8u + (blockIdx.x & 7u);
+}
+
 // Buckets that the fast kernel does not take but whose coordinates a wave finds side by side: the max norm, level widths
 // 3, 5, 6 and 7, sizes that are no power of two.  What depends on the size is scalar work, so one kernel serves all sizes.
 //   kBuckets  padded to 1024 .. 32768: a bucket is a few waves, whose totals meet in LDS; a workgroup holds whole buckets
@@ -47,13 +54,22 @@ namespace {
 //   d = 20 M, K = 8, s = 4, bucket 2400, max      174 -> 141 us
 //   d = 15 M, K = 5, s = 4, bucket 23648, max     84.7 -> 60.0 us
 //   d = 30 M, K = 8, s = 64, bucket 32768         271 -> 214 us
+// With a center the workers of a tile follow one another (center_order); quantiser, all tiles of a worker first / this:
+//   d = 60 M, K = 8, s = 16, bucket 992           577 -> 478 us
+//   d = 60 M, K = 8, s = 16, bucket 12000         548 -> 534 us
+//   d = 60 M, K = 8, s = 16, bucket 224           773 -> 497 us (lane by lane)
 enum Mode { kBuckets, kNarrow, kPre };
 template <int M, int CH, int KIND, bool CENTER, Mode MODE>
 __global__ void __launch_bounds__(MODE == kBuckets ? 1024 : 256) k_quantize_pack_bucket(const QParams p) {
     __shared__ float sm[16];
     extern __shared__ __align__(16) unsigned char strings[];
-    const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6), k = blockIdx.y;
-    const uint64_t unit = ((uint64_t)xcd_tile(blockIdx.x, gridDim.x, p.xcd_group) << p.log2_waves) + wave;
+    const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint32_t k = blockIdx.y, t = blockIdx.x;
+    if (CENTER) {
+        center_order(k, t);
+        if (t >= p.tiles) return;
+    }
+    const uint64_t unit = ((uint64_t)xcd_tile(t, p.tiles, p.xcd_group) << p.log2_waves) + wave;
     const uint32_t lg = p.log2N - (CH == 4 ? 11u : 10u);                         // log2 of a bucket's waves
     static_assert(CH == 2 || CH == 4, "");
     const WaveSpan s = MODE == kNarrow ? wave_span_dense<CH>(p, unit) : wave_span<CH>(p, unit, lg);
@@ -107,9 +123,14 @@ __global__ void __launch_bounds__(MODE == kBuckets ? 1024 : 256) k_quantize_pack
 template <int M, int KIND, bool CENTER>
 __global__ void __launch_bounds__(256) k_quantize_pack_lanes(const QParams p) {
     constexpr int CH = 2;
-    const uint32_t lane = threadIdx.x & 63u, k = blockIdx.y;
+    const uint32_t lane = threadIdx.x & 63u;
     const uint64_t N = 1ull << p.log2N;
-    const uint64_t slot0 = ((uint64_t)xcd_tile(blockIdx.x, gridDim.x, p.xcd_group) * 4u + (threadIdx.x >> 6)) * (CH * kChunk);
+    uint32_t k = blockIdx.y, t = blockIdx.x;
+    if (CENTER) {
+        center_order(k, t);
+        if (t >= p.tiles) return;
+    }
+    const uint64_t slot0 = ((uint64_t)xcd_tile(t, p.tiles, p.xcd_group) * 4u + (threadIdx.x >> 6)) * (CH * kChunk);
     LaneSpan span[CH];
     float v[CH][8];
 #pragma unroll
@@ -166,16 +187,10 @@ __global__ void __launch_bounds__((Geo<M, LOG2N, CENTER>::NW * 64)) kSixWaves k_
 
     // Grid: (tiles, workers), so that nothing has to be divided; with a center (8 * workers, y, z).
     const uint32_t tiles = p.full_tiles + p.tail_tiles;
-    uint32_t k, t;
+    uint32_t k = blockIdx.y, t = blockIdx.x;
     if (CENTER) {
-        // All workers read the same `center`: the K workgroups of one tile get ids 8 apart, so they run
-        // on one XCD one after the other, and all but the first find the tile of `center` in its L2.
-        k = blockIdx.x >> 3;
-        t = (blockIdx.z * gridDim.y + blockIdx.y) * 8u + (blockIdx.x & 7u);
+        center_order(k, t);
         if (t >= tiles) return;
-    } else {
-        k = blockIdx.y;
-        t = blockIdx.x;
     }
     t = xcd_tile(t, tiles, p.xcd_group);
     const float* __restrict__ xk = p.x + (uint64_t)k * p.x_stride;
@@ -437,9 +452,15 @@ __global__ void __launch_bounds__(1024) k_finish_norms(const QParams p, uint64_t
 // ---------------------------------------------------------------------------
 // Launch plumbing.
 // ---------------------------------------------------------------------------
+dim3 center_grid(uint32_t tiles, uint32_t workers) {
+    const uint32_t octets = (tiles + 7u) / 8u, gz = (octets + 65534u) / 65535u, gy = (octets + gz - 1u) / gz;
+    return dim3(8u * workers, gy, gz);
+}
+
 // CH, MODE: of k_quantize_pack_bucket; CH = 0: k_quantize_pack_lanes.
 template <int M, int CH, Mode MODE, int KIND, bool CENTER>
 void launch_general_one(const QParams& p, dim3 grid, dim3 block, hipStream_t st) {
+    if (CENTER) grid = center_grid(grid.x, grid.y);
     if constexpr (CH == 0) hipLaunchKernelGGL((k_quantize_pack_lanes<M, KIND, CENTER>), grid, block, 0, st, p);
     else hipLaunchKernelGGL((k_quantize_pack_bucket<M, CH, KIND, CENTER, MODE>), grid, block, ((block.x >> 6) * kStringBytes<M>), st, p);
 }
@@ -486,8 +507,7 @@ void launch_fast_one(const QParams& p, hipStream_t st) {
         return;
     }
     if (p.center) {
-        const uint32_t octets = (tiles + 7u) / 8u, gz = (octets + 65534u) / 65535u, gy = (octets + gz - 1u) / gz;
-        hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, true>), dim3(8u * p.group_workers, gy, gz),
+        hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, true>), center_grid(tiles, p.group_workers),
                            dim3((Geo<M, LOG2N, true>::NW * 64)), 0, st, p);
         return;
     }
@@ -686,6 +706,7 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         const bool dense = sh.N == sh.B || sh.nb == 1;
         p.ws_tiles_per_worker = (uint32_t)tiles;
         p.data_tiles = dense ? (sh.d + kPartialTile - 1) / kPartialTile : tiles;
+        p.tiles = (uint32_t)p.data_tiles;
         p.xcd_group = xcd_group_log2(kPartialTile);
         const dim3 grid((uint32_t)p.data_tiles, a.K), finish_grid((uint32_t)(sh.nb * a.K)), finish_block(finish_waves * kWaveSize);
         if (a.norm_kind == QESGD_NORM_L2) {
@@ -709,6 +730,7 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         launch_fast(p, sh.m, a.stream);
         return check_launch();
     }
+    p.tiles = (uint32_t)tiles;
     p.xcd_group = xcd_group_log2(tile);
     const dim3 grid((uint32_t)tiles, a.K);
     if (ch == 4) launch_general<4, kBuckets>(p, sh.m, a.norm_kind, grid, block, a.stream);

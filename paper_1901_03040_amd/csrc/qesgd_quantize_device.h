@@ -23,7 +23,8 @@ struct QParams {
     uint64_t nb;
     uint64_t norms_off, signs_off, levels_off;
     uint32_t log2N;
-    uint32_t log2_waves;         // general kernels: waves per workgroup
+    uint32_t log2_waves;         // general kernels: waves per workgroup ...
+    uint32_t tiles;              // ... and workgroups of a worker
     uint32_t full_tiles;         // fast kernels: tiles per worker that lie wholly inside the vector
     uint32_t tail_tiles;         // fast quantize kernel: ragged tiles per worker after those (0 or 1)
     uint32_t group_workers;      // workers covered by this launch
