@@ -534,6 +534,17 @@ __device__ __forceinline__ WaveSpan wave_span_dense(const QParams& p, uint64_t u
     return s;
 }
 
+// The float4 of each half chunk that lie inside the first `whole` coordinates (a multiple of 4, not 0); h: half_offset.
+template <int CH, bool CACHED>
+__device__ __forceinline__ void load_inside(const float* __restrict__ p, uint32_t h, uint32_t whole, vec4 (&a)[CH], vec4 (&b)[CH]) {
+#pragma unroll
+    for (uint32_t c = 0; c < CH; ++c) {
+        const uint32_t at = h + c * kChunk, ia = at < whole ? at : 0u, ib = at + kChunk / 2 < whole ? at + kChunk / 2 : 0u;
+        a[c] = CACHED ? load_cached(p + ia) : load_stream(p + ia);
+        b[c] = CACHED ? load_cached(p + ib) : load_stream(p + ib);
+    }
+}
+
 // Worker k's coordinates of the span, 0 beyond it.
 template <int CH, bool CENTER>
 __device__ __forceinline__ void load_span(const QParams& p, uint32_t k, const WaveSpan& s, uint32_t lane, float (&v)[CH][8]) {
@@ -544,22 +555,60 @@ __device__ __forceinline__ void load_span(const QParams& p, uint32_t k, const Wa
         return;
     }
     vec4 a[CH], b[CH], ca[CH], cb[CH];
-    if (p.ragged_cached) {
-        asm volatile("; cached");                         // keeps the arms apart (see load_halves)
-        load_ragged<CH, true>(x, lane, s.mine, a, b);
-        asm volatile("; cached end");
-    } else {
-        load_ragged<CH, false>(x, lane, s.mine, a, b);
-    }
-    if (CENTER) load_ragged<CH, true>(center, lane, s.mine, ca, cb);
+    if constexpr (CENTER && CH == 2) {
+        // A float4 that is not wholly inside is read at the wave's first coordinates and means nothing.  Behind a condition of
+        // its lane (as below) a load waits for those before it, the center's for x's: d = 12 M, K = 1, s = 16, bucket 12000
+        // 20.4 us, this 17.9.  (Without a center this is no faster, and with four chunks it takes 121 registers: d = 25.6 M, K = 4,
+        // s = 256, bucket 20000, no center 123 / 143 us.)
+        const uint32_t whole = s.mine & ~3u, h = half_offset(lane);
+        if (whole != 0u) {
+            if (p.ragged_cached) {
+                asm volatile("; cached");                 // keeps the arms apart (see load_halves)
+                load_inside<CH, true>(x, h, whole, a, b);
+                asm volatile("; cached end");
+            } else {
+                load_inside<CH, false>(x, h, whole, a, b);
+            }
+            load_inside<CH, true>(center, h, whole, ca, cb);
+        }
 #pragma unroll
-    for (int c = 0; c < CH; ++c) {
-        if (CENTER) {
+        for (uint32_t c = 0; c < CH; ++c) {
+            const uint32_t at = h + c * kChunk;
             a[c] -= ca[c];
             b[c] -= cb[c];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                a[c][e] = at < whole ? a[c][e] : 0.0f;
+                b[c][e] = at + kChunk / 2 < whole ? b[c][e] : 0.0f;
+            }
+            if (s.mine != whole) {                        // the vector ends off a float4 (buckets are multiples of 32)
+#pragma unroll
+                for (uint32_t e = 0; e < 3; ++e) {
+                    const uint32_t i = whole + e;
+                    if (at == whole && i < s.mine) a[c][e] = x[i] - center[i];
+                    if (at + kChunk / 2 == whole && i < s.mine) b[c][e] = x[i] - center[i];
+                }
+            }
         }
-        halves_to_lane(a[c], b[c], v[c]);
+    } else {
+        if (p.ragged_cached) {
+            asm volatile("; cached");
+            load_ragged<CH, true>(x, lane, s.mine, a, b);
+            asm volatile("; cached end");
+        } else {
+            load_ragged<CH, false>(x, lane, s.mine, a, b);
+        }
+        if (CENTER) {
+            load_ragged<CH, true>(center, lane, s.mine, ca, cb);
+#pragma unroll
+            for (int c = 0; c < CH; ++c) {
+                a[c] -= ca[c];
+                b[c] -= cb[c];
+            }
+        }
     }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) halves_to_lane(a[c], b[c], v[c]);
 }
 
 // The codes of CH x 512 coordinates that all exist, from coordinate i0 on, whose group numbers share their high word.
