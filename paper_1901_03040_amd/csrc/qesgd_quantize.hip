@@ -60,7 +60,7 @@ __device__ __forceinline__ void center_order(uint32_t& k, uint32_t& t) {
 //   d = 60 M, K = 8, s = 16, bucket 224           773 -> 497 us (lane by lane)
 enum Mode { kBuckets, kNarrow, kPre };
 template <int M, int CH, int KIND, bool CENTER, Mode MODE>
-__global__ void __launch_bounds__(MODE == kBuckets ? 1024 : 256) k_quantize_pack_bucket(const QParams p) {
+__device__ __forceinline__ void pack_bucket(const QParams& p) {
     __shared__ float sm[16];
     extern __shared__ __align__(16) unsigned char strings[];
     const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -116,6 +116,20 @@ __global__ void __launch_bounds__(MODE == kBuckets ? 1024 : 256) k_quantize_pack
         for (int c = 1; c < CH; ++c) sc[c] = sc[0];
     }
     encode_span<M, CH, KIND>(p, k, s, lane, strings + wave * kStringBytes<M>, v, sc);
+}
+// Two workgroups of 16 waves fit a CU if a wave has at most 96 scalar registers, of which the trap handler holds 16.  The
+// compiler counts without those and takes 82 for levels of 7 bits, with which one fits; their buckets padded to 16384 have a
+// kernel of their own that is held to 80 (quantiser, d = 25.6 M, K = 4, s = 128, bucket 16384 111 -> 89 us).  Smaller workgroups lose
+// by the limit (d = 3.5 M, K = 8, s = 128, bucket 992, max norm 27.3 -> 29.8 us).
+template <int M, int CH>
+constexpr bool kOwn16 = M == 7 && CH == 2;
+template <int M, int CH, int KIND, bool CENTER, Mode MODE>
+__global__ void __launch_bounds__((MODE != kBuckets ? 256 : kOwn16<M, CH> ? 512 : 1024)) k_quantize_pack_bucket(const QParams p) {
+    pack_bucket<M, CH, KIND, CENTER, MODE>(p);
+}
+template <int M, int KIND, bool CENTER>
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_num_sgpr(80))) k_quantize_pack_bucket16(const QParams p) {
+    pack_bucket<M, 2, KIND, CENTER, kBuckets>(p);
 }
 
 // The buckets that neither takes (see LaneSpan).  (Through whole-line loads and an exchange: d = 15 M, K = 5, s = 16,
@@ -461,8 +475,18 @@ dim3 center_grid(uint32_t tiles, uint32_t workers) {
 template <int M, int CH, Mode MODE, int KIND, bool CENTER>
 void launch_general_one(const QParams& p, dim3 grid, dim3 block, hipStream_t st) {
     if (CENTER) grid = center_grid(grid.x, grid.y);
-    if constexpr (CH == 0) hipLaunchKernelGGL((k_quantize_pack_lanes<M, KIND, CENTER>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((k_quantize_pack_bucket<M, CH, KIND, CENTER, MODE>), grid, block, ((block.x >> 6) * kStringBytes<M>), st, p);
+    const uint32_t lds = (block.x >> 6) * kStringBytes<M>;
+    if constexpr (CH == 0) {
+        hipLaunchKernelGGL((k_quantize_pack_lanes<M, KIND, CENTER>), grid, block, 0, st, p);
+    } else {
+        if constexpr (MODE == kBuckets && kOwn16<M, CH>) {
+            if (block.x == 1024) {
+                hipLaunchKernelGGL((k_quantize_pack_bucket16<M, KIND, CENTER>), grid, block, lds, st, p);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((k_quantize_pack_bucket<M, CH, KIND, CENTER, MODE>), grid, block, lds, st, p);
+    }
 }
 
 template <int M, int CH, Mode MODE>

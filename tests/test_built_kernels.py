@@ -1,5 +1,8 @@
 """What the built library holds, read from its own symbols (no GPU)."""
 import collections
+import os
+import re
+import struct
 import subprocess
 
 from paper_1901_03040_amd import binding, build
@@ -12,3 +15,40 @@ def test_every_kernel_is_built_once():
     stubs = collections.Counter(line.split()[-1] for line in table.splitlines() if "__device_stub__" in line)
     assert any("k_round_fused" in n for n in stubs) and any("k_quantize_pack_fast" in n for n in stubs)
     assert [n for n, copies in stubs.items() if copies > 1] == []
+
+
+READELF = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-readelf")
+
+
+def kernel_notes(tmp_path):
+    """{kernel symbol: its notes' plain numbers} of all gfx950 code objects in the library."""
+    with open(build.LIB, "rb") as f:
+        lib = f.read()
+    out = {}
+    for bundle in re.finditer(rb"__CLANG_OFFLOAD_BUNDLE__", lib):
+        at = bundle.end()
+        count, = struct.unpack_from("<Q", lib, at)
+        at += 8
+        for _ in range(count):
+            offset, size, name = struct.unpack_from("<QQQ", lib, at)
+            triple = lib[at + 24:at + 24 + name].decode()
+            at += 24 + name
+            if not triple.endswith("gfx950") or size == 0:
+                continue
+            path = tmp_path / f"{bundle.start()}.o"
+            path.write_bytes(lib[bundle.start() + offset:bundle.start() + offset + size])
+            notes = subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout
+            for kernel in re.split(r"\n  - (?=\.)", notes)[1:]:
+                symbol = re.search(r"\.symbol:\s*'?(\S+?)\.kd'?\s", kernel)
+                if symbol:
+                    out[symbol.group(1)] = {k: int(v) for k, v in re.findall(r"\n    \.(\w+):\s*(\d+)\b", "\n    " + kernel)}
+    return out
+
+
+def test_two_workgroups_of_sixteen_waves_fit_a_cu(tmp_path):
+    """Where the vector registers allow two (512 per lane and SIMD, eight waves), the scalar ones do too: 800 per SIMD, handed
+    out in steps of 16, 16 of them per wave to the trap handler, which the compiler does not count."""
+    kernels = {n: k for n, k in kernel_notes(tmp_path).items()
+               if "k_quantize_pack" in n and k["max_flat_workgroup_size"] == 1024 and k["vgpr_count"] <= 64}
+    assert any("k_quantize_pack_bucket" in n for n in kernels) and any("k_quantize_pack_fast" in n for n in kernels)
+    assert {n: k["sgpr_count"] for n, k in kernels.items() if k["sgpr_count"] > 80} == {}
