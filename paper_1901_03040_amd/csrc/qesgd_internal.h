@@ -31,6 +31,7 @@ constexpr uint64_t kCachedInputBytes = 96ull << 20;     // of the K input vector
 constexpr uint64_t kCachedRoundBytes = 192ull << 20;    // ... and of all that a round touches
 constexpr uint64_t kCachedCodeBytes = 160ull << 20;     // of the K packed blocks, which the server reads next
 constexpr uint64_t kCachedUpdateBytes = 256ull << 20;   // of the packed blocks and the five vectors of the update
+constexpr uint64_t kCachedRaggedBytes = 144ull << 20;   // of the quantiser's ragged waves, the codes and the center (see quantize_params)
 // The update alone (qesgd_apply_update), of its three or four vectors; non-temporal / ordinary, loads and stores, two
 // sets of vectors in turn: with zsum d = 5 M 16.5 / 14.8 us, 8 M 25.4 / 23.3, 10 M 31.5 / 31.3, 16 M 50.0 / 57.6;
 // without d = 8 M 15.6 / 14.7, 12 M 22.9 / 23.3, 25 M 46.6 / 52.2.

@@ -67,9 +67,9 @@ __device__ __forceinline__ void pack_bucket(const QParams& p) {
     uint32_t k = blockIdx.y, t = blockIdx.x;
     if (CENTER) {
         center_order(k, t);
-        if (t >= p.tiles) return;
+        if (t >= p.full_tiles) return;
     }
-    const uint64_t unit = ((uint64_t)xcd_tile(t, p.tiles, p.xcd_group) << p.log2_waves) + wave;
+    const uint64_t unit = ((uint64_t)xcd_tile(t, CENTER ? p.full_tiles : gridDim.x, p.xcd_group) << p.log2_waves) + wave;
     const uint32_t lg = p.log2N - (CH == 4 ? 11u : 10u);                         // log2 of a bucket's waves
     static_assert(CH == 2 || CH == 4, "");
     const WaveSpan s = MODE == kNarrow ? wave_span_dense<CH>(p, unit) : wave_span<CH>(p, unit, lg);
@@ -142,9 +142,9 @@ __global__ void __launch_bounds__(256) k_quantize_pack_lanes(const QParams p) {
     uint32_t k = blockIdx.y, t = blockIdx.x;
     if (CENTER) {
         center_order(k, t);
-        if (t >= p.tiles) return;
+        if (t >= p.full_tiles) return;
     }
-    const uint64_t slot0 = ((uint64_t)xcd_tile(t, p.tiles, p.xcd_group) * 4u + (threadIdx.x >> 6)) * (CH * kChunk);
+    const uint64_t slot0 = ((uint64_t)xcd_tile(t, CENTER ? p.full_tiles : gridDim.x, p.xcd_group) * 4u + (threadIdx.x >> 6)) * (CH * kChunk);
     LaneSpan span[CH];
     float v[CH][8];
 #pragma unroll
@@ -650,14 +650,22 @@ QParams quantize_params(const Shape& sh, const QuantizeArgs& a) {
     p.group_workers = a.K;
     p.x_cached = input_cached(sh, a.K);
     p.codes_cached = a.K * sh.lay.payload_bytes <= kCachedCodeBytes;
-    // The ragged waves of buckets that are no power of two are up to all of the input, so they follow the policy of the
-    // whole ones: an ordinary stream drives the center out of the memory-side cache, from which the second worker on
-    // reads it (quantiser, ordinary / this: d = 60 M, K = 8, s = 4, with a center, bucket 992 707 / 548 us, 2016 682 / 554, 3008
-    // 650 / 556; without one d = 25.6 M, K = 4, s = 256, bucket 2016 88.7 / 82.0, 992 88.7 / 85.3).
-    // But with codes that go out non-temporally, no center and a ragged wave behind each one to three whole ones the
-    // ordinary policy is better (non-temporal / this: K = 16, d = 25.6 M, s = 256, bucket 2016 396 / 351 us, 3008 381 / 350; K = 8,
-    // d = 60 M, s = 16, 2016 417 / 379; wider, s = 16, 5024 372 / 370; all ragged, s = 16, 992 375 / 392).
-    p.ragged_cached = p.x_cached || (!p.center && !p.codes_cached && sh.N > 2 * kChunk && sh.N <= 4096);
+    // The ragged waves of buckets that are no power of two are up to all of the input.  They keep the ordinary policy where
+    // they fit the memory-side cache next to what else is read again, the codes and the center; beyond that their stream drives
+    // those out.  Quantiser, K = 8, ordinary / non-temporal, us; MB of the ragged waves, the codes and the center:
+    //   s = 16, bucket 992     3.5 M (129 MB) 20.9 / 22.3, 5 M (185) 33.9 / 30.4
+    //   s = 16, bucket 1504    6.5 M (98) 34.6 / 39.6, 10 M (152) 58.7 / 59.4, 13 M (198) 84.2 / 76.5
+    //   s = 256, bucket 2016   5 M (124) 30.4 / 33.1, 6.5 M (160) 42.9 / 42.1, 10 M (248) 71.3 / 63.4
+    //   s = 256, bucket 12000  10 M (110) 71.7 / 73.5, 13 M (142) 96.3 / 94.1; with a center 8 M (120) 72.3 / 72.4
+    //   center, s = 16, 1504   5 M (104) 32.8 / 38.0, 8 M (154) 60.5 / 59.8, 60 M (890) 678 / 573
+    // With codes that go out non-temporally, no center and a ragged wave behind each one to three whole ones the ordinary
+    // policy is better at any size (K = 16, d = 25.6 M, s = 256, bucket 2016 351 / 396, 3008 350 / 381; K = 8, d = 60 M, s = 16,
+    // 2016 379 / 417; but 5024 370 / 372, 992 392 / 375); in buckets wider than 32768, read twice, the other is (K = 16,
+    // d = 25.6 M, s = 32, bucket 48000 640 / 575).
+    const uint64_t wave = (sh.N == 32768 ? 4u : 2u) * (uint64_t)kChunk;
+    const uint64_t kept = 4u * (uint64_t)a.K * sh.nb * (sh.B % wave) + (p.codes_cached ? a.K * sh.lay.payload_bytes : 0u) + (p.center ? 4u * sh.d : 0u);
+    p.ragged_cached = p.x_cached || (sh.N <= kMaxSinglePassBucket && kept <= kCachedRaggedBytes) ||
+                      (!p.center && !p.codes_cached && sh.N > 2 * kChunk && sh.N <= 4096);
     return p;
 }
 
@@ -730,7 +738,7 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         const bool dense = sh.N == sh.B || sh.nb == 1;
         p.ws_tiles_per_worker = (uint32_t)tiles;
         p.data_tiles = dense ? (sh.d + kPartialTile - 1) / kPartialTile : tiles;
-        p.tiles = (uint32_t)p.data_tiles;
+        p.full_tiles = (uint32_t)p.data_tiles;
         p.xcd_group = xcd_group_log2(kPartialTile);
         const dim3 grid((uint32_t)p.data_tiles, a.K), finish_grid((uint32_t)(sh.nb * a.K)), finish_block(finish_waves * kWaveSize);
         if (a.norm_kind == QESGD_NORM_L2) {
@@ -754,7 +762,7 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
         launch_fast(p, sh.m, a.stream);
         return check_launch();
     }
-    p.tiles = (uint32_t)tiles;
+    p.full_tiles = (uint32_t)tiles;
     p.xcd_group = xcd_group_log2(tile);
     const dim3 grid((uint32_t)tiles, a.K);
     if (ch == 4) launch_general<4, kBuckets>(p, sh.m, a.norm_kind, grid, block, a.stream);

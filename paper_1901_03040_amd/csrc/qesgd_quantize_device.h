@@ -11,6 +11,8 @@
 
 namespace qesgd {
 
+// In the order that a kernel reads it in: a field in the middle that moved the rest cost calls of one or two short kernels
+// 0.6 us (d = 0.9 M, K = 4, s = 16, bucket 65536 7.2 -> 7.8 us).  New ones go to the end.
 struct QParams {
     const float* x;
     const float* center;
@@ -23,9 +25,8 @@ struct QParams {
     uint64_t nb;
     uint64_t norms_off, signs_off, levels_off;
     uint32_t log2N;
-    uint32_t log2_waves;         // general kernels: waves per workgroup ...
-    uint32_t tiles;              // ... and workgroups of a worker
-    uint32_t full_tiles;         // fast kernels: tiles per worker that lie wholly inside the vector
+    uint32_t log2_waves;         // general kernels: waves per workgroup
+    uint32_t full_tiles;         // fast kernels: tiles per worker that lie wholly inside the vector; general ones: all
     uint32_t tail_tiles;         // fast quantize kernel: ragged tiles per worker after those (0 or 1)
     uint32_t group_workers;      // workers covered by this launch
     uint32_t xcd_group;          // fast quantize kernels: log2 of the tiles that one XCD takes in a row
@@ -36,9 +37,9 @@ struct QParams {
     uint32_t round;
     uint32_t worker0;
     float smax;
-    bool x_cached;               // read the vectors with the ordinary cache policy ...
-    bool ragged_cached;          // ... where a wave of the general kernels is ragged
+    bool x_cached;               // read the vectors with the ordinary cache policy
     bool codes_cached;           // write the level planes with the ordinary cache policy
+    bool ragged_cached;          // x_cached where a wave of the general kernels is ragged
 };
 
 // Kernel parameters of a quantise call, and the first launches of the dense two-pass path (qesgd_quantize.hip).
@@ -590,18 +591,17 @@ __device__ __forceinline__ void load_span(const QParams& p, uint32_t k, const Wa
                 }
             }
         }
+    } else if (p.ragged_cached) {
+        asm volatile("; cached");
+        load_tile<CH, CENTER, false>(x, center, lane, true, v, s.mine);
+        asm volatile("; cached end");
+        return;
     } else {
-        if (p.ragged_cached) {
-            asm volatile("; cached");
-            load_ragged<CH, true>(x, lane, s.mine, a, b);
-            asm volatile("; cached end");
-        } else {
-            load_ragged<CH, false>(x, lane, s.mine, a, b);
-        }
-        if (CENTER) {
-            load_ragged<CH, true>(center, lane, s.mine, ca, cb);
+        load_ragged<CH, false>(x, lane, s.mine, a, b);
+        if (CENTER) load_ragged<CH, true>(center, lane, s.mine, ca, cb);
 #pragma unroll
-            for (int c = 0; c < CH; ++c) {
+        for (int c = 0; c < CH; ++c) {
+            if (CENTER) {
                 a[c] -= ca[c];
                 b[c] -= cb[c];
             }
