@@ -31,6 +31,8 @@ constexpr uint64_t kCachedInputBytes = 96ull << 20;     // of the K input vector
 constexpr uint64_t kCachedRoundBytes = 192ull << 20;    // ... and of all that a round touches
 constexpr uint64_t kCachedCodeBytes = 160ull << 20;     // of the K packed blocks, which the server reads next
 constexpr uint64_t kCachedUpdateBytes = 256ull << 20;   // of the packed blocks and the five vectors of the update
+constexpr uint64_t kSixWaveInput = 320ull << 20;        // from here on the quantiser's streams are held to six waves per SIMD:
+constexpr uint64_t kSixWaveCodes = 48ull << 20;         // the vectors, or the packed blocks
 constexpr uint64_t kCachedRaggedBytes = 144ull << 20;   // of the quantiser's ragged waves, the codes and the center (see quantize_params)
 // The update alone (qesgd_apply_update), of its three or four vectors; non-temporal / ordinary, loads and stores, two
 // sets of vectors in turn: with zsum d = 5 M 16.5 / 14.8 us, 8 M 25.4 / 23.3, 10 M 31.5 / 31.3, 16 M 50.0 / 57.6;
@@ -59,6 +61,17 @@ inline uint64_t update_bytes(const Shape& sh, uint32_t K) { return K * sh.lay.pa
 inline bool input_cached(const Shape& sh, uint32_t K) {
     const uint64_t in = 4u * (uint64_t)K * sh.d;
     return in <= kCachedInputBytes && in + update_bytes(sh, K) <= kCachedRoundBytes;
+}
+
+// LDS that a workgroup of `waves` waves, which has `fixed` bytes of its own, asks for besides so that a CU (160 KiB, handed out in
+// steps of 1280 bytes; four SIMDs) takes 24 waves and no more: six per SIMD, whatever its registers allow.  0 where workgroups of
+// that size cannot make 24.  (As amdgpu_waves_per_eu this would hold for every launch, and the compiler drops that attribute
+// without a word where its lower bound is below what the workgroup's size implies.)
+constexpr uint32_t kLdsBytes = 160u << 10, kLdsStep = 1280;
+inline uint32_t six_wave_lds(uint32_t waves, uint32_t fixed) {
+    if (24u % waves != 0u) return 0;
+    const uint32_t share = kLdsBytes / (24u / waves) / kLdsStep * kLdsStep;
+    return share > fixed ? share - fixed : 0u;
 }
 
 struct QuantizeArgs {

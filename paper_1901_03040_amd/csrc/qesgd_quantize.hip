@@ -174,14 +174,21 @@ __global__ void __launch_bounds__(256) k_quantize_pack_lanes(const QParams p) {
     }
 }
 
-// At most six waves per SIMD for the kernels that stream whole tiles: their registers would allow eight, which are more
-// streams than the memory takes at full rate.  Quantiser, eight / six / four waves:
-//   d = 138 M, K = 8, s = 2, bucket 4096          800 / 780 / 846 us
-//   d = 60 M, K = 8, s = 4, bucket 2048           335 / 326 / 345 us
-//   d = 25.6 M, K = 16, s = 256, one bucket       551 / 533 / 570 us
-//   d = 25.6 M, K = 16, s = 256, bucket 8192      328 / 330 / 329 us
-//   d = 1 M, K = 8, s = 16, bucket 512            9.0 / 8.7 / 8.8 us
-#define kSixWaves __attribute__((amdgpu_waves_per_eu(1, 6)))
+// At most six waves per SIMD for the kernels that stream whole tiles, where it pays: their registers would allow eight, which
+// are more streams than the memory takes at full rate.  The launch says so by the LDS that it asks for (six_wave_lds).
+// Quantiser, eight / six waves, two inputs in turn, us; MB of the vectors + the codes:
+//   up to 4 waves per workgroup, from 320 MiB or 48 MiB of codes on
+//                  s = 2, 4096, 4222 + 263 MB 814 / 793;  s = 4, 2048, 1831 + 171 340 / 329;  s = 16, 512, 1559 + 243 415 / 398
+//                  s = 256, 2048, 183 + 51 38.3 / 37.6;  s = 2, 2048, 457 + 28 80.1 / 78.3;  s = 65536, 128, 97 + 51 26.8 / 26.3
+//                  but s = 2, 512, 97 + 6 17.8 / 18.7, 183 + 11 32.5 / 33.9, 366 + 22 64.2 / 64.7;  s = 16, 512, 122 + 19 25.0 / 25.6
+//   8 waves (8192), whose barrier wants more of them, where the codes go out non-temporally
+//                  s = 256, 1559 + 438 331 / 309, 779 + 219 166 / 156;  s = 4, 1831 + 171 334 / 336;  but s = 16, 779 + 121 146 / 153
+//   one bucket     s = 256, 1559 + 438 MB 551 / 533 (both passes; only the second one 536)
+//   with a center  one worker, s = 256, 2048, 527 + 148 MB 2% faster, or up to 2 bits, K = 2, s = 2, 2048, 457 + 28 131 / 128;
+//                  but K = 4, s = 256, 4096, 183 + 51 44.7 / 49.3
+// A workgroup of 16 waves is alone on a CU or one of two, four or eight waves per SIMD: four lose (bucket 16384, d = 138 M, K = 8,
+// s = 2 819 / 983).  k_quantize_pack_center is indifferent (d = 57 M, K = 4, s = 16, bucket 4096 232 / 231), the general kernels need
+// the waves (d = 20 M, K = 8, s = 4, bucket 2400, max norm 134 / 147).
 
 // One tile per workgroup.  (Walking several tiles per workgroup with the next tile's loads in flight was
 // measured and is slower: the packed stores of a long-lived workgroup spread out in time and the mixed
@@ -194,7 +201,7 @@ __global__ void __launch_bounds__(256) k_quantize_pack_lanes(const QParams p) {
 //   d = 60 M, K = 8, s = 4, bucket 2048      364 -> 341 us = 6.2 TB/s
 //   d = 60 M, K = 8, s = 256, bucket 1024    402 -> 396 us = 6.2 TB/s
 template <int M, int LOG2N, bool CENTER>
-__global__ void __launch_bounds__((Geo<M, LOG2N, CENTER>::NW * 64)) kSixWaves k_quantize_pack_fast(const QParams p) {
+__global__ void __launch_bounds__((Geo<M, LOG2N, CENTER>::NW * 64)) k_quantize_pack_fast(const QParams p) {
     constexpr int CH = Geo<M, LOG2N, CENTER>::CH;
     constexpr uint32_t TILE = Geo<M, LOG2N, CENTER>::TILE;
     __shared__ float sm[32];
@@ -328,7 +335,7 @@ __device__ __forceinline__ void partial_tile(const QParams& p, uint32_t k, uint3
 // never straddles two such buckets, so the scale is one scalar per workgroup.
 // Both walk (tiles, workers) in the same order, so that a vector that fits the L2s is found in the same one.
 template <bool CENTER>
-__global__ void __launch_bounds__(256) kSixWaves k_tile_partials_fast(const QParams p) {
+__global__ void __launch_bounds__(256) k_tile_partials_fast(const QParams p) {
     constexpr int KIND = QESGD_NORM_L2;
     __shared__ float sm[4];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
@@ -351,7 +358,7 @@ __global__ void __launch_bounds__(256) kSixWaves k_tile_partials_fast(const QPar
 // merged: every wave finishes its bucket's tree by itself while its coordinates are on their way, which
 // saves the launch between the passes; the bucket's first tile writes the scale.
 template <int M, bool CENTER>
-__global__ void __launch_bounds__(256) kSixWaves k_quantize_pack_pre_fast(const QParams p) {
+__global__ void __launch_bounds__(256) k_quantize_pack_pre_fast(const QParams p) {
     __shared__ __align__(16) unsigned char strings[4][kStringBytes<M> + 16];
     const uint32_t lane = threadIdx.x & 63u, wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t k = blockIdx.y;
@@ -521,6 +528,12 @@ void launch_partials(const QParams& p, dim3 grid, hipStream_t st) {
     else hipLaunchKernelGGL((k_tile_partials<KIND, false>), grid, dim3(256), 0, st, p);
 }
 
+// Dynamic LDS of a kernel that streams whole tiles (see k_quantize_pack_fast); fixed: what it has besides.
+uint32_t stream_lds(const QParams& p, uint32_t waves, uint32_t fixed) {
+    return p.six_waves && (waves < 8u || !p.codes_cached) ? six_wave_lds(waves, fixed) : 0u;
+}
+constexpr uint32_t kFastLds = 128;
+
 template <int M, int LOG2N>
 void launch_fast_one(const QParams& p, hipStream_t st) {
     const uint32_t tiles = p.full_tiles + p.tail_tiles;
@@ -532,11 +545,11 @@ void launch_fast_one(const QParams& p, hipStream_t st) {
     }
     if (p.center) {
         hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, true>), center_grid(tiles, p.group_workers),
-                           dim3((Geo<M, LOG2N, true>::NW * 64)), 0, st, p);
+                           dim3((Geo<M, LOG2N, true>::NW * 64)), stream_lds(p, Geo<M, LOG2N, true>::NW, kFastLds), st, p);
         return;
     }
     hipLaunchKernelGGL((k_quantize_pack_fast<M, LOG2N, false>), dim3(tiles, p.group_workers),
-                       dim3((Geo<M, LOG2N>::NW * 64)), 0, st, p);
+                       dim3((Geo<M, LOG2N>::NW * 64)), stream_lds(p, Geo<M, LOG2N>::NW, kFastLds), st, p);
 }
 
 template <int M>
@@ -568,8 +581,9 @@ void launch_fast(const QParams& p, uint32_t m, hipStream_t st) {
 
 template <int M>
 void launch_pre_fast_m(const QParams& p, dim3 blocks, hipStream_t st) {
-    if (p.center) hipLaunchKernelGGL((k_quantize_pack_pre_fast<M, true>), blocks, dim3(256), 0, st, p);
-    else hipLaunchKernelGGL((k_quantize_pack_pre_fast<M, false>), blocks, dim3(256), 0, st, p);
+    const uint32_t lds = stream_lds(p, 4, 4u * (kStringBytes<M> + 16u));
+    if (p.center) hipLaunchKernelGGL((k_quantize_pack_pre_fast<M, true>), blocks, dim3(256), lds, st, p);
+    else hipLaunchKernelGGL((k_quantize_pack_pre_fast<M, false>), blocks, dim3(256), lds, st, p);
 }
 
 void launch_pre_fast(const QParams& p, uint32_t m, dim3 blocks, hipStream_t st) {
@@ -650,6 +664,8 @@ QParams quantize_params(const Shape& sh, const QuantizeArgs& a) {
     p.group_workers = a.K;
     p.x_cached = input_cached(sh, a.K);
     p.codes_cached = a.K * sh.lay.payload_bytes <= kCachedCodeBytes;
+    p.six_waves = !p.x_cached && (!p.center || a.K == 1 || sh.m <= 2) &&
+                  (4u * (uint64_t)a.K * sh.d >= kSixWaveInput || a.K * sh.lay.payload_bytes >= kSixWaveCodes);
     // The ragged waves of buckets that are no power of two are up to all of the input.  They keep the ordinary policy where
     // they fit the memory-side cache next to what else is read again, the codes and the center; beyond that their stream drives
     // those out.  Quantiser, K = 8, ordinary / non-temporal, us; MB of the ragged waves, the codes and the center:
@@ -685,8 +701,9 @@ int launch_dense_norms(QParams& p, const Shape& sh, const QuantizeArgs& a) {
     p.xcd_group = xcd_group_log2(kPartialTile);
     p.merged = P <= kMergePartials;
     const dim3 grid((uint32_t)p.data_tiles, a.K);
-    if (p.center) hipLaunchKernelGGL(k_tile_partials_fast<true>, grid, dim3(256), 0, a.stream, p);
-    else hipLaunchKernelGGL(k_tile_partials_fast<false>, grid, dim3(256), 0, a.stream, p);
+    const uint32_t lds = stream_lds(p, 4, 16);
+    if (p.center) hipLaunchKernelGGL(k_tile_partials_fast<true>, grid, dim3(256), lds, a.stream, p);
+    else hipLaunchKernelGGL(k_tile_partials_fast<false>, grid, dim3(256), lds, a.stream, p);
     if (!p.merged) {
         uint32_t waves = 1;
         while (waves < 16 && (uint64_t)waves * 1024u < P) waves <<= 1;

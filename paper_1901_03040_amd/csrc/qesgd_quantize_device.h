@@ -40,6 +40,7 @@ struct QParams {
     bool x_cached;               // read the vectors with the ordinary cache policy
     bool codes_cached;           // write the level planes with the ordinary cache policy
     bool ragged_cached;          // x_cached where a wave of the general kernels is ragged
+    bool six_waves;              // host only: see stream_lds
 };
 
 // Kernel parameters of a quantise call, and the first launches of the dense two-pass path (qesgd_quantize.hip).

@@ -52,3 +52,32 @@ def test_two_workgroups_of_sixteen_waves_fit_a_cu(tmp_path):
                if "k_quantize_pack" in n and k["max_flat_workgroup_size"] == 1024 and k["vgpr_count"] <= 64}
     assert any("k_quantize_pack_bucket" in n for n in kernels) and any("k_quantize_pack_fast" in n for n in kernels)
     assert {n: k["sgpr_count"] for n, k in kernels.items() if k["sgpr_count"] > 80} == {}
+
+
+def host_values(tmp_path, body):
+    """Output of a program that sees the library's host-side rules (no HIP call is made)."""
+    src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
+    src.write_text('#include "qesgd_internal.h"\n#include <cstdio>\nusing namespace qesgd;\nint main() {\n' + body + "\nreturn 0; }\n")
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-Wno-deprecated-declarations", "-I/opt/rocm/include",
+                    f"-I{os.path.join(build.ROOT, 'include')}", f"-I{build.CSRC}", str(src), "-o", str(exe)], check=True)
+    return subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout
+
+
+def test_streaming_kernels_hold_six_waves_per_simd(tmp_path):
+    """The LDS that a streaming launch asks for, with what the built kernel has itself, leaves a CU 24 waves for workgroups of 2, 4
+    and 8 waves (buckets of 8192 among them); those of 16 ask for none."""
+    out = host_values(tmp_path, 'for (unsigned w : {2u, 4u, 8u, 16u}) std::printf("%u %u\\n", w, six_wave_lds(w, 0));')
+    ask = {int(w): int(b) for w, b in (line.split() for line in out.splitlines())}
+    assert ask.pop(16) == 0
+    seen = set()
+    for name, k in kernel_notes(tmp_path).items():
+        if not re.search("k_quantize_pack_fast|k_tile_partials_fast|k_quantize_pack_pre_fast", name):
+            continue
+        waves = k["max_flat_workgroup_size"] // 64
+        if waves == 16:
+            continue
+        seen.add(waves)
+        assert k["group_segment_fixed_size"] < ask[waves]
+        assert 160 * 1024 // ask[waves] * waves == 24 and ask[waves] % 1280 == 0, name
+        assert k["vgpr_count"] <= 80, name                   # otherwise the registers allow fewer than six anyway
+    assert seen == {2, 4, 8}
