@@ -237,7 +237,7 @@ int qesgd_round(const float* x_slab, uint64_t x_stride, const float* center, uin
     rc = aggregate_check(packed_slab, packed_stride, K, d, s, bucket, w_snap, zbar_out, u_out, zsum_inout, true,
                          stream, &sh2, &g);
     if (rc != QESGD_OK) return rc;
-    if (round_fused_covers(sh, norm_kind) && round_chunks(sh, K, center != nullptr, false)) return launch_round_fused(sh, q, g);
+    if (round_fused_covers(sh, norm_kind) && round_chunks(sh, K, center != nullptr)) return launch_round_fused(sh, q, g);
     rc = launch_quantize(sh, q);
     return rc != QESGD_OK ? rc : launch_aggregate(sh, g);
 }
@@ -258,7 +258,7 @@ int qesgd_gradient_round(const float* x_slab, uint64_t x_stride, uint64_t d, uin
     if (rc != QESGD_OK) return rc;
     if (!aligned(z_inout, 16)) return QESGD_ERR_ALIGN;
     g.z_acc = z_inout;
-    if (round_fused_covers(sh, norm_kind) && round_chunks(sh, K, false, true)) return launch_round_fused(sh, q, g);
+    if (round_fused_covers(sh, norm_kind) && round_chunks(sh, K, false)) return launch_round_fused(sh, q, g);
     rc = launch_quantize(sh, q);
     return rc != QESGD_OK ? rc : launch_aggregate(sh, g);
 }

@@ -113,60 +113,69 @@ bool dense_wide(const Shape& sh, uint32_t norm_kind);
 bool round_fused_covers(const Shape& sh, uint32_t norm_kind);
 // Tile of the one-launch round for buckets up to 16384.
 inline uint64_t round_tile(uint64_t N, uint32_t chunks) { return N > 2u * chunks * kChunk ? N : 2u * chunks * kChunk; }
-// One launch or two, and the chunks per wave of the one: 0 two launches, else 1 or 2 (always 2 from 8192 on; the
-// wide buckets' kernel has 1).  One launch takes the workers of a tile one after the other, about 1 us each (2.4 us with
-// buckets of 4096 and more, whose waves meet at a barrier per worker), which only a chip full of tiles hides; two
-// launches spread tiles and workers over the chip at once, and read the codes back.  Two sets of buffers in turn, us,
-// two launches / one.  "Bytes" are the K vectors', the packed blocks' and the update's; "odd" level widths are 3, 5, 6, 7,
-// which the two launches store and read the dearest.
-//   wide: up to 1250 MiB (138 M, K = 4, s = 16 1244 / 1320), from 1.5 M coordinates or up to 8 workers
-//   8192 and 16384, whose chain is the longest
-//     one generation of workgroups, K = 1, 2   0.5 M, K = 1, 8192 6.9 / 5.7; 1.5 M, K = 2, 8192 11.4 / 9.5; 2.4 M, K = 2,
-//                               16384 16.8 / 14.6; but 5000, K = 2, 8192 8.6 / 8.8; 1.5 M, 16384 11.6 / 13.7
-//     8 bits and more, K >= 8 from 8 M on, K >= 5 from 40 M on (K >= 16 with z_acc)   8 M, K = 8, 8192 89 / 81; 25 M, K = 16, 16384 480 / 468;
-//                               5 M, K = 8 56 / 56; but 25 M, K = 4 171 / 171; 12 M, K = 8, 16384, z_acc 143 / 145
-//     4 bits, K >= 16, 8192, from 20 M on      25 M 435 / 412; but 16384 430 / 443
-//     odd, K >= 4, from 10 M on (8192 alone with z_acc)   12 M, K = 8, s = 128 137 / 124; 25 M, K = 4, s = 32, 16384 185 / 175;
-//                               but 5 M, K = 4, s = 32 36 / 41; 25 M, K = 8, s = 32, 16384, z_acc 320 / 346
-//     center, K >= 8 (8 bits, 8192: K >= 4), from 8 M on   12 M, K = 16, s = 4 231 / 203; 12 M, K = 4, s = 256 96 / 90, s = 4 80 / 86
-//   up to 4096, below 1.5 M
-//     whole tiles, from 0.65 M on (2048, not odd: 0.98 M; 4096: odd alone), up to 16 workers
-//                               0.65 M, K = 16, s = 32, 128 21.5 / 18.4; 1 M, K = 16, bucket 128 22.6 / 16.5; 0.7 M, K = 9,
-//                               2048 13.5 / 14.7; 1 M, K = 32, bucket 128 37.6 / 47.5
-//     up to 5 workers           256, K = 5, bucket 128 8.6 / 7.3; 0.1 M, K = 5, 2048 8.7 / 8.6, K = 6 8.8 / 9.5; 0.3 M, K = 8, 512 8.8 / 10.5
-//     8 up to 1024 with whole tiles, not odd, no z_acc   47104, K = 8, s = 4, bucket 128 7.7 / 7.4, with a ragged tile 7.7 / 8.7
-//     8 from 0.9 M, 12 from 1.25 M on   1 M, K = 8, 512 15.0 / 14.4, K = 12 18.1 / 19.2; 1.3 M, K = 12, 512 20.8 / 19.5
-//     with 4096 2 workers, 4 from 0.9 M on   0.4 M, K = 4 8.5 / 9.5; 1 M, K = 4 11.5 / 9.7
-//   up to 4096, from 1.5 M on
-//     odd, but not K = 1, 2 beyond 1000 MiB   12 M, K = 8, s = 128, 512 133 / 115; 50 M, K = 16, s = 8, 512 935 / 845; 50 M, K = 2, s = 8 238 / 247
-//     up to 950 MiB, 1250 with 1 and 2 bits, 1100 with a center   25 M, K = 2, s = 16 122 / 109; 12 M, K = 16, s = 4 184 / 177;
-//                               25 M, K = 2, s = 256 126 / 127; 12 M, K = 16, s = 16 198 / 210
+// One launch or two, and the chunks per wave of the one: 0 two launches, else 1 or 2 (always 2 from 8192 on; the wide buckets'
+// kernel has 1).  One launch takes the workers of a tile one after the other, which only a chip full of tiles hides; two
+// launches spread tiles and workers over the chip at once, and read the codes back.  Drawn from 18000 shapes timed both ways
+// (d = 256 .. 60 M, K = 1 .. 32, all level widths, two sets of buffers in turn), where it takes 0.4% more than always the better
+// side; microseconds, two launches / one.  "Dear" level widths are 3, 5, 6, 7 and those of 8 bits and more, whose codes cost
+// the most to read back.
+//   8192 and 16384: a workgroup of 8 or 16 waves fills a CU, so 256 tiles are one generation, and it takes as long however few
+//   tiles it has.
+//     one generation, full enough for its workers   1.4 M, K = 3, s = 128, 8192 14.6 / 11.3; 3.6 M, K = 24, s = 65536, 16384 133.8 / 94.0;
+//                                  but 1.9 M, K = 2, s = 64, 16384 16.5 / 24.0; 1.6 M, K = 16, s = 32, 8192 37.7 / 48.7
+//     more, K >= 4, where a last one of up to four is half full, and the codes or the workers are many: dear, a center, 10 workers
+//     with 16384, beyond 2000 MiB  5.3 M, K = 24, s = 256, center, 8192 169 / 137; 8 M, K = 16, s = 4, 16384 134 / 122; 50 M, K = 16, s = 4,
+//                                  8192 800 / 761; 34 M, K = 32, s = 8, center, 8192 1453 / 1127; 50 M, K = 4, s = 256, 8192 366 / 341; but 31 M, K = 8,
+//                                  s = 4, 16384 292 / 301
+//   up to 4096, short vectors: the chain of K workers, at the ragged tile if there is one, against one launch more at first (8 us
+//   for two calls' worth of host work), then against what two launches take for the bytes, which grows with K too: the line
+//   rises with d, measured as a square.  One launch up to 0.3 M, K = 3 .. 8: bucket 128 .. 512, ragged 5.5 6.1 7.1 7.8 8.8 9.3, whole 5.4 5.2
+//   5.7 6.2 6.9 7.3; 4096, ragged 6.7 7.2 8.7 9.9 10.7 12.1; widths 3, 5, 6, 7 and 16 and a center add 0.5 to 2
+//                                  0.2 M, K = 3, 4096 11.6 / 6.8; 1 M, K = 8, 512 15.0 / 14.4; 47 K, K = 8, s = 4, 128, one ragged 7.7 / 8.7
+//     and by the bytes of the K vectors, the packed blocks and the update   25 M, K = 2, s = 16 122 / 109, s = 256 126 / 127; 12 M,
+//                                  K = 16, s = 16 198 / 210; 50 M, K = 16, s = 8 935 / 845, K = 2 238 / 247
 //     beyond, two chunks (one / two): from 8 bits on with K * m >= 32, with 4 bits from 12 workers on, and with a center
-//                               25 M, K = 16, s = 256, 512 503 / 505 / 467; 50 M, K = 8, s = 256, 256 575 / 563 / 536; 25 M, K = 16,
-//                               s = 16, 256 430 / 460 / 418; center, 25 M, K = 16, s = 256 617 / 521 / 485; but 25 M, K = 8, s = 16
-//                               238 / 261 / 248; 50 M, K = 2, s = 256 242 / 254 / 249; 12 M, K = 8, s = 4 110 / 101 / 114
-//     center with 1 and 2 bits: one chunk      25 M, K = 16, s = 4 509 / 449
-inline uint32_t round_chunks(const Shape& sh, uint32_t K, bool center, bool z_acc) {
-    const uint64_t bytes = 4u * (uint64_t)K * sh.d + update_bytes(sh, K), mib = bytes >> 20;
-    const uint64_t M = 1000000;
-    const bool odd = 32u % sh.m != 0u;
-    if (sh.N > kMaxSinglePassBucket) return bytes <= (1250ull << 20) && (sh.d >= (3u << 19) || K <= 8) ? 1 : 0;
-    if (sh.N > 4096) {
-        const bool narrow = sh.N == 8192;
-        bool pays;
-        if (center) pays = sh.d >= 8 * M && (K >= 8 || (K >= 4 && sh.m >= 8 && narrow));
-        else if (odd) pays = sh.d >= 10 * M && K >= 4 && (narrow || !z_acc);
-        else if (sh.m >= 8) pays = sh.d >= 8 * M && K >= (z_acc ? 16u : sh.d >= 40 * M ? 5u : 8u);
-        else pays = sh.m == 4 && sh.d >= 20 * M && K >= 16 && narrow;
-        const bool one_generation = K <= 2 && sh.d <= 256u * sh.N && sh.d >= (narrow ? (K - 1u) * 650000u : 1800000u);
-        return pays || one_generation ? 2 : 0;
+//                                  25 M, K = 16, s = 256, 512 503 / 505 / 467; 25 M, K = 16, s = 16, 256 430 / 460 / 418; but
+//                                  25 M, K = 8, s = 16 238 / 261 / 248; 12 M, K = 8, s = 4 110 / 101 / 114
+//   wide: up to 1250 MiB, beyond it with widths 3, 5, 6, 7 or a center   138 M, K = 4, s = 16 1244 / 1320; 58 M, K = 16, s = 32, center
+//                                  2526 / 2097; many workers from 0.55 M coordinates on (more than 16, one tile ragged: 1.5 M)
+//                                  0.72 M, K = 16, s = 64 30.8 / 25.0; 0.85 M, K = 32, s = 256 53 / 65; 216 K, K = 8, s = 4 11.2 / 13.5
+inline uint32_t round_chunks(const Shape& sh, uint32_t K, bool center) {
+    const uint64_t mib = (4u * (uint64_t)K * sh.d + update_bytes(sh, K)) >> 20;
+    const bool odd = 32u % sh.m != 0u, dear = odd || sh.m >= 8;
+    if (sh.N > kMaxSinglePassBucket) {
+        const bool whole = sh.d % 2048u == 0u;
+        if (mib >= 1250 && !center && !odd) return 0;
+        if (K <= (whole ? 8u : 7u)) return 1;
+        return sh.d >= (whole || K <= 16 ? 550000u : 3u << 19) ? 1 : 0;
     }
-    if (sh.d < (3u << 19)) {
-        const uint64_t tile = round_tile(sh.N, 1);
-        if ((odd || sh.N <= 2048) && K <= 16 && sh.d % tile == 0 && sh.d >= (odd || sh.N <= 1024 ? 5u << 17 : 15u << 16)) return 1;
-        if (sh.N == 4096) return K <= (sh.d < 900000 ? 2u : 4u) ? 1 : 0;
-        if (sh.N <= 1024 && !odd && !z_acc && K <= 8 && sh.d % tile == 0) return 1;
-        return K <= (sh.d < 900000 ? 5u : sh.d < 1250000 ? 8u : 12u) ? 1 : 0;
+    if (sh.N > 4096) {
+        const uint64_t tiles = (sh.d + sh.N - 1) / sh.N, generations = (tiles + 255u) / 256u, idle = 256u * generations - tiles;
+        const bool few8 = sh.N == 8192 && K <= 2;
+        if (generations == 1) {
+            uint32_t need = sh.N == 8192 ? 55u + 24u * K : 100u + 12u * K;
+            const uint32_t most = sh.N == 8192 ? (sh.m >= 8 ? 220u : 257u) : sh.m >= 8 ? 150u : 190u;
+            if (need > most || (sh.N == 16384 && odd && K >= 3)) need = most;
+            if (few8 && (K == 1 || sh.d % sh.N == 0u)) need = 0;
+            return tiles >= need ? 2 : 0;
+        }
+        if (few8 && generations == 2) return K == 1 || idle <= 128u ? 2 : 0;
+        if (generations > 4 && odd) return 2;
+        const bool heavy = dear || (center && (K >= 6 || mib > 1400)) || (sh.N == 16384 && K >= 10) ||
+                           (mib > 2000 && sh.m > 1 && K * sh.m >= (sh.N == 8192 ? 12u : 32u));
+        return K >= 4 && heavy && (generations > 4 || idle <= 128u) ? 2 : 0;
+    }
+    if (sh.d < 3000000u) {
+        const bool whole = sh.d % round_tile(sh.N, 1) == 0u;
+        const double M = (double)sh.d * 1e-6, M2 = M * M;
+        double most;
+        if (whole) {
+            most = (sh.N <= 1024 ? 8.5 : sh.N == 2048 ? 6.5 : 4.8) + (sh.N == 4096 ? 12.0 : 20.0) * M2;
+        } else {
+            most = (sh.N <= 512 ? 6.0 : sh.N == 1024 ? 5.6 : sh.N == 2048 ? 5.0 : 4.2) - (odd || sh.m == 16 ? 0.5 : 0.0) + (sh.N == 4096 ? 3.5 : 7.0) * M2;
+            if (center) most *= 0.9;
+        }
+        if (K > most) return 0;
     }
     if (odd) return K <= 2 && mib > 1000 ? 0 : 1;
     if (mib <= (sh.m < 4 ? 1250u : center ? 1100u : 950u)) return 1;

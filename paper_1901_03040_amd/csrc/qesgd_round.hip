@@ -27,7 +27,7 @@ int launch_round_fused(const Shape& sh, const QuantizeArgs& a, const AggregateAr
         p.xcd_group = xcd_group_log2(kWideWaves * kChunk);
         blocks = (sh.d + kWideWaves * kChunk - 1) / (kWideWaves * kChunk);
     } else {
-        chunks = round_chunks(sh, a.K, a.center != nullptr, g.z_acc != nullptr);
+        chunks = round_chunks(sh, a.K, a.center != nullptr);
         const uint64_t tile = round_tile(sh.N, chunks);
         blocks = (sh.nb * sh.N + tile - 1) / tile;
         p.full_tiles = (uint32_t)(sh.d / tile);

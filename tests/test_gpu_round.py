@@ -71,8 +71,9 @@ def test_one_launch_shapes_equal_two_calls(B, log2n, s, K):
 @pytest.mark.parametrize("s", [2, 16, 256])
 @pytest.mark.parametrize("d,K", [(1_572_864, 3), (1_572_863, 9), (1_600_037, 16), (4_800_000, 3)])
 def test_both_sides_of_the_one_launch_rule(B, bucket, s, d, K):
-    """Buckets up to 4096 take one launch from 1.5 M coordinates on, many workers with short vectors two.  The
-    vectors of (1_600_037, 16) are beyond the ordinary cache policy.  (Buckets of 32768 never take one launch.)"""
+    """Around 1.5 M coordinates, where buckets up to 4096 take one launch and 8192 and 16384 by how full their one
+    generation of workgroups is (just on either side of each line: test_gpu_round_routes.py).  The vectors of
+    (1_600_037, 16) are beyond the ordinary cache policy.  (Buckets of 32768 never take one launch.)"""
     g = torch.Generator(device="cuda").manual_seed(d + K)
     slab = torch.randn(K, (d + 63) // 64 * 64, generator=g, device="cuda") * 1e-3
     w = torch.randn(d, generator=g, device="cuda")
@@ -87,7 +88,7 @@ def test_both_sides_of_the_one_launch_rule(B, bucket, s, d, K):
     (11_000_003, 32, 512, 4, False), (11_000_003, 32, 512, 4, True), (11_000_003, 32, 512, 256, False),  # beyond 1.25 GB
     (11_000_000, 32, 8192, 16, False)])
 def test_sides_of_the_one_launch_rule_by_workers_and_size(B, d, K, bucket, s, centered):
-    """The lines between one launch and two: workers and length by bucket; beyond 1.25 GB level width and center."""
+    """Workers, length, level width and center on both routes, also beyond 1.25 GB."""
     g = torch.Generator(device="cuda").manual_seed(d + K)
     slab = torch.randn(K, (d + 63) // 64 * 64, generator=g, device="cuda") * 1e-3
     w = torch.randn(d, generator=g, device="cuda")
