@@ -193,13 +193,12 @@ __global__ void __launch_bounds__(256) k_quantize_pack_lanes(const QParams p) {
 // One tile per workgroup.  (Walking several tiles per workgroup with the next tile's loads in flight was
 // measured and is slower: the packed stores of a long-lived workgroup spread out in time and the mixed
 // read/write stream to HBM loses more than the prefetch gains.)
-// Bound by the mix of reads and writes: at d = 138 M, K = 8, s = 2, bucket 4096 it takes 811 us, 610 us with
-// the stores left out (7.3 TB/s) and 813 us without Philox.  Before (32 bytes per lane, ordinary policy,
-// general rounding, tiles dealt round-robin) / now, same machine, two inputs in turn:
-//   d = 138 M, K = 8, s = 2, bucket 4096     850 -> 811 us = 5.8 TB/s (one input again and again: 741 us)
-//   d = 25.6 M, K = 16, s = 256, bucket 8192 380 -> 334 us = 6.3 TB/s
-//   d = 60 M, K = 8, s = 4, bucket 2048      364 -> 341 us = 6.2 TB/s
-//   d = 60 M, K = 8, s = 256, bucket 1024    402 -> 396 us = 6.2 TB/s
+// Bound by the mix of reads and writes: at d = 138 M, K = 8, s = 2, bucket 4096, with eight waves per SIMD, it took 811 us,
+// 610 us with the stores left out (7.3 TB/s) and 813 us without Philox.  Before (32 bytes per lane, ordinary policy, general
+// rounding, tiles dealt round-robin) / with eight waves / with six, two inputs in turn:
+//   d = 138 M, K = 8, s = 2, bucket 4096     850 / 811 / 793 us = 5.9 TB/s
+//   d = 25.6 M, K = 16, s = 256, bucket 8192 380 / 331 / 309 us = 6.8 TB/s
+//   d = 60 M, K = 8, s = 4, bucket 2048      364 / 340 / 329 us = 6.4 TB/s
 template <int M, int LOG2N, bool CENTER>
 __global__ void __launch_bounds__((Geo<M, LOG2N, CENTER>::NW * 64)) k_quantize_pack_fast(const QParams p) {
     constexpr int CH = Geo<M, LOG2N, CENTER>::CH;

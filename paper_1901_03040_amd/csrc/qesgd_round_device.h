@@ -37,9 +37,10 @@ namespace {
 
 // Tile of a workgroup: chunks per wave and waves.  The running sum and the next worker's coordinates are
 // held in registers next to the current ones, so fewer chunks fit than in the plain quantiser: one up to 4096, where two
-// pay only beyond the caches (see round_chunks: 76 to 94 registers and 5 or 6 waves per SIMD against 137 to 161 and 3).
-// Buckets of 8192 and 16384 have two, one would need sixteen waves and more (8192, d = 12 M, K = 8, s = 4: 128 / 141 us).
-// Those of 16384 have 128 registers per lane and spill 44 to 128 bytes of them, 116 to 200 with a center or z_acc.
+// pay only beyond the caches (see round_chunks).  Registers, level widths that divide 32 / 3, 5, 6, 7: one chunk 75 to 94 /
+// 86 to 107, two 139 to 163.  Buckets of 8192 and 16384 have two, one would need sixteen waves and more (8192, d = 12 M,
+// K = 8, s = 4: 128 / 141 us).  Those of 8192 take 137 to 158 / 151 to 178, those of 16384 have 128 per lane and spill
+// 44 to 80 / 124 bytes and more of them, with a center or z_acc 116 to 200.
 template <int LOG2N, int CHUNKS>
 struct RoundGeo {
     static constexpr int CH = CHUNKS;
