@@ -34,6 +34,7 @@ constexpr uint64_t kCachedUpdateBytes = 256ull << 20;   // of the packed blocks 
 constexpr uint64_t kSixWaveInput = 320ull << 20;        // from here on the quantiser's streams are held to six waves per SIMD:
 constexpr uint64_t kSixWaveCodes = 48ull << 20;         // the vectors, or the packed blocks
 constexpr uint64_t kCachedRaggedBytes = 144ull << 20;   // of the quantiser's ragged waves, the codes and the center (see quantize_params)
+constexpr uint64_t kCachedGeneralCodeBytes = 288ull << 20;   // of the packed blocks, for the general kernels (see general_codes_cached)
 // The update alone (qesgd_apply_update), of its three or four vectors; non-temporal / ordinary, loads and stores, two
 // sets of vectors in turn: with zsum d = 5 M 16.5 / 14.8 us, 8 M 25.4 / 23.3, 10 M 31.5 / 31.3, 16 M 50.0 / 57.6;
 // without d = 8 M 15.6 / 14.7, 12 M 22.9 / 23.3, 25 M 46.6 / 52.2.
@@ -61,6 +62,15 @@ inline uint64_t update_bytes(const Shape& sh, uint32_t K) { return K * sh.lay.pa
 inline bool input_cached(const Shape& sh, uint32_t K) {
     const uint64_t in = 4u * (uint64_t)K * sh.d;
     return in <= kCachedInputBytes && in + update_bytes(sh, K) <= kCachedRoundBytes;
+}
+
+// The general kernels' codes of power-of-two buckets (the max norm; odd level widths are indifferent) are better written with the
+// ordinary policy as far as the memory-side cache holds part of them for the server's call.  Whole two-call round, max norm,
+// non-temporal / ordinary, us: K = 4, s = 65536, 20.6 M (167 MiB) 175 / 166, 31.8 M (257) 271 / 254; K = 4, s = 256, 38.9 M (167)
+// 282 / 273, 60 M (257) 438 / 415; K = 8, s = 256, 37.8 M (324) 427 / 439, 50 M (429) 566 / 593.  With a center the other one is
+// (K = 4, s = 256, 48.9 M 390 / 409), where buckets are no power of two neither (3424, K = 4, 38.9 M 277 / 280, 60 M 435 / 440).
+inline bool general_codes_cached(const Shape& sh, uint32_t K, bool center) {
+    return K * sh.lay.payload_bytes <= (!center && sh.N == sh.B ? kCachedGeneralCodeBytes : kCachedCodeBytes);
 }
 
 // LDS that a workgroup of `waves` waves, which has `fixed` bytes of its own, asks for besides so that a CU (160 KiB, handed out in

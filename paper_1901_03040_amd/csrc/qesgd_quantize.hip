@@ -780,6 +780,7 @@ int launch_quantize(const Shape& sh, const QuantizeArgs& a) {
     }
     p.full_tiles = (uint32_t)tiles;
     p.xcd_group = xcd_group_log2(tile);
+    p.codes_cached = general_codes_cached(sh, a.K, a.center != nullptr);
     const dim3 grid((uint32_t)tiles, a.K);
     if (ch == 4) launch_general<4, kBuckets>(p, sh.m, a.norm_kind, grid, block, a.stream);
     else if (sh.N >= 2 * kChunk) launch_general<2, kBuckets>(p, sh.m, a.norm_kind, grid, block, a.stream);

@@ -43,7 +43,8 @@ def test_edges_of_waves(oracle, B, bucket, last, s, norm_kind, with_center):
 
 @pytest.mark.parametrize("bucket,s,norm_kind,K,with_center", [
     (992, 4, 0, 3, True), (992, 256, 1, 3, False), (2016, 128, 0, 3, True), (2016, 65536, 0, 10, False), (3008, 65536, 1, 10, False),
-    (5024, 16, 0, 3, True), (12_000, 32, 1, 3, True), (20_000, 8, 0, 3, True), (48_000, 64, 0, 3, False), (48_000, 4, 1, 3, True)])
+    (5024, 16, 0, 3, True), (12_000, 32, 1, 3, True), (20_000, 8, 0, 3, True), (48_000, 64, 0, 3, False), (48_000, 4, 1, 3, True),
+    (2048, 65536, 1, 10, False), (256, 65536, 1, 10, False), (2048, 65536, 1, 17, False)])     # 170 and 289 MiB of codes
 def test_streams_beyond_the_caches(B, bucket, s, norm_kind, K, with_center):
     """More than 96 MiB of input (and with 10 workers 160 MiB of codes) against one call per worker, which stays below:
     the policy of the streams and the order of the workers change no bit."""

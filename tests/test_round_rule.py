@@ -7,8 +7,8 @@ from test_gpu_round_routes import LINES
 WHOLE = 1 << 40
 
 
-def routes(tmp_path, shapes):
-    """0 (two launches), 1 or 2 (chunks of a wave) for each (d, K, bucket, s, center), L2 scale, power-of-two or wide buckets."""
+def routes(tmp_path, shapes, rule="round_chunks"):
+    """What the rule says for each (d, K, bucket, s, center); round_chunks: 0 (two launches), 1 or 2 (chunks of a wave)."""
     body = "Shape sh{};\n"
     for d, K, bucket, s, center in shapes:
         lay = B.qesgd_layout_query(d, s, bucket)
@@ -16,7 +16,7 @@ def routes(tmp_path, shapes):
         log2n = max(3, (size - 1).bit_length())
         body += (f"sh.d = {d}ull; sh.s = {s}; sh.m = {lay.level_bits}; sh.B = {size}ull; sh.nb = {lay.n_buckets}ull; sh.N = {1 << log2n}ull; "
                  f"sh.log2N = {log2n}; sh.lay.payload_bytes = {lay.payload_bytes}ull; "
-                 f'std::printf("%u\\n", round_chunks(sh, {K}, {str(center).lower()}));\n')
+                 f'std::printf("%u\\n", (unsigned){rule}(sh, {K}, {str(center).lower()}));\n')
     return [int(v) for v in host_values(tmp_path, body).split()]
 
 
@@ -47,3 +47,10 @@ def test_measured_shapes_take_the_faster_side(tmp_path):
 def test_gpu_tests_of_the_lines_lie_on_both_sides(tmp_path):
     got = routes(tmp_path, [(d, K, bucket, s, form == "center") for d, bucket, s, K, form, _ in LINES])
     assert [c[:5] + (r,) for c, r in zip(LINES, got)] == LINES
+
+
+def test_policy_of_the_general_kernels_codes(tmp_path):
+    """The ordinary one up to 288 MiB with power-of-two buckets and no center, otherwise up to 160 MiB."""
+    shapes = [(20_588_235, 4, 2048, 65536, False), (60_000_000, 4, 256, 256, False), (37_777_777, 8, 2048, 256, False),
+              (48_888_888, 4, 2048, 256, True), (38_888_888, 4, 3424, 256, False), (19_000_000, 4, 3424, 256, True)]
+    assert routes(tmp_path, shapes, "general_codes_cached") == [1, 1, 0, 0, 0, 1]
