@@ -67,8 +67,8 @@ inline bool input_cached(const Shape& sh, uint32_t K) {
 // The general kernels' codes of power-of-two buckets (the max norm; odd level widths are indifferent) are better written with the
 // ordinary policy as far as the memory-side cache holds part of them for the server's call.  Whole two-call round, max norm,
 // non-temporal / ordinary, us: K = 4, s = 65536, 20.6 M (167 MiB) 175 / 166, 31.8 M (257) 271 / 254; K = 4, s = 256, 38.9 M (167)
-// 282 / 273, 60 M (257) 438 / 415; K = 8, s = 256, 37.8 M (324) 427 / 439, 50 M (429) 566 / 593.  With a center the other one is
-// (K = 4, s = 256, 48.9 M 390 / 409), where buckets are no power of two neither (3424, K = 4, 38.9 M 277 / 280, 60 M 435 / 440).
+// 282 / 273, 60 M (257) 438 / 415; K = 8, s = 256, 37.8 M (324) 427 / 439, 50 M (429) 566 / 593.  With a center, and in buckets that are
+// no power of two, the other one is (K = 4, s = 256, center, 48.9 M 390 / 409; 3424, 38.9 M 277 / 280, 60 M 435 / 440).
 inline bool general_codes_cached(const Shape& sh, uint32_t K, bool center) {
     return K * sh.lay.payload_bytes <= (!center && sh.N == sh.B ? kCachedGeneralCodeBytes : kCachedCodeBytes);
 }
